@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import weakref
 from typing import Optional
 
 import numpy as np
@@ -301,6 +302,13 @@ class NetBlob:
         return [DeviceBlob(d, t) for d in self.layers]
 
 
+def _adopt(lib, out, size: int) -> np.ndarray:
+    """The buffer an encoder returned as an array that releases it when the last reference goes."""
+    buf = (C.c_uint8 * size).from_address(out.value)
+    weakref.finalize(buf, lib.hac_free, C.c_void_p(out.value))
+    return np.frombuffer(buf, dtype=np.uint8)
+
+
 RI_FIELDS, RI_RICE = 0, 1
 
 
@@ -331,10 +339,7 @@ def hac_net_encode(Ws, formats, chunk_nnz: int = 0, ri_bits: int = 0, lut_bits: 
     opts = Opts(chunk_nnz, ri_bits, lut_bits, ri_coding, chunk_rows)
     out, size = C.c_void_p(), C.c_size_t()
     _check(lib.hac_net_encode(L, fm, ptrs, ns, ms, ms, C.byref(opts), C.byref(out), C.byref(size)), "hac_net_encode")
-    try:
-        data = np.ctypeslib.as_array(C.cast(out, C.POINTER(C.c_uint8)), shape=(size.value,)).copy()
-    finally:
-        lib.hac_free(out)
+    data = _adopt(lib, out, size.value)
     return NetBlob(data)
 
 
@@ -352,10 +357,7 @@ def _encode(fn_name: str, W: np.ndarray, chunk_nnz=0, ri_bits=0, lut_bits=0, ri_
     rc = getattr(lib, fn_name)(W.ctypes.data_as(C.POINTER(C.c_float)), W.shape[0], W.shape[1], ldw,
                                C.byref(opts), C.byref(out), C.byref(size))
     _check(rc, fn_name)
-    try:
-        data = np.ctypeslib.as_array(C.cast(out, C.POINTER(C.c_uint8)), shape=(size.value,)).copy()
-    finally:
-        lib.hac_free(out)
+    data = _adopt(lib, out, size.value)
     return Blob(data)
 
 
@@ -382,10 +384,7 @@ def im_encode(W: np.ndarray) -> Blob:
     rc = lib.im_encode(W.ctypes.data_as(C.POINTER(C.c_float)), W.shape[0], W.shape[1], W.shape[1], None,
                        C.byref(out), C.byref(size))
     _check(rc, "im_encode")
-    try:
-        data = np.ctypeslib.as_array(C.cast(out, C.POINTER(C.c_uint8)), shape=(size.value,)).copy()
-    finally:
-        lib.hac_free(out)
+    data = _adopt(lib, out, size.value)
     return Blob(data)
 
 
