@@ -415,7 +415,7 @@ int hac_choose_format(int64_t n, int64_t m, uint64_t nnz, uint32_t k);
  * histogram, the code bits, the gap bits for every Rice parameter and the bit
  * packing run on the GPU; the Huffman code, the choice of the parameter and the
  * prefix sums over columns are made on the host in between, so the call
- * synchronises `stream` (two or three times) and returns with the blob complete.
+ * synchronises `stream` (three times) and returns with the blob complete.
  * d_ws: hac_encode_dev_workspace_bytes(n, m) bytes, 256-byte aligned.  *desc
  * receives the header.  If d_blob is NULL or blob_capacity < desc->blob_bytes the
  * call returns HAC_EWORKSPACE with desc filled in: allocate desc->blob_bytes
@@ -424,6 +424,15 @@ size_t hac_encode_dev_workspace_bytes(int64_t n, int64_t m);
 int hac_encode_dev(uint32_t format, const float *d_W, int64_t n, int64_t m, int64_t ldw,
                    const hac_opts_t *opts, void *d_blob, size_t blob_capacity, hac_desc_t *desc,
                    void *d_ws, size_t ws_bytes, hac_stream_t stream);
+
+/* The same for a caller that does not know the blob's size: alloc(bytes, ctx) is
+ * called once, on the calling thread, when the size is known, and returns
+ * 256-byte aligned device memory that the caller owns (NULL: the call returns
+ * HAC_EWORKSPACE).  It must not throw. */
+typedef void *(*hac_alloc_t)(size_t bytes, void *ctx);
+int hac_encode_dev_alloc(uint32_t format, const float *d_W, int64_t n, int64_t m, int64_t ldw,
+                         const hac_opts_t *opts, hac_alloc_t alloc, void *alloc_ctx, hac_desc_t *desc,
+                         void *d_ws, size_t ws_bytes, hac_stream_t stream);
 
 /* Bytes of device workspace hac_dot / shac_dot need for a batch of B rows with
  * default launch settings (0 when none is needed: a single row, or a few rows

@@ -25,7 +25,7 @@ EXPORTS = (
     "hac_encode", "shac_encode", "hac_free", "hac_validate", "hac_describe", "hac_stats",
     "hac_decode_host", "hac_workspace_bytes", "hac_workspace_bytes_for", "hac_dot_route", "hac_dot", "shac_dot", "hac_decode_dev",
     "shac_decode_dev", "hac_strerror", "hac_last_hip_error", "im_encode", "im_dot",
-    "hac_encode_dev", "hac_encode_dev_workspace_bytes", "hac_choose_format",
+    "hac_encode_dev", "hac_encode_dev_alloc", "hac_encode_dev_workspace_bytes", "hac_choose_format",
     "hac_net_encode", "hac_net_describe", "hac_net_layer", "hac_net_validate", "hac_net_stats",
     "hac_net_decode_host", "hac_forward", "hac_forward_workspace_bytes", "hac_dot_noalloc", "hac_last_kernels",
 )
@@ -39,6 +39,9 @@ class HacError(RuntimeError):
         if status == -5:
             extra = f" (hipError {load_library().hac_last_hip_error()})"
         super().__init__(f"{where}: {msg}{extra} [{status}]")
+
+
+_ALLOC = C.CFUNCTYPE(C.c_void_p, C.c_size_t, C.c_void_p)
 
 
 class Opts(C.Structure):
@@ -128,6 +131,8 @@ def load_library() -> C.CDLL:
     lib.hac_encode_dev_workspace_bytes.restype = C.c_size_t
     lib.hac_encode_dev.argtypes = [C.c_uint32, vp, C.c_int64, C.c_int64, C.c_int64, C.POINTER(Opts), vp, C.c_size_t,
                                    C.POINTER(Desc), vp, C.c_size_t, vp]
+    lib.hac_encode_dev_alloc.argtypes = [C.c_uint32, vp, C.c_int64, C.c_int64, C.c_int64, C.POINTER(Opts), _ALLOC, vp,
+                                         C.POINTER(Desc), vp, C.c_size_t, vp]
     lib.hac_choose_format.argtypes = [C.c_int64, C.c_int64, C.c_uint64, C.c_uint32]
     lib.hac_net_encode.argtypes = [C.c_uint32, C.POINTER(C.c_uint32), C.POINTER(f32p), C.POINTER(C.c_int64),
                                    C.POINTER(C.c_int64), C.POINTER(C.c_int64), C.POINTER(Opts),
@@ -474,7 +479,7 @@ def hac_encode_dev(W, fmt: int = HAC_FORMAT_HAC, chunk_nnz: int = 0, ri_bits: in
                    ri_coding: int = 0, stream=None) -> DeviceBlob:
     """Encode a device matrix (2-D float32 CUDA tensor, unit column stride) on the device.
 
-    Calls the library twice: once to learn the blob's size, once to fill it.  Synchronises the stream.
+    The library asks for the blob's memory once it knows the size.  Synchronises the stream.
     """
     import torch
     if W.dtype != torch.float32 or W.dim() != 2 or not W.is_cuda or W.stride(1) != 1:
@@ -485,13 +490,22 @@ def hac_encode_dev(W, fmt: int = HAC_FORMAT_HAC, chunk_nnz: int = 0, ri_bits: in
     ws = torch.empty(lib.hac_encode_dev_workspace_bytes(n, m), dtype=torch.uint8, device=W.device)
     opts = Opts(chunk_nnz, ri_bits, lut_bits, ri_coding)
     desc = Desc()
-    sh = _stream_handle(stream)
-    rc = lib.hac_encode_dev(fmt, W.data_ptr(), n, m, ldw, C.byref(opts), None, 0, C.byref(desc), ws.data_ptr(), ws.numel(), sh)
-    if rc != -6:
-        _check(rc, "hac_encode_dev")
-    blob = torch.empty(int(desc.blob_bytes), dtype=torch.uint8, device=W.device)
-    _check(lib.hac_encode_dev(fmt, W.data_ptr(), n, m, ldw, C.byref(opts), blob.data_ptr(), blob.numel(), C.byref(desc),
-                              ws.data_ptr(), ws.numel(), sh), "hac_encode_dev")
+    blob, failed = None, None
+
+    def alloc(nbytes, _ctx):
+        nonlocal blob, failed
+        try:
+            blob = torch.empty(nbytes, dtype=torch.uint8, device=W.device)
+            return blob.data_ptr()
+        except Exception as e:                               # must not pass through the library
+            failed = e
+            return None
+
+    rc = lib.hac_encode_dev_alloc(fmt, W.data_ptr(), n, m, ldw, C.byref(opts), _ALLOC(alloc), None, C.byref(desc),
+                                  ws.data_ptr(), ws.numel(), _stream_handle(stream))
+    if failed is not None:
+        raise failed
+    _check(rc, "hac_encode_dev")
     return DeviceBlob(desc, blob)
 
 

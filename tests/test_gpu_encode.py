@@ -120,3 +120,31 @@ def test_strided_matrix_and_argument_checks(hac):
     assert lib.hac_encode_dev(1, Wbig.data_ptr(), n, m, m, None, None, 0, C.byref(desc), ws.data_ptr(), ws.numel(), None) == -6
     assert int(desc.blob_bytes) == hac.hac_encode(Wbig.cpu().numpy()).nbytes      # the size to allocate
     torch.cuda.synchronize()
+
+
+def tile_matrix(n, m, per_tile, k, seed):
+    """per_tile non-zeros (as far as they fit) in every 32 x 64 tile, k distinct values."""
+    rng = np.random.default_rng(seed)
+    W = np.zeros((n, m), np.float32)
+    values = np.unique(rng.standard_normal(k).astype(np.float32))
+    for r in range(0, n, 32):
+        for c in range(0, m, 64):
+            t = W[r:r + 32, c:c + 64]
+            at = rng.permutation(t.size)[:per_tile]
+            t[np.unravel_index(at, t.shape)] = rng.choice(values, at.size)
+    return W
+
+
+# the tile sizes where a list is no longer packed (256) and no longer queued (1024), remainders of rows
+# and columns, more segments per column than the 16 ranges they are summed in, a code table that
+# fits LDS and one that does not
+@pytest.mark.parametrize("n,m,per_tile,k", [(160, 128, 256, 9), (160, 128, 257, 9), (97, 130, 1024, 40), (97, 130, 1025, 40),
+                                            (64, 64, 2048, 5), (20011, 3, 5, 17), (9000, 300, 30, 512), (2080, 257, 200, 700)])
+def test_device_blob_at_the_edges_of_the_tiles(hac, n, m, per_tile, k):
+    W = tile_matrix(n, m, per_tile, k, 11)
+    Wd = torch.from_numpy(W).to(dev())
+    print(f"[case] encode_dev tiles {n} x {m}, {per_tile} a tile, k = {k}", flush=True)
+    assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_HAC).tensor.cpu().numpy(), hac.hac_encode(W).data)
+    assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_SHAC).tensor.cpu().numpy(), hac.shac_encode(W).data)
+    assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_SHAC, ri_coding=hac.RI_RICE).tensor.cpu().numpy(),
+                          hac.shac_encode(W, ri_coding=hac.RI_RICE).data)
