@@ -4,27 +4,30 @@
 // in the index map Pi; the form the paper uses for layers that are quantized but
 // hardly pruned, where the product really is a dense contraction).
 //
-// The pointers are what is read from memory (1 or 2 bytes per weight); a tile of
-// them is turned into fp32 through a copy of c in LDS and multiplied on the
-// matrix cores with v_mfma_f32_32x32x2_f32 (fp32 in, fp32 accumulate, so the
-// result keeps the accuracy of the vector path).
+// The pointers are what is read from memory (1 or 2 bytes per weight).  What bounds the product is the
+// matrix pipe: v_mfma_f32_32x32x2_f32 does 157 TFLOP/s at best, the bf16 instruction sixteen times that.
+// So every fp32 operand is written as three bf16 parts, x = x1 + x2 + x3 (8 significant bits each, 24 in
+// all: nothing of x is lost), and six of the nine products of parts are summed in fp32 on the matrix
+// cores: x1 w1, x1 w2, x2 w1, x2 w2, x1 w3, x3 w1.  The three left out are below 2^-22 of |x w| each,
+// and one rounding of the sum per 16 products of parts instead of one per two makes the result closer
+// to 64 bits than the fp32 instruction's (relative 2-norm error figures at plan_index_gemm).
+// X is split with truncations (two ANDs, two subtractions, exact) on the way to LDS, W's
+// representatives once per block in the table that pointers are looked up in.
+// An infinity or NaN among the operands makes its outputs non-finite (inf - inf in the split); such an
+// output, and one that overflowed, is computed again in plain fp32 before it is stored.
 //
-// Tiling: a block of 4 wavefronts owns 32 RT batch rows x 128 columns of Y
-// (RT = 2..8, chosen per launch so that the tiles fill the 256 CUs evenly) and
-// walks K = n in steps of 32; wavefront w owns the 32 columns [32 w, 32 w + 32)
-// of the tile and all its rows, as RT MFMA tiles (16 RT accumulator registers).
-// LDS holds the X tile row-major (a batch row's 32 k values side by side, rows 36
-// floats apart) and the decoded W tile k-major (32 consecutive columns of one k);
-// both are double buffered, the next tile's global loads are issued before the
-// MFMA loop of the current one and stored during its second half.
-// Lane layout of the instruction (checked on the device): A operand lane l holds
-// A[i = l % 32][k = l / 32], B operand lane l holds B[k = l / 32][j = l % 32],
-// accumulator register v of lane l is D[(v % 4) + 8 (v / 4) + 4 (l / 32)][l % 32].
-// The order of k inside a step is free as long as both operands agree: matrix
-// instruction kk of a step multiplies k = kk (lanes 0..31) and k = 16 + kk (lanes
-// 32..63), so a lane's 16 A values of a step are 16 consecutive floats of its row:
-// four 128-bit LDS reads instead of sixteen 32-bit ones, and the thread that
-// fetched four consecutive k of a row from X stores them with one 128-bit write.
+// Tiling: a block of 4 wavefronts owns 32 RT batch rows x 128 columns of Y (RT = 1..4) and walks K = n
+// in steps of 32; wavefront w owns the 32 columns [32 w, 32 w + 32) of the tile and all its rows, as RT
+// MFMA tiles (two sums each, 32 RT accumulator registers).  LDS holds one K step of X and W, both with the 32 k of a
+// row (a column) side by side, part by part, 208 bytes apart, so that an operand is one 128-bit read and 16
+// lanes' reads fall on different banks.  The next step's global loads fly during the matrix
+// instructions; two blocks share a CU, so that one splits and stores while the other multiplies.
+// Measured (MI355X), fp32 instruction -> bf16 parts: 4608 x 512 layer pruned 60 %, 12544 rows, whole call
+// 580 -> 352 us (59 GFLOP, 168 TFLOP/s; a call includes decoding the stream, about 30 us); unpruned map of that size,
+// 784 rows, 60.0 -> 35.5 us.
+// Lane layout of v_mfma_f32_32x32x16_bf16: A operand lane l holds A[i = l % 32][k = 8 (l / 32) + 0..7], B
+// operand lane l holds B[k = 8 (l / 32) + 0..7][j = l % 32], accumulator register v of lane l is
+// D[(v % 4) + 8 (v / 4) + 4 (l / 32)][l % 32].
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -33,17 +36,43 @@
 namespace {
 
 constexpr int BN = 128, BK = 32;
-constexpr int LDB = BN + 4;                        // LDS row pitch of the W tile (floats)
-constexpr int LDA = BK + 4;                        // LDS row pitch of the X tile: 36 floats, so that 16 lanes'
-                                                   // 128-bit accesses to 16 rows fall on 64 different banks
-constexpr int kMinRT = 2, kMaxRT = 8;              // row tiles of 32 per block
+constexpr int PART = 2 * BK, PITCH = 3 * PART + 16;   // bytes: one part of a row's K step, one row in LDS
+constexpr int kMinRT = 1, kMaxRT = 4;              // row tiles of 32 per block
 constexpr uint32_t kLutLdsMax = 4096;              // representatives kept in LDS
 
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-template <typename IdxT> struct IdxRegs;
-template <> struct IdxRegs<uint8_t> { uint4 v[1]; };
-template <> struct IdxRegs<uint16_t> { uint4 v[2]; };
+// Four neighbouring pointers of one row of the map.
+template <typename IdxT> struct Ptr4;
+template <> struct Ptr4<uint8_t> {
+    typedef uint32_t raw;
+    static __device__ __forceinline__ uint32_t get(raw w, int c) { return (w >> (8 * c)) & 255u; }
+    static __device__ __forceinline__ void ld(const uint8_t* p, uint32_t* out) {
+        const uint32_t w = *reinterpret_cast<const uint32_t*>(p);
+        out[0] = w & 255u; out[1] = (w >> 8) & 255u; out[2] = (w >> 16) & 255u; out[3] = w >> 24;
+    }
+};
+template <> struct Ptr4<uint16_t> {
+    typedef uint2 raw;
+    static __device__ __forceinline__ uint32_t get(raw w, int c) { return ((c & 2 ? w.y : w.x) >> (16 * (c & 1))) & 65535u; }
+    static __device__ __forceinline__ void ld(const uint16_t* p, uint32_t* out) {
+        const uint2 w = *reinterpret_cast<const uint2*>(p);
+        out[0] = w.x & 65535u; out[1] = w.x >> 16; out[2] = w.y & 65535u; out[3] = w.y >> 16;
+    }
+};
+
+// w = w1 + w2 + w3: { w1 | w2 << 16, w3 }.  Rounded to nearest (ties upwards in magnitude), so that the
+// parts' signs vary and the left-out products have no bias; cut off instead where rounding could overflow.
+__device__ __forceinline__ uint2 split_weight(float w)
+{
+    const uint32_t up = fabsf(w) < 1e38f ? 0x8000u : 0u;
+    const uint32_t h1 = (__float_as_uint(w) + up) & 0xffff0000u;
+    const float r1 = w - __uint_as_float(h1);
+    const uint32_t h2 = (__float_as_uint(r1) + up) & 0xffff0000u;
+    const float r2 = r1 - __uint_as_float(h2);
+    return make_uint2((h1 >> 16) | h2, __float_as_uint(r2) >> 16);
+}
 
 __device__ __forceinline__ uint32_t logical_tile(uint32_t tiles_padded)
 {
@@ -53,7 +82,7 @@ __device__ __forceinline__ uint32_t logical_tile(uint32_t tiles_padded)
 }
 
 template <typename IdxT, bool LUT_LDS, int RT, bool XVEC>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, 2)
 index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
                   const IdxT* __restrict__ idx, uint64_t pitch,          // pitch in elements, a multiple of 16
                   const float* __restrict__ codebook, uint32_t k_sym, uint32_t zero_first,
@@ -62,10 +91,10 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
                   uint32_t splits, uint32_t steps_per_split, float* __restrict__ part)
 {
     constexpr int BM = 32 * RT;
-    extern __shared__ float lds[];
-    float* As = lds;                                   // [2][BM][LDA]
-    float* Bs = lds + 2 * BM * LDA;                    // [2][BK][LDB]
-    float* lut = Bs + 2 * BK * LDB;                    // [k_sym + zero_first] when LUT_LDS
+    extern __shared__ __align__(16) float lds[];
+    char* As = reinterpret_cast<char*>(lds);           // [BM] rows of PITCH bytes
+    char* Bs = As + BM * PITCH;                        // [BN] columns of PITCH bytes
+    uint2* lut = reinterpret_cast<uint2*>(Bs + BN * PITCH);   // [k_sym + zero_first] when LUT_LDS
     // work item = (tile, K split); with more than one split a block writes its partial tile to
     // part[split][B][m] and a second kernel adds the splits in order
     const uint32_t item = logical_tile(gridDim.x);
@@ -76,57 +105,41 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const uint32_t l32 = lane & 31, half = lane >> 5;
 
-    // pointer -> value table: entry 0 is 0.0 when the pointers were written with an offset of one
+    // pointer -> value; entry 0 is 0.0 when the pointers were written with an offset of one
     const uint32_t k_tot = k_sym + zero_first;
-    if (LUT_LDS) {
-        for (uint32_t i = t; i < k_tot; i += 256)
-            lut[i] = (zero_first && i == 0) ? 0.0f : codebook[i - zero_first];
-    }
-    auto value_of = [&](uint32_t p) -> float {
-        if (LUT_LDS) return lut[p];
-        return (zero_first && p == 0) ? 0.0f : codebook[p - zero_first];
-    };
+    auto value_of = [&](uint32_t p) -> float { return (zero_first && p == 0) ? 0.0f : codebook[p - zero_first]; };
+    if (LUT_LDS)
+        for (uint32_t i = t; i < k_tot; i += 256) lut[i] = split_weight(value_of(i));
+    auto parts_of = [&](uint32_t p) -> uint2 { return LUT_LDS ? lut[p] : split_weight(value_of(p)); };
 
-    // global -> register staging of one K step; two sets, so that a tile's loads are issued two
-    // steps before the tile is needed (one whole step before its stores to LDS begin)
-    struct Stage { float4 ra[RT]; IdxRegs<IdxT> rb; };
-    const uint32_t a_row = t >> 3, a_kq = t & 7;       // rows a_row + 32 r, k = 4 a_kq .. 4 a_kq + 3
-    const uint32_t b_k = t >> 3, b_seg = t & 7;        // idx row b_k, columns 16 b_seg .. 16 b_seg + 15
-    // Rows past B and index columns past the pitch are read from a clamped, valid address: a K
-    // step that lies wholly inside n then issues the same loads on every path, and the wait before
-    // a tile's stores can leave the younger tile's loads in flight.  A row past B multiplies a copy
-    // of row B - 1; rows of the product are independent and those are never stored.  Only the
-    // last, partial K step takes the guarded path.
+    // Global -> registers.  X: rows a_row + 32 r, k = 4 q .. 4 q + 3; map: rows 4 q .. 4 q + 3, columns
+    // b_col .. b_col + 3 (four k of a column in one thread, so that a part of them is one 64-bit store).
+    // Rows past B and columns past the pitch are read from a clamped, valid address and never stored;
+    // only the last, partial K step is guarded.
+    struct Stage { float4 ra[RT]; typename Ptr4<IdxT>::raw rb[4]; };
+    const uint32_t q = t & 7, a_row = t >> 3, b_col = 4 * (t >> 3);
     const float* xrow[RT];
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
         const uint32_t row = m0 + a_row + 32 * r;
-        xrow[r] = X + (uint64_t)(row < B ? row : B - 1) * ldx + 4 * a_kq;
+        xrow[r] = X + (uint64_t)(row < B ? row : B - 1) * ldx + 4 * q;
     }
-    const bool col_ok = n0 + 16 * b_seg < pitch;
-    const IdxT* icol = idx + (col_ok ? n0 + 16 * b_seg : 0);
-    constexpr int NV = sizeof(IdxT) == 1 ? 1 : 2;
-    // a K step that lies wholly inside n: the same loads on every path
+    const IdxT* icol = idx + (n0 + b_col < pitch ? n0 + b_col : 0);
     auto load_full = [&](uint32_t k0, Stage& st) {
-        if (XVEC) {
-#pragma unroll
-            for (int r = 0; r < RT; ++r) st.ra[r] = *reinterpret_cast<const float4*>(xrow[r] + k0);
-        } else {
-#pragma unroll
-            for (int r = 0; r < RT; ++r) {
-                const float* p = xrow[r] + k0;
-                st.ra[r] = make_float4(p[0], p[1], p[2], p[3]);
-            }
-        }
-        const uint4* p = reinterpret_cast<const uint4*>(icol + (uint64_t)(k0 + b_k) * pitch);
-#pragma unroll
-        for (int q = 0; q < NV; ++q) st.rb.v[q] = p[q];
-    };
-    // the last, partial K step: guarded element by element
-    auto load_tail = [&](uint32_t k0, Stage& st) {
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
-            const uint32_t k = k0 + 4 * a_kq;
+            const float* p = xrow[r] + k0;
+            if (XVEC) st.ra[r] = *reinterpret_cast<const float4*>(p);
+            else st.ra[r] = make_float4(p[0], p[1], p[2], p[3]);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            st.rb[j] = *reinterpret_cast<const typename Ptr4<IdxT>::raw*>(icol + (uint64_t)(k0 + 4 * q + j) * pitch);
+    };
+    auto load_tail = [&](uint32_t k0, Stage& st) {
+        const uint32_t k = k0 + 4 * q;
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
             const float* p = xrow[r] + k0;
             float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             if (k < n) v.x = p[0];
@@ -136,139 +149,106 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
             st.ra[r] = v;
         }
 #pragma unroll
-        for (int q = 0; q < NV; ++q) st.rb.v[q] = make_uint4(0, 0, 0, 0);
-        if (k0 + b_k < n) {
-            const uint4* p = reinterpret_cast<const uint4*>(icol + (uint64_t)(k0 + b_k) * pitch);
+        for (int j = 0; j < 4; ++j) {                  // (past the end: any row of the map, X is 0 there)
+            const uint32_t kj = k + j < n ? k + j : n - 1;
+            st.rb[j] = *reinterpret_cast<const typename Ptr4<IdxT>::raw*>(icol + (uint64_t)kj * pitch);
+        }
+    };
+    // registers -> LDS.  __builtin_amdgcn_perm(hi, lo, ..) packs the upper (lower) halves of two words.
+    auto upper = [](uint32_t hi, uint32_t lo) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); };
+    auto lower = [](uint32_t hi, uint32_t lo) { return __builtin_amdgcn_perm(hi, lo, 0x05040100u); };
+    auto store = [&](const Stage& st) {
 #pragma unroll
-            for (int q = 0; q < NV; ++q) st.rb.v[q] = p[q];
+        for (int c = 0; c < 4; ++c) {
+            uint2 w[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[j] = parts_of(Ptr4<IdxT>::get(st.rb[j], c));
+            char* b = Bs + (b_col + c) * PITCH + 8 * q;
+            *reinterpret_cast<uint2*>(b) = make_uint2(lower(w[1].x, w[0].x), lower(w[3].x, w[2].x));
+            *reinterpret_cast<uint2*>(b + PART) = make_uint2(upper(w[1].x, w[0].x), upper(w[3].x, w[2].x));
+            *reinterpret_cast<uint2*>(b + 2 * PART) = make_uint2(lower(w[1].y, w[0].y), lower(w[3].y, w[2].y));
         }
-    };
-    // registers -> LDS in pieces, so that the work can be spread over the MFMA loop
-    auto store_a = [&](uint32_t buf, int r, const Stage& st) {          // rows a_row + 32 r of the X tile
-        float* a = As + buf * BM * LDA + (a_row + 32 * r) * LDA + 4 * a_kq;
-        *reinterpret_cast<float4*>(a) = make_float4(st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w);
-    };
-    // pointers -> values (columns 16 b_seg + 4 q .. + 3 of the W tile), then values -> LDS: two steps,
-    // so that the table lookups can be issued some matrix instructions before their results are stored
-    auto lookup_b = [&](int q, const Stage& st) -> float4 {
-        float4 o;
-        if constexpr (sizeof(IdxT) == 1) {
-            const uint32_t u = q == 0 ? st.rb.v[0].x : q == 1 ? st.rb.v[0].y : q == 2 ? st.rb.v[0].z : st.rb.v[0].w;
-            o.x = value_of(u & 255u); o.y = value_of((u >> 8) & 255u);
-            o.z = value_of((u >> 16) & 255u); o.w = value_of(u >> 24);
-        } else {
-            const uint4 v = st.rb.v[q >> 1];
-            const uint32_t u0 = (q & 1) ? v.z : v.x, u1 = (q & 1) ? v.w : v.y;
-            o.x = value_of(u0 & 65535u); o.y = value_of(u0 >> 16);
-            o.z = value_of(u1 & 65535u); o.w = value_of(u1 >> 16);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+            const float x[4] = {st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w};
+            uint32_t h[4], h2[4], h3[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                h[j] = __float_as_uint(x[j]);
+                const float r1 = x[j] - __uint_as_float(h[j] & 0xffff0000u);
+                h2[j] = __float_as_uint(r1);
+                h3[j] = __float_as_uint(r1 - __uint_as_float(h2[j] & 0xffff0000u));
+            }
+            char* a = As + (a_row + 32 * r) * PITCH + 8 * q;
+            *reinterpret_cast<uint2*>(a) = make_uint2(upper(h[1], h[0]), upper(h[3], h[2]));
+            *reinterpret_cast<uint2*>(a + PART) = make_uint2(upper(h2[1], h2[0]), upper(h2[3], h2[2]));
+            *reinterpret_cast<uint2*>(a + 2 * PART) = make_uint2(upper(h3[1], h3[0]), upper(h3[3], h3[2]));
         }
-        return o;
-    };
-    auto store_b = [&](uint32_t buf, int q, const float4& o) {
-        float* b = Bs + buf * BK * LDB + b_k * LDB + 16 * b_seg;
-        *reinterpret_cast<float4*>(b + 4 * q) = o;
     };
 
-    f32x16 acc[RT];
+    // x1 w1 has a sum of its own: the instruction rounds a sum once per 16 k, and the five others, 2^-8 of it
+    // and less, would each round the large sum again (one sum for all six:
+    // 5.8 times the error at 4608 x 512, 12544 rows, and 1.6 times that of the fp32 instruction)
+    f32x16 acc[RT], low[RT];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+        for (int v = 0; v < 16; ++v) acc[i][v] = low[i][v] = 0.0f;
+
+    auto multiply = [&]() {
+        const char* a = As + l32 * PITCH + 16 * half;
+        const char* b = Bs + (wave * 32 + l32) * PITCH + 16 * half;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {                  // 16 k each
+            bf16x8 w[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) w[p] = *reinterpret_cast<const bf16x8*>(b + p * PART + 32 * h);
+#pragma unroll
+            for (int i = 0; i < RT; ++i) {
+                bf16x8 x[3];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) x[p] = *reinterpret_cast<const bf16x8*>(a + 32 * i * PITCH + p * PART + 32 * h);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], w[0], low[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[2], low[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], w[1], low[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], w[0], low[i], 0, 0, 0);
+                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[1], low[i], 0, 0, 0);
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[0], acc[i], 0, 0, 0);
+            }
+        }
+    };
 
     const uint32_t all_steps = (n + BK - 1) / BK;
     const uint32_t kt0 = split * steps_per_split;
     const uint32_t ksteps = kt0 + steps_per_split < all_steps ? kt0 + steps_per_split : all_steps;   // one past the last
-
-    // Multiply the tile in LDS buffer `buf`; with STORE, meanwhile move the tile held in `st` to the
-    // other buffer (nobody reads it during this step), a piece at a time between the matrix
-    // instructions.
-    auto multiply = [&](uint32_t buf, bool store, const Stage& st) {
-        const float* a = As + buf * BM * LDA + l32 * LDA + 16 * half;
-        const float* b = Bs + buf * BK * LDB + wave * 32 + l32 + 16 * half * LDB;
-        // a quarter step's operands (4 k per lane) are fetched from LDS before the matrix
-        // instructions of the quarter before issue
-        float4 av[RT];
-        float bv[4];
-        float4 wv[4];                                  // the next W tile's values between lookup and store
-#pragma unroll
-        for (int q = 0; q < 4; ++q) wv[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-        for (int i = 0; i < RT; ++i) av[i] = *reinterpret_cast<const float4*>(a + 32 * i * LDA);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bv[j] = b[j * LDB];
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-            float4 nav[RT];
-            float nbv[4];
-#pragma unroll
-            for (int i = 0; i < RT; ++i) nav[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) nbv[j] = 0.0f;
-            if (qd + 1 < 4) {
-#pragma unroll
-                for (int i = 0; i < RT; ++i) nav[i] = *reinterpret_cast<const float4*>(a + 32 * i * LDA + 4 * (qd + 1));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) nbv[j] = b[(4 * (qd + 1) + j) * LDB];
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int kk = 4 * qd + j;
-                __builtin_amdgcn_sched_barrier(0);     // keep the LDS reads ahead of the matrix instructions
-#pragma unroll
-                for (int i = 0; i < RT; ++i) {
-                    const float ak = j == 0 ? av[i].x : j == 1 ? av[i].y : j == 2 ? av[i].z : av[i].w;
-                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(ak, bv[j], acc[i], 0, 0, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (store) {
-                    if (kk >= 2 && kk - 2 < RT) store_a(buf ^ 1, kk - 2, st);
-                    if (kk >= 6 && kk < 10) wv[kk - 6] = lookup_b(kk - 6, st);
-                    if (kk >= 8 && kk < 12) store_b(buf ^ 1, kk - 8, wv[kk - 8]);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < RT; ++i) av[i] = nav[i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bv[j] = nbv[j];
-        }
-    };
-    auto store_all = [&](uint32_t buf, const Stage& st) {
-#pragma unroll
-        for (int r = 0; r < RT; ++r) store_a(buf, r, st);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) store_b(buf, q, lookup_b(q, st));
-    };
-
-    // Full K steps [kt0, kfull) are pipelined: while tile kt is multiplied, tile kt + 1 (requested a
-    // step earlier) moves to LDS and tile kt + 2 is requested.  A partial last step follows on its own.
     const uint32_t nfull = n / BK;
-    const uint32_t kfull = ksteps < nfull ? ksteps : nfull;
-    Stage s0, s1;
-    __syncthreads();                                   // the table is complete before the first lookup
-    if (kt0 < kfull) {
-        load_full(kt0 * BK, s0);
-        if (kt0 + 1 < kfull) load_full((kt0 + 1) * BK, s1);
-        store_all(kt0 & 1, s0);
+    Stage st;
+    auto load = [&](uint32_t kt) { if (kt < nfull) load_full(kt * BK, st); else load_tail(kt * BK, st); };
+    if (kt0 < ksteps) load(kt0);
+    for (uint32_t kt = kt0; kt < ksteps; ++kt) {
+        __syncthreads();                               // the table is complete, the last step's tiles are read
+        store(st);
         __syncthreads();
-        for (uint32_t kt = kt0; kt < kfull; kt += 2) {
-            if (kt + 2 < kfull) load_full((kt + 2) * BK, s0);
-            multiply(kt & 1, kt + 1 < kfull, s1);
-            __syncthreads();
-            if (kt + 1 < kfull) {
-                if (kt + 3 < kfull) load_full((kt + 3) * BK, s1);
-                multiply((kt + 1) & 1, kt + 2 < kfull, s0);
-                __syncthreads();
-            }
-        }
+        if (kt + 1 < ksteps) load(kt + 1);
+        multiply();
     }
-    if (kfull < ksteps && kfull >= kt0) {              // the partial step (n is not a multiple of 32)
-        load_tail(kfull * BK, s0);
-        store_all(kfull & 1, s0);
-        __syncthreads();
-        multiply(kfull & 1, false, s0);
-    }
+
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] += low[i][v];
 
     const uint32_t col = n0 + wave * 32 + l32;
+    const uint32_t k0 = kt0 * BK, k1 = ksteps * BK < n ? ksteps * BK : n;
+    // an output that is not finite, once more in plain fp32 (rare, and only as fast as that)
+    auto redo = [&](uint32_t row) -> float {
+        const float* x = X + (uint64_t)row * ldx;
+        const IdxT* p = idx + col;
+        float v = 0.0f;
+#pragma unroll 4
+        for (uint32_t k = k0; k < k1; ++k) v = fmaf(x[k], value_of(p[(uint64_t)k * pitch]), v);
+        return v;
+    };
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
 #pragma unroll
@@ -278,6 +258,21 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
                 if (splits == 1) Y[(uint64_t)row * ldy + col] = acc[i][v];
                 else part[((uint64_t)split * B + row) * m + col] = acc[i][v];
             }
+        }
+    }
+    // (a thread reads back only what it stored itself)
+    uint32_t odd = 0;
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) odd |= (uint32_t)!(fabsf(acc[i][v]) <= 3.402823466e38f);
+    if (odd && col < m) {
+#pragma unroll 1
+        for (uint32_t e = 0; e < 16 * RT; ++e) {
+            const uint32_t v = e & 15, row = m0 + (e >> 4) * 32 + (v & 3) + 8 * (v >> 2) + 4 * half;
+            if (row >= B) continue;
+            float* y = splits == 1 ? Y + (uint64_t)row * ldy + col : part + ((uint64_t)split * B + row) * m + col;
+            if (!(fabsf(*y) <= 3.402823466e38f)) *y = redo(row);
         }
     }
 }
@@ -294,20 +289,6 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
 // ---------------------------------------------------------------------------
 constexpr int SB_NB = 8, SB_COLS = 256, SB_GROUPS = 4;     // widest layout: 64 column lanes x 4 row groups
 constexpr uint32_t kSmallMaxRows = 1024;           // rows of W per block (32 KB of X in LDS)
-
-template <typename IdxT> struct Ptr4;
-template <> struct Ptr4<uint8_t> {
-    static __device__ __forceinline__ void ld(const uint8_t* p, uint32_t* out) {
-        const uint32_t w = *reinterpret_cast<const uint32_t*>(p);
-        out[0] = w & 255u; out[1] = (w >> 8) & 255u; out[2] = (w >> 16) & 255u; out[3] = w >> 24;
-    }
-};
-template <> struct Ptr4<uint16_t> {
-    static __device__ __forceinline__ void ld(const uint16_t* p, uint32_t* out) {
-        const uint2 w = *reinterpret_cast<const uint2*>(p);
-        out[0] = w.x & 65535u; out[1] = w.x >> 16; out[2] = w.y & 65535u; out[3] = w.y >> 16;
-    }
-};
 
 template <typename IdxT, bool LUT_LDS, bool WIDE>
 __global__ void __launch_bounds__(256)
@@ -433,7 +414,7 @@ namespace hac_internal {
 
 static size_t index_gemm_lds_bytes(uint32_t k_tot, int rt)
 {
-    return sizeof(float) * (2 * 32 * rt * LDA + 2 * BK * LDB + (k_tot <= kLutLdsMax ? k_tot : 0));
+    return (size_t)(32 * rt + BN) * PITCH + (k_tot <= kLutLdsMax ? sizeof(uint2) * k_tot : 0);
 }
 
 GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m)
@@ -463,34 +444,31 @@ GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m)
     }
     const uint64_t tiles_n = (m + BN - 1) / BN;
     const uint32_t steps = (n + BK - 1) / BK;
-    // Row tiles per block: the time of a launch goes like (rounds of tiles over the CUs) x (rows per
-    // tile); blocks of up to 4 row tiles fit a CU two at a time and then share its matrix pipes.
-    // Pick the shape with the fewest padded rows per CU, the larger tile on ties (less re-reading
-    // of the index map).
-    int best_rt = kMinRT;
-    double best_cost = 1e300;
+    // Row tiles per block and K splits: the pair with the shortest estimate.  A step of 32 k takes a block
+    // about 0.47 us x (row tiles + 1.5 for the W tile) while another block shares its CU (measured:
+    // 4608 x 512, 12544 rows, 4 row tiles: 2.6 us), 0.6 of that alone; 512 blocks run at once.  With
+    // tiles for at most half of them K is split, keeping at least 8 steps per split, and the pass that adds
+    // the splits writes and reads their partial tiles (about 4 TB/s, 3 us for the launch).
+    // Relative 2-norm error against 64 bits, fp32 instruction -> bf16 parts: 4608 x 512 map, 784 rows
+    // 2.8e-7 -> 1.4e-7; pruned 60 %, 12544 rows 5.4e-7 -> 1.5e-7; 64 x 100, 5000 rows 1.0e-7 -> 4.2e-8.
+    double best = 1e300;
     for (int rt = kMinRT; rt <= kMaxRT; ++rt) {
         const uint64_t tiles = (uint64_t)((B + 32 * rt - 1) / (32 * rt)) * tiles_n;
-        const uint64_t slots = rt <= 4 ? 512 : 256;
-        const uint64_t rounds = (tiles + slots - 1) / slots;
-        const double cost = (double)rounds * rt * (rt <= 4 ? 2.0 : 1.0);
-        if (cost <= best_cost) { best_cost = cost; best_rt = rt; }
+        uint32_t splits = 1;
+        if (tiles <= 256) {
+            splits = (uint32_t)(512 / tiles);
+            const uint32_t most = steps / 8 ? steps / 8 : 1;
+            if (splits > most) splits = most;
+            if (splits > 32) splits = 32;
+        }
+        const uint32_t per = (steps + splits - 1) / splits;
+        splits = (steps + per - 1) / per;                                 // no empty split
+        const uint64_t items = tiles * splits, rounds = (items + 511) / 512;
+        double us = 0.47 * (items <= 256 ? 0.6 : 1.0) * (double)rounds * per * (rt + 1.5);
+        if (splits > 1) us += 3.0 + 2e-6 * (double)splits * B * m;
+        if (us <= best) { best = us; p.rt = (uint32_t)rt; p.tiles = tiles; p.splits = splits; p.steps_per_split = per; }
     }
-    p.rt = (uint32_t)best_rt;
-    const uint64_t tiles = (uint64_t)((B + 32 * best_rt - 1) / (32 * best_rt)) * tiles_n;
-    // a tile's K loop is serial (about 3 us per step of 32): with tiles for at most half of the
-    // CUs, K is split until there are about two work items per CU, keeping at least 8 steps per split
-    uint32_t splits = 1;
-    if (tiles <= 128) {
-        splits = (uint32_t)((512 + tiles - 1) / tiles);
-        const uint32_t most = steps / 8 ? steps / 8 : 1;
-        if (splits > most) splits = most;
-        if (splits > 32) splits = 32;
-    }
-    p.steps_per_split = (steps + splits - 1) / splits;
-    p.splits = (steps + p.steps_per_split - 1) / p.steps_per_split;       // no empty split
     p.part_bytes = p.splits > 1 ? (size_t)p.splits * B * m * sizeof(float) : 0;
-    p.tiles = tiles;
     p.steps = steps;
     return p;
 }
@@ -522,13 +500,10 @@ template <typename IdxT, bool LUT_LDS, typename... Args>
 void launch_rt(uint32_t rt, Args&&... args)
 {
     switch (rt) {
+    case 1: launch_one<IdxT, LUT_LDS, 1>(args...); break;
     case 2: launch_one<IdxT, LUT_LDS, 2>(args...); break;
     case 3: launch_one<IdxT, LUT_LDS, 3>(args...); break;
-    case 4: launch_one<IdxT, LUT_LDS, 4>(args...); break;
-    case 5: launch_one<IdxT, LUT_LDS, 5>(args...); break;
-    case 6: launch_one<IdxT, LUT_LDS, 6>(args...); break;
-    case 7: launch_one<IdxT, LUT_LDS, 7>(args...); break;
-    default: launch_one<IdxT, LUT_LDS, 8>(args...); break;
+    default: launch_one<IdxT, LUT_LDS, 4>(args...); break;
     }
 }
 

@@ -213,3 +213,39 @@ def test_im_dot_argument_checks(hac):
     X = torch.zeros((4, 2100), device=dev())
     assert lib.im_dot(C.byref(td.desc), td.tensor.data_ptr(), X.data_ptr(), 4, 2100, Y.data_ptr(), 20, None, 0, None, None) == -6
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("B,n,m", [(33, 31, 5), (64, 32, 128), (65, 33, 129), (225, 300, 20), (700, 517, 260)])
+@pytest.mark.parametrize("bits", [8, 16])
+def test_split_operands(hac, B, n, m, bits):
+    """Operands of 24 significant bits over a wide range of magnitudes, strided X; every product needs its
+    second- and third-order parts for this bound: fp32 sums of n terms in any order, (n + 8) 2^-24 |X| . |W|."""
+    rng = np.random.default_rng(B * 1000 + n + bits)
+    k = 100 if bits == 8 else 700
+    reps = (rng.standard_normal(k) * np.exp2(rng.integers(-12, 12, k))).astype(np.float32)
+    W = rng.choice(reps, (n, m))
+    W.flat[:min(k, W.size)] = reps[:min(k, W.size)]
+    X = (rng.standard_normal((B, n)) * np.exp2(rng.integers(-12, 12, (B, n)))).astype(np.float32)
+    Xd = torch.zeros((B, n + 3), device=dev())[:, :n]
+    Xd.copy_(torch.from_numpy(X))
+    Y = hac.im_dot(hac.im_encode(W).to_device(dev()), Xd).cpu().numpy().astype(np.float64)
+    err = np.abs(Y - X.astype(np.float64) @ W.astype(np.float64))
+    bound = (n + 8) * 2.0 ** -24 * (np.abs(X).astype(np.float64) @ np.abs(W).astype(np.float64))
+    assert (err <= bound).all(), float((err / bound).max())
+
+
+def test_not_finite_and_largest(hac):
+    """Infinities, NaN and values near the largest float give what fp32 products and sums give."""
+    W = workloads.make_layer(257, 130, 0.02, 0.0, 64, "kmeans", 5)
+    X = workloads.make_batch(70, 257, 3)
+    X[3, 7], X[11, 256], X[40, 0] = np.inf, np.nan, -np.inf
+    X[64, 5], X[65, 5] = 3.4e38, -3.4e38
+    X[66, 6] = np.array([0x7f800001], np.uint32).view(np.float32)[0]      # a NaN in its lowest bit only
+    Y = hac.im_dot(hac.im_encode(W).to_device(dev()), torch.from_numpy(X).to(dev())).cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = X.astype(np.float64) @ W.astype(np.float64)
+    assert np.array_equal(np.isnan(Y), np.isnan(ref)) and np.array_equal(np.isinf(Y), np.isinf(ref))
+    ok = np.isfinite(ref)
+    scale = np.abs(np.where(np.isfinite(X), X, 0)).astype(np.float64) @ np.abs(W).astype(np.float64)
+    assert (np.abs(Y[ok] - ref[ok]) <= TOL * scale[ok]).all()
+    assert np.array_equal(Y[~ok & ~np.isnan(ref)], ref[~ok & ~np.isnan(ref)])
