@@ -451,6 +451,11 @@ GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m)
     // the splits writes and reads their partial tiles (about 4 TB/s, 3 us for the launch).
     // Relative 2-norm error against 64 bits, fp32 instruction -> bf16 parts: 4608 x 512 map, 784 rows
     // 2.8e-7 -> 1.4e-7; pruned 60 %, 12544 rows 5.4e-7 -> 1.5e-7; 64 x 100, 5000 rows 1.0e-7 -> 4.2e-8.
+    // Index map (2 or 1 bytes a pointer) and partial tiles together stay within the 16 MB array of
+    // hac_dot_noalloc wherever the map does.
+    const uint64_t kRoom = (16u << 20) - 512, map8 = (uint64_t)n * ((m + 15) / 16 * 16);
+    const uint64_t room = 2 * map8 < kRoom ? kRoom - 2 * map8 : map8 < kRoom ? kRoom - map8 : ~0ull;
+    const uint64_t fit = room / ((uint64_t)B * m * sizeof(float) + 1);
     double best = 1e300;
     for (int rt = kMinRT; rt <= kMaxRT; ++rt) {
         const uint64_t tiles = (uint64_t)((B + 32 * rt - 1) / (32 * rt)) * tiles_n;
@@ -460,6 +465,7 @@ GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m)
             const uint32_t most = steps / 8 ? steps / 8 : 1;
             if (splits > most) splits = most;
             if (splits > 32) splits = 32;
+            if (splits > fit) splits = fit > 1 ? (uint32_t)fit : 1;
         }
         const uint32_t per = (steps + splits - 1) / splits;
         splits = (steps + per - 1) / per;                                 // no empty split
