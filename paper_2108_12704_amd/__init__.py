@@ -310,7 +310,8 @@ class NetBlob:
 def _adopt(lib, out, size: int) -> np.ndarray:
     """The buffer an encoder returned as an array that releases it when the last reference goes."""
     buf = (C.c_uint8 * size).from_address(out.value)
-    weakref.finalize(buf, lib.hac_free, C.c_void_p(out.value))
+    # not at exit: an array may still be alive then, and the process gives its memory back by itself
+    weakref.finalize(buf, lib.hac_free, C.c_void_p(out.value)).atexit = False
     return np.frombuffer(buf, dtype=np.uint8)
 
 
