@@ -1,5 +1,6 @@
 """The host encoders on several threads write the blob they write on one (byte for byte), and it decodes to W."""
 import os
+import time
 
 import numpy as np
 import pytest
@@ -15,9 +16,10 @@ def layer(n, m, density, k, seed):
     return W
 
 
-# one tall column, one wide row, fewer rows than parts, columns that are empty, dense without zeros, more values than fit a byte
+# one tall column, one wide row, fewer rows than parts, columns that are empty, dense without zeros, more values than fit a byte;
+# the widest matrix whose rows are scanned several at a time, the next one, and a group that does not divide 1024
 SHAPES = [(200000, 1, 0.3, 7), (1, 200000, 0.3, 7), (9, 30011, 0.5, 40), (4099, 67, 0.0, 1), (517, 523, 1.0, 300),
-          (1031, 257, 0.02, 5)]
+          (1031, 257, 0.02, 5), (3001, 64, 0.4, 9), (3001, 65, 0.4, 9), (30011, 7, 0.9, 9), (1, 1, 1.0, 1)]
 
 
 @pytest.mark.parametrize("n,m,density,k", SHAPES)
@@ -37,3 +39,33 @@ def test_threads_do_not_change_the_blob(n, m, density, k, encode):
     assert np.array_equal(blob.data, alone.data)
     assert blob.validate(deep=True) == 0
     assert np.array_equal(blob.decode_host()[0], W)
+
+
+@pytest.mark.parametrize("m", [1, 7, 64])
+def test_rows_apart_give_the_same_blob(m):
+    """Rows side by side are scanned several at a time, rows with other columns between them one by one."""
+    wide = layer(5003, m + 3, 0.3, 9, 11 + m)
+    part = wide[:, :m]
+    assert np.array_equal(hac.hac_encode(part).data, hac.hac_encode(np.ascontiguousarray(part)).data)
+
+
+@pytest.mark.parametrize("apart", [0, 1])
+def test_time_grows_with_the_size(apart):
+    """Less than one non-zero per row on one CPU: the lists that collect them must not be copied over and over.
+    Eight times the rows take eight times as long; a list that grows by a fixed amount took 64 to 100 times."""
+    def seconds(n):
+        W = np.zeros((n, 1 + apart), np.float32)[:, :1]
+        W[1:, 0] = np.where(np.random.default_rng(3).random(n - 1) < 0.3, 2.0, 0.0)
+        return min(timed(W) for _ in range(2))
+
+    def timed(W):
+        start = time.perf_counter()
+        hac.hac_encode(W)
+        return time.perf_counter() - start
+    cpus = os.sched_getaffinity(0)
+    os.sched_setaffinity(0, {min(cpus)})
+    try:
+        small, large = seconds(250_000), seconds(2_000_000)
+    finally:
+        os.sched_setaffinity(0, cpus)
+    assert large < 30 * small, (small, large)
