@@ -7,14 +7,13 @@
 // The pointers are what is read from memory (1 or 2 bytes per weight).  What bounds the product is the
 // matrix pipe: v_mfma_f32_32x32x2_f32 does 157 TFLOP/s at best, the bf16 instruction sixteen times that.
 // So every fp32 operand is written as three bf16 parts, x = x1 + x2 + x3 (8 significant bits each, 24 in
-// all: nothing of x is lost), and six of the nine products of parts are summed in fp32 on the matrix
-// cores: x1 w1, x1 w2, x2 w1, x2 w2, x1 w3, x3 w1.  The three left out are below 2^-22 of |x w| each,
-// and one rounding of the sum per 16 products of parts instead of one per two makes the result closer
-// to 64 bits than the fp32 instruction's (relative 2-norm error figures at plan_index_gemm).
-// X is split with truncations (two ANDs, two subtractions, exact) on the way to LDS, W's
+// all), and six of the nine products of parts are summed in fp32 on the matrix cores: x1 w1, x1 w2, x2 w1,
+// x2 w2, x1 w3, x3 w1.  The three left out are below 2^-23 of |x w|, and one rounding of the sum per 16 products
+// of parts instead of one per two makes the result closer to 64 bits than the fp32 instruction's
+// (relative 2-norm error figures at plan_index_gemm).  X is split with truncations on the way to LDS, W's
 // representatives once per block in the table that pointers are looked up in.
-// An infinity or NaN among the operands makes its outputs non-finite (inf - inf in the split); such an
-// output, and one that overflowed, is computed again in plain fp32 before it is stored.
+// An infinity or NaN makes the parts NaN (inf - inf): a block whose sums are not finite computes its tile with
+// the fp32 instruction instead.
 //
 // Tiling: a block of 4 wavefronts owns 32 RT batch rows x 128 columns of Y (RT = 1..4) and walks K = n
 // in steps of 32; wavefront w owns the 32 columns [32 w, 32 w + 32) of the tile and all its rows, as RT
@@ -70,8 +69,8 @@ __device__ __forceinline__ uint2 split_weight(float w)
     const uint32_t h1 = (__float_as_uint(w) + up) & 0xffff0000u;
     const float r1 = w - __uint_as_float(h1);
     const uint32_t h2 = (__float_as_uint(r1) + up) & 0xffff0000u;
-    const float r2 = r1 - __uint_as_float(h2);
-    return make_uint2((h1 >> 16) | h2, __float_as_uint(r2) >> 16);
+    const uint32_t h3 = __float_as_uint(r1 - __uint_as_float(h2));
+    return make_uint2((h1 >> 16) | h2, h3 >> 16);
 }
 
 __device__ __forceinline__ uint32_t logical_tile(uint32_t tiles_padded)
@@ -81,8 +80,10 @@ __device__ __forceinline__ uint32_t logical_tile(uint32_t tiles_padded)
     return (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
 }
 
+// (blocks per CU: as many as the LDS of a K step lets in for 2 to 4 row tiles; left to itself the compiler spends
+// registers on the fp32 pass and one block fewer fits)
 template <typename IdxT, bool LUT_LDS, int RT, bool XVEC>
-__global__ void __launch_bounds__(256, 2)
+__global__ void __launch_bounds__(256, RT == 4 ? 2 : RT == 3 ? 3 : 4)
 index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
                   const IdxT* __restrict__ idx, uint64_t pitch,          // pitch in elements, a multiple of 16
                   const float* __restrict__ codebook, uint32_t k_sym, uint32_t zero_first,
@@ -108,8 +109,6 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
     // pointer -> value; entry 0 is 0.0 when the pointers were written with an offset of one
     const uint32_t k_tot = k_sym + zero_first;
     auto value_of = [&](uint32_t p) -> float { return (zero_first && p == 0) ? 0.0f : codebook[p - zero_first]; };
-    if (LUT_LDS)
-        for (uint32_t i = t; i < k_tot; i += 256) lut[i] = split_weight(value_of(i));
     auto parts_of = [&](uint32_t p) -> uint2 { return LUT_LDS ? lut[p] : split_weight(value_of(p)); };
 
     // Global -> registers.  X: rows a_row + 32 r, k = 4 q .. 4 q + 3; map: rows 4 q .. 4 q + 3, columns
@@ -224,31 +223,98 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
     const uint32_t nfull = n / BK;
     Stage st;
     auto load = [&](uint32_t kt) { if (kt < nfull) load_full(kt * BK, st); else load_tail(kt * BK, st); };
-    if (kt0 < ksteps) load(kt0);
-    for (uint32_t kt = kt0; kt < ksteps; ++kt) {
-        __syncthreads();                               // the table is complete, the last step's tiles are read
+    // true if f holds for any thread of the block: a word per wavefront and a barrier (0.3 us less per vote than
+    // __syncthreads_or); every vote has words of its own
+    __shared__ uint32_t votes[2][4];
+    auto block_any = [&](bool f, int which) -> bool {
+        const bool mine = __any(f);
+        if (lane == 0) votes[which][wave] = mine ? 1u : 0u;
+        __syncthreads();
+        return (votes[which][0] | votes[which][1] | votes[which][2] | votes[which][3]) != 0;
+    };
+    // a sum is not finite (an infinity or NaN among the operands, or an overflow)
+    auto unfit = [&]() -> bool {
+        uint32_t bad = 0;
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) bad |= (uint32_t)!(fabsf(acc[i][v] + low[i][v]) <= 3.402823466e38f);
+        return bad != 0;
+    };
+    // a look at the first step's X: where all of X is not finite, parts are not tried first
+    load(kt0);                                         // (in flight while the table is made)
+    if (LUT_LDS)
+        for (uint32_t i = t; i < k_tot; i += 256) lut[i] = split_weight(value_of(i));
+    bool again = false;
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {
+        const float x[4] = {st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) again |= !(fabsf(x[j]) <= 3.402823466e38f);
+    }
+    again = block_any(again, 0);                       // (a barrier: the table is complete)
+    for (uint32_t kt = again ? ksteps : kt0; kt < ksteps; ++kt) {
+        __syncthreads();                               // the last step's tiles are read
         store(st);
         __syncthreads();
         if (kt + 1 < ksteps) load(kt + 1);
         multiply();
     }
-
+    if (!again) again = block_any(unfit(), 1);
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][v] += low[i][v];
 
+    // The tile once more with the fp32 instruction (157 TFLOP/s at best) where parts will not do: the same loads, one fp32
+    // value per operand in LDS.  The order of k inside a step is free as long as both operands agree:
+    // instruction kk multiplies k = kk (lanes 0..31) and k = 16 + kk (lanes 32..63), so that a lane's 16
+    // values of a step are four 128-bit reads.  It costs such a tile what it cost before parts were used, and
+    // the steps walked until that is known.
+    if (again) {
+        constexpr int P32 = BK + 4;                    // floats between rows: 16 lanes' reads fall on different banks
+        static_assert(4 * P32 <= PITCH, "the fp32 tiles take the place of the parts");
+        float* Af = reinterpret_cast<float*>(As);
+        float* Bf = reinterpret_cast<float*>(Bs);
+        if (LUT_LDS)
+            for (uint32_t i = t; i < k_tot; i += 256) lut[i].x = __float_as_uint(value_of(i));   // (the vote was a barrier)
+        auto fp32_of = [&](uint32_t p) -> float { return LUT_LDS ? __uint_as_float(lut[p].x) : value_of(p); };
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+        load(kt0);
+        for (uint32_t kt = kt0; kt < ksteps; ++kt) {
+            __syncthreads();
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float w[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) w[j] = fp32_of(Ptr4<IdxT>::get(st.rb[j], c));
+                *reinterpret_cast<float4*>(Bf + (b_col + c) * P32 + 4 * q) = make_float4(w[0], w[1], w[2], w[3]);
+            }
+#pragma unroll
+            for (int r = 0; r < RT; ++r) *reinterpret_cast<float4*>(Af + (a_row + 32 * r) * P32 + 4 * q) = st.ra[r];
+            __syncthreads();
+            if (kt + 1 < ksteps) load(kt + 1);
+            const float* a = Af + l32 * P32 + 16 * half;
+            const float* b = Bf + (wave * 32 + l32) * P32 + 16 * half;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const float4 w4 = *reinterpret_cast<const float4*>(b + 4 * h);
+                const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    const float4 x4 = *reinterpret_cast<const float4*>(a + 32 * i * P32 + 4 * h);
+                    const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[j], w[j], acc[i], 0, 0, 0);
+                }
+            }
+        }
+    }
+
     const uint32_t col = n0 + wave * 32 + l32;
-    const uint32_t k0 = kt0 * BK, k1 = ksteps * BK < n ? ksteps * BK : n;
-    // an output that is not finite, once more in plain fp32 (rare, and only as fast as that)
-    auto redo = [&](uint32_t row) -> float {
-        const float* x = X + (uint64_t)row * ldx;
-        const IdxT* p = idx + col;
-        float v = 0.0f;
-#pragma unroll 4
-        for (uint32_t k = k0; k < k1; ++k) v = fmaf(x[k], value_of(p[(uint64_t)k * pitch]), v);
-        return v;
-    };
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
 #pragma unroll
@@ -258,21 +324,6 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
                 if (splits == 1) Y[(uint64_t)row * ldy + col] = acc[i][v];
                 else part[((uint64_t)split * B + row) * m + col] = acc[i][v];
             }
-        }
-    }
-    // (a thread reads back only what it stored itself)
-    uint32_t odd = 0;
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) odd |= (uint32_t)!(fabsf(acc[i][v]) <= 3.402823466e38f);
-    if (odd && col < m) {
-#pragma unroll 1
-        for (uint32_t e = 0; e < 16 * RT; ++e) {
-            const uint32_t v = e & 15, row = m0 + (e >> 4) * 32 + (v & 3) + 8 * (v >> 2) + 4 * half;
-            if (row >= B) continue;
-            float* y = splits == 1 ? Y + (uint64_t)row * ldy + col : part + ((uint64_t)split * B + row) * m + col;
-            if (!(fabsf(*y) <= 3.402823466e38f)) *y = redo(row);
         }
     }
 }
@@ -491,7 +542,7 @@ void launch_one(dim3 grid, size_t lds, hipStream_t stream, hipError_t& err,
                 uint32_t tiles, uint32_t x_vec, uint32_t splits, uint32_t steps_per_split, float* d_part)
 {
     auto k = x_vec ? index_gemm_kernel<IdxT, LUT_LDS, RT, true> : index_gemm_kernel<IdxT, LUT_LDS, RT, false>;
-    if (lds > 64 * 1024) {
+    if (lds > 63 * 1024) {                             // (the votes take some of the 64 KB a kernel gets without asking)
         err = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err != hipSuccess) return;
     }

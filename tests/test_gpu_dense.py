@@ -249,3 +249,58 @@ def test_not_finite_and_largest(hac):
     scale = np.abs(np.where(np.isfinite(X), X, 0)).astype(np.float64) @ np.abs(W).astype(np.float64)
     assert (np.abs(Y[ok] - ref[ok]) <= TOL * scale[ok]).all()
     assert np.array_equal(Y[~ok & ~np.isnan(ref)], ref[~ok & ~np.isnan(ref)])
+
+
+def product_bound(X, W, factor):
+    """factor 2^-24 |X| . |W|, and what lies below the smallest fp32."""
+    return factor * 2.0 ** -24 * (np.abs(X).astype(np.float64) @ np.abs(W).astype(np.float64)) + X.shape[1] * 2.0 ** -149
+
+
+# every row tile count, one and several K splits, pointers of 8 and 16 bits, a value list that fits LDS and one that does not
+@pytest.mark.parametrize("B,n,m,k", [(33, 700, 130, 64), (100, 2100, 40, 300), (300, 96, 1000, 64), (2000, 257, 520, 5000)])
+@pytest.mark.parametrize("where", ["first", "last", "all"])
+def test_rows_that_are_not_finite(hac, B, n, m, k, where):
+    """A tile with infinities or NaN is computed in fp32: those rows are what fp32 gives, the others stay right."""
+    rng = np.random.default_rng(B + n)
+    reps = rng.standard_normal(k).astype(np.float32)
+    W = rng.choice(reps, (n, m))
+    X = rng.standard_normal((B, n)).astype(np.float32)
+    rows = np.arange(0, B, 7)
+    if where == "all":
+        X[rows] = np.nan
+        X[rows + 1 - (rows + 1) // B] = np.inf
+    else:
+        X[rows, 0 if where == "first" else n - 1] = np.where(np.arange(rows.size) % 2, np.nan, -np.inf)
+    print(f"[case] not finite {where}: {B} x {n} x {m}, k = {k}", flush=True)
+    Y = hac.im_dot(hac.im_encode(W).to_device(dev()), torch.from_numpy(X).to(dev())).cpu().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = X.astype(np.float64) @ W.astype(np.float64)
+    assert np.array_equal(np.isnan(Y), np.isnan(ref)) and np.array_equal(np.isinf(Y), np.isinf(ref))
+    assert np.array_equal(Y[np.isinf(ref)], ref[np.isinf(ref)])
+    ok = np.isfinite(X).all(axis=1)
+    assert (np.abs(Y[ok] - ref[ok]) <= product_bound(X[ok], W, n + 8)).all()
+
+
+def test_a_batch_of_nan_costs_about_as_much(hac):
+    """The fp32 tile pass takes about twice the time of the parts (1.6 to 2.7 times as measured); one thread per output took 60 times."""
+    B, n, m = 784, 2304, 512
+    db = hac.im_encode(np.random.default_rng(1).choice(np.linspace(-1, 1, 50).astype(np.float32), (n, m))).to_device(dev())
+    Y = torch.empty((B, m), device=dev())
+    ws = torch.empty(hac.hac_workspace_bytes(db.desc, B) + 256, dtype=torch.uint8, device=dev())
+
+    def seconds(X):
+        best = float("inf")
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                hac.im_dot(db, X, Y=Y, workspace=ws)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+    X = torch.randn((B, n), device=dev())
+    plain = seconds(X)
+    X[:, n // 2] = float("nan")
+    assert seconds(X) < 8 * plain
+    assert seconds(torch.full_like(X, float("inf"))) < 8 * plain
