@@ -12,8 +12,9 @@
 // of parts instead of one per two makes the result closer to 64 bits than the fp32 instruction's
 // (relative 2-norm error figures at plan_index_gemm).  X is split with truncations on the way to LDS, W's
 // representatives once per block in the table that pointers are looked up in.
-// An infinity or NaN makes the parts NaN (inf - inf): a block whose sums are not finite computes its tile with
-// the fp32 instruction instead.
+// Below 2^-110 a third part has no room for the last bits, and an infinity or NaN makes the parts NaN
+// (inf - inf).  A block that meets such an operand, or whose sums are not finite, computes its tile with the fp32
+// instruction instead.
 //
 // Tiling: a block of 4 wavefronts owns 32 RT batch rows x 128 columns of Y (RT = 1..4) and walks K = n
 // in steps of 32; wavefront w owns the 32 columns [32 w, 32 w + 32) of the tile and all its rows, as RT
@@ -63,13 +64,16 @@ template <> struct Ptr4<uint16_t> {
 
 // w = w1 + w2 + w3: { w1 | w2 << 16, w3 }.  Rounded to nearest (ties upwards in magnitude), so that the
 // parts' signs vary and the left-out products have no bias; cut off instead where rounding could overflow.
-__device__ __forceinline__ uint2 split_weight(float w)
+// `cut` collects the third parts' fp32 patterns: what a bf16 has no room for is in the lower 16 bits (not
+// zero below 2^-110 only).
+__device__ __forceinline__ uint2 split_weight(float w, uint32_t& cut)
 {
     const uint32_t up = fabsf(w) < 1e38f ? 0x8000u : 0u;
     const uint32_t h1 = (__float_as_uint(w) + up) & 0xffff0000u;
     const float r1 = w - __uint_as_float(h1);
     const uint32_t h2 = (__float_as_uint(r1) + up) & 0xffff0000u;
     const uint32_t h3 = __float_as_uint(r1 - __uint_as_float(h2));
+    cut |= h3;
     return make_uint2((h1 >> 16) | h2, h3 >> 16);
 }
 
@@ -109,7 +113,8 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
     // pointer -> value; entry 0 is 0.0 when the pointers were written with an offset of one
     const uint32_t k_tot = k_sym + zero_first;
     auto value_of = [&](uint32_t p) -> float { return (zero_first && p == 0) ? 0.0f : codebook[p - zero_first]; };
-    auto parts_of = [&](uint32_t p) -> uint2 { return LUT_LDS ? lut[p] : split_weight(value_of(p)); };
+    uint32_t cut = 0;                                  // lower half not 0: some operand is more than its three parts
+    auto parts_of = [&](uint32_t p) -> uint2 { return LUT_LDS ? lut[p] : split_weight(value_of(p), cut); };
 
     // Global -> registers.  X: rows a_row + 32 r, k = 4 q .. 4 q + 3; map: rows 4 q .. 4 q + 3, columns
     // b_col .. b_col + 3 (four k of a column in one thread, so that a part of them is one 64-bit store).
@@ -178,6 +183,10 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
                 h2[j] = __float_as_uint(r1);
                 h3[j] = __float_as_uint(r1 - __uint_as_float(h2[j] & 0xffff0000u));
             }
+            // (two three-operand ORs; from plain C the compiler reorders the whole step around them: 336 -> 359 us at
+            // 4608 x 512, 12544 rows)
+            asm("v_or3_b32 %0, %1, %2, %0" : "+v"(cut) : "v"(h3[0]), "v"(h3[1]));
+            asm("v_or3_b32 %0, %1, %2, %0" : "+v"(cut) : "v"(h3[2]), "v"(h3[3]));
             char* a = As + (a_row + 32 * r) * PITCH + 8 * q;
             *reinterpret_cast<uint2*>(a) = make_uint2(upper(h[1], h[0]), upper(h[3], h[2]));
             *reinterpret_cast<uint2*>(a + PART) = make_uint2(upper(h2[1], h2[0]), upper(h2[3], h2[2]));
@@ -232,25 +241,26 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
         __syncthreads();
         return (votes[which][0] | votes[which][1] | votes[which][2] | votes[which][3]) != 0;
     };
-    // a sum is not finite (an infinity or NaN among the operands, or an overflow)
+    // an operand was cut short, or a sum is not finite (an infinity or NaN among the operands, or an overflow)
     auto unfit = [&]() -> bool {
-        uint32_t bad = 0;
+        uint32_t bad = cut & 0xffffu;
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) bad |= (uint32_t)!(fabsf(acc[i][v] + low[i][v]) <= 3.402823466e38f);
         return bad != 0;
     };
-    // a look at the first step's X: where all of X is not finite, parts are not tried first
+    // a look at the first step's X (non-finite, or small enough to be cut) and at the table: where all of X, or a
+    // representative, is like this, parts are not tried first
     load(kt0);                                         // (in flight while the table is made)
     if (LUT_LDS)
-        for (uint32_t i = t; i < k_tot; i += 256) lut[i] = split_weight(value_of(i));
-    bool again = false;
+        for (uint32_t i = t; i < k_tot; i += 256) lut[i] = split_weight(value_of(i), cut);
+    bool again = (cut & 0xffffu) != 0;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
         const float x[4] = {st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) again |= !(fabsf(x[j]) <= 3.402823466e38f);
+        for (int j = 0; j < 4; ++j) again |= !(fabsf(x[j]) <= 3.402823466e38f) || (x[j] != 0.0f && fabsf(x[j]) < 0x1p-110f);
     }
     again = block_any(again, 0);                       // (a barrier: the table is complete)
     for (uint32_t kt = again ? ksteps : kt0; kt < ksteps; ++kt) {

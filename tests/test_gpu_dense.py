@@ -304,3 +304,31 @@ def test_a_batch_of_nan_costs_about_as_much(hac):
     X[:, n // 2] = float("nan")
     assert seconds(X) < 8 * plain
     assert seconds(torch.full_like(X, float("inf"))) < 8 * plain
+
+
+# exponents of X and of W: at and below where a third bf16 part runs out of room, subnormal X, W, and products just above
+# the smallest normal number from operands that are not small
+@pytest.mark.parametrize("ex,ew", [(-104, 0), (-109, 0), (-111, 0), (-118, 20), (-126, 20), (-135, 30), (0, -109), (0, -118), (20, -126), (-70, -50)])
+@pytest.mark.parametrize("B,n,m,k", [(33, 700, 130, 64), (300, 96, 200, 5000)])
+def test_small_operands(hac, ex, ew, B, n, m, k):
+    """Operands of any size keep all their bits (as products and sums of fp32 do)."""
+    rng = np.random.default_rng(B + 200 + ex)
+    W = rng.choice((rng.uniform(1, 2, k) * 2.0 ** ew).astype(np.float32), (n, m))        # one sign: bits that are cut add up
+    X = (rng.uniform(1, 2, (B, n)) * 2.0 ** ex).astype(np.float32)
+    print(f"[case] small operands 2^{ex} x 2^{ew}", flush=True)
+    Y = hac.im_dot(hac.im_encode(W).to_device(dev()), torch.from_numpy(X).to(dev())).cpu().numpy().astype(np.float64)
+    err = np.abs(Y - X.astype(np.float64) @ W.astype(np.float64))
+    assert (err <= product_bound(X, W, n + 8)).all()
+
+
+def test_small_operands_among_others(hac):
+    """One small entry in an otherwise empty row, one representative that is small, each at the end of a long loop."""
+    rng = np.random.default_rng(4)
+    n, m, B = 1100, 140, 70
+    X = rng.standard_normal((B, n)).astype(np.float32)
+    X[9], X[9, n - 1] = 0.0, np.float32(1.2345678 * 2.0 ** -118)
+    W = rng.choice(rng.standard_normal(50).astype(np.float32), (n, m))
+    W[:, 3], W[n - 2, 3] = 0.0, np.float32(1.7654321 * 2.0 ** -115)
+    Y = hac.im_dot(hac.im_encode(W).to_device(dev()), torch.from_numpy(X).to(dev())).cpu().numpy().astype(np.float64)
+    err = np.abs(Y - X.astype(np.float64) @ W.astype(np.float64))
+    assert (err <= product_bound(X, W, n + 8)).all()
