@@ -8,10 +8,10 @@
 // matrix pipe: v_mfma_f32_32x32x2_f32 does 157 TFLOP/s at best, the bf16 instruction sixteen times that.
 // So every fp32 operand is written as three bf16 parts, x = x1 + x2 + x3 (8 significant bits each, 24 in
 // all), and six of the nine products of parts are summed in fp32 on the matrix cores: x1 w1, x1 w2, x2 w1,
-// x2 w2, x1 w3, x3 w1.  The three left out are below 2^-23 of |x w|, and one rounding of the sum per 16 products
+// x2 w2, x1 w3, x3 w1.  The three left out are together below 2^-25 of |x w|, and one rounding of the sum per 16 products
 // of parts instead of one per two makes the result closer to 64 bits than the fp32 instruction's
-// (relative 2-norm error figures at plan_index_gemm).  X is split with truncations on the way to LDS, W's
-// representatives once per block in the table that pointers are looked up in.
+// (relative 2-norm error figures at plan_index_gemm).  X is split on the way to LDS, W's representatives once per block in
+// the table that pointers are looked up in; every part is rounded to nearest.
 // Below 2^-110 a third part has no room for the last bits, and an infinity or NaN makes the parts NaN
 // (inf - inf).  A block that meets such an operand, or whose sums are not finite, computes its tile with the fp32
 // instruction instead.
@@ -76,6 +76,11 @@ __device__ __forceinline__ uint2 split_weight(float w, uint32_t& cut)
     cut |= h3;
     return make_uint2((h1 >> 16) | h2, h3 >> 16);
 }
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t two_bf16(f32x2 v) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2)); }   // to nearest even
+__device__ __forceinline__ f32x2 two_f32(uint32_t p) { return f32x2{__uint_as_float(p << 16), __uint_as_float(p & 0xffff0000u)}; }
 
 __device__ __forceinline__ uint32_t logical_tile(uint32_t tiles_padded)
 {
@@ -175,22 +180,23 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
             const float x[4] = {st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w};
-            uint32_t h[4], h2[4], h3[4];
+            uint32_t p1[2], p2[2], p3[2];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                h[j] = __float_as_uint(x[j]);
-                const float r1 = x[j] - __uint_as_float(h[j] & 0xffff0000u);
-                h2[j] = __float_as_uint(r1);
-                h3[j] = __float_as_uint(r1 - __uint_as_float(h2[j] & 0xffff0000u));
+            for (int j = 0; j < 2; ++j) {
+                const f32x2 v = {x[2 * j], x[2 * j + 1]};
+                p1[j] = two_bf16(v);
+                const f32x2 r1 = v - two_f32(p1[j]);
+                p2[j] = two_bf16(r1);
+                const f32x2 r2 = r1 - two_f32(p2[j]);
+                p3[j] = two_bf16(r2);
+                // (a three-operand OR; from plain C the compiler reorders the whole step around it: 336 -> 359 us at
+                // 4608 x 512, 12544 rows)
+                asm("v_or3_b32 %0, %1, %2, %0" : "+v"(cut) : "v"(r2.x), "v"(r2.y));
             }
-            // (two three-operand ORs; from plain C the compiler reorders the whole step around them: 336 -> 359 us at
-            // 4608 x 512, 12544 rows)
-            asm("v_or3_b32 %0, %1, %2, %0" : "+v"(cut) : "v"(h3[0]), "v"(h3[1]));
-            asm("v_or3_b32 %0, %1, %2, %0" : "+v"(cut) : "v"(h3[2]), "v"(h3[3]));
             char* a = As + (a_row + 32 * r) * PITCH + 8 * q;
-            *reinterpret_cast<uint2*>(a) = make_uint2(upper(h[1], h[0]), upper(h[3], h[2]));
-            *reinterpret_cast<uint2*>(a + PART) = make_uint2(upper(h2[1], h2[0]), upper(h2[3], h2[2]));
-            *reinterpret_cast<uint2*>(a + 2 * PART) = make_uint2(upper(h3[1], h3[0]), upper(h3[3], h3[2]));
+            *reinterpret_cast<uint2*>(a) = make_uint2(p1[0], p1[1]);
+            *reinterpret_cast<uint2*>(a + PART) = make_uint2(p2[0], p2[1]);
+            *reinterpret_cast<uint2*>(a + 2 * PART) = make_uint2(p3[0], p3[1]);
         }
     };
 
@@ -255,7 +261,7 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
     load(kt0);                                         // (in flight while the table is made)
     if (LUT_LDS)
         for (uint32_t i = t; i < k_tot; i += 256) lut[i] = split_weight(value_of(i), cut);
-    bool again = (cut & 0xffffu) != 0;
+    bool again = (cut & 0xffffu) != 0 || n == 1;
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
         const float x[4] = {st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w};

@@ -332,3 +332,21 @@ def test_small_operands_among_others(hac):
     Y = hac.im_dot(hac.im_encode(W).to_device(dev()), torch.from_numpy(X).to(dev())).cpu().numpy().astype(np.float64)
     err = np.abs(Y - X.astype(np.float64) @ W.astype(np.float64))
     assert (err <= product_bound(X, W, n + 8)).all()
+
+
+@pytest.mark.parametrize("n,terms", [(1, 1), (2, 2), (700, 1), (700, 2), (700, 4), (700, 8), (4608, 1)])
+def test_sums_of_few_terms(hac, n, terms):
+    """Short sums, and long ones of which few terms are not zero: (terms + 1) 2^-24 |X| . |W|.  That is the
+    rounding of the result (2^-24), the products of parts left out (together 2^-25) and terms - 1 roundings on
+    the way; the fp32 instruction's own sums come to `terms` roundings.  A product alone (n = 1) is the fp32 product."""
+    rng = np.random.default_rng(n + terms)
+    B, m = 300, 150
+    W = rng.choice(rng.standard_normal(60).astype(np.float32), (n, m))
+    X = np.zeros((B, n), np.float32)
+    for b in range(B):
+        X[b, rng.permutation(n)[:terms]] = rng.standard_normal(terms)
+    Y = hac.im_dot(hac.im_encode(W).to_device(dev()), torch.from_numpy(X).to(dev())).cpu().numpy()
+    err = np.abs(Y.astype(np.float64) - X.astype(np.float64) @ W.astype(np.float64))
+    assert (err <= product_bound(X, W, terms + 1)).all()
+    if n == 1:
+        assert np.array_equal(Y, X * W)
