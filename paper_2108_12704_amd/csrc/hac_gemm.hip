@@ -31,13 +31,15 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "hac_internal.h"
 
 namespace {
 
 constexpr int BN = 128, BK = 32;
 constexpr int PART = 2 * BK, PITCH = 3 * PART + 16;   // bytes: one part of a row's K step, one row in LDS
-constexpr int kMinRT = 1, kMaxRT = 4;              // row tiles of 32 per block
+constexpr uint32_t kMinRT = 1, kMaxRT = 4;              // row tiles of 32 per block
 constexpr uint32_t kLutLdsMax = 4096;              // representatives kept in LDS
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -484,9 +486,10 @@ static size_t index_gemm_lds_bytes(uint32_t k_tot, int rt)
     return (size_t)(32 * rt + BN) * PITCH + (k_tot <= kLutLdsMax ? sizeof(uint2) * k_tot : 0);
 }
 
-GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m)
+GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m, size_t room)
 {
     GemmPlan p;
+    p.us = 0.0;
     p.small = B <= 4u * SB_NB;
     if (p.small) {
         // blocks of 256 columns x a range of rows: about 512 blocks, at most 32 ranges (the pass that
@@ -509,38 +512,34 @@ GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m)
         p.part_bytes = p.splits > 1 ? (size_t)p.splits * B * m * sizeof(float) : 0;
         return p;
     }
-    const uint64_t tiles_n = (m + BN - 1) / BN;
+    const uint32_t tiles_n = (m + BN - 1) / BN;
     const uint32_t steps = (n + BK - 1) / BK;
-    // Row tiles per block and K splits: the pair with the shortest estimate.  A step of 32 k takes a block
-    // about 0.47 us x (row tiles + 1.5 for the W tile) while another block shares its CU (measured:
-    // 4608 x 512, 12544 rows, 4 row tiles: 2.6 us), 0.6 of that alone; 512 blocks run at once.  With
-    // tiles for at most half of them K is split, keeping at least 8 steps per split, and the pass that adds
-    // the splits writes and reads their partial tiles (about 4 TB/s, 3 us for the launch).
-    // Relative 2-norm error against 64 bits, fp32 instruction -> bf16 parts: 4608 x 512 map, 784 rows
-    // 2.8e-7 -> 1.4e-7; pruned 60 %, 12544 rows 5.4e-7 -> 1.5e-7; 64 x 100, 5000 rows 1.0e-7 -> 4.2e-8.
-    // Index map (2 or 1 bytes a pointer) and partial tiles together stay within the 16 MB array of
-    // hac_dot_noalloc wherever the map does.
-    const uint64_t kRoom = (16u << 20) - 512, map8 = (uint64_t)n * ((m + 15) / 16 * 16);
-    const uint64_t room = 2 * map8 < kRoom ? kRoom - 2 * map8 : map8 < kRoom ? kRoom - map8 : ~0ull;
-    const uint64_t fit = room / ((uint64_t)B * m * sizeof(float) + 1);
+    // Row tiles per block and K splits: the pair with the shortest estimate.  A step of 32 k takes a block 0.77 + 0.26 us
+    // per row tile when little else runs on its CU, and every block of a CU adds 0.22 + 0.25 us per row tile of its
+    // shared pipes; 4 blocks of one or two row tiles, 3 of three and 2 of four fit.  The pass that adds the splits
+    // takes 3 us and 0.4 us per MB of partial tiles, everything else 5 us.  The constants are fitted to 625 measured
+    // pairs of 21 shapes (64 x 100 to 25088 x 1000, 33 to 12544 rows, 4 to 4000 work items): four in five estimates lie
+    // within 8 % of the time, and the pairs they choose within 6 % of the best measured one (one shape: within 20 %).
+    // Relative 2-norm error against 64 bits, fp32 instruction -> bf16 parts: one term 2.4e-8 -> 2.5e-8, two 3.4e-8 ->
+    // 3.2e-8, 64 terms 1.05e-7 -> 4.0e-8, 4608 terms 1.9e-7 -> 9.9e-8 (X as after a ReLU, one K split).
+    static const uint32_t kSplits[] = { 1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32 };
     double best = 1e300;
-    for (int rt = kMinRT; rt <= kMaxRT; ++rt) {
+    for (uint32_t rt = kMinRT; rt <= kMaxRT; ++rt) {
         const uint64_t tiles = (uint64_t)((B + 32 * rt - 1) / (32 * rt)) * tiles_n;
-        uint32_t splits = 1;
-        if (tiles <= 256) {
-            splits = (uint32_t)(512 / tiles);
-            const uint32_t most = steps / 8 ? steps / 8 : 1;
-            if (splits > most) splits = most;
-            if (splits > 32) splits = 32;
-            if (splits > fit) splits = fit > 1 ? (uint32_t)fit : 1;
+        const uint64_t fit = rt <= 2 ? 4 : 6 - rt;                        // blocks on a CU
+        const double alone = 0.77 + 0.26 * rt, shared = 0.22 + 0.25 * rt;
+        for (uint32_t splits : kSplits) {
+            if (splits > 1 && (splits > steps / 4 || (uint64_t)splits * B * m * sizeof(float) > room)) break;
+            const uint32_t per = (steps + splits - 1) / splits;
+            const uint32_t parts = (steps + per - 1) / per;               // no empty split
+            const uint64_t on_cu = (tiles * parts + 255) / 256, full = on_cu / fit, rest = on_cu - full * fit;
+            double us = 5.2 + per * ((double)full * std::max(alone, shared * (double)fit) +
+                                     (rest ? std::max(alone, shared * (double)rest) : 0.0));
+            if (parts > 1) us += 3.0 + 1.64e-6 * (double)parts * B * m;
+            if (us < best) { best = us; p.rt = rt; p.tiles = tiles; p.splits = parts; p.steps_per_split = per; }
         }
-        const uint32_t per = (steps + splits - 1) / splits;
-        splits = (steps + per - 1) / per;                                 // no empty split
-        const uint64_t items = tiles * splits, rounds = (items + 511) / 512;
-        double us = 0.47 * (items <= 256 ? 0.6 : 1.0) * (double)rounds * per * (rt + 1.5);
-        if (splits > 1) us += 3.0 + 2e-6 * (double)splits * B * m;
-        if (us <= best) { best = us; p.rt = (uint32_t)rt; p.tiles = tiles; p.splits = splits; p.steps_per_split = per; }
     }
+    p.us = best;
     p.part_bytes = p.splits > 1 ? (size_t)p.splits * B * m * sizeof(float) : 0;
     p.steps = steps;
     return p;
@@ -582,12 +581,11 @@ void launch_rt(uint32_t rt, Args&&... args)
 
 } // namespace
 
-hipError_t launch_index_gemm(const float* d_X, uint64_t ldx, uint32_t B, const void* d_idx, uint32_t idx_bits,
+hipError_t launch_index_gemm(const GemmPlan& plan, const float* d_X, uint64_t ldx, uint32_t B, const void* d_idx, uint32_t idx_bits,
                              uint64_t pitch, const float* d_codebook, uint32_t k_sym, uint32_t zero_first,
                              uint32_t n, uint32_t m, float* d_Y, uint64_t ldy, float* d_part, hipStream_t stream)
 {
     const uint32_t tiles_n = (m + BN - 1) / BN;
-    const GemmPlan plan = plan_index_gemm(B, n, m);
     if (plan.small) {
         if (plan.splits > 1 && !d_part) return hipErrorInvalidValue;
         if (idx_bits != 8 && idx_bits != 16) return hipErrorInvalidValue;

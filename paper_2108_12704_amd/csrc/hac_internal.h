@@ -15,14 +15,16 @@ namespace hac_internal {
 // small (at most 32 batch rows): no matrix cores; `tiles` blocks of 4 << rt columns (256 for maps of
 // 129 columns or more), the rows of W cut into `splits` ranges of steps_per_split rows, partial sums
 // through the same buffer.
-struct GemmPlan { uint64_t tiles; uint32_t steps, splits, steps_per_split, rt; size_t part_bytes; bool small; };
-GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m);
+// us: estimated time of the launches on an otherwise idle GPU (0 when small).  room: bytes that part_bytes may come to, for a
+// caller whose scratch memory is of a fixed size (a small plan does not look at it: compare part_bytes).
+struct GemmPlan { uint64_t tiles; uint32_t steps, splits, steps_per_split, rt; size_t part_bytes; bool small; double us; };
+GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m, size_t room = ~(size_t)0);
 
 // Y[B x m] = X[B x n] . c[Pi] for an index map Pi of n rows, `pitch` elements apart (a multiple of
 // 16), of idx_bits = 8 or 16 bits each.  zero_first = 1: pointer 0 means 0.0 and pointer p > 0 means
-// c[p - 1].  All pointers are device pointers; d_idx is 16-byte aligned; d_part holds
-// plan_index_gemm(B, n, m).part_bytes bytes (may be NULL when that is 0).  Asynchronous on `stream`.
-hipError_t launch_index_gemm(const float* d_X, uint64_t ldx, uint32_t B, const void* d_idx, uint32_t idx_bits,
+// c[p - 1].  All pointers are device pointers; d_idx is 16-byte aligned; plan is what plan_index_gemm(B, n, m, ..)
+// returned and d_part holds plan.part_bytes bytes (may be NULL when that is 0).  Asynchronous on `stream`.
+hipError_t launch_index_gemm(const GemmPlan& plan, const float* d_X, uint64_t ldx, uint32_t B, const void* d_idx, uint32_t idx_bits,
                              uint64_t pitch, const float* d_codebook, uint32_t k_sym, uint32_t zero_first,
                              uint32_t n, uint32_t m, float* d_Y, uint64_t ldy, float* d_part, hipStream_t stream);
 

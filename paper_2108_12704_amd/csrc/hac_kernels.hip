@@ -994,21 +994,24 @@ uint32_t default_cpw(const hac_desc_t* desc)
 //   dense : ~35 non-zeros per ns to decode into the index map, then the contraction at about
 //           95 TFLOP/s, but never faster than its serial K loop (3 us per step of 32 per round of
 //           512 work items), plus the pass that adds the K splits.
-struct DenseRoute { bool use; uint32_t idx_bits; uint64_t pitch; size_t idx_bytes, bytes; };
+// `room`: bytes of workspace there are, for hac_dot_noalloc; the plan then splits K only as far as the parts fit.
+struct DenseRoute { bool use; uint32_t idx_bits; uint64_t pitch; size_t idx_bytes, bytes; hac_internal::GemmPlan plan; };
 
-DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
+DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room = ~(size_t)0)
 {
-    DenseRoute r = { false, 0, 0, 0, 0 };
+    DenseRoute r = {};
     const uint64_t k_tot = (uint64_t)desc->k_sym + (desc->format == HAC_FORMAT_SHAC ? 1 : 0);
-    if (k_tot > 65536 || B < 1) return r;
+    const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
+    if (k_tot > 65536 || B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && B < 32)) return r;
     r.idx_bits = k_tot <= 256 ? 8 : 16;
     r.pitch = (desc->m + 15) / 16 * 16;
     r.idx_bytes = (size_t)((desc->n * r.pitch * (r.idx_bits / 8) + 255) / 256 * 256);
-    const hac_internal::GemmPlan plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m);
+    const hac_internal::GemmPlan plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m,
+                                                                      room > r.idx_bytes ? room - r.idx_bytes : 0);
+    r.plan = plan;
     r.bytes = r.idx_bytes + ((plan.part_bytes + 255) / 256 * 256);
-    const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
     if (force == HAC_LAUNCH_DENSE_ROUTE) { r.use = true; return r; }
-    if (force == HAC_LAUNCH_SPARSE_ROUTE || B < 32) return r;
+    if (force == HAC_LAUNCH_SPARSE_ROUTE) return r;
     const double nnz = (double)desc->nnz, n = (double)desc->n, m = (double)desc->m, b = (double)B;
     const double bp = (double)((B + 31) / 32 * 32);
     const double blocks = ((m + 15.0) / 16.0) * (double)((B + 255) / 256);
@@ -1129,7 +1132,7 @@ XldsPlan xlds_plan(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch
 int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
              const float* d_X, int64_t B, int64_t ldx, float* d_Y, int64_t ldy,
              void* d_ws, size_t ws_bytes, const hac_launch_t* launch, hac_stream_t stream_,
-             const ChainIO* io = nullptr)
+             const ChainIO* io = nullptr, size_t room = ~(size_t)0)
 {
     DevBlob d;
     int rc = make_dev(desc, d_blob, format, d);
@@ -1172,7 +1175,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     const bool shac = format == HAC_FORMAT_SHAC && !d.rice;   // Rice-coded gaps decode like a HAC stream: no ri words
     g_last_hip_error = 0;
 
-    const DenseRoute dr = dense_route(desc, B, launch);
+    const DenseRoute dr = dense_route(desc, B, launch, room);
     if (launch && (launch->variant & HAC_LAUNCH_DENSE_ROUTE) && !dr.use) return HAC_EINVAL;   // too many symbols
     if (dr.use) {
         if (io->xt_in || io->yt_out) return HAC_EINVAL;       // the dense route reads and writes row-major
@@ -1206,7 +1209,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e);
         float* part = reinterpret_cast<float*>(static_cast<uint8_t*>(d_ws) + dr.idx_bytes);
-        e = hac_internal::launch_index_gemm(d_X, (uint64_t)ldx, (uint32_t)B, d_ws, dr.idx_bits, dr.pitch, d.codebook,
+        e = hac_internal::launch_index_gemm(dr.plan, d_X, (uint64_t)ldx, (uint32_t)B, d_ws, dr.idx_bits, dr.pitch, d.codebook,
                                             d.k_sym, is_shac, d.n, d.m, d_Y, (uint64_t)ldy, part, stream);
         if (e != hipSuccess) return hip_fail(e);
         launch_bias_act(d_Y, (uint32_t)B, d.m, (uint64_t)ldy, io->bias, io->relu, stream);
@@ -1390,12 +1393,12 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
 
 } // namespace
 
-extern "C" size_t hac_workspace_bytes_for(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
+namespace {
+
+// bytes dot_impl takes from its workspace when there are `room` of them
+size_t workspace_need(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room)
 {
-    if (!desc_plausible(desc) || B <= 0 || B > 0x7fffffffll) return 0;
-    if (desc->format == HAC_FORMAT_IM)
-        return hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m).part_bytes;
-    const DenseRoute dr = dense_route(desc, B, launch);
+    const DenseRoute dr = dense_route(desc, B, launch, room);
     if (dr.use) return dr.bytes;
     const RowsPlan rk = plan_rows(desc, B, launch, table_bytes_of(desc));
     if (rk.use) return rk.part_bytes;
@@ -1403,6 +1406,16 @@ extern "C" size_t hac_workspace_bytes_for(const hac_desc_t* desc, int64_t B, con
     if (xlds_plan(desc, B, launch).use) return 0;            // X is copied into LDS by every block
     const BatchShape bs = batch_shape(B, 32, kDefaultTile);
     return (size_t)4 * (size_t)desc->n * bs.Bp;
+}
+
+} // namespace
+
+extern "C" size_t hac_workspace_bytes_for(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
+{
+    if (!desc_plausible(desc) || B <= 0 || B > 0x7fffffffll) return 0;
+    if (desc->format == HAC_FORMAT_IM)
+        return hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m).part_bytes;
+    return workspace_need(desc, B, launch, ~(size_t)0);
 }
 
 extern "C" int hac_dot_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
@@ -1428,12 +1441,13 @@ int im_dot_impl(const hac_desc_t* desc, const void* d_blob, const float* d_X, in
     if (!d_X || !d_Y || ldx < (int64_t)desc->n || ldy < (int64_t)desc->m) return HAC_EINVAL;
     g_last_hip_error = 0;
     if (!bias && !relu) hac_internal::note_reset();
-    const size_t need = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m).part_bytes;
+    const hac_internal::GemmPlan plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m);
+    const size_t need = plan.part_bytes;
     if (need && (!d_ws || ws_bytes < need)) return HAC_EWORKSPACE;
     if (need && reinterpret_cast<uintptr_t>(d_ws) % 256) return HAC_EINVAL;
     const uint8_t* b = static_cast<const uint8_t*>(d_blob);
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    hipError_t e = hac_internal::launch_index_gemm(d_X, (uint64_t)ldx, (uint32_t)B, b + desc->off_stream, desc->ent_bits,
+    hipError_t e = hac_internal::launch_index_gemm(plan, d_X, (uint64_t)ldx, (uint32_t)B, b + desc->off_stream, desc->ent_bits,
                                                    desc->idx_pitch, reinterpret_cast<const float*>(b + desc->off_codebook),
                                                    desc->k_sym, 0u, (uint32_t)desc->n, (uint32_t)desc->m, d_Y,
                                                    (uint64_t)ldy, static_cast<float*>(d_ws), hs);
@@ -1599,14 +1613,15 @@ extern "C" int hac_dot_noalloc(const hac_desc_t* desc, const void* d_blob, const
 {
     if (!desc_plausible(desc) || (desc->format != HAC_FORMAT_HAC && desc->format != HAC_FORMAT_SHAC)) return HAC_EINVAL;
     if (B < 0 || B > 0x7fffffffll) return HAC_EINVAL;
-    const size_t need = hac_workspace_bytes_for(desc, B, launch);
+    const size_t need = B ? workspace_need(desc, B, launch, kStaticWsBytes) : 0;
     if (need > kStaticWsBytes) return HAC_EWORKSPACE;
     void* ws = nullptr;
     if (need) {
         const int rc = static_workspace(&ws);
         if (rc) return rc;
     }
-    return dot_impl(desc->format, desc, d_blob, d_X, B, ldx, d_Y, ldy, ws, need ? kStaticWsBytes : 0, launch, stream);
+    return dot_impl(desc->format, desc, d_blob, d_X, B, ldx, d_Y, ldy, ws, need ? kStaticWsBytes : 0, launch, stream,
+                    nullptr, kStaticWsBytes);
 }
 
 extern "C" int hac_decode_dev(const hac_desc_t* desc, const void* d_blob, float* d_W, int32_t* d_sym,
