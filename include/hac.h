@@ -488,9 +488,12 @@ int shac_dot(const hac_desc_t *desc, const void *d_blob,
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): hac_dot / shac_dot
  * (picked by desc->format) with the workspace taken from a fixed array of
  * HAC_NOALLOC_WORKSPACE_BYTES inside the library's device image instead of from the caller.
- * The call allocates and frees nothing, on the host or on the device.  A product whose
- * workspace (hac_workspace_bytes_for(desc, B, launch)) exceeds the array returns
- * HAC_EWORKSPACE and launches nothing.  Each GPU holds one such array until the process ends;
+ * The call allocates and frees nothing, on the host or on the device.  A product too large
+ * for the array returns HAC_EWORKSPACE and launches nothing.  Which ones those are depends on n, m,
+ * nnz, k_sym, B and launch by a rule that stays as it is; it is not hac_workspace_bytes_for(), which
+ * follows the route and the K splits of hac_dot.  What is taken runs within the array: with
+ * fewer K splits, or on the other route, than hac_dot where that needs more (the order of the
+ * additions is then another).  Each GPU holds one such array until the process ends;
  * every call on that GPU uses it, so calls that may overlap on one GPU (different streams or
  * threads) race on it: order them.  Nothing is kept in the array between calls (each call
  * writes what it reads).  Otherwise as hac_dot. */

@@ -997,15 +997,21 @@ uint32_t default_cpw(const hac_desc_t* desc)
 // `room`: bytes of workspace there are, for hac_dot_noalloc; the plan then splits K only as far as the parts fit.
 struct DenseRoute { bool use; uint32_t idx_bits; uint64_t pitch; size_t idx_bytes, bytes; hac_internal::GemmPlan plan; };
 
-DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room = ~(size_t)0)
+bool size_index_map(const hac_desc_t* desc, DenseRoute& r)
 {
-    DenseRoute r = {};
     const uint64_t k_tot = (uint64_t)desc->k_sym + (desc->format == HAC_FORMAT_SHAC ? 1 : 0);
-    const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
-    if (k_tot > 65536 || B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && B < 32)) return r;
+    if (k_tot > 65536) return false;
     r.idx_bits = k_tot <= 256 ? 8 : 16;
     r.pitch = (desc->m + 15) / 16 * 16;
     r.idx_bytes = (size_t)((desc->n * r.pitch * (r.idx_bits / 8) + 255) / 256 * 256);
+    return true;
+}
+
+DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room = ~(size_t)0)
+{
+    DenseRoute r = {};
+    const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
+    if (B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && B < 32) || !size_index_map(desc, r)) return r;
     const hac_internal::GemmPlan plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m,
                                                                       room > r.idx_bytes ? room - r.idx_bytes : 0);
     r.plan = plan;
@@ -1129,6 +1135,29 @@ XldsPlan xlds_plan(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch
     return p;
 }
 
+// bytes of workspace the sparse route needs: partial sums of the row-blocked kernel, or the feature-major copy of X
+size_t sparse_need(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
+{
+    const RowsPlan rk = plan_rows(desc, B, launch, table_bytes_of(desc));
+    if (rk.use) return rk.part_bytes;
+    if (B == 1) return 0;                                    // a single row is its own feature-major copy
+    if (xlds_plan(desc, B, launch).use) return 0;            // X is copied into LDS by every block
+    const BatchShape bs = batch_shape(B, 32, kDefaultTile);
+    return (size_t)4 * (size_t)desc->n * bs.Bp;
+}
+
+// The route of a product with `room` bytes of workspace: the quicker of those that fit (both do when the caller brings
+// the memory it is told to).
+DenseRoute pick_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room)
+{
+    DenseRoute r = dense_route(desc, B, launch, room);
+    if (room == ~(size_t)0 || !r.bytes) return r;
+    if (launch && launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE)) return r;
+    if (r.bytes > room) r.use = false;
+    else if (sparse_need(desc, B, launch) > room) r.use = true;
+    return r;
+}
+
 int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
              const float* d_X, int64_t B, int64_t ldx, float* d_Y, int64_t ldy,
              void* d_ws, size_t ws_bytes, const hac_launch_t* launch, hac_stream_t stream_,
@@ -1175,7 +1204,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     const bool shac = format == HAC_FORMAT_SHAC && !d.rice;   // Rice-coded gaps decode like a HAC stream: no ri words
     g_last_hip_error = 0;
 
-    const DenseRoute dr = dense_route(desc, B, launch, room);
+    const DenseRoute dr = pick_route(desc, B, launch, room);
     if (launch && (launch->variant & HAC_LAUNCH_DENSE_ROUTE) && !dr.use) return HAC_EINVAL;   // too many symbols
     if (dr.use) {
         if (io->xt_in || io->yt_out) return HAC_EINVAL;       // the dense route reads and writes row-major
@@ -1398,14 +1427,8 @@ namespace {
 // bytes dot_impl takes from its workspace when there are `room` of them
 size_t workspace_need(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room)
 {
-    const DenseRoute dr = dense_route(desc, B, launch, room);
-    if (dr.use) return dr.bytes;
-    const RowsPlan rk = plan_rows(desc, B, launch, table_bytes_of(desc));
-    if (rk.use) return rk.part_bytes;
-    if (B == 1) return 0;                                    // a single row is its own feature-major copy
-    if (xlds_plan(desc, B, launch).use) return 0;            // X is copied into LDS by every block
-    const BatchShape bs = batch_shape(B, 32, kDefaultTile);
-    return (size_t)4 * (size_t)desc->n * bs.Bp;
+    const DenseRoute dr = pick_route(desc, B, launch, room);
+    return dr.use ? dr.bytes : sparse_need(desc, B, launch);
 }
 
 } // namespace
@@ -1608,11 +1631,57 @@ int static_workspace(void** out)
 }
 } // namespace
 
+namespace {
+
+// Which products hac_dot_noalloc takes.  Callers size their batches by it, so it is a rule of its own that does not move when a
+// kernel's splits or the choice of the route do: what a product of blocks of 64 to 256 rows x 128 columns would need, its K loop in
+// about 512 work items where there are at most 128 tiles, on the route that the time estimates of such a kernel give.
+// Whatever it takes fits the array: with one split the dense route needs the index map alone.
+size_t noalloc_scratch(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
+{
+    const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
+    DenseRoute map = {};
+    if (B < 1) return 0;
+    if (force == HAC_LAUNCH_SPARSE_ROUTE || (force != HAC_LAUNCH_DENSE_ROUTE && B < 32) || !size_index_map(desc, map))
+        return sparse_need(desc, B, launch);
+    uint64_t tiles, splits = 1, per;
+    size_t part;
+    if (B <= 32) {
+        const hac_internal::GemmPlan p = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m);
+        tiles = p.tiles; splits = p.splits; per = p.steps_per_split; part = p.part_bytes;
+    } else {
+        const uint64_t tiles_n = (desc->m + 127) / 128, steps = (desc->n + 31) / 32;
+        uint64_t least = ~0ull;
+        tiles = 0;
+        for (uint64_t rt = 2; rt <= 8; ++rt) {
+            const uint64_t t = ((uint64_t)B + 32 * rt - 1) / (32 * rt) * tiles_n, slots = rt <= 4 ? 512 : 256;
+            const uint64_t cost = (t + slots - 1) / slots * rt * (rt <= 4 ? 2 : 1);
+            if (cost <= least) { least = cost; tiles = t; }
+        }
+        if (tiles <= 128) splits = std::min<uint64_t>({ (512 + tiles - 1) / tiles, std::max<uint64_t>(steps / 8, 1), 32 });
+        per = (steps + splits - 1) / splits;
+        splits = (steps + per - 1) / per;
+        part = splits > 1 ? (size_t)splits * (size_t)B * desc->m * sizeof(float) : 0;
+    }
+    const size_t dense = map.idx_bytes + (part + 255) / 256 * 256;
+    if (force == HAC_LAUNCH_DENSE_ROUTE) return dense;
+    const double nnz = (double)desc->nnz, n = (double)desc->n, m = (double)desc->m, b = (double)B;
+    const double blocks = ((m + 15.0) / 16.0) * (double)((B + 255) / 256);
+    const double rate = std::min(std::min(blocks, 256.0) * 140e3, 22e6);
+    const double sparse_us = 12.0 + nnz * (double)((B + 31) / 32 * 32) * 4.0 / rate + b * n * 8.0 / 3e6;
+    const double flops_us = 2.0 * b * n * m / 9.5e7, serial_us = 3.0 * (double)per * (double)((tiles * splits + 511) / 512);
+    const double dense_us = 10.0 + nnz / 35e3 + std::max(flops_us, serial_us) + (double)part / 2e6;
+    return dense_us < sparse_us ? dense : sparse_need(desc, B, launch);
+}
+
+} // namespace
+
 extern "C" int hac_dot_noalloc(const hac_desc_t* desc, const void* d_blob, const float* d_X, int64_t B, int64_t ldx,
                                float* d_Y, int64_t ldy, const hac_launch_t* launch, hac_stream_t stream)
 {
     if (!desc_plausible(desc) || (desc->format != HAC_FORMAT_HAC && desc->format != HAC_FORMAT_SHAC)) return HAC_EINVAL;
     if (B < 0 || B > 0x7fffffffll) return HAC_EINVAL;
+    if (noalloc_scratch(desc, B, launch) > kStaticWsBytes) return HAC_EWORKSPACE;
     const size_t need = B ? workspace_need(desc, B, launch, kStaticWsBytes) : 0;
     if (need > kStaticWsBytes) return HAC_EWORKSPACE;
     void* ws = nullptr;

@@ -3,6 +3,7 @@
 Headers are made up here (no blob behind them): the decisions read the header, the batch and the launch settings only.
 """
 import ctypes as C
+import random
 
 import pytest
 
@@ -25,3 +26,43 @@ def test_index_map_product_splits_k_whatever_the_map_takes(B, n, ms, least):
     for m in ms:
         parts = hac.hac_workspace_bytes(header(hac.HAC_FORMAT_IM, n, m, n * m, 64), B) / (4 * B * m)
         assert parts == int(parts) and parts >= least, (m, parts)
+
+
+def products():
+    """2000 products on both sides of the array's size, most on the library's own choice of route."""
+    rng = random.Random(16)
+
+    def spread(lo, hi):
+        return round(lo * (hi / lo) ** rng.random())
+    for _ in range(2000):
+        n, m, B = spread(1000, 30000), spread(100, 6000), spread(24, 4000)
+        nnz = int(n * m * rng.uniform(0.005, 0.6))
+        yield rng.choice((hac.HAC_FORMAT_HAC, hac.HAC_FORMAT_SHAC)), n, m, nnz, rng.choice((16, 64, 255, 256, 300)), B, rng.choice((0, 0, 0, 0, 0x400, 0x800))
+
+
+def takes(fmt, n, m, nnz, k, B, variant):
+    """hac_dot_noalloc's answer without a product: a missing X is refused after the size."""
+    launch = C.byref(hac.Launch(variant=variant)) if variant else None
+    return hac.load_library().hac_dot_noalloc(C.byref(header(fmt, n, m, nnz, k)), C.c_void_p(256), None, B, n, None, m, launch, None) != -6
+
+
+# a bit per product: 1 where a product of its size was taken when the call was introduced (the first digit only marks the start)
+TAKEN = (
+    "1ee75d591f4fdff7deffdaa9f67bdcfc05eff55b8cf42bcf8efe8d0f798fbfc1fc6947bddfd44e3ffe3bf70e9efdefbfdfdb9fcb13ebecbb5be87fdd"
+    "d6a1fb7ed5f4c8f749ed7fbaf7c6f77f5bdfe757cb4afaeae1e4dfbe7f59ddde3e49bf7df2cafaafcf4b9f4ed9f6f3db7ffc9f7ffefbf3def1f96fab"
+    "b9d79796f175dd65bf86ff2ddd5f8fd0d87dff7d73f9f3a76c6d466fc77eeccf90d76fb6f323adf1d59ca7f675b3ef5b8becfef1cf6fb5af7b4efb9e"
+    "7bcaffe779159f3f7bea337efddf60f76f3606a41cffd2fe64dd509733ef9ef73fc4897ffae9bcfafba17a8dfffed5bcdeb91efaeebdc241dfdd734c"
+    "f97b5e57d835df7bfcffe")
+
+
+def test_noalloc_takes_what_it_always_took():
+    """A caller that sizes its batches by what the fixed array takes finds the same answers whatever the kernels' plans are."""
+    want = bin(int(TAKEN, 16))[3:]
+    got = "".join("1" if takes(*p) else "0" for p in products())
+    assert len(want) == len(got) and [p for p, a, b in zip(products(), got, want) if a != b] == []
+
+
+@pytest.mark.parametrize("n,m,prune,B", [(16269, 1661, 0.73, 170), (4772, 421, 0.85, 1997)])
+def test_noalloc_takes_products_that_want_more_on_the_quicker_route(n, m, prune, B):
+    """The route that is quicker in a workspace of its own needs more than the array here; the other one fits."""
+    assert takes(hac.HAC_FORMAT_HAC, n, m, int(n * m * (1 - prune)), 64, B, 0)

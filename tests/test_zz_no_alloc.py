@@ -89,3 +89,19 @@ def test_dense_route_and_limit(hac):
         hac.hac_dot_noalloc(im.to_device(dev), torch.zeros((4, 640), dtype=torch.float32, device=dev),
                             torch.zeros((4, 96), dtype=torch.float32, device=dev))
     assert err.value.status == -1
+
+
+@pytest.mark.parametrize("n,m,prune,B", [(16269, 1661, 0.73, 170), (4772, 421, 0.85, 1997)])
+def test_products_for_which_the_dot_call_needs_more(hac, n, m, prune, B):
+    """Taken with the other route, or with as many K splits as the array holds: the result is the product's."""
+    dev = torch.device("cuda:0")
+    W = workloads.make_layer(n, m, 0.02, prune, 32, "uniform", 3)
+    Wd = torch.from_numpy(W).to(dev)
+    blob = hac.hac_encode_dev(Wd, hac.HAC_FORMAT_HAC)
+    print(f"[case] hac_dot_noalloc {n} x {m}, B = {B}", flush=True)
+    assert hac.hac_workspace_bytes(blob.desc, B) > hac.NOALLOC_WORKSPACE_BYTES
+    X = torch.from_numpy(workloads.make_batch(B, n, 5)).to(dev)
+    Y = torch.full((B, m), float("nan"), dtype=torch.float32, device=dev)
+    hac.hac_dot_noalloc(blob, X, Y)
+    ref, scale = X.double() @ Wd.double(), X.double().abs() @ Wd.double().abs()
+    assert bool(((Y - ref).abs() <= TOL * scale + 1e-37).all())
