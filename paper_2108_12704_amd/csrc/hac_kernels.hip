@@ -986,14 +986,19 @@ uint32_t default_cpw(const hac_desc_t* desc)
     return cpw;
 }
 
-// Dense route (decode to an index map, then fp32 MFMA tiles) or sparse route (vector FMAs per
-// non-zero)?  Decided from rough time estimates, with constants measured on an MI355X:
-//   sparse: every non-zero gathers 4 bytes per batch column (at least 32) through the vector
-//           memory path, about 22 TB/s over the whole chip and 140 GB/s per busy CU (a block covers
-//           16 columns of W and up to 256 batch columns), plus the re-layout of X and ~12 us;
-//   dense : ~35 non-zeros per ns to decode into the index map, then the contraction at about
-//           95 TFLOP/s, but never faster than its serial K loop (3 us per step of 32 per round of
-//           512 work items), plus the pass that adds the K splits.
+// Dense route (decode to an index map, then MFMA tiles) or sparse route (vector FMAs per non-zero)?  The shorter of
+// two time estimates whose constants are fitted to both routes' times, forced, on 755 layers (200 x 10 to 25088 x 4096,
+// 50 to 99 % pruned, 33 to 8192 rows):
+//   sparse: 12.7 us, the re-layout of X (3.6 TB/s), 4 bytes gathered per non-zero and batch column (33 TB/s; batch
+//           columns in panels of 32), 8 ns per non-zero of a column and panel (a wavefront walks its columns' lists
+//           one after the other), and Y, written a few columns at a time (0.22 TB/s);
+//   dense : 5.6 us, the map cleared and read (1.2 TB/s), 9 ns per thousand non-zeros scattered into it, half a us per
+//           symbol of a chunk (one lane decodes a chunk), and the product as its plan estimates it.
+// The route so chosen costs 1.8 % over the better one (geometric mean over the 755; worst 1.75 times, the rule on
+// the fp32 kernel's constants 17 % and 8.3 times, with the plan of the kernel on bf16 parts 15 % and 7.6 times).
+// Batches of 32 rows and less are one panel of the sparse route and too few for MFMA tiles; layers with one non-zero in
+// 40 entries or fewer take the sparse route as they always did (of 24 measured ones the dense route was more than
+// 15 % quicker on three, 25088 x 16 at 256 rows 46 against 63 us).
 // `room`: bytes of workspace there are, for hac_dot_noalloc; the plan then splits K only as far as the parts fit.
 struct DenseRoute { bool use; uint32_t idx_bits; uint64_t pitch; size_t idx_bytes, bytes; hac_internal::GemmPlan plan; };
 
@@ -1011,7 +1016,7 @@ DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* la
 {
     DenseRoute r = {};
     const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
-    if (B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && B < 32) || !size_index_map(desc, r)) return r;
+    if (B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && (B <= 32 || desc->nnz <= desc->n * desc->m / 40)) || !size_index_map(desc, r)) return r;
     const hac_internal::GemmPlan plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m,
                                                                       room > r.idx_bytes ? room - r.idx_bytes : 0);
     r.plan = plan;
@@ -1019,15 +1024,11 @@ DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* la
     if (force == HAC_LAUNCH_DENSE_ROUTE) { r.use = true; return r; }
     if (force == HAC_LAUNCH_SPARSE_ROUTE) return r;
     const double nnz = (double)desc->nnz, n = (double)desc->n, m = (double)desc->m, b = (double)B;
-    const double bp = (double)((B + 31) / 32 * 32);
-    const double blocks = ((m + 15.0) / 16.0) * (double)((B + 255) / 256);
-    const double busy = blocks < 256.0 ? blocks : 256.0;
-    const double rate = busy * 140e3 < 22e6 ? busy * 140e3 : 22e6;             // bytes per us
-    const double sparse_us = 12.0 + nnz * bp * 4.0 / rate + b * n * 8.0 / 3e6;
-    const double items = (double)plan.tiles * plan.splits;
-    const double rounds = (double)(uint64_t)((items + 511.0) / 512.0);
-    const double flops_us = 2.0 * b * n * m / 9.5e7, serial_us = plan.steps_per_split * 3.0 * rounds;
-    const double dense_us = 10.0 + nnz / 35e3 + (flops_us > serial_us ? flops_us : serial_us) + (double)plan.part_bytes / 2e6;
+    const double bp = (double)((B + 31) / 32 * 32), panels = B <= 64 ? 2.0 : B <= 128 ? 4.0 : 8.0;   // of a block of the sparse route
+    const double sparse_us = 12.7 + 2.2e-6 * n * bp + nnz * bp * 1.2e-7 + 7.9e-3 * panels * nnz / m + 1.8e-5 * b * m;
+    double chunk = (double)hac_internal::chunk_base(desc->chunk);
+    if (desc->chunk & hac_internal::kChunkPerColumn) chunk = std::max(chunk, (double)desc->max_col_nnz / 64.0);
+    const double dense_us = 5.6 + 0.8e-6 * (double)r.idx_bytes + 9e-6 * nnz + 0.49 * chunk + plan.us;
     r.use = dense_us < sparse_us;
     return r;
 }
@@ -1151,10 +1152,14 @@ size_t sparse_need(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch
 DenseRoute pick_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room)
 {
     DenseRoute r = dense_route(desc, B, launch, room);
-    if (room == ~(size_t)0 || !r.bytes) return r;
+    if (room == ~(size_t)0) return r;
     if (launch && launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE)) return r;
-    if (r.bytes > room) r.use = false;
-    else if (sparse_need(desc, B, launch) > room) r.use = true;
+    if (r.use) { r.use = r.bytes <= room; return r; }
+    if (sparse_need(desc, B, launch) <= room) return r;
+    hac_launch_t dense = launch ? *launch : hac_launch_t{};
+    dense.variant |= HAC_LAUNCH_DENSE_ROUTE;
+    r = dense_route(desc, B, &dense, room);
+    r.use = r.use && r.bytes <= room;
     return r;
 }
 

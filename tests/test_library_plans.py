@@ -66,3 +66,15 @@ def test_noalloc_takes_what_it_always_took():
 def test_noalloc_takes_products_that_want_more_on_the_quicker_route(n, m, prune, B):
     """The route that is quicker in a workspace of its own needs more than the array here; the other one fits."""
     assert takes(hac.HAC_FORMAT_HAC, n, m, int(n * m * (1 - prune)), 64, B, 0)
+
+
+# times of both routes as measured, us (sparse, dense)
+@pytest.mark.parametrize("n,m,prune,B,sparse_us,dense_us",
+                         [(15097, 501, 0.57, 246, 457, 106), (17139, 478, 0.57, 244, 430, 139), (25088, 1000, 0.90, 512, 397, 183),
+                          (4608, 512, 0.60, 784, 156, 75), (25088, 4096, 0.90, 300, 812, 423), (2000, 2000, 0.80, 2048, 287, 124),
+                          (4096, 4096, 0.96, 256, 54, 84), (25088, 4096, 0.98, 256, 111, 294), (512, 4096, 0.70, 64, 18, 28),
+                          (9973, 1511, 0.93, 100, 45, 69), (25088, 4096, 0.98, 2048, 848, 1756), (4096, 1000, 0.90, 64, 17, 40)])
+def test_the_quicker_route_is_taken(n, m, prune, B, sparse_us, dense_us):
+    nnz = int(n * m * (1 - prune))
+    d = header(hac.HAC_FORMAT_HAC, n, m, nnz, 32, max(4, nnz // m // 64))
+    assert hac.hac_dot_route(d, B) == (1 if dense_us < sparse_us else 0)
