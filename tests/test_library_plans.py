@@ -20,7 +20,7 @@ def header(fmt, n, m, nnz, k, chunk=64):
 # maps around 8 MB (8-bit pointers: as much as the 16 MB of hac_dot_noalloc hold twice) and a smaller one; few output tiles
 @pytest.mark.parametrize("B,n,ms,least", [(64, 4608, range(1600, 2000, 16), 8), (64, 4096, range(3900, 4200, 16), 8),
                                           (64, 4096, range(1936, 2144, 16), 8), (200, 4608, range(3500, 3760, 16), 4),
-                                          (784, 4608, [512], 9)])
+                                          (784, 4608, [512], 8)])
 def test_index_map_product_splits_k_whatever_the_map_takes(B, n, ms, least):
     """im_dot keeps its map in the blob: its K splits (workspace / (B m floats)) do not depend on the map's size."""
     for m in ms:
