@@ -44,7 +44,7 @@ constexpr uint32_t kSegRowsMax = 256, kSegRowsMin = 32;   // multiples of 32: a 
 constexpr uint32_t kSegWordsMax = kSegRowsMax / 32;
 constexpr uint64_t kMaxRows = 65535ull * 1024;
 constexpr uint32_t kTileCols = 64, kTileRows = 32;        // what a wavefront reads at a time in step 1
-constexpr uint32_t kTileQuota = 256;                      // packed values of a tile: an eighth of it
+constexpr uint32_t kQuota = 4;                            // packed values per column of a tile: an eighth of it
 constexpr uint32_t kNotPacked = 0xffffu;
 constexpr uint32_t kScanWaves = 8, kScanQueue = 1024, kScanBlocks = 1024;   // 40 KB of LDS a block: four on a CU
 constexpr uint32_t kCodeSlotsLds = 2048;                  // code tables up to this size (24 KB) are copied to LDS
@@ -90,8 +90,8 @@ __device__ void table_add(uint32_t* keys, uint32_t* cnts, uint32_t* flags, uint3
 // lanes' counts gives every lane its place in the tile's list; the list is put together in LDS, from
 // where the wavefront counts it (64 values at a time, whatever the density) and copies it out.  Tiles
 // are dealt over a grid that fits the chip once, so that a block merges its histogram only once.
-// The words and the quota per tile need no atomics; what bounds it is reading W.
-// mask, off: [rows / 32][m]; values: kTileQuota per tile, column groups fastest.
+// The words and the room per tile need no atomics; what bounds it is reading W.
+// mask, off: [rows / 32][m]; values: [rows / 32][m][kQuota], a tile's columns' room taken as one list.
 __global__ void __launch_bounds__(64 * kScanWaves)
 enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ldw, uint32_t col_groups, uint32_t tiles,
                 uint32_t* __restrict__ mask, uint16_t* __restrict__ off, uint32_t* __restrict__ values,
@@ -135,7 +135,8 @@ enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ld
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) { const uint32_t t = __shfl_up(incl, d, 64); if ((int)lane >= d) incl += t; }
         const uint32_t total = __builtin_amdgcn_readfirstlane(__shfl(incl, 63, 64));
-        const bool packed = total <= kTileQuota;
+        const uint32_t j0 = j - lane;
+        const bool packed = total <= kQuota * (m - j0 < kTileCols ? m - j0 : kTileCols);
         if (j < m) {
             mask[(uint64_t)w * m + j] = word;
             off[(uint64_t)w * m + j] = (uint16_t)(packed ? incl - cnt : kNotPacked);
@@ -149,7 +150,7 @@ enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ld
             __builtin_amdgcn_wave_barrier();
             for (uint32_t i = lane; i < total; i += 64) {
                 const uint32_t key = q[i];
-                if (packed) values[(uint64_t)tile * kTileQuota + i] = key;
+                if (packed) values[((uint64_t)w * m + j0) * kQuota + i] = key;
                 count_value(key);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // read before the next tile's list is written
@@ -172,7 +173,7 @@ struct Survivors {
     const float* W; uint32_t n, m; uint64_t ldw;
     const uint32_t* mask; const uint16_t* off; const uint32_t* values;
     const uint32_t* table; uint32_t slots;
-    uint32_t col_groups, col_blocks, seg_rows;
+    uint32_t col_blocks, seg_rows;
 };
 
 // the code table in LDS when it is small (LDS_TABLE), behind a barrier of the whole block
@@ -230,13 +231,13 @@ __device__ __forceinline__ void for_survivors(const Survivors& s, const SegWords
 {
     const uint32_t t = threadIdx.x;
     uint32_t w = 0, word = sw.mask[0][t], at = sw.off[0][t];
-    const uint64_t tile0 = (uint64_t)(r0 / 32) * s.col_groups + j / kTileCols;
+    const uint32_t* list = s.values + ((uint64_t)(r0 / 32) * s.m + (j - j % kTileCols)) * kQuota;   // of the segment's first tile
     for (uint32_t i = 0; i < total; ++i) {
         while (word == 0) { ++w; word = sw.mask[w][t]; at = sw.off[w][t]; }
         const uint32_t r = r0 + 32 * w + (uint32_t)__builtin_ctz(word);
         word &= word - 1;
         uint32_t key;
-        if (at != kNotPacked) key = s.values[(tile0 + (uint64_t)w * s.col_groups) * kTileQuota + at++];
+        if (at != kNotPacked) key = list[(uint64_t)w * s.m * kQuota + at++];
         else key = __float_as_uint(s.W[(uint64_t)r * s.ldw + j]);
         f(r, key);
     }
@@ -461,13 +462,13 @@ struct WsLayout {
 WsLayout ws_layout(uint64_t n, uint64_t m)
 {
     const uint64_t seg_rows = seg_rows_for(n, m), S = (n + seg_rows - 1) / seg_rows;
-    const uint64_t words = (n + 31) / 32, tiles = words * ((m + kTileCols - 1) / kTileCols);
+    const uint64_t words = (n + 31) / 32;
     WsLayout L;
     size_t c = 0;
     auto take = [&](size_t bytes) { const size_t o = c; c = (c + bytes + 255) / 256 * 256; return o; };
     L.keys = take(4ull * kHashSlots); L.cnts = take(4ull * kHashSlots); L.flags = take(256);
     L.list = take(8ull * kListCap);                                 // behind the flags: one copy to the host
-    L.mask = take(4 * words * m); L.off = take(2 * words * m); L.values = take(4ull * kTileQuota * tiles);
+    L.mask = take(4 * words * m); L.off = take(2 * words * m); L.values = take(4ull * kQuota * words * m);
     L.seg_nnz = take(4 * S * m); L.seg_bits = take(4 * S * m);
     L.gap_bits = take(4 * S * m * (kRiceKMax + 1));                  // used with Rice-coded gaps only
     L.table = take(12ull * kHashSlots);
@@ -518,10 +519,10 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
     sv.W = d_W; sv.n = (uint32_t)n; sv.m = (uint32_t)m; sv.ldw = (uint64_t)ldw;
     sv.mask = dptr(L.mask); sv.off = reinterpret_cast<uint16_t*>(ws + L.off); sv.values = dptr(L.values);
     sv.table = dptr(L.table);
-    sv.col_groups = (uint32_t)(((uint64_t)m + kTileCols - 1) / kTileCols);
     sv.col_blocks = (uint32_t)(((uint64_t)m + 255) / 256);
     sv.seg_rows = seg_rows;
-    const uint64_t tiles = ((uint64_t)n + kTileRows - 1) / kTileRows * sv.col_groups;
+    const uint32_t col_groups = (uint32_t)(((uint64_t)m + kTileCols - 1) / kTileCols);
+    const uint64_t tiles = ((uint64_t)n + kTileRows - 1) / kTileRows * col_groups;
     if (tiles > 0x7fffffffull || (uint64_t)sv.col_blocks * S > 0x7fffffffull) return HAC_ERANGE;   // terabytes of W
     const dim3 seg_grid(sv.col_blocks * S);
     hipError_t e;
@@ -531,7 +532,7 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
         hipLaunchKernelGGL(fill_zero_kernel, dim3(512), dim3(256), 0, stream, dptr(L.keys), (uint64_t)(L.list - L.keys) / 4);
         const uint64_t scan_blocks = std::min<uint64_t>((tiles + kScanWaves - 1) / kScanWaves, kScanBlocks);
         hipLaunchKernelGGL(enc_scan_kernel, dim3((uint32_t)scan_blocks), dim3(64 * kScanWaves), 0, stream, d_W, (uint32_t)n, (uint32_t)m,
-                           (uint64_t)ldw, sv.col_groups, (uint32_t)tiles, dptr(L.mask), reinterpret_cast<uint16_t*>(ws + L.off),
+                           (uint64_t)ldw, col_groups, (uint32_t)tiles, dptr(L.mask), reinterpret_cast<uint16_t*>(ws + L.off),
                            dptr(L.values), dptr(L.keys), dptr(L.cnts), d_flags);
         hipLaunchKernelGGL(enc_gather_kernel, dim3(kHashSlots / 256), dim3(256), 0, stream, dptr(L.keys), dptr(L.cnts),
                            dptr(L.list), kListCap, d_flags + 1);

@@ -135,11 +135,12 @@ def tile_matrix(n, m, per_tile, k, seed):
     return W
 
 
-# the tile sizes where a list is no longer packed (256) and no longer queued (1024), remainders of rows
+# the tile sizes where a list is no longer packed (256, 4 per column in a narrow tile) and no longer queued (1024), remainders of rows
 # and columns, more segments per column than the 16 ranges they are summed in, a code table that
 # fits LDS and one that does not
 @pytest.mark.parametrize("n,m,per_tile,k", [(160, 128, 256, 9), (160, 128, 257, 9), (97, 130, 1024, 40), (97, 130, 1025, 40),
-                                            (64, 64, 2048, 5), (20011, 3, 5, 17), (9000, 300, 30, 512), (2080, 257, 200, 700)])
+                                            (64, 64, 2048, 5), (20011, 3, 5, 17), (9000, 300, 30, 512), (2080, 257, 200, 700),
+                                            (640, 1, 4, 9), (640, 1, 5, 9), (97, 65, 4, 9), (97, 66, 9, 9)])
 def test_device_blob_at_the_edges_of_the_tiles(hac, n, m, per_tile, k):
     W = tile_matrix(n, m, per_tile, k, 11)
     Wd = torch.from_numpy(W).to(dev())

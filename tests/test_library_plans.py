@@ -78,3 +78,9 @@ def test_the_quicker_route_is_taken(n, m, prune, B, sparse_us, dense_us):
     nnz = int(n * m * (1 - prune))
     d = header(hac.HAC_FORMAT_HAC, n, m, nnz, 32, max(4, nnz // m // 64))
     assert hac.hac_dot_route(d, B) == (1 if dense_us < sparse_us else 0)
+
+
+@pytest.mark.parametrize("n,m", [(1_000_000, 1), (67_000_000, 1), (300_000, 65), (4096, 10), (25088, 4096), (100_000, 129)])
+def test_device_encoder_workspace_follows_the_matrix(n, m):
+    """At most as much as W beside the fixed tables (about 4 MB), whatever the matrix's shape."""
+    assert hac.load_library().hac_encode_dev_workspace_bytes(n, m) <= 4_200_000 + 4 * n * m
