@@ -498,7 +498,7 @@ def hac_encode_dev(W, fmt: int = HAC_FORMAT_HAC, chunk_nnz: int = 0, ri_bits: in
         try:
             blob = torch.empty(nbytes, dtype=torch.uint8, device=W.device)
             return blob.data_ptr()
-        except Exception as e:                               # must not pass through the library
+        except BaseException as e:                           # must not pass through the library (an interrupt included)
             failed = e
             return None
 

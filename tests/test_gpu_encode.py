@@ -201,3 +201,22 @@ def test_an_empty_column_costs_no_walk(hac):
     full = seconds()
     W[:, 1] = 0.0
     assert seconds() < 3 * full + 1e-3
+
+
+@pytest.mark.parametrize("error", [MemoryError, KeyboardInterrupt])
+def test_what_stops_the_allocation_reaches_the_caller(hac, monkeypatch, error):
+    """The blob's memory is asked for inside the library's call: an error there comes out as itself."""
+    W = torch.from_numpy(workloads.scaled(1, 300, 70)).to(dev())
+    real, calls = torch.empty, []
+
+    def empty(*a, **k):
+        calls.append(a)
+        if len(calls) > 1:                                    # the first is the workspace
+            raise error()
+        return real(*a, **k)
+    with monkeypatch.context() as patch:
+        patch.setattr(torch, "empty", empty)
+        with pytest.raises(error):
+            hac.hac_encode_dev(W, hac.HAC_FORMAT_HAC)
+    assert len(calls) == 2
+    assert hac.hac_encode_dev(W, hac.HAC_FORMAT_HAC).tensor.numel() > 0
