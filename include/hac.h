@@ -464,10 +464,11 @@ int hac_dot_route(const hac_desc_t *desc, int64_t B, const hac_launch_t *launch)
  * Two routes.  Sparse: every non-zero is decoded and applied to the batch by
  * vector FMAs.  Dense: the stream is decoded once into an index map
  * (Sect. III-C1) in the workspace and multiplied tile by tile on the matrix
- * cores (fp32 MFMA); with few output tiles the K loop is split and the parts
+ * cores (fp32 operands as three bf16 parts each, or in fp32 where parts would
+ * lose bits; fp32 sums); with few output tiles the K loop is split and the parts
  * are added in a fixed order.  The library estimates both times from desc and
- * B (the dense route wins for layers that are a fifth or more non-zero at
- * batches of several hundred rows) and takes the shorter; hac_dot_route() tells
+ * B (the dense route wins for layers that are a tenth or more non-zero at
+ * batches of a hundred rows or more, and for narrow ones) and takes the shorter; hac_dot_route() tells
  * which.  HAC_LAUNCH_SPARSE_ROUTE / HAC_LAUNCH_DENSE_ROUTE in launch->variant
  * force one (the dense route needs at most 65536 symbols). */
 int hac_dot(const hac_desc_t *desc, const void *d_blob,

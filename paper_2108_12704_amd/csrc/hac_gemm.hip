@@ -23,8 +23,8 @@
 // lanes' reads fall on different banks.  The next step's global loads fly during the matrix
 // instructions; two blocks share a CU, so that one splits and stores while the other multiplies.
 // Measured (MI355X), fp32 instruction -> bf16 parts: 4608 x 512 layer pruned 60 %, 12544 rows, whole call
-// 580 -> 352 us (59 GFLOP, 168 TFLOP/s; a call includes decoding the stream, about 30 us); unpruned map of that size,
-// 784 rows, 60.0 -> 35.5 us.
+// 580 -> 354 us (59 GFLOP; a call includes decoding the stream, about 25 us); unpruned map of that size,
+// 784 rows, 60.0 -> 39.5 us.  Matrix pipes 44 % busy at 12544 rows, four vector instructions beside each matrix one.
 // Lane layout of v_mfma_f32_32x32x16_bf16: A operand lane l holds A[i = l % 32][k = 8 (l / 32) + 0..7], B
 // operand lane l holds B[k = 8 (l / 32) + 0..7][j = l % 32], accumulator register v of lane l is
 // D[(v % 4) + 8 (v / 4) + 4 (l / 32)][l % 32].

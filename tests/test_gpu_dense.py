@@ -1,5 +1,5 @@
 """GPU parity of the matrix-core paths: im_dot (index map, Sect. III-C1) and the dense
-route of hac_dot / shac_dot (decode to an index map, then fp32 MFMA tiles).
+route of hac_dot / shac_dot (decode to an index map, then MFMA tiles).
 
 Same bar as the vector path: |Y - Yref|_ij <= 1e-5 (|X| . |W|)_ij and
 max |Y - Yref| <= 1e-5 max |Yref|, Yref the dense fp64 product of the oracle.
