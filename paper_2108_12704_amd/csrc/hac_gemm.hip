@@ -8,7 +8,7 @@
 // matrix pipe: v_mfma_f32_32x32x2_f32 does 157 TFLOP/s at best, the bf16 instruction sixteen times that.
 // So every fp32 operand is written as three bf16 parts, x = x1 + x2 + x3 (8 significant bits each, 24 in
 // all), and six of the nine products of parts are summed in fp32 on the matrix cores: x1 w1, x1 w2, x2 w1,
-// x2 w2, x1 w3, x3 w1.  The three left out are together below 2^-25 of |x w|, and one rounding of the sum per 16 products
+// x2 w2, x1 w3, x3 w1.  The three left out are together below 2^-24 of |x w|, and one rounding of the sum per 16 products
 // of parts instead of one per two makes the result closer to 64 bits than the fp32 instruction's
 // (relative 2-norm error figures at plan_index_gemm).  X is split on the way to LDS, W's representatives once per block in
 // the table that pointers are looked up in; every part is rounded to nearest.

@@ -337,7 +337,7 @@ def test_small_operands_among_others(hac):
 @pytest.mark.parametrize("n,terms", [(1, 1), (2, 2), (700, 1), (700, 2), (700, 4), (700, 8), (4608, 1)])
 def test_sums_of_few_terms(hac, n, terms):
     """Short sums, and long ones of which few terms are not zero: (terms + 1) 2^-24 |X| . |W|.  That is the
-    rounding of the result (2^-24), the products of parts left out (together 2^-25) and terms - 1 roundings on
+    rounding of the result (2^-24), the products of parts left out (together 2^-24) and terms - 1 roundings on
     the way; the fp32 instruction's own sums come to `terms` roundings.  A product alone (n = 1) is the fp32 product."""
     rng = np.random.default_rng(n + terms)
     B, m = 300, 150
