@@ -23,8 +23,8 @@
 // lanes' reads fall on different banks.  The next step's global loads fly during the matrix
 // instructions; two blocks share a CU, so that one splits and stores while the other multiplies.
 // Measured (MI355X), fp32 instruction -> bf16 parts: 4608 x 512 layer pruned 60 %, 12544 rows, whole call
-// 580 -> 354 us (59 GFLOP; a call includes decoding the stream, about 25 us); unpruned map of that size,
-// 784 rows, 60.0 -> 39.5 us.  Matrix pipes 44 % busy at 12544 rows, four vector instructions beside each matrix one.
+// 580 -> 351 us (59 GFLOP; a call includes decoding the stream, about 25 us); unpruned map of that size,
+// 784 rows, 60.0 -> 37.4 us.  Matrix pipes 44 % busy at 12544 rows, four vector instructions beside each matrix one.
 // Lane layout of v_mfma_f32_32x32x16_bf16: A operand lane l holds A[i = l % 32][k = 8 (l / 32) + 0..7], B
 // operand lane l holds B[k = 8 (l / 32) + 0..7][j = l % 32], accumulator register v of lane l is
 // D[(v % 4) + 8 (v / 4) + 4 (l / 32)][l % 32].
@@ -250,26 +250,24 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
         return (votes[which][0] | votes[which][1] | votes[which][2] | votes[which][3]) != 0;
     };
     // an operand was cut short, or a sum is not finite (an infinity or NaN among the operands, or an overflow)
+    // (x * 0 is NaN exactly then: one instruction per sum; a comparison each took 0.2 us a block)
     auto unfit = [&]() -> bool {
-        uint32_t bad = cut & 0xffffu;
+        float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) bad |= (uint32_t)!(fabsf(acc[i][v] + low[i][v]) <= 3.402823466e38f);
-        return bad != 0;
+            for (int v = 0; v < 16; ++v) t[v & 3] = fmaf(acc[i][v] + low[i][v], 0.0f, t[v & 3]);
+        return (cut & 0xffffu) != 0 || !((t[0] + t[1]) + (t[2] + t[3]) == 0.0f);
     };
-    // a look at the first step's X (non-finite, or small enough to be cut) and at the table: where all of X, or a
+    // a look at some of the first step's X (non-finite, or small enough to be cut) and at the table: where all of X, or a
     // representative, is like this, parts are not tried first
     load(kt0);                                         // (in flight while the table is made)
     if (LUT_LDS)
         for (uint32_t i = t; i < k_tot; i += 256) lut[i] = split_weight(value_of(i), cut);
     bool again = (cut & 0xffffu) != 0 || n == 1;
+    const float seen[4] = {st.ra[0].x, st.ra[0].y, st.ra[0].z, st.ra[0].w};
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
-        const float x[4] = {st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) again |= !(fabsf(x[j]) <= 3.402823466e38f) || (x[j] != 0.0f && fabsf(x[j]) < 0x1p-110f);
-    }
+    for (int j = 0; j < 4; ++j) again |= !(fabsf(seen[j]) <= 3.402823466e38f) || (seen[j] != 0.0f && fabsf(seen[j]) < 0x1p-110f);
     again = block_any(again, 0);                       // (a barrier: the table is complete)
     for (uint32_t kt = again ? ksteps : kt0; kt < ksteps; ++kt) {
         __syncthreads();                               // the last step's tiles are read

@@ -989,13 +989,14 @@ uint32_t default_cpw(const hac_desc_t* desc)
 // Dense route (decode to an index map, then MFMA tiles) or sparse route (vector FMAs per non-zero)?  The shorter of
 // two time estimates whose constants are fitted to both routes' times, forced, on 755 layers (200 x 10 to 25088 x 4096,
 // 50 to 99 % pruned, 33 to 8192 rows):
-//   sparse: 12.7 us, the re-layout of X (3.6 TB/s), 4 bytes gathered per non-zero and batch column (33 TB/s; batch
-//           columns in panels of 32), 8 ns per non-zero of a column and panel (a wavefront walks its columns' lists
-//           one after the other), and Y, written a few columns at a time (0.22 TB/s);
+//   sparse: 12.8 us, the re-layout of X (4.3 TB/s), 4 bytes gathered per non-zero and batch column (35 TB/s; batch
+//           columns in panels of 32), 9 ns per non-zero of a column and panel (a wavefront walks its columns' lists
+//           one after the other), and Y, written a few columns at a time (0.21 TB/s);
 //   dense : 5.6 us, the map cleared and read (1.2 TB/s), 9 ns per thousand non-zeros scattered into it, half a us per
 //           symbol of a chunk (one lane decodes a chunk), and the product as its plan estimates it.
-// The route so chosen costs 1.8 % over the better one (geometric mean over the 755; worst 1.75 times, the rule on
-// the fp32 kernel's constants 17 % and 8.3 times, with the plan of the kernel on bf16 parts 15 % and 7.6 times).
+// The route so chosen costs 1.8 % over the better one (geometric mean over the 755; worst 2.5 times) and 1.5 % on 200 other
+// layers (worst 1.5 times); the fp32 kernel's constants with its plan cost 18 % (8.3 times), with the plan of the
+// kernel on bf16 parts 15 % (7.6 times).
 // Batches of 32 rows and less are one panel of the sparse route and too few for MFMA tiles; layers with one non-zero in
 // 40 entries or fewer take the sparse route as they always did (of 24 measured ones the dense route was more than
 // 15 % quicker on three, 25088 x 16 at 256 rows 46 against 63 us).
@@ -1024,8 +1025,8 @@ DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* la
     if (force == HAC_LAUNCH_DENSE_ROUTE) { r.use = true; return r; }
     if (force == HAC_LAUNCH_SPARSE_ROUTE) return r;
     const double nnz = (double)desc->nnz, n = (double)desc->n, m = (double)desc->m, b = (double)B;
-    const double bp = (double)((B + 31) / 32 * 32), panels = B <= 64 ? 2.0 : B <= 128 ? 4.0 : 8.0;   // of a block of the sparse route
-    const double sparse_us = 12.7 + 2.2e-6 * n * bp + nnz * bp * 1.2e-7 + 7.9e-3 * panels * nnz / m + 1.8e-5 * b * m;
+    const double bp = (double)((B + 31) / 32 * 32), panels = std::min(bp / 32.0, 8.0);      // of a block of the sparse route
+    const double sparse_us = 12.8 + 1.85e-6 * n * bp + nnz * bp * 1.15e-7 + 8.9e-3 * panels * nnz / m + 1.87e-5 * b * m;
     double chunk = (double)hac_internal::chunk_base(desc->chunk);
     if (desc->chunk & hac_internal::kChunkPerColumn) chunk = std::max(chunk, (double)desc->max_col_nnz / 64.0);
     const double dense_us = 5.6 + 0.8e-6 * (double)r.idx_bytes + 9e-6 * nnz + 0.49 * chunk + plan.us;
