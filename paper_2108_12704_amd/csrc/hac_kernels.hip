@@ -994,7 +994,7 @@ uint32_t default_cpw(const hac_desc_t* desc)
 //           one after the other), and Y, written a few columns at a time (0.21 TB/s);
 //   dense : 5.6 us, the map cleared and read (1.2 TB/s), 9 ns per thousand non-zeros scattered into it, half a us per
 //           symbol of a chunk (one lane decodes a chunk), and the product as its plan estimates it.
-// The route so chosen costs 1.9 % over the better one (geometric mean over the 755; worst 2.5 times) and 1.5 % on 200 other
+// The route so chosen costs 1.9 % over the better one (geometric mean over the 755; worst 2.5 times) and 1.7 % on 200 other
 // layers (worst 1.5 times); the fp32 kernel's constants with its plan cost 18 % (8.3 times), with the plan of the
 // kernel on bf16 parts 15 % (7.6 times).
 // Batches of 32 rows and less are one panel of the sparse route and too few for MFMA tiles; layers with one non-zero in
