@@ -257,12 +257,12 @@ transpose_pad_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64
     }
 }
 
-// Same re-layout for panels of exactly 32 batch columns: a block turns 32 batch rows x 128
-// features into one contiguous 16 KB piece of a panel.  With X 16-byte aligned (vec = 1) the
-// reads are 128-bit (512 bytes per batch row) and so are the writes.
+// Same re-layout for panels of 32 batch columns or more (wp a multiple of 32): a block turns 32 batch rows x 128
+// features into 128-byte pieces of a panel's rows (one contiguous 16 KB piece for wp = 32).  With X 16-byte aligned
+// (vec = 1) the reads are 128-bit (512 bytes per batch row) and so are the writes.
 __global__ void __launch_bounds__(256)
 transpose_panel32_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64_t ldx,
-                         float* __restrict__ XT, uint32_t vec)
+                         float* __restrict__ XT, uint32_t vec, uint32_t wp)
 {
     __shared__ float tile[32][129];
     const uint32_t r0 = blockIdx.x * 128, b0 = blockIdx.y * 32;
@@ -301,14 +301,14 @@ transpose_panel32_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, ui
         }
     }
     __syncthreads();
-    float* out = XT + (uint64_t)blockIdx.y * n * 32 + (uint64_t)r0 * 32;
+    float* out = XT + (uint64_t)(b0 / wp) * n * wp + (uint64_t)r0 * wp + b0 % wp;
 #pragma unroll
     for (uint32_t i = 0; i < 4; ++i) {
         const uint32_t idx = threadIdx.x + 256 * i;              // float4 index: 128 features x 8 quads of batch
         const uint32_t r = idx >> 3, bq = (idx & 7) * 4;
         if (r0 + r < n) {
             const float4 v = make_float4(tile[bq][r], tile[bq + 1][r], tile[bq + 2][r], tile[bq + 3][r]);
-            *reinterpret_cast<float4*>(out + (uint64_t)r * 32 + bq) = v;
+            *reinterpret_cast<float4*>(out + (uint64_t)r * wp + bq) = v;
         }
     }
 }
@@ -338,12 +338,12 @@ __device__ __forceinline__ void wave_sync()
 
 // What happens to a finished sum before it is stored: + bias[column], max(., 0), and where it
 // goes.  yt = nullptr: Y[b * ldy + column].  yt set: the feature-major layout the next layer of
-// a chain reads as its XT, panels of wp batch columns, yt[(b / wp) * m * wp + column * wp + b % wp],
-// with 0 in the padded batch columns.
+// a chain reads as its XT, panels of wp = yt_width batch columns, yt[(b / wp) * m * wp + column * wp + b % wp].
+// What the padded batch columns hold does not matter: their sums are not stored.
 struct Epilogue {
     const float* bias;
     float* yt;
-    uint32_t relu;
+    uint32_t relu, yt_width;
 };
 
 __device__ __forceinline__ float epilogue_apply(const Epilogue& e, float v, uint32_t col)
@@ -363,7 +363,9 @@ struct EntryGroup {
 };
 
 // Accumulate list entries with CSC positions [lo, hi) (list index = position - winbase).
-template <int NB, int kPipe>
+// OWN: kPipe entries have a sum of their own first, instead of one chain of all the list's entries.  With few lane groups a
+// chain is long (relative error against 64 bits: 4096 x 4096, 4 % non-zero, two groups 1.2e-7 -> 8.0e-8).
+template <int NB, int kPipe, bool OWN>
 __device__ __forceinline__ void fma_entries(const uint2* list, uint32_t winbase, uint32_t lo, uint32_t hi,
                                             uint32_t ng, uint32_t grp, const float* xt, uint32_t Bp,
                                             float (&acc)[NB])
@@ -383,7 +385,14 @@ __device__ __forceinline__ void fma_entries(const uint2* list, uint32_t winbase,
         for (int k = 0; k < kPipe; ++k) {
             const float wv = __uint_as_float(G.e[k].y);
 #pragma unroll
-            for (int i2 = 0; i2 < NB; ++i2) acc[i2] = fmaf(G.x[k][i2], wv, acc[i2]);
+            for (int i2 = 0; i2 < NB; ++i2) {
+                if (!OWN) acc[i2] = fmaf(G.x[k][i2], wv, acc[i2]);
+                else G.x[0][i2] = k ? fmaf(G.x[k][i2], wv, G.x[0][i2]) : G.x[0][i2] * wv;
+            }
+        }
+        if (OWN) {
+#pragma unroll
+            for (int i2 = 0; i2 < NB; ++i2) acc[i2] += G.x[0][i2];
         }
     }
     // last, partial group: only the entries that exist are fetched (a lane that is switched off asks
@@ -405,7 +414,14 @@ __device__ __forceinline__ void fma_entries(const uint2* list, uint32_t winbase,
         for (int k = 0; k < kPipe; ++k) {
             const float wv = __uint_as_float(G.e[k].y);          // 0.0 for an entry that does not exist
 #pragma unroll
-            for (int i2 = 0; i2 < NB; ++i2) acc[i2] = fmaf(G.x[k][i2], wv, acc[i2]);
+            for (int i2 = 0; i2 < NB; ++i2) {
+                if (!OWN) acc[i2] = fmaf(G.x[k][i2], wv, acc[i2]);
+                else G.x[0][i2] = k ? fmaf(G.x[k][i2], wv, G.x[0][i2]) : G.x[0][i2] * wv;
+            }
+        }
+        if (OWN) {
+#pragma unroll
+            for (int i2 = 0; i2 < NB; ++i2) acc[i2] += G.x[0][i2];
         }
     }
 }
@@ -515,7 +531,8 @@ __device__ __forceinline__ void block_sync_lds()
 // MP: several passes (npass > 1); the single-pass variant has no pass loop and no barrier.
 // EPI: the epilogue (bias, max(., 0), feature-major output) is compiled in; a plain product runs
 // the variant without it, which needs fewer registers (the single-pass kernel would spill one).
-template <bool SHAC, int NB, bool MP, bool EPI>
+// OWN: see fma_entries (off for many passes of 32 batch columns: eight lane groups keep the chains short, and it costs 0.7 % at 256 rows).
+template <bool SHAC, int NB, bool MP, bool EPI, bool OWN>
 __global__ void __launch_bounds__((BatchTraits<NB>::kMaxThreads))
 dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t Bp, uint32_t B,
                  float* __restrict__ Y, uint64_t ldy, uint32_t cpw, uint32_t gw, uint32_t npass,
@@ -621,9 +638,11 @@ dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t Bp, uint32_t 
             float a[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i) a[i] = (carried && part_words) ? part[(p * NB + i) * kWave + lane] : 0.0f;
-            // (the single-pass kernel with the epilogue compiled in keeps one fetch fewer in flight: with ten it spills)
-            constexpr int kPipe = BatchTraits<NB>::kPipe - ((EPI && !MP && NB == 4) ? 1 : 0);
-            if (t < hi) fma_entries<NB, kPipe>(list, winbase, t, hi, ng, grp, xt + p * panel, pass_w, a);
+            // (the single-pass kernel with the epilogue compiled in spills with ten fetches in flight; without it, it takes
+            // nine too, so that a chain adds in the order of single calls)
+            constexpr int kPipe = BatchTraits<NB>::kPipe - ((!MP && NB == 4) ? 1 : 0);
+            // (a lane whose batch columns are all padding fetches nothing)
+            if (t < hi && boff + p * pass_w < B) fma_entries<NB, kPipe, OWN>(list, winbase, t, hi, ng, grp, xt + p * panel, pass_w, a);
             if (last) {
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
@@ -633,8 +652,7 @@ dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t Bp, uint32_t 
                     if (grp == 0) {
                         if constexpr (EPI) {
                             if (epi.yt)
-                                epi.yt[((uint64_t)(b / pass_w) * d.m + cc) * pass_w + (b % pass_w)] =
-                                    b < B ? epilogue_apply(epi, v, cc) : 0.0f;
+                                { if (b < B) epi.yt[((uint64_t)(b / epi.yt_width) * d.m + cc) * epi.yt_width + (b % epi.yt_width)] = epilogue_apply(epi, v, cc); }
                             else if (b < B) Y[(uint64_t)b * ldy + cc] = epilogue_apply(epi, v, cc);
                         } else {
                             if (b < B) Y[(uint64_t)b * ldy + cc] = v;
@@ -972,6 +990,21 @@ BatchShape batch_shape(int64_t B, uint32_t pass_w, uint32_t tile_b)
 constexpr size_t kLdsLimit = 160 * 1024;
 constexpr uint32_t kDefaultTile = 256;
 
+// Batch columns of a panel of the feature-major copy of X, the same for every kernel that reads or writes one: as many as
+// the batch has (a power of two, at most 256) while a panel stays within the 4 MB of an XCD's L2.  A wider panel means
+// fewer passes over the list and longer rows: 4096 x 4096, 4 % non-zero, 128 rows 29.4 (32 columns) -> 25.3 (64) -> 23.4 us
+// (128); 1000 x 4096, 10 %, 256 rows 43.4 -> 31.6 -> 26.2 us; but 25088 rows of W, 256 rows of X: 109.4 (32 columns, 3.2 MB),
+// 115.5 (64), 155.9 us (256).
+constexpr double kPanelBytes = 3.4e6;
+
+uint32_t xt_width(uint64_t n, int64_t B)
+{
+    uint32_t w = 1;
+    while (w < (uint32_t)(B < 256 ? B : 256)) w <<= 1;
+    while (w > 32 && 4.0 * (double)n * w > kPanelBytes) w >>= 1;
+    return w;
+}
+
 uint32_t round_up(uint32_t v, uint32_t q) { return (v + q - 1) / q * q; }
 
 // columns per wavefront: fill the 64 decode lanes, but keep enough wavefronts in flight
@@ -1037,6 +1070,7 @@ DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* la
 } // namespace
 
 #include "hac_rows.h"
+#include "hac_split.h"
 
 namespace {
 
@@ -1082,11 +1116,12 @@ void launch_bias_act(float* d_Y, uint32_t B, uint32_t m, uint64_t ldy, const flo
 }
 
 template <bool SHAC, bool EPI>
-batch_kern_t pick_batch_kernel(uint32_t nb, bool multipass)
+batch_kern_t pick_batch_kernel(uint32_t nb, bool multipass, bool own)
 {
-    if (nb == 1) return dot_batch_kernel<SHAC, 1, false, EPI>;
-    if (nb == 2) return dot_batch_kernel<SHAC, 2, false, EPI>;
-    return multipass ? dot_batch_kernel<SHAC, 4, true, EPI> : dot_batch_kernel<SHAC, 4, false, EPI>;
+    if (nb == 1) return dot_batch_kernel<SHAC, 1, false, EPI, true>;
+    if (nb == 2) return dot_batch_kernel<SHAC, 2, false, EPI, true>;
+    if (!multipass) return dot_batch_kernel<SHAC, 4, false, EPI, true>;
+    return own ? dot_batch_kernel<SHAC, 4, true, EPI, true> : dot_batch_kernel<SHAC, 4, true, EPI, false>;
 }
 
 // per-wave LDS words for the stream (and ri) words of a wave's columns
@@ -1137,6 +1172,69 @@ XldsPlan xlds_plan(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch
     return p;
 }
 
+// Several wavefronts per column (hac_split.h)?  `direct`: a lane takes a non-zero and reads X as it is (`copy`: from the
+// feature-major copy all the same, because the caller asked for one), else lanes take batch columns of the copy.
+struct SplitPlan { bool use, direct, copy; uint32_t nbd; size_t lds; SplitParams p; };
+
+constexpr uint64_t kDirectFloats = 1u << 19;     // of X; a larger one is always re-laid out (see HAC_LAUNCH_REUSE_XT)
+
+SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
+{
+    SplitPlan s = {};
+    if (B < 2 || desc->format == HAC_FORMAT_IM) return s;
+    if (launch) {
+        const uint32_t plain = HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE | HAC_LAUNCH_REUSE_XT | HAC_LAUNCH_NO_ROWS_KERNEL |
+                               (B <= 4 ? HAC_LAUNCH_NO_X_LDS : 0u);
+        if (launch->variant & ~plain || launch->cols_per_wave || launch->waves_per_block || launch->list_entries ||
+            launch->staging_words || launch->pass_width || launch->free_running || launch->tile_width) return s;
+    }
+    const uint64_t n = desc->n, m = desc->m;
+    // X as it is where that is little work for the L1s (a column reads nearly all lines of X; 0.1 ns per entry of W and row of X)
+    // against the 4 us of a launch that re-lays it out: 10673 x 492, 10 rows (5.2 us of lines) 33.3 as it is, 27.1 re-laid out;
+    // 4469 x 1686, 4 rows (3.0 us) 9.9 and 10.8
+    const double l1_us = 1.0e-7 * (double)n * (double)m * (double)B;       // every column reads all lines of X
+    s.direct = n * (uint64_t)B <= kDirectFloats && l1_us < 4.0;
+    if (!s.direct && (B <= 4 || xlds_plan(desc, B, launch).use)) return s;
+    uint32_t width = xt_width(n, B);
+    if (s.direct) {                                                        // tiles of at most 32 batch columns, all about as wide
+        const uint64_t each = ((uint64_t)B + ((uint64_t)B + 31) / 32 - 1) / (((uint64_t)B + 31) / 32);
+        width = each <= 4 ? 4u : each <= 8 ? 8u : each <= 16 ? 16u : each <= 24 ? 24u : 32u;
+    }
+    s.copy = launch && (launch->variant & HAC_LAUNCH_NO_X_LDS);
+    s.nbd = s.direct ? width : 0u;
+    const uint64_t tiles = ((uint64_t)B + width - 1) / width;
+    const uint64_t turn = s.direct ? 64u : 8u * 64u / (width / 4u);       // entries of a wavefront's turn
+    uint32_t split_log2 = 0;
+    // as many wavefronts per column as leave 16 to a CU, a second one up to 24 (6559 x 300, 28 % non-zero, 4 rows: 8 per column
+    // 11.5 us, 16 per column 20.2; 1719 x 2287, 28 %, 3 rows: one 12.1 us, two 9.3)
+    while (split_log2 < 4 && (m * tiles << (split_log2 + 1)) <= (split_log2 ? 4096u : 6144u) && (turn << split_log2) < desc->max_col_nnz) ++split_log2;
+    // one wavefront per column after all: the other kernels are as good or better, but for a few rows and short columns
+    // (8 rows of X, 512 x 4096, 10 % non-zero: 9.9 -> 7.3 us; 2 rows, 4096 x 4096, 40 %: 17.7 against 36.1)
+    if (split_log2 == 0 && (!s.direct || desc->max_col_nnz > 256)) return s;
+    const uint32_t waves_log2 = split_log2 < 2 ? 2u : split_log2, cols_log2 = waves_log2 - split_log2;
+    SplitParams& p = s.p;
+    p.waves = 1u << waves_log2; p.cols = 1u << cols_log2; p.cols_log2 = cols_log2; p.split_log2 = split_log2;
+    p.width = width;
+    const uint64_t nblocks = (m + p.cols - 1) >> cols_log2;
+    if (nblocks * tiles > 0x7ffffff0ull) return s;
+    p.nblocks = (uint32_t)nblocks; p.tiles = (uint32_t)tiles;
+    // everything a block needs has to fit: its columns' words, its non-zeros in one list, a lane for each of its chunks
+    const uint32_t chunk_least = hac_internal::chunk_base(desc->chunk);
+    uint64_t col_chunks = (desc->max_col_nnz + chunk_least - 1) / chunk_least;
+    if ((desc->chunk & hac_internal::kChunkPerColumn) && col_chunks > 64) col_chunks = 64;
+    if (col_chunks << cols_log2 > (uint64_t)p.waves * kWave) return s;
+    const bool ri_fields = desc->format == HAC_FORMAT_SHAC && desc->ri_coding == HAC_RI_FIELDS;
+    const double words = ((double)desc->max_col_bits / 32.0) * p.cols + 16.0 +
+                         (ri_fields ? (double)desc->max_col_nnz * p.cols * desc->ri_bits / 32.0 + 16.0 : 0.0);
+    const double lds = (double)table_bytes_of(desc) + 4.0 * (std::max(words, 2.0 * p.waves * width) + 32.0) + 8.0 * (double)desc->max_col_nnz * p.cols;
+    if (lds > (double)kLdsLimit) return s;
+    p.sbuf_words = round_up(std::max((uint32_t)words + 1u, 2u * p.waves * width), 4);
+    p.list_cap = (uint32_t)desc->max_col_nnz * p.cols;
+    s.lds = table_bytes_of(desc) + 4ull * p.sbuf_words + 8ull * p.list_cap;
+    s.use = s.lds <= kLdsLimit;
+    return s;
+}
+
 // bytes of workspace the sparse route needs: partial sums of the row-blocked kernel, or the feature-major copy of X
 size_t sparse_need(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
 {
@@ -1180,10 +1278,11 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     const char* const tf[2] = { "false", "true" };
     if (!io->xt_in && (!d_X || ldx < (int64_t)desc->n)) return HAC_EINVAL;
     if (!io->yt_out && (!d_Y || ldy < (int64_t)desc->m)) return HAC_EINVAL;
-    const Epilogue epi = { io->bias, io->yt_out, io->relu };
+    const Epilogue epi = { io->bias, io->yt_out, io->relu, xt_width(desc->m, B) };   // the next layer's n is m
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    uint32_t cpw = default_cpw(desc), wpb = 0, list_cap = 0, sbuf_words = 0, pass_w = 32, tile_b = kDefaultTile;
+    uint32_t cpw = default_cpw(desc), wpb = 0, list_cap = 0, sbuf_words = 0, pass_w = xt_width(desc->n, B), tile_b = kDefaultTile;
     bool reuse_xt = false, list_kernel = false;
+    if (pass_w < 32) pass_w = 32;
     if (launch) {
         if (launch->cols_per_wave > 32 || launch->waves_per_block > 16) return HAC_EINVAL;
         if (launch->cols_per_wave) cpw = launch->cols_per_wave;
@@ -1204,7 +1303,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         if (launch->free_running > 1) return HAC_EINVAL;
         if (launch->tile_width) tile_b = launch->tile_width;
         if (tile_b != 32 && tile_b != 64 && tile_b != 128 && tile_b != 256) return HAC_EINVAL;
-        if (tile_b < pass_w) return HAC_EINVAL;
+        if (tile_b < pass_w) { if (launch->pass_width) return HAC_EINVAL; pass_w = tile_b; }
     }
     const uint32_t nwaves = (d.m + cpw - 1) / cpw;
     const bool shac = format == HAC_FORMAT_SHAC && !d.rice;   // Rice-coded gaps decode like a HAC stream: no ri words
@@ -1280,7 +1379,10 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         hipError_t e = hipGetLastError();
         return e == hipSuccess ? HAC_OK : hip_fail(e);
     }
-    const XldsPlan xp = io->xt_in ? XldsPlan{ false, 0, 0, 0, 0 } : xlds_plan(desc, B, launch);
+    const SplitPlan sp = plan_split(desc, B, launch);
+    if (reuse_xt && ((uint64_t)d.n * (uint64_t)B <= kDirectFloats || (!launch->pass_width && pass_w != std::max(32u, xt_width(d.n, B)))))
+        reuse_xt = false;                                     // an earlier call need not have left a copy of this layout
+    const XldsPlan xp = io->xt_in || sp.use ? XldsPlan{ false, 0, 0, 0, 0 } : xlds_plan(desc, B, launch);
     if (xp.use) {
         // 2 to 8 batch rows and a short X: the block's own copy of X in LDS, lanes multiply what they decode
         if (!sbuf_words) sbuf_words = default_staging_words(desc, cpw);
@@ -1306,18 +1408,22 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     }
     const BatchShape bs = batch_shape(B, pass_w, tile_b);
     const float* XT = io->xt_in ? io->xt_in : d_X;           // B = 1: X is its own feature-major copy
+    const bool direct = sp.use && sp.direct && !sp.copy;
     if (B > 1 && !io->xt_in) {
-        const size_t need = 4ull * d.n * bs.Bp;
-        if (!d_ws || ws_bytes < need) return HAC_EWORKSPACE;
-        if (reinterpret_cast<uintptr_t>(d_ws) % 256) return HAC_EINVAL;
+        // (X read as it is needs no workspace; it is asked for all the same, so that what a call takes does not depend on the kernel)
+        const size_t need = direct ? sparse_need(desc, B, launch) : 4ull * d.n * bs.Bp;
+        if (need && (!d_ws || ws_bytes < need)) return HAC_EWORKSPACE;
+        if (need && reinterpret_cast<uintptr_t>(d_ws) % 256) return HAC_EINVAL;
+    }
+    if (B > 1 && !io->xt_in && !direct) {
         float* xt = static_cast<float*>(d_ws);
         XT = xt;
         if (!reuse_xt) {
-            if (bs.gw * bs.nb == 32) {
-                dim3 grid((d.n + 127) / 128, (uint32_t)((B + 31) / 32));     // panels of padding only are never read
+            if (bs.gw * bs.nb >= 32) {
+                dim3 grid((d.n + 127) / 128, (uint32_t)((B + 31) / 32));     // what lies past the batch is never read
                 const uint32_t vec = (reinterpret_cast<uintptr_t>(d_X) % 16 == 0 && ldx % 4 == 0) ? 1u : 0u;
                 hipLaunchKernelGGL(transpose_panel32_kernel, grid, dim3(256), 0, stream,
-                                   d_X, (uint32_t)B, d.n, (uint64_t)ldx, xt, vec);
+                                   d_X, (uint32_t)B, d.n, (uint64_t)ldx, xt, vec, bs.gw * bs.nb);
                 note_kernel("transpose_panel32_kernel");
             } else {
                 dim3 grid((d.n + 31) / 32, (bs.Bp + 31) / 32);
@@ -1328,6 +1434,28 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return hip_fail(e);
         }
+    }
+    if (sp.use) {
+        typedef void (*split_kern_t)(DevBlob, SplitParams, const float*, uint32_t, uint64_t, uint32_t, float*, uint64_t, Epilogue);
+        split_kern_t k;
+        switch (sp.nbd) {
+        case 0: k = shac ? dot_split_kernel<true, 0> : dot_split_kernel<false, 0>; break;
+        case 4: k = shac ? dot_split_kernel<true, 4> : dot_split_kernel<false, 4>; break;
+        case 8: k = shac ? dot_split_kernel<true, 8> : dot_split_kernel<false, 8>; break;
+        case 16: k = shac ? dot_split_kernel<true, 16> : dot_split_kernel<false, 16>; break;
+        case 24: k = shac ? dot_split_kernel<true, 24> : dot_split_kernel<false, 24>; break;
+        default: k = shac ? dot_split_kernel<true, 32> : dot_split_kernel<false, 32>; break;
+        }
+        if (sp.lds > 64 * 1024) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sp.lds);
+            if (e != hipSuccess) return hip_fail(e);
+        }
+        const uint32_t items = sp.p.nblocks * sp.p.tiles;
+        hipLaunchKernelGGL(k, dim3((items + 7) / 8 * 8), dim3(sp.p.waves * kWave), sp.lds, stream, d, sp.p, direct ? d_X : XT,
+                           direct ? 1u : xt_width(d.n, B), direct ? (uint64_t)ldx : 1u, (uint32_t)B, d_Y, (uint64_t)ldy, epi);
+        note_kernel("dot_split_kernel<%s, %u>", tf[shac], sp.nbd);
+        hipError_t e = hipGetLastError();
+        return e == hipSuccess ? HAC_OK : hip_fail(e);
     }
     // per-wave LDS: the stream (and ri) words of the wave's columns, and the list of one batch's non-zeros
     if (!sbuf_words) sbuf_words = default_staging_words(desc, cpw);
@@ -1410,9 +1538,10 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     if (items > 0x7ffffff0ull) return HAC_EINVAL;
     const uint32_t grid = (uint32_t)((items + 7) / 8 * 8);
     const bool with_epilogue = io->bias || io->relu || io->yt_out;
+    const bool own = bs.npass == 1 || bs.gw * bs.nb > 32;
     batch_kern_t k = with_epilogue
-        ? (shac ? pick_batch_kernel<true, true>(bs.nb, bs.npass > 1) : pick_batch_kernel<false, true>(bs.nb, bs.npass > 1))
-        : (shac ? pick_batch_kernel<true, false>(bs.nb, bs.npass > 1) : pick_batch_kernel<false, false>(bs.nb, bs.npass > 1));
+        ? (shac ? pick_batch_kernel<true, true>(bs.nb, bs.npass > 1, own) : pick_batch_kernel<false, true>(bs.nb, bs.npass > 1, own))
+        : (shac ? pick_batch_kernel<true, false>(bs.nb, bs.npass > 1, own) : pick_batch_kernel<false, false>(bs.nb, bs.npass > 1, own));
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1421,7 +1550,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     hipLaunchKernelGGL(k, dim3(grid), dim3(wpb * kWave), lds, stream,
                        d, XT, bs.Bp, (uint32_t)B, d_Y, (uint64_t)ldy, cpw, bs.gw, bs.npass, list_cap, sbuf_words, part_words, nblocks,
                        sync_passes, epi);
-    note_kernel("dot_batch_kernel<%s, %u, %s, %s>", tf[shac], bs.nb, tf[bs.nb == 4 && bs.npass > 1], tf[with_epilogue]);
+    note_kernel("dot_batch_kernel<%s, %u, %s, %s, %s>", tf[shac], bs.nb, tf[bs.nb == 4 && bs.npass > 1], tf[with_epilogue], tf[own]);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? HAC_OK : hip_fail(e);
 }
@@ -1521,7 +1650,8 @@ int plan_chain(const hac_layer_t* layers, uint32_t L, int64_t B, ChainPlan& P)
     for (uint32_t l = 0; l < L; ++l) {
         const hac_desc_t* d = layers[l].desc;
         P.sparse[l] = layer_sparse(d, B);
-        P.wants_xt[l] = P.sparse[l] && !xlds_plan(d, B, nullptr).use;
+        const SplitPlan sp = plan_split(d, B, nullptr);
+        P.wants_xt[l] = P.sparse[l] && (sp.use ? !sp.direct : !xlds_plan(d, B, nullptr).use);
         if (l + 1 < L) P.act_bytes = std::max<size_t>(P.act_bytes, (size_t)4 * P.Bp * (size_t)d->m);
     }
     P.act_bytes = (P.act_bytes + 255) / 256 * 256;

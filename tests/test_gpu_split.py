@@ -1,0 +1,111 @@
+"""dot_split_kernel (several wavefronts per column) against the oracle's dense fp64 product, at the edges of its splits.
+
+Tolerance: |Y - Yref| <= 1e-5 (|X| . |W|) componentwise (fp32 sums of at most a few thousand terms stay below 1e-6 of it).
+"""
+import numpy as np
+import pytest
+
+from oracle import dot as odot
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+ENCODERS = {"hac": ("hac_encode", {}), "shac": ("shac_encode", {}), "rice": ("shac_encode", {"ri_coding": 1})}
+
+
+@pytest.fixture(scope="module")
+def hac():
+    import paper_2108_12704_amd as lib
+    assert torch.cuda.is_available(), "GPU tests need a device"
+    return lib
+
+
+def matrix(n, m, density, seed, k=24):
+    rng = np.random.default_rng(seed)
+    values = np.sort(rng.standard_normal(k)).astype(np.float32)
+    W = np.where(rng.random((n, m)) < density, values[rng.integers(0, k, (n, m))], np.float32(0)).astype(np.float32)
+    W[:, 0] = 0                                              # an empty column first, one in the middle, one at the end
+    W[:, m // 2] = 0
+    W[:, -1] = 0
+    if m > 3:
+        W[:, 1] = values[rng.integers(0, k, n)]              # a column without a zero: the longest
+    return W
+
+
+def run(hac, fmt, W, X, strided=False):
+    enc, kw = ENCODERS[fmt]
+    db = getattr(hac, enc)(W, **kw).to_device("cuda:0")
+    dot = hac.hac_dot if fmt == "hac" else hac.shac_dot
+    B, n = X.shape
+    m = W.shape[1]
+    if not strided:
+        Y = dot(db, torch.from_numpy(X).cuda(), launch=hac.Launch(variant=0x400))
+        return Y, hac.hac_last_kernels()
+    Xp = torch.full((B, n + 3), float("nan"), device="cuda:0")
+    Yp = torch.full((B, m + 5), 7.0, device="cuda:0")
+    Xp[:, 1:n + 1] = torch.from_numpy(X)                     # rows of X that start at an odd address
+    Y = dot(db, Xp[:, 1:n + 1], Y=Yp[:, :m], launch=hac.Launch(variant=0x400))
+    assert bool((Yp[:, m:] == 7.0).all())
+    return Y, hac.hac_last_kernels()
+
+
+def check(Y, X, W):
+    ref, scale = odot.dense_dot(X, W), odot.abs_dot(X, W)
+    assert bool((np.abs(Y.cpu().numpy().astype(np.float64) - ref) <= 1e-5 * scale + 1e-37).all())
+
+
+# columns at and around those of a block (1, 2, 4), every width of a tile of X read as it is, one more row than a tile has
+@pytest.mark.parametrize("fmt", sorted(ENCODERS))
+@pytest.mark.parametrize("n,m,density,B,nbd", [(70, 1, 0.3, 2, 4), (300, 5, 0.3, 4, 4), (500, 300, 0.3, 5, 8), (500, 1025, 0.2, 8, 8),
+                                               (257, 2049, 0.1, 9, 16), (900, 33, 0.4, 16, 16), (3001, 10, 0.2, 17, 24),
+                                               (640, 65, 0.3, 25, 32), (640, 65, 0.02, 33, 24), (1200, 40, 0.3, 64, 32),
+                                               (4100, 21, 0.1, 65, 24), (2000, 3, 0.5, 200, 32)])
+def test_x_as_it_is(hac, fmt, n, m, density, B, nbd):
+    W = matrix(n, m, density, n + m)
+    X = np.random.default_rng(B).standard_normal((B, n)).astype(np.float32)
+    print(f"[case] split {fmt} {n}x{m} B={B}", flush=True)
+    Y, kernels = run(hac, fmt, W, X)
+    assert kernels == [f"dot_split_kernel<{'true' if fmt == 'shac' else 'false'}, {nbd}>"]
+    check(Y, X, W)
+    Ys, _ = run(hac, fmt, W, X, strided=True)
+    assert torch.equal(Ys, Y)
+
+
+# batches whose last panel or quad of batch columns is not full; two, four and sixteen wavefronts per column
+@pytest.mark.parametrize("fmt", sorted(ENCODERS))
+@pytest.mark.parametrize("n,m,density,B", [(9000, 1500, 0.03, 5), (4000, 1500, 0.03, 31), (9973, 700, 0.05, 37), (9973, 200, 0.05, 70),
+                                           (26000, 40, 0.05, 130), (9000, 130, 0.02, 300)])
+def test_rows_of_the_copy(hac, fmt, n, m, density, B):
+    W = matrix(n, m, density, n + m)
+    W[:, 1] *= (np.arange(n) % 5 == 0)                        # (all of a tall column's non-zeros have to fit the list)
+    X = np.random.default_rng(B).standard_normal((B, n)).astype(np.float32)
+    X[-1] = np.nan                                            # a row of X reaches its own row of Y only
+    print(f"[case] split, copy {fmt} {n}x{m} B={B}", flush=True)
+    Y, kernels = run(hac, fmt, W, X)
+    assert kernels[-1] == f"dot_split_kernel<{'true' if fmt == 'shac' else 'false'}, 0>" and len(kernels) == 2
+    check(Y[:-1], X[:-1], W)
+    assert bool(torch.isnan(Y[-1][torch.from_numpy((W != 0).any(0)).cuda()]).all())
+    Ys, _ = run(hac, fmt, W, X, strided=True)
+    assert torch.equal(Ys[:-1], Y[:-1])
+
+
+def test_a_column_too_long_for_the_list_takes_the_other_kernel(hac):
+    W = matrix(24000, 4, 0.9, 3)
+    X = np.random.default_rng(1).standard_normal((6, 24000)).astype(np.float32)
+    print("[case] split, long column", flush=True)
+    Y, kernels = run(hac, "hac", W, X)
+    assert not any("split" in k for k in kernels)
+    check(Y, X, W)
+
+
+def test_an_old_copy_of_x_is_only_reused_where_every_call_leaves_one(hac):
+    """HAC_LAUNCH_REUSE_XT (0x100) after a call that read X as it is: the copy is made, not assumed."""
+    rng = np.random.default_rng(5)
+    narrow, wide = matrix(1200, 20, 0.2, 1), matrix(1200, 4096, 0.05, 2)
+    X = rng.standard_normal((40, 1200)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    dn, dw = hac.hac_encode(narrow).to_device("cuda:0"), hac.shac_encode(wide).to_device("cuda:0")
+    ws = torch.full((max(hac.hac_workspace_bytes(d.desc, 40) for d in (dn, dw)) // 4,), float("nan"), device="cuda:0").view(torch.uint8)
+    print("[case] reuse of the copy", flush=True)
+    check(hac.hac_dot(dn, Xd, workspace=ws), X, narrow)
+    check(hac.shac_dot(dw, Xd, workspace=ws, launch=hac.Launch(variant=0x500)), X, wide)
