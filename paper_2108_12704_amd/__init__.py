@@ -1,6 +1,6 @@
 """Thin Python binding of libhac (see include/hac.h for the contract).
 
-Argument marshalling only: encoders run in the C++ host library, every step
+Argument marshalling only (for the dot calls in csrc/hac_bind.cpp): encoders run in the C++ host library, every step
 of Y = X.W runs in the HIP kernels.  PyTorch supplies device memory and the
 stream.  There is no CPU fallback: a missing library is an error.
 """
@@ -407,44 +407,38 @@ def _stream_handle(stream) -> int:
     return int(s.cuda_stream)
 
 
-def _dot(fn_name: str, dblob: DeviceBlob, X, Y=None, workspace=None, launch: Optional[Launch] = None,
-         stream=None):
-    import torch
-    lib = load_library()
-    if X.dtype != torch.float32 or X.dim() != 2 or not X.is_cuda:
-        raise TypeError("X must be a 2-D float32 CUDA tensor")
-    if X.stride(1) != 1:
-        X = X.contiguous()
-    B, n = X.shape
-    if n != dblob.n:
-        raise ValueError("X has the wrong width")
-    if Y is None:
-        Y = torch.empty((B, dblob.m), dtype=torch.float32, device=X.device)
-    elif Y.dtype != torch.float32 or Y.shape != (B, dblob.m) or Y.stride(1) != 1 or not Y.is_cuda:
-        raise TypeError("Y must be a B x m float32 CUDA tensor with unit column stride")
-    need = hac_workspace_bytes(dblob.desc, B, launch)
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    ldx = X.stride(0) if B > 1 else max(n, 1)
-    ldy = Y.stride(0) if B > 1 else max(dblob.m, 1)
-    rc = getattr(lib, fn_name)(C.byref(dblob.desc), dblob.tensor.data_ptr(), X.data_ptr(), B, ldx,
-                               Y.data_ptr(), ldy, ws_ptr, ws_bytes,
-                               C.byref(launch) if launch is not None else None,
-                               _stream_handle(stream))
-    _check(rc, fn_name)
-    return Y
+_bound = None
+
+
+def _native():
+    """The native call path (csrc/hac_bind.cpp), bound to the library; raise if it has not been built."""
+    global _bound
+    if _bound is None:
+        import importlib.machinery
+        import importlib.util
+
+        import torch  # noqa: F401  (the module's symbols)
+        path = os.path.join(_HERE, "_hacbind.so")
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: run `python __graft_entry__.py` (build) first")
+        loader = importlib.machinery.ExtensionFileLoader("_hacbind", path)
+        mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_hacbind", loader))
+        loader.exec_module(mod)
+        lib = load_library()
+        mod.bind(_check, *(C.cast(getattr(lib, f), C.c_void_p).value for f in (
+            "hac_dot", "shac_dot", "im_dot", "hac_dot_noalloc", "hac_workspace_bytes_for", "hac_forward", "hac_forward_workspace_bytes")))
+        _bound = mod
+    return _bound
 
 
 def hac_dot(dblob: DeviceBlob, X, Y=None, workspace=None, launch=None, stream=None):
     """Y = X . W for a HAC blob on the device (asynchronous on the stream)."""
-    return _dot("hac_dot", dblob, X, Y, workspace, launch, stream)
+    return (_bound or _native()).hac_dot(dblob, X, Y, workspace, launch, stream)
 
 
 def shac_dot(dblob: DeviceBlob, X, Y=None, workspace=None, launch=None, stream=None):
     """Y = X . W for an sHAC blob on the device (asynchronous on the stream)."""
-    return _dot("shac_dot", dblob, X, Y, workspace, launch, stream)
+    return (_bound or _native()).shac_dot(dblob, X, Y, workspace, launch, stream)
 
 
 def hac_last_kernels() -> list:
@@ -459,21 +453,7 @@ NOALLOC_WORKSPACE_BYTES = 16 << 20
 def hac_dot_noalloc(dblob: DeviceBlob, X, Y, launch: Optional[Launch] = None, stream=None):
     """hac_dot / shac_dot (by the blob's format) with the workspace inside the library: the call
     allocates nothing, so X and Y must be given, contiguous along their rows."""
-    import torch
-    lib = load_library()
-    if X.dtype != torch.float32 or X.dim() != 2 or not X.is_cuda or X.stride(1) != 1:
-        raise TypeError("X must be a 2-D float32 CUDA tensor with unit column stride")
-    B, n = X.shape
-    if n != dblob.n:
-        raise ValueError("X has the wrong width")
-    if Y.dtype != torch.float32 or Y.shape != (B, dblob.m) or Y.stride(1) != 1 or not Y.is_cuda:
-        raise TypeError("Y must be a B x m float32 CUDA tensor with unit column stride")
-    ldx = X.stride(0) if B > 1 else max(n, 1)
-    ldy = Y.stride(0) if B > 1 else max(dblob.m, 1)
-    rc = lib.hac_dot_noalloc(C.byref(dblob.desc), dblob.tensor.data_ptr(), X.data_ptr(), B, ldx, Y.data_ptr(), ldy,
-                             C.byref(launch) if launch is not None else None, _stream_handle(stream))
-    _check(rc, "hac_dot_noalloc")
-    return Y
+    return (_bound or _native()).hac_dot_noalloc(dblob, X, Y, launch, stream)
 
 
 def hac_encode_dev(W, fmt: int = HAC_FORMAT_HAC, chunk_nnz: int = 0, ri_bits: int = 0, lut_bits: int = 0,
@@ -528,7 +508,7 @@ def hac_dot_route(desc: Desc, B: int, launch: Optional["Launch"] = None) -> int:
 
 def im_dot(dblob: DeviceBlob, X, Y=None, workspace=None, stream=None):
     """Y = X . W for an index-map blob on the device (asynchronous on the stream)."""
-    return _dot("im_dot", dblob, X, Y, workspace, None, stream)
+    return (_bound or _native()).im_dot(dblob, X, Y, workspace, stream)
 
 
 def _layer_array(layers):
@@ -553,30 +533,7 @@ def hac_forward_workspace_bytes(layers, B: int) -> int:
 
 def hac_forward(layers, X, Y=None, workspace=None, stream=None):
     """Y = act_L(... act_0(X . W_0 + b_0) ... . W_L + b_L); layers: (DeviceBlob, bias or None, relu) per layer."""
-    import torch
-    lib = load_library()
-    if X.dtype != torch.float32 or X.dim() != 2 or not X.is_cuda:
-        raise TypeError("X must be a 2-D float32 CUDA tensor")
-    if X.stride(1) != 1:
-        X = X.contiguous()
-    B = X.shape[0]
-    m_out = layers[-1][0].m
-    if Y is None:
-        Y = torch.empty((B, m_out), dtype=torch.float32, device=X.device)
-    elif Y.dtype != torch.float32 or Y.shape != (B, m_out) or Y.stride(1) != 1 or not Y.is_cuda:
-        raise TypeError("Y must be a B x m float32 CUDA tensor with unit column stride")
-    arr = _layer_array(layers)
-    need = int(lib.hac_forward_workspace_bytes(arr, len(layers), B))
-    if workspace is None and need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=X.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    ldx = X.stride(0) if B > 1 else max(X.shape[1], 1)
-    ldy = Y.stride(0) if B > 1 else max(m_out, 1)
-    rc = lib.hac_forward(arr, len(layers), X.data_ptr(), B, ldx, Y.data_ptr(), ldy, ws_ptr, ws_bytes,
-                         _stream_handle(stream))
-    _check(rc, "hac_forward")
-    return Y
+    return (_bound or _native()).hac_forward(layers, X, Y, workspace, stream)
 
 
 def hac_decode_dev(dblob: DeviceBlob, stream=None):

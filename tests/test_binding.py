@@ -1,0 +1,63 @@
+"""The native call path of the binding: arguments by position and name, and what it refuses, without a GPU."""
+import pytest
+
+import paper_2108_12704_amd as hac
+
+torch = pytest.importorskip("torch")
+
+X = "X must be a 2-D float32 CUDA tensor"
+
+
+@pytest.mark.parametrize("call,args,kw,error,text", [
+    ("hac_dot", (), {}, TypeError, "missing argument 'dblob'"),
+    ("hac_dot", (None,), {}, TypeError, "missing argument 'X'"),
+    ("hac_dot", (None, torch.zeros(2, 3)), {}, TypeError, X),                       # not on the GPU
+    ("shac_dot", (), {"dblob": None, "X": [[1.0]]}, TypeError, X),                  # not a tensor
+    ("im_dot", (None, torch.zeros(2, 3), None, None, None, None), {}, TypeError, "too many arguments"),
+    ("im_dot", (None, torch.zeros(2, 3)), {"launch": None}, TypeError, "unexpected keyword argument 'launch'"),
+    ("hac_dot", (None, torch.zeros(2, 3)), {"X": None}, TypeError, "multiple values for argument 'X'"),
+    ("hac_dot_noalloc", (None, torch.zeros(2, 3), None), {}, TypeError, X + " with unit column stride"),
+    ("hac_forward", ([], torch.zeros(2, 3, dtype=torch.float64)), {}, TypeError, X),
+])
+def test_refused_arguments(call, args, kw, error, text):
+    with pytest.raises(error, match=text):
+        getattr(hac._native(), call)(*args, **kw)
+
+
+def test_public_calls_go_through_it():
+    with pytest.raises(TypeError, match=X):
+        hac.hac_dot(None, torch.zeros(2, 3))
+    with pytest.raises(TypeError, match=X):
+        hac.hac_forward([], torch.zeros(2, 3))
+
+
+@pytest.mark.gpu
+def test_results_buffers_and_errors_on_the_gpu():
+    import numpy as np
+    W = np.zeros((300, 40), np.float32)
+    W[::7, ::3] = 0.5
+    db = hac.hac_encode(W).to_device("cuda:0")
+    x = torch.rand(6, 300, device="cuda:0")
+    y = torch.full((6, 40), -1.0, device="cuda:0")
+    ws = torch.empty(max(hac.hac_workspace_bytes(db.desc, 6), 256), dtype=torch.uint8, device="cuda:0")
+    print("[case] binding", flush=True)
+    ref = x.double().cpu() @ torch.from_numpy(W).double()
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    assert hac.hac_dot(db, x, Y=y, workspace=ws, launch=hac.Launch(), stream=stream) is y
+    stream.synchronize()
+    assert torch.allclose(y.cpu().double(), ref, rtol=1e-5, atol=1e-5)              # (43 terms of at most 0.5)
+    assert torch.equal(hac.hac_dot(db, x.t().contiguous().t()), y)                  # rows of X not contiguous
+    assert hac.hac_dot(db, x[:0]).shape == (0, 40)
+    assert hac.hac_dot_noalloc(db, x, y) is y
+    for bad in (y[:5], y.double(), y.cpu(), torch.empty(40, 6, device="cuda:0").t()):
+        with pytest.raises(TypeError, match="Y must be"):
+            hac.hac_dot(db, x, Y=bad)
+    with pytest.raises(ValueError, match="X has the wrong width"):
+        hac.hac_dot(db, x[:, 1:])
+    with pytest.raises(hac.HacError) as e:
+        hac.shac_dot(db, x)
+    assert e.value.status == -1 and "shac_dot" in str(e.value)
+    with pytest.raises(TypeError, match="bias must be"):
+        hac.hac_forward([(db, torch.zeros(39, device="cuda:0"), True)], x)
+    assert torch.equal(hac.hac_forward([(db, None, np.bool_(False))], x), hac.hac_dot(db, x))
