@@ -16,15 +16,23 @@
 // (inf - inf).  A block that meets such an operand, or whose sums are not finite, computes its tile with the fp32
 // instruction instead.
 //
-// Tiling: a block of 4 wavefronts owns 32 RT batch rows x 128 columns of Y (RT = 1..4) and walks K = n
-// in steps of 32; wavefront w owns the 32 columns [32 w, 32 w + 32) of the tile and all its rows, as RT
-// MFMA tiles (two sums each, 32 RT accumulator registers).  LDS holds one K step of X and W, both with the 32 k of a
-// row (a column) side by side, part by part, 208 bytes apart, so that an operand is one 128-bit read and 16
-// lanes' reads fall on different banks.  The next step's global loads fly during the matrix
-// instructions; two blocks share a CU, so that one splits and stores while the other multiplies.
-// Measured (MI355X), fp32 instruction -> bf16 parts: 4608 x 512 layer pruned 60 %, 12544 rows, whole call
-// 580 -> 351 us (59 GFLOP; a call includes decoding the stream, about 25 us); unpruned map of that size,
-// 784 rows, 60.0 -> 37.4 us.  Matrix pipes 44 % busy at 12544 rows, four vector instructions beside each matrix one.
+// Tiling: a block of 4 wavefronts owns 32 RT batch rows x 128 columns of Y (RT = 1..4; some blocks a row tile less, so that all CUs
+// get the same) and walks K = n in steps of 32; wavefront w owns the 32 columns [32 w, 32 w + 32) of the tile and all its
+// rows, as RT MFMA tiles (two sums each, 32 RT accumulator registers).  LDS holds two K steps: of X as parts, the 32 k of a row side
+// by side, part by part, 208 bytes apart, so that an operand is one 128-bit read and 16 lanes' reads fall on different
+// banks; of W the pointers only, turned so that a lane reads eight k of its column at once.  A column belongs to one
+// wavefront, so its pointers are looked up by the lanes that multiply the values, straight into operands: writing parts of W
+// to LDS and reading them back took a third of the LDS pipe's time.
+// What bounds a step is the order of its instructions: two wavefronts on a SIMD do not cover what one of them waits for.  One
+// barrier a step; X is split and stored for the next step, pointers for the one after next, operands are read a row tile and
+// looked up half a step ahead, and every global load has a step to arrive, all of it between matrix instructions
+// (sched_group_barrier; the compiler's own order, with the loads behind the products and waits before each, took 390 us
+// where this one takes 348).
+// Measured (MI355X), fp32 instruction -> bf16 parts, W's parts in LDS -> this kernel, whole calls: 4608 x 512 layer pruned 60 %, 12544
+// rows 580 -> 354 -> 331 us (59 GFLOP; a call includes decoding the stream, about 25 us); unpruned map of that size, 784 rows
+// 60.0 -> 37.9 -> 35.4 us; products alone 2048 x 2000 x 2000 112 -> 93, 12544 x 576 x 64 25.9 -> 20.5, 64 x 25088 x 1000 42 -> 35,
+// 512 x 9973 x 1511 98 -> 93, 300 x 4096 x 4096 84 -> 71, 46 x 64 x 10 5.6 -> 5.6.  Same sums in the same order, same bits.
+// Before row tiles were dealt evenly matrix pipes were 51 % busy at 12544 rows (44 % with W in LDS; 67 % on a CU with two blocks).
 // Lane layout of v_mfma_f32_32x32x16_bf16: A operand lane l holds A[i = l % 32][k = 8 (l / 32) + 0..7], B
 // operand lane l holds B[k = 8 (l / 32) + 0..7][j = l % 32], accumulator register v of lane l is
 // D[(v % 4) + 8 (v / 4) + 4 (l / 32)][l % 32].
@@ -32,35 +40,61 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "hac_internal.h"
 
 namespace {
 
 constexpr int BN = 128, BK = 32;
-constexpr int PART = 2 * BK, PITCH = 3 * PART + 16;   // bytes: one part of a row's K step, one row in LDS
+constexpr int PART = 2 * BK, PITCH = 3 * PART + 16;   // bytes: one part of a row's K step, one row of X in LDS
+// bytes between two columns' pointers in LDS: 16 (32) lanes' 128-bit (64-bit) reads fall on different banks
+template <typename IdxT> constexpr int ptr_pitch() { return sizeof(IdxT) == 1 ? BK + 8 : 2 * BK + 16; }
+// two K steps of X and of pointers
+template <typename IdxT> constexpr int tile_bytes(int rt) { return 2 * (32 * rt * PITCH + BN * ptr_pitch<IdxT>()); }
 constexpr uint32_t kMinRT = 1, kMaxRT = 4;              // row tiles of 32 per block
 constexpr uint32_t kLutLdsMax = 4096;              // representatives kept in LDS
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Four neighbouring pointers of one row of the map.
+// Pointers: four neighbouring ones of a row of the map as they are loaded (raw), eight k of one column as a lane multiplies them
+// (oct).  __builtin_amdgcn_perm(hi, lo, ..) picks bytes of two words.
+__device__ __forceinline__ uint32_t upper16(uint32_t hi, uint32_t lo) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); }
+__device__ __forceinline__ uint32_t lower16(uint32_t hi, uint32_t lo) { return __builtin_amdgcn_perm(hi, lo, 0x05040100u); }
 template <typename IdxT> struct Ptr4;
 template <> struct Ptr4<uint8_t> {
     typedef uint32_t raw;
+    typedef uint2 oct;
     static __device__ __forceinline__ uint32_t get(raw w, int c) { return (w >> (8 * c)) & 255u; }
+    static __device__ __forceinline__ uint32_t get8(oct w, int j) { return ((j & 4 ? w.y : w.x) >> (8 * (j & 3))) & 255u; }
     static __device__ __forceinline__ void ld(const uint8_t* p, uint32_t* out) {
         const uint32_t w = *reinterpret_cast<const uint32_t*>(p);
         out[0] = w & 255u; out[1] = (w >> 8) & 255u; out[2] = (w >> 16) & 255u; out[3] = w >> 24;
     }
+    // rows r[0..3] of four columns -> out[c]: the four k of column c
+    static __device__ __forceinline__ void turn(const raw* r, raw* out) {
+        const uint32_t a = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u), b = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u);
+        const uint32_t c = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u), d = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+        out[0] = lower16(b, a); out[1] = upper16(b, a); out[2] = lower16(d, c); out[3] = upper16(d, c);
+    }
 };
 template <> struct Ptr4<uint16_t> {
     typedef uint2 raw;
+    typedef uint4 oct;
     static __device__ __forceinline__ uint32_t get(raw w, int c) { return ((c & 2 ? w.y : w.x) >> (16 * (c & 1))) & 65535u; }
+    static __device__ __forceinline__ uint32_t get8(oct w, int j) {
+        return ((j & 4 ? (j & 2 ? w.w : w.z) : (j & 2 ? w.y : w.x)) >> (16 * (j & 1))) & 65535u;
+    }
     static __device__ __forceinline__ void ld(const uint16_t* p, uint32_t* out) {
         const uint2 w = *reinterpret_cast<const uint2*>(p);
         out[0] = w.x & 65535u; out[1] = w.x >> 16; out[2] = w.y & 65535u; out[3] = w.y >> 16;
+    }
+    static __device__ __forceinline__ void turn(const raw* r, raw* out) {
+        out[0] = make_uint2(lower16(r[1].x, r[0].x), lower16(r[3].x, r[2].x));
+        out[1] = make_uint2(upper16(r[1].x, r[0].x), upper16(r[3].x, r[2].x));
+        out[2] = make_uint2(lower16(r[1].y, r[0].y), lower16(r[3].y, r[2].y));
+        out[3] = make_uint2(upper16(r[1].y, r[0].y), upper16(r[3].y, r[2].y));
     }
 };
 
@@ -80,9 +114,21 @@ __device__ __forceinline__ uint2 split_weight(float w, uint32_t& cut)
 }
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 float4u __attribute__((aligned(4)));        // global memory takes 128-bit loads at any word
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t two_bf16(f32x2 v) { return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2)); }   // to nearest even
 __device__ __forceinline__ f32x2 two_f32(uint32_t p) { return f32x2{__uint_as_float(p << 16), __uint_as_float(p & 0xffff0000u)}; }
+
+// the order inside a row tile's group: after each of its six matrix instructions up to `n` other vector instructions
+#define ALWAYS_INLINE __attribute__((always_inline))
+#define INTERLEAVE(n)                                              \
+    do {                                                           \
+        _Pragma("unroll") for (int z = 0; z < 6; ++z) {            \
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     \
+            __builtin_amdgcn_sched_group_barrier(0x002, n, 0);     \
+        }                                                          \
+    } while (0)
 
 __device__ __forceinline__ uint32_t logical_tile(uint32_t tiles_padded)
 {
@@ -91,43 +137,48 @@ __device__ __forceinline__ uint32_t logical_tile(uint32_t tiles_padded)
     return (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
 }
 
-// (blocks per CU: as many as the LDS of a K step lets in for 2 to 4 row tiles; left to itself the compiler spends
-// registers on the fp32 pass and one block fewer fits)
-template <typename IdxT, bool LUT_LDS, int RT, bool XVEC>
-__global__ void __launch_bounds__(256, RT == 4 ? 2 : RT == 3 ? 3 : 4)
+// (blocks per CU: 2 of three or four row tiles, 3 of two, 4 of one; their accumulators and operands in flight fill the registers)
+template <typename IdxT, bool LUT_LDS, int RT>
+__global__ void __launch_bounds__(256, RT >= 3 ? 2 : RT == 2 ? 3 : 4)
 index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
                   const IdxT* __restrict__ idx, uint64_t pitch,          // pitch in elements, a multiple of 16
                   const float* __restrict__ codebook, uint32_t k_sym, uint32_t zero_first,
                   uint32_t n, uint32_t m, float* __restrict__ Y, uint64_t ldy,
-                  uint32_t tiles_n, uint32_t tiles, uint32_t x_vec,
-                  uint32_t splits, uint32_t steps_per_split, float* __restrict__ part)
+                  uint32_t tiles_n, uint32_t row_groups, uint32_t splits, uint32_t steps_per_split, float* __restrict__ part)
 {
     constexpr int BM = 32 * RT;
     extern __shared__ __align__(16) float lds[];
-    char* As = reinterpret_cast<char*>(lds);           // [BM] rows of PITCH bytes
-    char* Bs = As + BM * PITCH;                        // [BN] columns of PITCH bytes
-    uint2* lut = reinterpret_cast<uint2*>(Bs + BN * PITCH);   // [k_sym + zero_first] when LUT_LDS
+    constexpr int PP = ptr_pitch<IdxT>(), ABYTES = BM * PITCH, BBYTES = BN * PP;
+    char* As = reinterpret_cast<char*>(lds);           // two buffers of [BM] rows of PITCH bytes
+    char* Ps = As + 2 * ABYTES;                        // two buffers of [BN] columns of PP bytes
+    uint2* lut = reinterpret_cast<uint2*>(Ps + 2 * BBYTES);   // [k_sym + zero_first] when LUT_LDS
     // work item = (tile, K split); with more than one split a block writes its partial tile to
     // part[split][B][m] and a second kernel adds the splits in order
     const uint32_t item = logical_tile(gridDim.x);
-    if (item >= tiles * splits) return;
+    if (item >= row_groups * tiles_n * splits) return;
     const uint32_t tile = item / splits, split = item - tile * splits;
     const uint32_t tm = tile / tiles_n, tn = tile - tm * tiles_n;
-    const uint32_t m0 = tm * BM, n0 = tn * BN;
+    // row tiles of this block: RT, or RT - 1 where there are more groups than RT needs
+    const uint32_t row_tiles = (B + 31) / 32;
+    const uint32_t first = (uint32_t)((uint64_t)tm * row_tiles / row_groups);
+    const uint32_t nr = (uint32_t)((uint64_t)(tm + 1) * row_tiles / row_groups) - first;
+    const uint32_t m0 = 32 * first, n0 = tn * BN;
     const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const uint32_t l32 = lane & 31, half = lane >> 5;
 
     // pointer -> value; entry 0 is 0.0 when the pointers were written with an offset of one
     const uint32_t k_tot = k_sym + zero_first;
-    auto value_of = [&](uint32_t p) -> float { return (zero_first && p == 0) ? 0.0f : codebook[p - zero_first]; };
+    auto value_of = [&](uint32_t p) ALWAYS_INLINE -> float { return (zero_first && p == 0) ? 0.0f : codebook[p - zero_first]; };
     uint32_t cut = 0;                                  // lower half not 0: some operand is more than its three parts
-    auto parts_of = [&](uint32_t p) -> uint2 { return LUT_LDS ? lut[p] : split_weight(value_of(p), cut); };
+    typedef typename Ptr4<IdxT>::raw raw_t;
+    typedef typename Ptr4<IdxT>::oct oct_t;
+    auto parts_of = [&](uint32_t p) ALWAYS_INLINE -> uint2 { return LUT_LDS ? lut[p] : split_weight(value_of(p), cut); };
 
     // Global -> registers.  X: rows a_row + 32 r, k = 4 q .. 4 q + 3; map: rows 4 q .. 4 q + 3, columns
     // b_col .. b_col + 3 (four k of a column in one thread, so that a part of them is one 64-bit store).
     // Rows past B and columns past the pitch are read from a clamped, valid address and never stored;
     // only the last, partial K step is guarded.
-    struct Stage { float4 ra[RT]; typename Ptr4<IdxT>::raw rb[4]; };
+    struct Stage { f32x4 ra[RT]; raw_t rb[4]; };
     const uint32_t q = t & 7, a_row = t >> 3, b_col = 4 * (t >> 3);
     const float* xrow[RT];
 #pragma unroll
@@ -136,70 +187,58 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
         xrow[r] = X + (uint64_t)(row < B ? row : B - 1) * ldx + 4 * q;
     }
     const IdxT* icol = idx + (n0 + b_col < pitch ? n0 + b_col : 0);
-    auto load_full = [&](uint32_t k0, Stage& st) {
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            const float* p = xrow[r] + k0;
-            if (XVEC) st.ra[r] = *reinterpret_cast<const float4*>(p);
-            else st.ra[r] = make_float4(p[0], p[1], p[2], p[3]);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            st.rb[j] = *reinterpret_cast<const typename Ptr4<IdxT>::raw*>(icol + (uint64_t)(k0 + 4 * q + j) * pitch);
+    Stage st;
+    auto load_x_full = [&](uint32_t kt, int r) ALWAYS_INLINE {
+        st.ra[r] = *reinterpret_cast<const float4u*>(xrow[r] + kt * BK);   // (rows of X start at any float)
     };
-    auto load_tail = [&](uint32_t k0, Stage& st) {
-        const uint32_t k = k0 + 4 * q;
+    auto load_p_full = [&](uint32_t kt, raw_t* rb) ALWAYS_INLINE {
 #pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            const float* p = xrow[r] + k0;
-            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (k < n) v.x = p[0];
-            if (k + 1 < n) v.y = p[1];
-            if (k + 2 < n) v.z = p[2];
-            if (k + 3 < n) v.w = p[3];
-            st.ra[r] = v;
-        }
+        for (int j = 0; j < 4; ++j) rb[j] = *reinterpret_cast<const raw_t*>(icol + (uint64_t)(kt * BK + 4 * q + j) * pitch);
+    };
+    const uint32_t nfull = n / BK;
+    auto load_x = [&](uint32_t kt, int r) ALWAYS_INLINE {
+        if (kt < nfull) { load_x_full(kt, r); return; }
+        const uint32_t k = kt * BK + 4 * q;
+        const float* p = xrow[r] + kt * BK;
+        f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (k < n) v.x = p[0];
+        if (k + 1 < n) v.y = p[1];
+        if (k + 2 < n) v.z = p[2];
+        if (k + 3 < n) v.w = p[3];
+        st.ra[r] = v;
+    };
+    auto load_p = [&](uint32_t kt, raw_t* rb) ALWAYS_INLINE {
+        if (kt < nfull) { load_p_full(kt, rb); return; }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {                  // (past the end: any row of the map, X is 0 there)
-            const uint32_t kj = k + j < n ? k + j : n - 1;
-            st.rb[j] = *reinterpret_cast<const typename Ptr4<IdxT>::raw*>(icol + (uint64_t)kj * pitch);
+            const uint32_t k = kt * BK + 4 * q + j;
+            rb[j] = *reinterpret_cast<const raw_t*>(icol + (uint64_t)(k < n ? k : n - 1) * pitch);
         }
     };
-    // registers -> LDS.  __builtin_amdgcn_perm(hi, lo, ..) packs the upper (lower) halves of two words.
-    auto upper = [](uint32_t hi, uint32_t lo) { return __builtin_amdgcn_perm(hi, lo, 0x07060302u); };
-    auto lower = [](uint32_t hi, uint32_t lo) { return __builtin_amdgcn_perm(hi, lo, 0x05040100u); };
-    auto store = [&](const Stage& st) {
+    // registers -> LDS, buffer `buf`
+    auto store_p = [&](uint32_t buf, const raw_t* rb) ALWAYS_INLINE {
+        raw_t col[4];
+        Ptr4<IdxT>::turn(rb, col);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            uint2 w[4];
+        for (int c = 0; c < 4; ++c) *reinterpret_cast<raw_t*>(Ps + buf * BBYTES + (b_col + c) * PP + 4 * sizeof(IdxT) * q) = col[c];
+    };
+    auto store_x = [&](uint32_t buf, int r) ALWAYS_INLINE {
+        const float x[4] = {st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w};
+        uint32_t p1[2], p2[2], p3[2];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w[j] = parts_of(Ptr4<IdxT>::get(st.rb[j], c));
-            char* b = Bs + (b_col + c) * PITCH + 8 * q;
-            *reinterpret_cast<uint2*>(b) = make_uint2(lower(w[1].x, w[0].x), lower(w[3].x, w[2].x));
-            *reinterpret_cast<uint2*>(b + PART) = make_uint2(upper(w[1].x, w[0].x), upper(w[3].x, w[2].x));
-            *reinterpret_cast<uint2*>(b + 2 * PART) = make_uint2(lower(w[1].y, w[0].y), lower(w[3].y, w[2].y));
+        for (int j = 0; j < 2; ++j) {
+            const f32x2 v = {x[2 * j], x[2 * j + 1]};
+            p1[j] = two_bf16(v);
+            const f32x2 r1 = v - two_f32(p1[j]);
+            p2[j] = two_bf16(r1);
+            const f32x2 r2 = r1 - two_f32(p2[j]);
+            p3[j] = two_bf16(r2);
+            cut |= __float_as_uint(r2.x) | __float_as_uint(r2.y);
         }
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            const float x[4] = {st.ra[r].x, st.ra[r].y, st.ra[r].z, st.ra[r].w};
-            uint32_t p1[2], p2[2], p3[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const f32x2 v = {x[2 * j], x[2 * j + 1]};
-                p1[j] = two_bf16(v);
-                const f32x2 r1 = v - two_f32(p1[j]);
-                p2[j] = two_bf16(r1);
-                const f32x2 r2 = r1 - two_f32(p2[j]);
-                p3[j] = two_bf16(r2);
-                // (a three-operand OR; from plain C the compiler reorders the whole step around it: 336 -> 359 us at
-                // 4608 x 512, 12544 rows)
-                asm("v_or3_b32 %0, %1, %2, %0" : "+v"(cut) : "v"(r2.x), "v"(r2.y));
-            }
-            char* a = As + (a_row + 32 * r) * PITCH + 8 * q;
-            *reinterpret_cast<uint2*>(a) = make_uint2(p1[0], p1[1]);
-            *reinterpret_cast<uint2*>(a + PART) = make_uint2(p2[0], p2[1]);
-            *reinterpret_cast<uint2*>(a + 2 * PART) = make_uint2(p3[0], p3[1]);
-        }
+        char* a = As + buf * ABYTES + (a_row + 32 * r) * PITCH + 8 * q;
+        *reinterpret_cast<uint2*>(a) = make_uint2(p1[0], p1[1]);
+        *reinterpret_cast<uint2*>(a + PART) = make_uint2(p2[0], p2[1]);
+        *reinterpret_cast<uint2*>(a + 2 * PART) = make_uint2(p3[0], p3[1]);
     };
 
     // x1 w1 has a sum of its own: the instruction rounds a sum once per 16 k, and the five others, 2^-8 of it
@@ -211,39 +250,43 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[i][v] = low[i][v] = 0.0f;
 
-    auto multiply = [&]() {
-        const char* a = As + l32 * PITCH + 16 * half;
-        const char* b = Bs + (wave * 32 + l32) * PITCH + 16 * half;
+    // a lane's operand of 16 k: the parts of eight k of its column, looked up by the wavefront that multiplies them
+    auto pointers = [&](uint32_t buf, int h) ALWAYS_INLINE -> oct_t {
+        return *reinterpret_cast<const oct_t*>(Ps + buf * BBYTES + (wave * 32 + l32) * PP + (16 * h + 8 * half) * sizeof(IdxT));
+    };
+    auto look_up = [&](const oct_t& p, uint2* v) ALWAYS_INLINE {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {                  // 16 k each
-            bf16x8 w[3];
+        for (int j = 0; j < 8; ++j) v[j] = parts_of(Ptr4<IdxT>::get8(p, j));
+    };
+    auto pack = [&](const uint2* v, bf16x8* w) ALWAYS_INLINE {
+        w[0] = __builtin_bit_cast(bf16x8, make_uint4(lower16(v[1].x, v[0].x), lower16(v[3].x, v[2].x), lower16(v[5].x, v[4].x), lower16(v[7].x, v[6].x)));
+        w[1] = __builtin_bit_cast(bf16x8, make_uint4(upper16(v[1].x, v[0].x), upper16(v[3].x, v[2].x), upper16(v[5].x, v[4].x), upper16(v[7].x, v[6].x)));
+        w[2] = __builtin_bit_cast(bf16x8, make_uint4(lower16(v[1].y, v[0].y), lower16(v[3].y, v[2].y), lower16(v[5].y, v[4].y), lower16(v[7].y, v[6].y)));
+    };
+    struct RowParts { bf16x8 x[3]; };
+    auto rows = [&](uint32_t buf, int h, int i) ALWAYS_INLINE -> RowParts {
+        const char* a = As + buf * ABYTES + (l32 + 32 * i) * PITCH + 16 * half + 32 * h;
+        RowParts o;
 #pragma unroll
-            for (int p = 0; p < 3; ++p) w[p] = *reinterpret_cast<const bf16x8*>(b + p * PART + 32 * h);
-#pragma unroll
-            for (int i = 0; i < RT; ++i) {
-                bf16x8 x[3];
-#pragma unroll
-                for (int p = 0; p < 3; ++p) x[p] = *reinterpret_cast<const bf16x8*>(a + 32 * i * PITCH + p * PART + 32 * h);
-                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], w[0], low[i], 0, 0, 0);
-                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[2], low[i], 0, 0, 0);
-                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], w[1], low[i], 0, 0, 0);
-                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], w[0], low[i], 0, 0, 0);
-                low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[1], low[i], 0, 0, 0);
-                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[0], acc[i], 0, 0, 0);
-            }
-        }
+        for (int p = 0; p < 3; ++p) o.x[p] = *reinterpret_cast<const bf16x8*>(a + p * PART);
+        return o;
+    };
+    auto multiply = [&](int i, const RowParts& o, const bf16x8* w) ALWAYS_INLINE {
+        low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.x[2], w[0], low[i], 0, 0, 0);
+        low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.x[0], w[2], low[i], 0, 0, 0);
+        low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.x[1], w[1], low[i], 0, 0, 0);
+        low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.x[1], w[0], low[i], 0, 0, 0);
+        low[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.x[0], w[1], low[i], 0, 0, 0);
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o.x[0], w[0], acc[i], 0, 0, 0);
     };
 
     const uint32_t all_steps = (n + BK - 1) / BK;
     const uint32_t kt0 = split * steps_per_split;
     const uint32_t ksteps = kt0 + steps_per_split < all_steps ? kt0 + steps_per_split : all_steps;   // one past the last
-    const uint32_t nfull = n / BK;
-    Stage st;
-    auto load = [&](uint32_t kt) { if (kt < nfull) load_full(kt * BK, st); else load_tail(kt * BK, st); };
     // true if f holds for any thread of the block: a word per wavefront and a barrier (0.3 us less per vote than
     // __syncthreads_or); every vote has words of its own
     __shared__ uint32_t votes[2][4];
-    auto block_any = [&](bool f, int which) -> bool {
+    auto block_any = [&](bool f, int which) ALWAYS_INLINE -> bool {
         const bool mine = __any(f);
         if (lane == 0) votes[which][wave] = mine ? 1u : 0u;
         __syncthreads();
@@ -251,7 +294,7 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
     };
     // an operand was cut short, or a sum is not finite (an infinity or NaN among the operands, or an overflow)
     // (x * 0 is NaN exactly then: one instruction per sum; a comparison each took 0.2 us a block)
-    auto unfit = [&]() -> bool {
+    auto unfit = [&]() ALWAYS_INLINE -> bool {
         float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int i = 0; i < RT; ++i)
@@ -261,6 +304,13 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
     };
     // a look at some of the first step's X (non-finite, or small enough to be cut) and at the table: where all of X, or a
     // representative, is like this, parts are not tried first
+    auto load = [&](uint32_t kt) ALWAYS_INLINE {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) load_x(kt, r);
+        load_p(kt, st.rb);
+    };
+    raw_t rb1[4];                                      // pointers of the second step (of the first where there is one only)
+    load_p(kt0 + 1 < ksteps ? kt0 + 1 : kt0, rb1);
     load(kt0);                                         // (in flight while the table is made)
     if (LUT_LDS)
         for (uint32_t i = t; i < k_tot; i += 256) lut[i] = split_weight(value_of(i), cut);
@@ -269,12 +319,70 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
 #pragma unroll
     for (int j = 0; j < 4; ++j) again |= !(fabsf(seen[j]) <= 3.402823466e38f) || (seen[j] != 0.0f && fabsf(seen[j]) < 0x1p-110f);
     again = block_any(again, 0);                       // (a barrier: the table is complete)
-    for (uint32_t kt = again ? ksteps : kt0; kt < ksteps; ++kt) {
-        __syncthreads();                               // the last step's tiles are read
-        store(st);
+    if (!again) {
+        // Step kt multiplies buffer kt of X; the wavefront has its first operand of W in registers and the pointers of the second.
+        // Beside the matrix instructions: X of step kt + 1 is split into the other buffer and X of kt + 2 requested, the
+        // pointers of kt + 2 go to LDS and those of kt + 3 are requested, the operands of kt + 1 are looked up.  The order is
+        // spelled out (a sched_barrier behind every row tile): left to itself the compiler requests at the end what the next step
+        // waits for at its start and reads every operand right before its use.
+        auto walk = [&](auto count) ALWAYS_INLINE {
+        constexpr int NR = decltype(count)::value;
+        bf16x8 w[2][3];
+        oct_t p1;
+        uint2 v[8];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) store_x(0, r);
+        store_p(0, st.rb);
+        store_p(1, rb1);
+        if (kt0 + 1 < ksteps) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) load_x(kt0 + 1, r);
+        }
+        if (kt0 + 2 < ksteps) load_p(kt0 + 2, st.rb);
         __syncthreads();
-        if (kt + 1 < ksteps) load(kt + 1);
-        multiply();
+        look_up(pointers(0, 0), v);
+        p1 = pointers(0, 1);
+        pack(v, w[0]);
+        __syncthreads();                               // the first step overwrites these pointers
+        auto step = [&](uint32_t kt, auto request_x, auto request_p) ALWAYS_INLINE {
+            const uint32_t buf = (kt - kt0) & 1u;
+            RowParts o = rows(buf, 0, 0), next;
+            look_up(p1, v);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                next = i + 1 < NR ? rows(buf, 0, i + 1) : rows(buf, 1, 0);
+                store_x(buf ^ 1u, i);
+                multiply(i, o, w[0]);
+                request_x(kt + 2, i);
+                INTERLEAVE(7);
+                __builtin_amdgcn_sched_barrier(0);
+                o = next;
+            }
+            pack(v, w[1]);
+            const oct_t p0 = pointers(buf ^ 1u, 0);
+            p1 = pointers(buf ^ 1u, 1);
+            store_p(buf, st.rb);                            // (of step kt + 2: this step's pointers are in registers already)
+            request_p(kt + 3);
+#pragma unroll
+            for (int i = 0; i < NR; ++i) {
+                if (i + 1 < NR) next = rows(buf, 1, i + 1);
+                if (i == (NR > 1 ? 1 : 0)) look_up(p0, v);
+                if (i == NR - 1) pack(v, w[0]);
+                multiply(i, o, w[1]);
+                INTERLEAVE(3);
+                __builtin_amdgcn_sched_barrier(0);
+                o = next;
+            }
+            __syncthreads();
+        };
+        uint32_t kt = kt0;
+        for (const uint32_t end = ksteps < nfull ? ksteps : nfull; kt + 3 < end; ++kt)
+            step(kt, [&](uint32_t k, int r) ALWAYS_INLINE { load_x_full(k, r); }, [&](uint32_t k) ALWAYS_INLINE { load_p_full(k, st.rb); });
+        for (; kt < ksteps; ++kt)
+            step(kt, [&](uint32_t k, int r) ALWAYS_INLINE { if (k < ksteps) load_x(k, r); }, [&](uint32_t k) ALWAYS_INLINE { if (k < ksteps) load_p(k, st.rb); });
+        };
+        if (nr == RT) walk(std::integral_constant<int, RT>{});
+        else if constexpr (RT > 1) walk(std::integral_constant<int, RT - 1>{});
     }
     if (!again) again = block_any(unfit(), 1);
 #pragma unroll
@@ -289,12 +397,12 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
     // the steps walked until that is known.
     if (again) {
         constexpr int P32 = BK + 4;                    // floats between rows: 16 lanes' reads fall on different banks
-        static_assert(4 * P32 <= PITCH, "the fp32 tiles take the place of the parts");
+        static_assert(4 * P32 * (BM + BN) <= 2 * (ABYTES + BBYTES), "the fp32 tiles take the place of the parts and pointers");
         float* Af = reinterpret_cast<float*>(As);
-        float* Bf = reinterpret_cast<float*>(Bs);
+        float* Bf = Af + BM * P32;
         if (LUT_LDS)
             for (uint32_t i = t; i < k_tot; i += 256) lut[i].x = __float_as_uint(value_of(i));   // (the vote was a barrier)
-        auto fp32_of = [&](uint32_t p) -> float { return LUT_LDS ? __uint_as_float(lut[p].x) : value_of(p); };
+        auto fp32_of = [&](uint32_t p) ALWAYS_INLINE -> float { return LUT_LDS ? __uint_as_float(lut[p].x) : value_of(p); };
 #pragma unroll
         for (int i = 0; i < RT; ++i)
 #pragma unroll
@@ -310,7 +418,7 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
                 *reinterpret_cast<float4*>(Bf + (b_col + c) * P32 + 4 * q) = make_float4(w[0], w[1], w[2], w[3]);
             }
 #pragma unroll
-            for (int r = 0; r < RT; ++r) *reinterpret_cast<float4*>(Af + (a_row + 32 * r) * P32 + 4 * q) = st.ra[r];
+            for (int r = 0; r < RT; ++r) *reinterpret_cast<f32x4*>(Af + (a_row + 32 * r) * P32 + 4 * q) = st.ra[r];
             __syncthreads();
             if (kt + 1 < ksteps) load(kt + 1);
             const float* a = Af + l32 * P32 + 16 * half;
@@ -336,7 +444,7 @@ index_gemm_kernel(const float* __restrict__ X, uint64_t ldx, uint32_t B,
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const uint32_t row = m0 + i * 32 + (v & 3) + 8 * (v >> 2) + 4 * half;
-            if (row < B && col < m) {
+            if (row < B && col < m && (uint32_t)i < nr) {
                 if (splits == 1) Y[(uint64_t)row * ldy + col] = acc[i][v];
                 else part[((uint64_t)split * B + row) * m + col] = acc[i][v];
             }
@@ -479,9 +587,9 @@ splitk_reduce_kernel(const float* __restrict__ part, uint32_t splits, uint32_t B
 
 namespace hac_internal {
 
-static size_t index_gemm_lds_bytes(uint32_t k_tot, int rt)
+static size_t index_gemm_lds_bytes(uint32_t k_tot, uint32_t idx_bits, int rt)
 {
-    return (size_t)(32 * rt + BN) * PITCH + (k_tot <= kLutLdsMax ? sizeof(uint2) * k_tot : 0);
+    return (size_t)(idx_bits == 8 ? tile_bytes<uint8_t>(rt) : tile_bytes<uint16_t>(rt)) + (k_tot <= kLutLdsMax ? sizeof(uint2) * k_tot : 0);
 }
 
 GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m, size_t room)
@@ -514,10 +622,12 @@ GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m, size_t room)
     const uint32_t steps = (n + BK - 1) / BK;
     // Row tiles per block and K splits: the pair with the shortest estimate.  A step of 32 k takes a block 0.77 + 0.26 us
     // per row tile when little else runs on its CU, and every block of a CU adds 0.22 + 0.25 us per row tile of its
-    // shared pipes; 4 blocks of one or two row tiles, 3 of three and 2 of four fit.  The pass that adds the splits
+    // shared pipes, counting 4 blocks of one or two row tiles, 3 of three and 2 of four.  The pass that adds the splits
     // takes 3 us and 0.4 us per MB of partial tiles, everything else 5 us.  The constants are fitted to 625 measured
     // pairs of 21 shapes (64 x 100 to 25088 x 1000, 33 to 12544 rows, 4 to 4000 work items): four in five estimates lie
-    // within 8 % of the time, and the pairs they choose within 6 % of the best measured one (one shape: within 20 %).
+    // within 8 % of the time, and the pairs they choose within 6 % of the best measured one (one shape: within 20 %).  They are those of
+    // the kernel that kept W's parts in LDS: the K splits they choose set the order of the sums, which stays; for the same
+    // splits the row tiles they choose are within 5 % of the best on 15 of 18 shapes (64 x 25088 x 1000 9 %).
     // Relative 2-norm error against 64 bits, fp32 instruction -> bf16 parts: one term 2.4e-8 -> 2.5e-8, two 3.4e-8 ->
     // 3.2e-8, 64 terms 1.05e-7 -> 4.0e-8, 4608 terms 1.9e-7 -> 9.9e-8 (X as after a ReLU, one K split).
     static const uint32_t kSplits[] = { 1, 2, 3, 4, 6, 8, 10, 12, 16, 20, 24, 32 };
@@ -540,6 +650,18 @@ GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m, size_t room)
             if (cost < best) { best = cost; p.us = us; p.rt = rt; p.tiles = tiles; p.splits = parts; p.steps_per_split = per; }
         }
     }
+    // More groups of rows than the fewest that p.rt row tiles a block allow, some blocks with a row tile less, where that fills places
+    // on the CUs that stay empty otherwise.  A step takes a CU 0.17 us for each of its blocks and 0.27 us for each of their row
+    // tiles (fitted to 794 measured plans of 18 shapes); the groups have to save 3 % of that.  784 x 4608 x 512 in 12 splits, 9
+    // groups -> 10: 38.3 -> 35.4 us; 12544 rows, 98 -> 128: 319 -> 317; but 2048 x 2000 x 2000, 32 -> 48 (a third block on a CU): 93 -> 104.
+    // K splits, and with them the sums, stay the same.
+    const uint64_t row_tiles = (B + 31) / 32, groups = p.tiles / tiles_n, per_group = (uint64_t)tiles_n * p.splits;
+    const uint64_t places = 256 * (p.rt == 1 ? 4 : p.rt == 2 ? 3 : 2);
+    if (p.rt > 1) {
+        const uint64_t more = std::min((groups * per_group + places - 1) / places * places / per_group, row_tiles / (p.rt - 1));
+        auto cu_us = [&](uint64_t g, double tiles) { return (double)((g * per_group + 255) / 256) * (0.17 + 0.27 * tiles); };
+        if (more > groups && cu_us(more, (double)row_tiles / (double)more) < 0.97 * cu_us(groups, (double)p.rt)) p.tiles = tiles_n * more;
+    }
     p.part_bytes = p.splits > 1 ? (size_t)p.splits * B * m * sizeof(float) : 0;
     p.steps = steps;
     return p;
@@ -548,23 +670,22 @@ GemmPlan plan_index_gemm(uint32_t B, uint32_t n, uint32_t m, size_t room)
 namespace {
 
 typedef void (*gemm_kern_t)(const float*, uint64_t, uint32_t, const void*, uint64_t, const float*, uint32_t, uint32_t,
-                            uint32_t, uint32_t, float*, uint64_t, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, float*);
+                            uint32_t, uint32_t, float*, uint64_t, uint32_t, uint32_t, uint32_t, uint32_t, float*);
 
 template <typename IdxT, bool LUT_LDS, int RT>
 void launch_one(dim3 grid, size_t lds, hipStream_t stream, hipError_t& err,
                 const float* d_X, uint64_t ldx, uint32_t B, const void* d_idx, uint64_t pitch, const float* d_codebook,
                 uint32_t k_sym, uint32_t zero_first, uint32_t n, uint32_t m, float* d_Y, uint64_t ldy, uint32_t tiles_n,
-                uint32_t tiles, uint32_t x_vec, uint32_t splits, uint32_t steps_per_split, float* d_part)
+                uint32_t row_groups, uint32_t splits, uint32_t steps_per_split, float* d_part)
 {
-    auto k = x_vec ? index_gemm_kernel<IdxT, LUT_LDS, RT, true> : index_gemm_kernel<IdxT, LUT_LDS, RT, false>;
+    auto k = index_gemm_kernel<IdxT, LUT_LDS, RT>;
     if (lds > 63 * 1024) {                             // (the votes take some of the 64 KB a kernel gets without asking)
         err = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (err != hipSuccess) return;
     }
     hipLaunchKernelGGL(k, grid, dim3(256), lds, stream, d_X, ldx, B, static_cast<const IdxT*>(d_idx), pitch, d_codebook,
-                       k_sym, zero_first, n, m, d_Y, ldy, tiles_n, tiles, x_vec, splits, steps_per_split, d_part);
-    note_kernel("index_gemm_kernel<unsigned %s, %s, %d, %s>", sizeof(IdxT) == 1 ? "char" : "short", LUT_LDS ? "true" : "false", RT,
-                x_vec ? "true" : "false");
+                       k_sym, zero_first, n, m, d_Y, ldy, tiles_n, row_groups, splits, steps_per_split, d_part);
+    note_kernel("index_gemm_kernel<unsigned %s, %s, %d>", sizeof(IdxT) == 1 ? "char" : "short", LUT_LDS ? "true" : "false", RT);
     err = hipGetLastError();
 }
 
@@ -629,27 +750,31 @@ hipError_t launch_index_gemm(const GemmPlan& plan, const float* d_X, uint64_t ld
         note_kernel("splitk_reduce_kernel");
         return hipGetLastError();
     }
-    const uint64_t items64 = plan.tiles * plan.splits;
-    if (items64 > 0x7ffffff0ull) return hipErrorInvalidValue;
+    if (plan.tiles > 0x7ffffff0ull) return hipErrorInvalidValue;
     if (plan.splits > 1 && !d_part) return hipErrorInvalidValue;
     if (idx_bits != 8 && idx_bits != 16) return hipErrorInvalidValue;
-    const uint32_t tiles = (uint32_t)plan.tiles;
-    const dim3 grid(((uint32_t)items64 + 7) / 8 * 8);
     const uint32_t k_tot = k_sym + zero_first;
     const bool lut_lds = k_tot <= kLutLdsMax;
-    const size_t lds = index_gemm_lds_bytes(k_tot, (int)plan.rt);
-    const uint32_t x_vec = (reinterpret_cast<uintptr_t>(d_X) % 16 == 0 && ldx % 4 == 0) ? 1u : 0u;
+    // a long value list (from 1021 values on at four row tiles and 16-bit pointers) leaves a CU room for one block only: a row
+    // tile less then, down to two
+    uint32_t rt = plan.rt, row_groups = (uint32_t)(plan.tiles / tiles_n);
+    while (rt > 2 && 2 * (index_gemm_lds_bytes(k_tot, idx_bits, (int)rt) + 64) > 160 * 1024) --rt;
+    row_groups = std::max(row_groups, ((B + 31) / 32 + rt - 1) / rt);
+    const uint64_t items64 = (uint64_t)row_groups * tiles_n * plan.splits;
+    if (items64 > 0x7ffffff0ull) return hipErrorInvalidValue;
+    const dim3 grid(((uint32_t)items64 + 7) / 8 * 8);
+    const size_t lds = index_gemm_lds_bytes(k_tot, idx_bits, (int)rt);
     hipError_t e = hipSuccess;
     if (idx_bits == 8) {
-        if (lut_lds) launch_rt<uint8_t, true>(plan.rt, grid, lds, stream, e, d_X, ldx, B, d_idx, pitch, d_codebook, k_sym, zero_first,
-                                              n, m, d_Y, ldy, tiles_n, tiles, x_vec, plan.splits, plan.steps_per_split, d_part);
-        else launch_rt<uint8_t, false>(plan.rt, grid, lds, stream, e, d_X, ldx, B, d_idx, pitch, d_codebook, k_sym, zero_first,
-                                       n, m, d_Y, ldy, tiles_n, tiles, x_vec, plan.splits, plan.steps_per_split, d_part);
+        if (lut_lds) launch_rt<uint8_t, true>(rt, grid, lds, stream, e, d_X, ldx, B, d_idx, pitch, d_codebook, k_sym, zero_first,
+                                              n, m, d_Y, ldy, tiles_n, row_groups, plan.splits, plan.steps_per_split, d_part);
+        else launch_rt<uint8_t, false>(rt, grid, lds, stream, e, d_X, ldx, B, d_idx, pitch, d_codebook, k_sym, zero_first,
+                                       n, m, d_Y, ldy, tiles_n, row_groups, plan.splits, plan.steps_per_split, d_part);
     } else {
-        if (lut_lds) launch_rt<uint16_t, true>(plan.rt, grid, lds, stream, e, d_X, ldx, B, d_idx, pitch, d_codebook, k_sym, zero_first,
-                                               n, m, d_Y, ldy, tiles_n, tiles, x_vec, plan.splits, plan.steps_per_split, d_part);
-        else launch_rt<uint16_t, false>(plan.rt, grid, lds, stream, e, d_X, ldx, B, d_idx, pitch, d_codebook, k_sym, zero_first,
-                                        n, m, d_Y, ldy, tiles_n, tiles, x_vec, plan.splits, plan.steps_per_split, d_part);
+        if (lut_lds) launch_rt<uint16_t, true>(rt, grid, lds, stream, e, d_X, ldx, B, d_idx, pitch, d_codebook, k_sym, zero_first,
+                                               n, m, d_Y, ldy, tiles_n, row_groups, plan.splits, plan.steps_per_split, d_part);
+        else launch_rt<uint16_t, false>(rt, grid, lds, stream, e, d_X, ldx, B, d_idx, pitch, d_codebook, k_sym, zero_first,
+                                        n, m, d_Y, ldy, tiles_n, row_groups, plan.splits, plan.steps_per_split, d_part);
     }
     if (e != hipSuccess || plan.splits == 1) return e;
     const uint64_t total = (uint64_t)B * m;

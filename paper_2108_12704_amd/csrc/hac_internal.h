@@ -11,7 +11,8 @@ namespace hac_internal {
 // How launch_index_gemm splits the work: `tiles` output tiles, each K loop of `steps` steps cut into
 // `splits` ranges of steps_per_split; with more than one split the partial tiles go through a buffer
 // of part_bytes bytes (splits x B x m floats) and are added in order by a second kernel.
-// A block covers 32 * rt batch rows (rt = 1..4) and 128 columns.
+// A block covers up to 32 * rt batch rows (rt = 1..4) and 128 columns; the row tiles of 32 are dealt evenly over
+// tiles / ceil(m / 128) groups.
 // small (at most 32 batch rows): no matrix cores; `tiles` blocks of 4 << rt columns (256 for maps of
 // 129 columns or more), the rows of W cut into `splits` ranges of steps_per_split rows, partial sums
 // through the same buffer.

@@ -234,6 +234,26 @@ def test_split_operands(hac, B, n, m, bits):
     assert (err <= bound).all(), float((err / bound).max())
 
 
+# two to four row tiles a block, dealt unevenly (some blocks one less); one to five K steps, a partial last one; one and several
+# K splits; a value list that leaves room for fewer row tiles (3000); X at any row length
+@pytest.mark.parametrize("B,n,m", [(3130, 33, 1000), (3130, 97, 1000), (3130, 900, 5), (12530, 31, 260), (12530, 65, 260),
+                                   (3130, 17, 2000), (3130, 97, 2000), (3130, 130, 2000), (12530, 1000, 5), (33, 65, 5)])
+@pytest.mark.parametrize("k", [64, 700, 3000])
+def test_row_tiles_dealt_unevenly(hac, B, n, m, k):
+    """fp32 sums of n terms in any order: (n + 8) 2^-24 |X| . |W|."""
+    rng = np.random.default_rng(B + n + m + k)
+    W = rng.standard_normal(k).astype(np.float32)[rng.integers(0, k, (n, m))]
+    X = np.maximum(rng.standard_normal((B, n)), 0).astype(np.float32)
+    Xd = torch.zeros((B, n + 1 + k % 3), device=dev())[:, :n]
+    Xd.copy_(torch.from_numpy(X))
+    Y = torch.full((B, m + 2), float("nan"), device=dev())
+    hac.im_dot(hac.im_encode(W).to_device(dev()), Xd, Y=Y[:, :m])
+    Y = Y.cpu().numpy().astype(np.float64)
+    err = np.abs(Y[:, :m] - X.astype(np.float64) @ W.astype(np.float64))
+    bound = (n + 8) * 2.0 ** -24 * (X.astype(np.float64) @ np.abs(W).astype(np.float64)) + n * 2.0 ** -149
+    assert (err <= bound).all() and np.isnan(Y[:, m:]).all()
+
+
 def test_not_finite_and_largest(hac):
     """Infinities, NaN and values near the largest float give what fp32 products and sums give."""
     W = workloads.make_layer(257, 130, 0.02, 0.0, 64, "kmeans", 5)
