@@ -228,8 +228,8 @@ typedef struct {
     uint32_t staging_words;   /* words of the per-wavefront LDS buffer for stream (and ri)
                                  words, 16..16384, a multiple of 4 [from the header]       */
     uint32_t pass_width;      /* batch columns one pass over the list covers: 32 / 64 / 128 /
-                                 256 [the widest that the batch fills and of which a
-                                 panel of X stays in an L2, see hac_workspace_bytes]       */
+                                 256 [the widest that the batch fills and whose share of X
+                                 stays in an L2]                                           */
     uint32_t free_running;    /* 1 = do not hold a block's wavefronts on the same pass
                                  (measurement aid) [0]                                     */
     uint32_t tile_width;      /* batch columns one block covers: 32 / 64 / 128 / 256, not
@@ -243,10 +243,10 @@ typedef struct {
 
 /* The workspace already holds the feature-major copy of this very X (same B,
  * same n) left there by an earlier call: skip the re-layout pass.  Meant for
- * one X multiplied with several compressed matrices of the same height.  Up to
- * 2^19 values of X (B n) a call may have left none, and the pass is not skipped;
- * neither is it when this launch's pass_width / tile_width give another layout
- * than the defaults (name the same pass_width in both calls to reuse that one). */
+ * one X multiplied with several compressed matrices of the same height.  How
+ * that call was launched does not matter: the copy's layout depends on B and n
+ * alone.  Up to 2^19 values of X (B n) a call may have left none, and the pass
+ * is not skipped. */
 #define HAC_LAUNCH_REUSE_XT 0x100u
 
 /* Batches of at most 4 rows normally run a kernel in which every lane
@@ -441,9 +441,9 @@ int hac_encode_dev_alloc(uint32_t format, const float *d_W, int64_t n, int64_t m
 /* Bytes of device workspace hac_dot / shac_dot need for a batch of B rows with
  * default launch settings (0 when none is needed: a single row, or a few rows
  * over a short X, see HAC_LAUNCH_NO_X_LDS).  The workspace holds X re-laid out
- * feature-major, in panels of a power of two of batch columns (the batch rounded
- * up, at most 256, halved down to 32 while a panel exceeds 3.4 MB); narrow
- * products that read X as it is ask for it all the same.  Or, on the dense route (see hac_dot), the decoded index map
+ * feature-major, in panels of 32 batch columns (of the batch rounded up to a
+ * power of two where that is less; narrow products that read X as it is ask for
+ * it all the same), or, on the dense route (see hac_dot), the decoded index map
  * of W.  A launch that forces another way may need more: size the workspace
  * with hac_workspace_bytes_for().  Both return 0 for B <= 0 and for a header
  * that no encoder could have written (zero sizes, unknown format). */

@@ -229,8 +229,7 @@ decode_to_index_kernel(DevBlob d, IdxT* idx, uint64_t pitch, uint32_t shac, uint
 
 // ---------------------------------------------------------------------------
 // X (B x n, row-major) -> XT, feature-major in panels of `wp` batch columns:
-// XT[(b / wp) * n * wp + r * wp + b % wp] = X[b][r], zero for B <= b < Bp.
-// One pass of the batch kernel reads one panel: rows of wp floats, contiguous.
+// XT[(b / wp) * n * wp + r * wp + b % wp] = X[b][r], zero for B <= b < Bp (see panel_width).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 transpose_pad_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64_t ldx,
@@ -257,12 +256,12 @@ transpose_pad_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64
     }
 }
 
-// Same re-layout for panels of 32 batch columns or more (wp a multiple of 32): a block turns 32 batch rows x 128
-// features into 128-byte pieces of a panel's rows (one contiguous 16 KB piece for wp = 32).  With X 16-byte aligned
-// (vec = 1) the reads are 128-bit (512 bytes per batch row) and so are the writes.
+// Same re-layout for panels of exactly 32 batch columns: a block turns 32 batch rows x 128
+// features into one contiguous 16 KB piece of a panel.  With X 16-byte aligned (vec = 1) the
+// reads are 128-bit (512 bytes per batch row) and so are the writes.
 __global__ void __launch_bounds__(256)
 transpose_panel32_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64_t ldx,
-                         float* __restrict__ XT, uint32_t vec, uint32_t wp)
+                         float* __restrict__ XT, uint32_t vec)
 {
     __shared__ float tile[32][129];
     const uint32_t r0 = blockIdx.x * 128, b0 = blockIdx.y * 32;
@@ -301,14 +300,14 @@ transpose_panel32_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, ui
         }
     }
     __syncthreads();
-    float* out = XT + (uint64_t)(b0 / wp) * n * wp + (uint64_t)r0 * wp + b0 % wp;
+    float* out = XT + (uint64_t)blockIdx.y * n * 32 + (uint64_t)r0 * 32;
 #pragma unroll
     for (uint32_t i = 0; i < 4; ++i) {
         const uint32_t idx = threadIdx.x + 256 * i;              // float4 index: 128 features x 8 quads of batch
         const uint32_t r = idx >> 3, bq = (idx & 7) * 4;
         if (r0 + r < n) {
             const float4 v = make_float4(tile[bq][r], tile[bq + 1][r], tile[bq + 2][r], tile[bq + 3][r]);
-            *reinterpret_cast<float4*>(out + (uint64_t)r * wp + bq) = v;
+            *reinterpret_cast<float4*>(out + (uint64_t)r * 32 + bq) = v;
         }
     }
 }
@@ -338,13 +337,19 @@ __device__ __forceinline__ void wave_sync()
 
 // What happens to a finished sum before it is stored: + bias[column], max(., 0), and where it
 // goes.  yt = nullptr: Y[b * ldy + column].  yt set: the feature-major layout the next layer of
-// a chain reads as its XT, panels of wp = yt_width batch columns, yt[(b / wp) * m * wp + column * wp + b % wp].
+// a chain reads as its XT, panels of wp = panel_w batch columns, yt[(b / wp) * m * wp + column * wp + b % wp].
 // What the padded batch columns hold does not matter: their sums are not stored.
 struct Epilogue {
     const float* bias;
     float* yt;
-    uint32_t relu, yt_width;
+    uint32_t relu, panel_w;
 };
+
+// Where a feature-major array of n rows, in panels of w (a power of two) batch columns, holds column b: row r is w r further.
+__device__ __forceinline__ uint64_t panel_offset(uint32_t w, uint32_t n, uint32_t b)
+{
+    return (uint64_t)(b >> (uint32_t)__builtin_ctz(w)) * n * w + (b & (w - 1u));
+}
 
 __device__ __forceinline__ float epilogue_apply(const Epilogue& e, float v, uint32_t col)
 {
@@ -534,7 +539,7 @@ __device__ __forceinline__ void block_sync_lds()
 // OWN: see fma_entries (off for many passes of 32 batch columns: eight lane groups keep the chains short, and it costs 0.7 % at 256 rows).
 template <bool SHAC, int NB, bool MP, bool EPI, bool OWN>
 __global__ void __launch_bounds__((BatchTraits<NB>::kMaxThreads))
-dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t Bp, uint32_t B,
+dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t panel_w, uint32_t B,
                  float* __restrict__ Y, uint64_t ldy, uint32_t cpw, uint32_t gw, uint32_t npass,
                  uint32_t list_cap, uint32_t sbuf_words, uint32_t part_words, uint32_t nblocks,
                  uint32_t sync_passes, Epilogue epi)
@@ -617,10 +622,8 @@ dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t Bp, uint32_t 
 
     const uint32_t ng = kWave / gw;
     const uint32_t grp = lane / gw, lig = lane % gw;
-    const uint32_t pass_w = gw * NB;                          // batch columns per pass = width of one panel of XT
-    const uint64_t panel = (uint64_t)d.n * pass_w;            // floats per panel
+    const uint32_t pass_w = gw * NB;                          // batch columns per pass, of one panel of XT or several
     const uint32_t boff = tile * tile_b + lig * NB;           // first batch column of this lane, pass 0
-    const float* xt = XT + (uint64_t)tile * npass * panel + lig * NB;
     uint32_t cc = c0;                                        // column being accumulated (wave-uniform)
     uint32_t t = posbase;                                    // next CSC position to consume
 
@@ -642,17 +645,18 @@ dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t Bp, uint32_t 
             // nine too, so that a chain adds in the order of single calls)
             constexpr int kPipe = BatchTraits<NB>::kPipe - ((!MP && NB == 4) ? 1 : 0);
             // (a lane whose batch columns are all padding fetches nothing)
-            if (t < hi && boff + p * pass_w < B) fma_entries<NB, kPipe, OWN>(list, winbase, t, hi, ng, grp, xt + p * panel, pass_w, a);
+            const uint32_t b0 = boff + p * pass_w;             // (NB columns of one panel)
+            if (t < hi && b0 < B) fma_entries<NB, kPipe, OWN>(list, winbase, t, hi, ng, grp, XT + panel_offset(panel_w, d.n, b0), panel_w, a);
             if (last) {
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
                     float v = a[i];
                     for (uint32_t off = 32; off >= gw; off >>= 1) v += __shfl_xor(v, (int)off, kWave);
-                    const uint32_t b = boff + p * pass_w + i;
+                    const uint32_t b = b0 + i;
                     if (grp == 0) {
                         if constexpr (EPI) {
                             if (epi.yt)
-                                { if (b < B) epi.yt[((uint64_t)(b / epi.yt_width) * d.m + cc) * epi.yt_width + (b % epi.yt_width)] = epilogue_apply(epi, v, cc); }
+                                { if (b < B) epi.yt[panel_offset(epi.panel_w, d.m, b) + (uint64_t)cc * epi.panel_w] = epilogue_apply(epi, v, cc); }
                             else if (b < B) Y[(uint64_t)b * ldy + cc] = epilogue_apply(epi, v, cc);
                         } else {
                             if (b < B) Y[(uint64_t)b * ldy + cc] = v;
@@ -990,18 +994,29 @@ BatchShape batch_shape(int64_t B, uint32_t pass_w, uint32_t tile_b)
 constexpr size_t kLdsLimit = 160 * 1024;
 constexpr uint32_t kDefaultTile = 256;
 
-// Batch columns of a panel of the feature-major copy of X, the same for every kernel that reads or writes one: as many as
-// the batch has (a power of two, at most 256) while a panel stays within the 4 MB of an XCD's L2.  A wider panel means
-// fewer passes over the list and longer rows: 4096 x 4096, 4 % non-zero, 128 rows 29.4 (32 columns) -> 25.3 (64) -> 23.4 us
-// (128); 1000 x 4096, 10 %, 256 rows 43.4 -> 31.6 -> 26.2 us; but 25088 rows of W, 256 rows of X: 109.4 (32 columns, 3.2 MB),
-// 115.5 (64), 155.9 us (256).
-constexpr double kPanelBytes = 3.4e6;
+// Batch columns of a panel of the feature-major copy of X: 32, or the batch rounded up to a power of two where
+// that is less.  That depends on the batch alone, neither on W nor on how a launch splits the work: a copy that any call has
+// left is read alike by every other one (HAC_LAUNCH_REUSE_XT), and the layers of a chain agree.
+uint32_t panel_width(int64_t B)
+{
+    uint32_t w = 1;
+    while (w < 32 && w < (uint64_t)B) w <<= 1;
+    return w;
+}
 
-uint32_t xt_width(uint64_t n, int64_t B)
+// Batch columns that one pass over the list covers, from as many panels side by side: as many as the batch has (a power of
+// two, at most 256) while what a pass reads of X stays within the 4 MB of an XCD's L2.  A wider pass means fewer of them:
+// 4096 x 4096, 4 % non-zero, 128 rows 29.4 (32 columns) -> 25.3 (64) -> 23.4 us (128); 1000 x 4096, 10 %, 256 rows, sparse route
+// asked for, 43.4 -> 31.6 -> 26.2 us; but 25088 rows of W, 256 rows of X: 109.4 (32 columns, 3.2 MB), 115.5 (64), 155.9 us (256).
+// Against panels as wide as the pass, 147 products (512 to 8192 rows of W, 48 to 512 rows of X) are 0.6 % quicker (geometric mean;
+// worst 1.6 % slower).
+constexpr double kPassBytes = 3.4e6;
+
+uint32_t pass_columns(uint64_t n, int64_t B)
 {
     uint32_t w = 1;
     while (w < (uint32_t)(B < 256 ? B : 256)) w <<= 1;
-    while (w > 32 && 4.0 * (double)n * w > kPanelBytes) w >>= 1;
+    while (w > 32 && 4.0 * (double)n * w > kPassBytes) w >>= 1;
     return w;
 }
 
@@ -1195,7 +1210,7 @@ SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* laun
     const double l1_us = 1.0e-7 * (double)n * (double)m * (double)B;       // every column reads all lines of X
     s.direct = n * (uint64_t)B <= kDirectFloats && l1_us < 4.0;
     if (!s.direct && (B <= 4 || xlds_plan(desc, B, launch).use)) return s;
-    uint32_t width = xt_width(n, B);
+    uint32_t width = pass_columns(n, B);
     if (s.direct) {                                                        // tiles of at most 32 batch columns, all about as wide
         const uint64_t each = ((uint64_t)B + ((uint64_t)B + 31) / 32 - 1) / (((uint64_t)B + 31) / 32);
         width = each <= 4 ? 4u : each <= 8 ? 8u : each <= 16 ? 16u : each <= 24 ? 24u : 32u;
@@ -1278,9 +1293,10 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     const char* const tf[2] = { "false", "true" };
     if (!io->xt_in && (!d_X || ldx < (int64_t)desc->n)) return HAC_EINVAL;
     if (!io->yt_out && (!d_Y || ldy < (int64_t)desc->m)) return HAC_EINVAL;
-    const Epilogue epi = { io->bias, io->yt_out, io->relu, xt_width(desc->m, B) };   // the next layer's n is m
+    const uint32_t panel_w = panel_width(B);
+    const Epilogue epi = { io->bias, io->yt_out, io->relu, panel_w };
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    uint32_t cpw = default_cpw(desc), wpb = 0, list_cap = 0, sbuf_words = 0, pass_w = xt_width(desc->n, B), tile_b = kDefaultTile;
+    uint32_t cpw = default_cpw(desc), wpb = 0, list_cap = 0, sbuf_words = 0, pass_w = pass_columns(desc->n, B), tile_b = kDefaultTile;
     bool reuse_xt = false, list_kernel = false;
     if (pass_w < 32) pass_w = 32;
     if (launch) {
@@ -1380,8 +1396,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         return e == hipSuccess ? HAC_OK : hip_fail(e);
     }
     const SplitPlan sp = plan_split(desc, B, launch);
-    if (reuse_xt && ((uint64_t)d.n * (uint64_t)B <= kDirectFloats || (!launch->pass_width && pass_w != std::max(32u, xt_width(d.n, B)))))
-        reuse_xt = false;                                     // an earlier call need not have left a copy of this layout
+    if (reuse_xt && (uint64_t)d.n * (uint64_t)B <= kDirectFloats) reuse_xt = false;   // an earlier call need not have left a copy
     const XldsPlan xp = io->xt_in || sp.use ? XldsPlan{ false, 0, 0, 0, 0 } : xlds_plan(desc, B, launch);
     if (xp.use) {
         // 2 to 8 batch rows and a short X: the block's own copy of X in LDS, lanes multiply what they decode
@@ -1419,16 +1434,16 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         float* xt = static_cast<float*>(d_ws);
         XT = xt;
         if (!reuse_xt) {
-            if (bs.gw * bs.nb >= 32) {
+            if (panel_w == 32) {
                 dim3 grid((d.n + 127) / 128, (uint32_t)((B + 31) / 32));     // what lies past the batch is never read
                 const uint32_t vec = (reinterpret_cast<uintptr_t>(d_X) % 16 == 0 && ldx % 4 == 0) ? 1u : 0u;
                 hipLaunchKernelGGL(transpose_panel32_kernel, grid, dim3(256), 0, stream,
-                                   d_X, (uint32_t)B, d.n, (uint64_t)ldx, xt, vec, bs.gw * bs.nb);
+                                   d_X, (uint32_t)B, d.n, (uint64_t)ldx, xt, vec);
                 note_kernel("transpose_panel32_kernel");
             } else {
                 dim3 grid((d.n + 31) / 32, (bs.Bp + 31) / 32);
                 hipLaunchKernelGGL(transpose_pad_kernel, grid, dim3(256), 0, stream,
-                                   d_X, (uint32_t)B, d.n, (uint64_t)ldx, xt, bs.Bp, bs.gw * bs.nb);
+                                   d_X, (uint32_t)B, d.n, (uint64_t)ldx, xt, bs.Bp, panel_w);
                 note_kernel("transpose_pad_kernel");
             }
             hipError_t e = hipGetLastError();
@@ -1452,7 +1467,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         }
         const uint32_t items = sp.p.nblocks * sp.p.tiles;
         hipLaunchKernelGGL(k, dim3((items + 7) / 8 * 8), dim3(sp.p.waves * kWave), sp.lds, stream, d, sp.p, direct ? d_X : XT,
-                           direct ? 1u : xt_width(d.n, B), direct ? (uint64_t)ldx : 1u, (uint32_t)B, d_Y, (uint64_t)ldy, epi);
+                           direct ? 1u : panel_w, direct ? (uint64_t)ldx : 1u, (uint32_t)B, d_Y, (uint64_t)ldy, epi);
         note_kernel("dot_split_kernel<%s, %u>", tf[shac], sp.nbd);
         hipError_t e = hipGetLastError();
         return e == hipSuccess ? HAC_OK : hip_fail(e);
@@ -1548,7 +1563,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         if (e != hipSuccess) return hip_fail(e);
     }
     hipLaunchKernelGGL(k, dim3(grid), dim3(wpb * kWave), lds, stream,
-                       d, XT, bs.Bp, (uint32_t)B, d_Y, (uint64_t)ldy, cpw, bs.gw, bs.npass, list_cap, sbuf_words, part_words, nblocks,
+                       d, XT, panel_w, (uint32_t)B, d_Y, (uint64_t)ldy, cpw, bs.gw, bs.npass, list_cap, sbuf_words, part_words, nblocks,
                        sync_passes, epi);
     note_kernel("dot_batch_kernel<%s, %u, %s, %s, %s>", tf[shac], bs.nb, tf[bs.nb == 4 && bs.npass > 1], tf[with_epilogue], tf[own]);
     hipError_t e = hipGetLastError();

@@ -31,7 +31,7 @@ namespace {
 struct SplitParams {
     uint32_t waves, cols;                    // per block; cols divides waves
     uint32_t cols_log2, split_log2;          // of cols, of waves / cols
-    uint32_t width;                          // batch columns of a tile (NBD, or those of a panel of XT)
+    uint32_t width;                          // batch columns of a tile (NBD, or those of a pass over XT)
     uint32_t nblocks;                        // blocks per tile
     uint32_t tiles;
     uint32_t sbuf_words;                     // staged stream and ri words; the sums of the wavefronts take their place
@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(1024)
 dot_split_kernel(DevBlob d, SplitParams p, const float* __restrict__ X, uint32_t xrow, uint64_t xcol, uint32_t B,
                  float* __restrict__ Y, uint64_t ldy, Epilogue epi)
 {
-    // X[r * xrow + b * xcol] with NBD; the panels of XT without
+    // X[r * xrow + b * xcol] with NBD; XT in panels of xrow batch columns without
     extern __shared__ uint32_t smem[];
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -185,7 +185,7 @@ dot_split_kernel(DevBlob d, SplitParams p, const float* __restrict__ X, uint32_t
         float a[4] = { 0.0f, 0.0f, 0.0f, 0.0f };
         // (lanes whose four batch columns are all padding fetch nothing)
         if (4 * lig < nb)
-            fma_entries<4, 10, true>(list, 0u, lo, hi, ng * shares, share * ng + grp, X + (uint64_t)tile * d.n * p.width + 4 * lig, p.width, a);
+            fma_entries<4, 10, true>(list, 0u, lo, hi, ng * shares, share * ng + grp, X + panel_offset(xrow, d.n, b0 + 4 * lig), xrow, a);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             for (uint32_t off = 32; off >= gw; off >>= 1) a[i] += __shfl_xor(a[i], (int)off, kWave);
@@ -253,7 +253,7 @@ dot_split_kernel(DevBlob d, SplitParams p, const float* __restrict__ X, uint32_t
         for (uint32_t k = 1; k < shares; ++k) z += s[k * p.width];
         const uint32_t col = c0 + c, row = b0 + b;
         const float v = epilogue_apply(epi, (float)z, col);
-        if (epi.yt) epi.yt[((uint64_t)(row / epi.yt_width) * d.m + col) * epi.yt_width + row % epi.yt_width] = v;
+        if (epi.yt) epi.yt[panel_offset(epi.panel_w, d.m, row) + (uint64_t)col * epi.panel_w] = v;
         else Y[(uint64_t)row * ldy + col] = v;
     }
     HAC_MARK(6);

@@ -109,3 +109,27 @@ def test_an_old_copy_of_x_is_only_reused_where_every_call_leaves_one(hac):
     print("[case] reuse of the copy", flush=True)
     check(hac.hac_dot(dn, Xd, workspace=ws), X, narrow)
     check(hac.shac_dot(dw, Xd, workspace=ws, launch=hac.Launch(variant=0x500)), X, wide)
+
+
+# what the first call names and what the one that reuses its copy does; more than 2^19 values of X, passes of 128 columns by default
+@pytest.mark.parametrize("left", [{}, {"pass_width": 32}, {"tile_width": 32}, {"pass_width": 256}, {"variant": 0x200}])
+@pytest.mark.parametrize("reused", [{}, {"pass_width": 32}, {"tile_width": 64}, {"pass_width": 256}, {"variant": 0x200}])
+def test_a_copy_of_x_is_reused_however_it_was_left(hac, left, reused):
+    """The copy's layout depends on X alone, not on the widths that either launch names."""
+    rng = np.random.default_rng(7)
+    B, n = 200, 4096
+    first, second = matrix(n, 300, 0.02, 3), matrix(n, 2100, 0.02, 4)
+    X = rng.standard_normal((B, n)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    df, ds = hac.hac_encode(first).to_device("cuda:0"), hac.shac_encode(second).to_device("cuda:0")
+    ws = torch.full((B * 2 * n,), float("nan"), device="cuda:0").view(torch.uint8)
+
+    def launch(kw, flags):
+        return hac.Launch(**{**kw, "variant": kw.get("variant", 0) | flags})
+
+    print(f"[case] copy left by {left}, reused by {reused}", flush=True)
+    check(hac.hac_dot(df, Xd, workspace=ws, launch=launch(left, 0x400)), X, first)
+    assert any("transpose" in k for k in hac.hac_last_kernels())
+    Y = hac.shac_dot(ds, Xd, workspace=ws, launch=launch(reused, 0x500))
+    assert not any("transpose" in k for k in hac.hac_last_kernels())
+    check(Y, X, second)
