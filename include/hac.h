@@ -245,8 +245,8 @@ typedef struct {
  * same n) left there by an earlier call: skip the re-layout pass.  Meant for
  * one X multiplied with several compressed matrices of the same height.  How
  * that call was launched does not matter: the copy's layout depends on B and n
- * alone.  Up to 2^19 values of X (B n) a call may have left none, and the pass
- * is not skipped. */
+ * alone.  Where X is short enough for LDS (see HAC_LAUNCH_NO_X_LDS) a call may
+ * have left none, and the pass is not skipped. */
 #define HAC_LAUNCH_REUSE_XT 0x100u
 
 /* Batches of at most 4 rows normally run a kernel in which every lane

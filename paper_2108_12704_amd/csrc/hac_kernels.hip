@@ -1156,10 +1156,12 @@ uint32_t default_staging_words(const hac_desc_t* desc, uint32_t cpw)
 // better off with the list kernel.
 struct XldsPlan { bool use; uint32_t nb, wpb, x_words; size_t lds; };
 
+bool fits_x_lds(uint64_t n, int64_t B) { return B >= 2 && B <= 8 && n * (B <= 2 ? 2u : B <= 4 ? 4u : 8u) <= 8192; }
+
 XldsPlan xlds_plan(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
 {
     XldsPlan p = { false, 0, 0, 0, 0 };
-    if (B < 2 || B > 8 || desc->format == HAC_FORMAT_IM) return p;
+    if (!fits_x_lds(desc->n, B) || desc->format == HAC_FORMAT_IM) return p;
     uint32_t cpw = default_cpw(desc), wpb = 0, sbuf_words = 0;
     if (launch) {
         if (launch->variant & (HAC_LAUNCH_NO_X_LDS | HAC_LAUNCH_LIST_KERNEL | HAC_LAUNCH_REUSE_XT | HAC_LAUNCH_DENSE_ROUTE)) return p;
@@ -1169,7 +1171,6 @@ XldsPlan xlds_plan(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch
     }
     if (!sbuf_words) sbuf_words = default_staging_words(desc, cpw);
     p.nb = B <= 2 ? 2u : B <= 4 ? 4u : 8u;
-    if (desc->n * p.nb > 8192) return p;
     if (p.nb == 8 && desc->nnz > (1u << 19)) return p;
     p.x_words = round_up((uint32_t)desc->n * p.nb, 4);
     const uint32_t k4 = (desc->k_sym + 3u) & ~3u;
@@ -1191,7 +1192,7 @@ XldsPlan xlds_plan(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch
 // feature-major copy all the same, because the caller asked for one), else lanes take batch columns of the copy.
 struct SplitPlan { bool use, direct, copy; uint32_t nbd; size_t lds; SplitParams p; };
 
-constexpr uint64_t kDirectFloats = 1u << 19;     // of X; a larger one is always re-laid out (see HAC_LAUNCH_REUSE_XT)
+constexpr uint64_t kDirectFloats = 1u << 19;     // of X; a larger one is always re-laid out
 
 SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
 {
@@ -1396,7 +1397,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         return e == hipSuccess ? HAC_OK : hip_fail(e);
     }
     const SplitPlan sp = plan_split(desc, B, launch);
-    if (reuse_xt && (uint64_t)d.n * (uint64_t)B <= kDirectFloats) reuse_xt = false;   // an earlier call need not have left a copy
+    if (reuse_xt && fits_x_lds(d.n, B)) reuse_xt = false;     // an earlier call may have kept X in LDS and left no copy
     const XldsPlan xp = io->xt_in || sp.use ? XldsPlan{ false, 0, 0, 0, 0 } : xlds_plan(desc, B, launch);
     if (xp.use) {
         // 2 to 8 batch rows and a short X: the block's own copy of X in LDS, lanes multiply what they decode
@@ -1451,7 +1452,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         }
     }
     if (sp.use) {
-        typedef void (*split_kern_t)(DevBlob, SplitParams, const float*, uint32_t, uint64_t, uint32_t, float*, uint64_t, Epilogue);
+        typedef void (*split_kern_t)(DevBlob, SplitParams, const float*, uint32_t, uint64_t, uint32_t, float*, uint64_t, float*, Epilogue);
         split_kern_t k;
         switch (sp.nbd) {
         case 0: k = shac ? dot_split_kernel<true, 0> : dot_split_kernel<false, 0>; break;
@@ -1465,9 +1466,14 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sp.lds);
             if (e != hipSuccess) return hip_fail(e);
         }
-        const uint32_t items = sp.p.nblocks * sp.p.tiles;
-        hipLaunchKernelGGL(k, dim3((items + 7) / 8 * 8), dim3(sp.p.waves * kWave), sp.lds, stream, d, sp.p, direct ? d_X : XT,
-                           direct ? 1u : panel_w, direct ? (uint64_t)ldx : 1u, (uint32_t)B, d_Y, (uint64_t)ldy, epi);
+        SplitParams p = sp.p;
+        // a call with a workspace leaves the copy there also where it needs none itself, as every kernel that reads one does: 0.06 us
+        // a call (73 products of 4.5 to 35 us, 0.4 %), against the 3 to 4 us of a pass over X in each call that reuses it
+        float* copy = direct && io == &none && !reuse_xt && sparse_need(desc, B, launch) ? static_cast<float*>(d_ws) : nullptr;
+        const uint32_t threads = p.waves * kWave, units = copy ? (uint32_t)((B + panel_w - 1) / panel_w) * d.n : 0u;
+        p.copies = (units + threads - 1) / threads;
+        hipLaunchKernelGGL(k, dim3((p.nblocks * p.tiles + 7) / 8 * 8 + p.copies), dim3(threads), sp.lds, stream, d, p, direct ? d_X : XT,
+                           direct ? 1u : panel_w, direct ? (uint64_t)ldx : 1u, (uint32_t)B, d_Y, (uint64_t)ldy, copy, epi);
         note_kernel("dot_split_kernel<%s, %u>", tf[shac], sp.nbd);
         hipError_t e = hipGetLastError();
         return e == hipSuccess ? HAC_OK : hip_fail(e);

@@ -14,7 +14,8 @@
 //     X as it is (NBD = 4, 8, 16, 24 or 32, the batch columns of a block): a lane takes a non-zero and fetches one value of each of
 //             the block's rows of X.  Neighbouring lanes hold neighbouring rows of W, so that at the densities where
 //             columns are long a wavefront's fetch touches few lines, and no copy of X is written first: a launch
-//             less, which for small products is a third of the call;
+//             less, which for small products is a third of the call (blocks behind those of the product leave the copy
+//             all the same, for a later call with HAC_LAUNCH_REUSE_XT);
 //   sums    : over the lanes of a wavefront, then over a column's wavefronts through LDS, always in the same order, the last
 //             of them in 64 bits.
 // Measured (MI355X, kernels back to back), one wavefront per column -> this kernel: 500 x 300, 30 % non-zero, 8 rows 8.3 -> 5.5 us;
@@ -34,6 +35,7 @@ struct SplitParams {
     uint32_t width;                          // batch columns of a tile (NBD, or those of a pass over XT)
     uint32_t nblocks;                        // blocks per tile
     uint32_t tiles;
+    uint32_t copies;                         // blocks behind those of the product, which leave the copy of X
     uint32_t sbuf_words;                     // staged stream and ri words; the sums of the wavefronts take their place
     uint32_t list_cap;                       // non-zeros of a block's columns
 };
@@ -62,17 +64,47 @@ __device__ __forceinline__ void finish_pieces(PieceRegs& p, uint4* dst, const ui
     for (uint32_t i = threadIdx.x + 2 * blockDim.x; i < n4; i += blockDim.x) dst[i] = src[i];
 }
 
+// The feature-major copy of X (panels of w batch columns) by the blocks behind the first `before`: a thread reads one feature
+// of a panel's rows of X (neighbouring lanes neighbouring features) and writes a row of the panel, up to a whole line; four
+// columns a thread, so that eight threads share a line, took 0.2 us more.  They run beside the product's own blocks, which
+// are few where X is read as it is.
+__device__ __forceinline__ void leave_copy(uint32_t before, const float* __restrict__ X, uint64_t ldx, uint32_t B, uint32_t n,
+                                           float* __restrict__ XT, uint32_t w)
+{
+    const uint32_t u = (blockIdx.x - before) * blockDim.x + threadIdx.x, p = u / n, r = u - p * n, b0 = p * w;
+    if (b0 >= B) return;
+    float* to = XT + (uint64_t)b0 * n + (uint64_t)r * w;
+    if (w < 4) {                                                           // (two rows of X: w = 2)
+        *reinterpret_cast<float2*>(to) = make_float2(X[r], X[ldx + r]);
+        return;
+    }
+    for (uint32_t k0 = 0; k0 < w && b0 + k0 < B; k0 += 16) {
+        float v[16];
+#pragma unroll
+        for (uint32_t k = 0; k < 16; ++k) v[k] = X[(uint64_t)(b0 + k0 + k < B ? b0 + k0 + k : B - 1) * ldx + r];
+#pragma unroll
+        for (uint32_t k = 0; k < 16; k += 4)
+            if (k0 + k < w) *reinterpret_cast<float4*>(to + k0 + k) = make_float4(v[k], v[k + 1], v[k + 2], v[k + 3]);
+    }
+}
+
 template <bool SHAC, int NBD>
 __global__ void __launch_bounds__(1024)
 dot_split_kernel(DevBlob d, SplitParams p, const float* __restrict__ X, uint32_t xrow, uint64_t xcol, uint32_t B,
-                 float* __restrict__ Y, uint64_t ldy, Epilogue epi)
+                 float* __restrict__ Y, uint64_t ldy, float* __restrict__ copy, Epilogue epi)
 {
     // X[r * xrow + b * xcol] with NBD; XT in panels of xrow batch columns without
     extern __shared__ uint32_t smem[];
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const uint32_t item = logical_block(gridDim.x);
-    if (item >= p.nblocks * p.tiles) return;
+    // (one branch for both, and the size of the grid read here: a branch more, or the arguments' last line read only where the
+    // block size is needed, is another trip to memory before the work, 0.25 us of 5)
+    const uint32_t grid = gridDim.x - p.copies, item = logical_block(grid);
+    const bool behind = NBD != 0 && blockIdx.x >= grid;
+    if (behind | (item >= p.nblocks * p.tiles)) {
+        if (behind) leave_copy(grid, X, xcol, B, d.n, copy, epi.panel_w);
+        return;
+    }
     const uint32_t tile = item / p.nblocks;
     const uint32_t c0 = (item - tile * p.nblocks) << p.cols_log2;          // < m: there are ceil(m / cols) blocks
     const uint32_t ncols = d.m - c0 < p.cols ? d.m - c0 : p.cols;
@@ -107,7 +139,7 @@ dot_split_kernel(DevBlob d, SplitParams p, const float* __restrict__ X, uint32_t
 
     // chunks of this wavefront: at least 16 where there are that many, 32 where most CUs have nothing to do (840 x 82,
     // 37 % non-zero, 10 rows: 6.6 -> 6.1 us; but 23016 x 246, 35 %, 19 rows: 42.1 -> 45.9)
-    const uint32_t nchunks = some ? glast - gfirst : 0u, least = gridDim.x > 128u ? 16u : 32u;
+    const uint32_t nchunks = some ? glast - gfirst : 0u, least = grid > 128u ? 16u : 32u;
     uint32_t per = (nchunks + p.waves - 1) / p.waves;
     per = per < least ? least : per;                                       // at most 64: nchunks <= 64 waves
     const uint32_t g = gfirst + wib * per + lane;

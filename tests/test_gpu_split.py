@@ -99,7 +99,7 @@ def test_a_column_too_long_for_the_list_takes_the_other_kernel(hac):
 
 
 def test_an_old_copy_of_x_is_only_reused_where_every_call_leaves_one(hac):
-    """HAC_LAUNCH_REUSE_XT (0x100) after a call that read X as it is: the copy is made, not assumed."""
+    """HAC_LAUNCH_REUSE_XT (0x100) after a call that read X as it is."""
     rng = np.random.default_rng(5)
     narrow, wide = matrix(1200, 20, 0.2, 1), matrix(1200, 4096, 0.05, 2)
     X = rng.standard_normal((40, 1200)).astype(np.float32)
@@ -133,3 +133,26 @@ def test_a_copy_of_x_is_reused_however_it_was_left(hac, left, reused):
     Y = hac.shac_dot(ds, Xd, workspace=ws, launch=launch(reused, 0x500))
     assert not any("transpose" in k for k in hac.hac_last_kernels())
     check(Y, X, second)
+
+
+# rows of a panel of 2, 4, 8, 16 and 32 columns, full or not; X too short for a second launch, or kept in LDS by other matrices
+@pytest.mark.parametrize("B,n", [(2, 4097), (3, 2049), (5, 1025), (8, 1300), (13, 700), (29, 333), (32, 64), (40, 1200), (200, 1111), (8, 500), (2, 4096)])
+@pytest.mark.parametrize("fmt", ["hac", "shac"])
+def test_a_call_that_reads_x_as_it_is_leaves_the_copy_too(hac, B, n, fmt):
+    """HAC_LAUNCH_REUSE_XT after one launch that re-laid nothing out: no pass over X, and the sums of the wide matrix are right."""
+    narrow, wide = matrix(n, 20, 0.3, 1), matrix(n, 4096, 0.05, 2)
+    wide[:, 1] *= (np.arange(n) % 5 == 0)
+    X = np.random.default_rng(B).standard_normal((B, n)).astype(np.float32)
+    Xd = torch.full((B, n + 3), float("nan"), device="cuda:0")
+    Xd[:, 1:n + 1] = torch.from_numpy(X)
+    Xd = Xd[:, 1:n + 1]
+    dn, dw = hac.hac_encode(narrow).to_device("cuda:0"), getattr(hac, fmt + "_encode")(wide).to_device("cuda:0")
+    reuse = hac.Launch(variant=0x700)                         # reuse the copy, sparse route, the kernel that reads it
+    ws = torch.full((B * 2 * n + 64,), float("nan"), device="cuda:0").view(torch.uint8)
+    print(f"[case] copy left beside the product {fmt} {n} B={B}", flush=True)
+    check(hac.hac_dot(dn, Xd, workspace=ws, launch=hac.Launch(variant=0x400)), X, narrow)
+    assert [k.split("<")[0] for k in hac.hac_last_kernels()] == ["dot_split_kernel"]
+    Y = (hac.hac_dot if fmt == "hac" else hac.shac_dot)(dw, Xd, workspace=ws, launch=reuse)
+    in_lds = B <= 8 and n * (1 << (B - 1).bit_length()) <= 8192
+    assert any("transpose" in k for k in hac.hac_last_kernels()) == in_lds
+    check(Y, X, wide)
