@@ -9,6 +9,7 @@
 
 #include <ATen/ATen.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
@@ -77,12 +78,23 @@ const at::Tensor& tensor_of(PyObject* o, const char* otherwise)
     return THPVariable_Unpack(o);
 }
 
+at::Tensor empty(at::IntArrayRef sizes, at::ScalarType type, const at::Tensor& like)
+{
+    return at::empty(sizes, at::TensorOptions().dtype(type).device(like.device()));
+}
+
+at::Tensor with_rows(const at::Tensor& X)                    // rows of X contiguous: X, or a copy
+{
+    if (X.stride(1) == 1) return X;
+    return X.contiguous();
+}
+
 bool float_cuda(const at::Tensor& t) { return t.scalar_type() == at::kFloat && t.is_cuda(); }
 
 // Y: given and fit to take the result, or made here.
 at::Tensor result(PyObject* y, const at::Tensor& X, int64_t B, int64_t m)
 {
-    if (y == Py_None) return at::empty({B, m}, at::TensorOptions().dtype(at::kFloat).device(X.device()));
+    if (y == Py_None) return empty({B, m}, at::kFloat, X);
     const char* what = "Y must be a B x m float32 CUDA tensor with unit column stride";
     const at::Tensor& Y = tensor_of(y, what);
     if (Y.scalar_type() != at::kFloat || Y.dim() != 2 || Y.size(0) != B || Y.size(1) != m || Y.stride(1) != 1 || !Y.is_cuda()) raise(PyExc_TypeError, what);
@@ -95,7 +107,7 @@ Scratch scratch(PyObject* workspace, const at::Tensor& X, size_t need)
 {
     Scratch s{ {}, nullptr, 0 };
     if (workspace != Py_None) s.keep = tensor_of(workspace, "workspace must be a tensor");
-    else if (need) s.keep = at::empty({(int64_t)need}, at::TensorOptions().dtype(at::kByte).device(X.device()));
+    else if (need) s.keep = empty({(int64_t)need}, at::kByte, X);
     else return s;
     s.ptr = s.keep.data_ptr();
     s.bytes = (size_t)s.keep.numel() * s.keep.element_size();
@@ -145,14 +157,13 @@ template <class F> PyObject* guarded(F&& f)
     try {
         return f();
     } catch (const Raised&) {
-    } catch (const c10::Error& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+        return nullptr;
     } catch (const std::bad_alloc&) {
-        PyErr_NoMemory();
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return PyErr_NoMemory();
+    } catch (const std::exception&) {                        // torch's as Python sees them: torch.OutOfMemoryError among them
+        torch::translate_exception_to_python(std::current_exception());
+        return nullptr;
     }
-    return nullptr;
 }
 
 const hac_launch_t* launch_of(PyObject* launch, std::unique_ptr<Struct<hac_launch_t>>& keep)
@@ -180,7 +191,7 @@ PyObject* dot(Which which, PyObject* const* args, Py_ssize_t n, PyObject* kwname
         }
         at::Tensor X = tensor_of(a[1], "X must be a 2-D float32 CUDA tensor");
         if (!float_cuda(X) || X.dim() != 2) raise(PyExc_TypeError, "X must be a 2-D float32 CUDA tensor");
-        if (X.stride(1) != 1) X = X.contiguous();
+        X = with_rows(X);
         const Blob blob(a[0]);
         const hac_desc_t* d = blob.desc.get();
         const int64_t B = X.size(0), rows = (int64_t)d->n, m = (int64_t)d->m;
@@ -247,7 +258,7 @@ PyObject* py_forward(PyObject*, PyObject* const* args, Py_ssize_t n, PyObject* k
         arguments(args, n, kwnames, names, 2, 5, a);
         at::Tensor X = tensor_of(a[1], "X must be a 2-D float32 CUDA tensor");
         if (!float_cuda(X) || X.dim() != 2) raise(PyExc_TypeError, "X must be a 2-D float32 CUDA tensor");
-        if (X.stride(1) != 1) X = X.contiguous();
+        X = with_rows(X);
         const int64_t B = X.size(0);
         Ref seq(PySequence_Fast(a[0], "layers must be a sequence"));
         const Py_ssize_t L = PySequence_Fast_GET_SIZE(seq.p);

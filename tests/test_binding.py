@@ -61,3 +61,24 @@ def test_results_buffers_and_errors_on_the_gpu():
     with pytest.raises(TypeError, match="bias must be"):
         hac.hac_forward([(db, torch.zeros(39, device="cuda:0"), True)], x)
     assert torch.equal(hac.hac_forward([(db, None, np.bool_(False))], x), hac.hac_dot(db, x))
+
+
+@pytest.mark.gpu
+def test_out_of_memory_is_torchs_exception():
+    """The limit is checked before the driver is asked: nothing is allocated."""
+    import numpy as np
+    W = np.zeros((300, 40), np.float32)
+    W[::7, ::3] = 0.5
+    db = hac.hac_encode(W).to_device("cuda:0")
+    x = torch.rand(1 << 21, 300, device="cuda:0")              # Y: 336 MB
+    print("[case] out of memory", flush=True)
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-6)
+    try:
+        for call in (lambda: hac.hac_dot(db, x), lambda: hac.hac_forward([(db, None, False)], x),                   # Y
+                     lambda: hac.hac_dot(db, x, Y=x[:, :40], launch=hac.Launch(variant=0x400)),                     # the copy of X
+                     lambda: hac.hac_dot(db, x.view(300, -1).t(), Y=x[:, :40])):                                    # rows of X
+            with pytest.raises(torch.OutOfMemoryError):
+                call()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
