@@ -78,14 +78,22 @@ const at::Tensor& tensor_of(PyObject* o, const char* otherwise)
     return THPVariable_Unpack(o);
 }
 
+// Other Python threads run while the allocator may free and retry, as with the tensor calls of Python.
+struct GilReleased {
+    PyThreadState* state = PyEval_SaveThread();
+    ~GilReleased() { PyEval_RestoreThread(state); }
+};
+
 at::Tensor empty(at::IntArrayRef sizes, at::ScalarType type, const at::Tensor& like)
 {
+    const GilReleased released;
     return at::empty(sizes, at::TensorOptions().dtype(type).device(like.device()));
 }
 
 at::Tensor with_rows(const at::Tensor& X)                    // rows of X contiguous: X, or a copy
 {
     if (X.stride(1) == 1) return X;
+    const GilReleased released;
     return X.contiguous();
 }
 
