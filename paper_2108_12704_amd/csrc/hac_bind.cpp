@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <memory>
+#include <optional>
 #include <vector>
 
 #include "../../include/hac.h"
@@ -97,12 +98,44 @@ at::Tensor with_rows(const at::Tensor& X)                    // rows of X contig
     return X.contiguous();
 }
 
+// The stream of a call.  Where the caller names another one than X's device is on, it is that device's current one while the
+// call's buffers are made: a copy of X is queued, and everything made here is used, freed and made anew, in the order of the
+// stream that the product runs on.
+struct OnStream {
+    hac_stream_t handle;
+    std::optional<c10::hip::HIPStream> before;
+    OnStream(PyObject* stream, const at::Tensor& X)
+    {
+        if (stream == Py_None) { handle = (hac_stream_t)c10::hip::getCurrentHIPStream().stream(); return; }
+        Ref h(PyObject_GetAttr(stream, g_stream));
+        Ref i(PyNumber_Long(h.p));
+        handle = (hac_stream_t)PyLong_AsVoidPtr(i.p);
+        if (!handle && PyErr_Occurred()) throw Raised{};
+        const c10::hip::HIPStream current = c10::hip::getCurrentHIPStream(X.device().index());
+        if ((hac_stream_t)current.stream() == handle) return;
+        c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal((hipStream_t)handle, X.device().index()));
+        before = current;
+    }
+    ~OnStream() { if (before) c10::hip::setCurrentHIPStream(*before); }
+    OnStream(const OnStream&) = delete;
+    OnStream& operator=(const OnStream&) = delete;
+    // a result made here is the caller's to use on the stream it was on: not made anew before that is done
+    void hand_over(const at::Tensor& Y) const
+    {
+        if (before) Y.record_stream(c10::Stream(c10::Stream::UNSAFE, c10::Device(c10::DeviceType::CUDA, before->device_index()), before->id()));
+    }
+};
+
 bool float_cuda(const at::Tensor& t) { return t.scalar_type() == at::kFloat && t.is_cuda(); }
 
 // Y: given and fit to take the result, or made here.
-at::Tensor result(PyObject* y, const at::Tensor& X, int64_t B, int64_t m)
+at::Tensor result(PyObject* y, const at::Tensor& X, int64_t B, int64_t m, const OnStream& on)
 {
-    if (y == Py_None) return empty({B, m}, at::kFloat, X);
+    if (y == Py_None) {
+        at::Tensor Y = empty({B, m}, at::kFloat, X);
+        on.hand_over(Y);
+        return Y;
+    }
     const char* what = "Y must be a B x m float32 CUDA tensor with unit column stride";
     const at::Tensor& Y = tensor_of(y, what);
     if (Y.scalar_type() != at::kFloat || Y.dim() != 2 || Y.size(0) != B || Y.size(1) != m || Y.stride(1) != 1 || !Y.is_cuda()) raise(PyExc_TypeError, what);
@@ -120,16 +153,6 @@ Scratch scratch(PyObject* workspace, const at::Tensor& X, size_t need)
     s.ptr = s.keep.data_ptr();
     s.bytes = (size_t)s.keep.numel() * s.keep.element_size();
     return s;
-}
-
-hac_stream_t stream_of(PyObject* stream)
-{
-    if (stream == Py_None) return (hac_stream_t)c10::hip::getCurrentHIPStream().stream();
-    Ref h(PyObject_GetAttr(stream, g_stream));
-    Ref i(PyNumber_Long(h.p));
-    void* p = PyLong_AsVoidPtr(i.p);
-    if (!p && PyErr_Occurred()) throw Raised{};
-    return (hac_stream_t)p;
 }
 
 void check(int rc, const char* where)
@@ -199,23 +222,23 @@ PyObject* dot(Which which, PyObject* const* args, Py_ssize_t n, PyObject* kwname
         }
         at::Tensor X = tensor_of(a[1], "X must be a 2-D float32 CUDA tensor");
         if (!float_cuda(X) || X.dim() != 2) raise(PyExc_TypeError, "X must be a 2-D float32 CUDA tensor");
+        const OnStream on(a[5], X);
         X = with_rows(X);
         const Blob blob(a[0]);
         const hac_desc_t* d = blob.desc.get();
         const int64_t B = X.size(0), rows = (int64_t)d->n, m = (int64_t)d->m;
         if (X.size(1) != rows) raise(PyExc_ValueError, "X has the wrong width");
-        at::Tensor Y = result(a[2], X, B, m);
+        at::Tensor Y = result(a[2], X, B, m, on);
         std::unique_ptr<Struct<hac_launch_t>> keep;
         const hac_launch_t* launch = launch_of(a[4], keep);
         const Scratch ws = scratch(a[3], X, a[3] == Py_None ? g_api.ws_bytes(d, B, launch) : 0);
         const int64_t ldx = B > 1 ? X.stride(0) : std::max<int64_t>(rows, 1), ldy = B > 1 ? Y.stride(0) : std::max<int64_t>(m, 1);
-        const hac_stream_t s = stream_of(a[5]);
         const float* x = static_cast<const float*>(X.data_ptr());
         float* y = static_cast<float*>(Y.data_ptr());
         const auto f = which == HAC ? g_api.hac_dot : which == SHAC ? g_api.shac_dot : g_api.im_dot;
         int rc;
         Py_BEGIN_ALLOW_THREADS
-        rc = f(d, blob.data, x, B, ldx, y, ldy, ws.ptr, ws.bytes, launch, s);
+        rc = f(d, blob.data, x, B, ldx, y, ldy, ws.ptr, ws.bytes, launch, on.handle);
         Py_END_ALLOW_THREADS
         check(rc, where[which]);
         if (a[2] != Py_None) { Py_INCREF(a[2]); return a[2]; }
@@ -241,16 +264,16 @@ PyObject* py_noalloc(PyObject*, PyObject* const* args, Py_ssize_t n, PyObject* k
         const int64_t B = X.size(0), rows = (int64_t)d->n, m = (int64_t)d->m;
         if (X.size(1) != rows) raise(PyExc_ValueError, "X has the wrong width");
         if (a[2] == Py_None) raise(PyExc_TypeError, "Y must be a B x m float32 CUDA tensor with unit column stride");
-        const at::Tensor Y = result(a[2], X, B, m);
+        const OnStream on(a[4], X);
+        const at::Tensor Y = result(a[2], X, B, m, on);
         std::unique_ptr<Struct<hac_launch_t>> keep;
         const hac_launch_t* launch = launch_of(a[3], keep);
         const int64_t ldx = B > 1 ? X.stride(0) : std::max<int64_t>(rows, 1), ldy = B > 1 ? Y.stride(0) : std::max<int64_t>(m, 1);
-        const hac_stream_t s = stream_of(a[4]);
         const float* x = static_cast<const float*>(X.data_ptr());
         float* y = static_cast<float*>(Y.data_ptr());
         int rc;
         Py_BEGIN_ALLOW_THREADS
-        rc = g_api.noalloc(d, blob.data, x, B, ldx, y, ldy, launch, s);
+        rc = g_api.noalloc(d, blob.data, x, B, ldx, y, ldy, launch, on.handle);
         Py_END_ALLOW_THREADS
         check(rc, "hac_dot_noalloc");
         Py_INCREF(a[2]);
@@ -266,6 +289,7 @@ PyObject* py_forward(PyObject*, PyObject* const* args, Py_ssize_t n, PyObject* k
         arguments(args, n, kwnames, names, 2, 5, a);
         at::Tensor X = tensor_of(a[1], "X must be a 2-D float32 CUDA tensor");
         if (!float_cuda(X) || X.dim() != 2) raise(PyExc_TypeError, "X must be a 2-D float32 CUDA tensor");
+        const OnStream on(a[4], X);
         X = with_rows(X);
         const int64_t B = X.size(0);
         Ref seq(PySequence_Fast(a[0], "layers must be a sequence"));
@@ -294,15 +318,14 @@ PyObject* py_forward(PyObject*, PyObject* const* args, Py_ssize_t n, PyObject* k
             arr[i].activation = relu ? HAC_ACT_RELU : HAC_ACT_NONE;
         }
         const int64_t m = (int64_t)arr[L - 1].desc->m;
-        at::Tensor Y = result(a[2], X, B, m);
+        at::Tensor Y = result(a[2], X, B, m, on);
         const Scratch ws = scratch(a[3], X, a[3] == Py_None ? g_api.forward_ws(arr.data(), (uint32_t)L, B) : 0);
         const int64_t ldx = B > 1 ? X.stride(0) : std::max<int64_t>(X.size(1), 1), ldy = B > 1 ? Y.stride(0) : std::max<int64_t>(m, 1);
-        const hac_stream_t s = stream_of(a[4]);
         const float* x = static_cast<const float*>(X.data_ptr());
         float* y = static_cast<float*>(Y.data_ptr());
         int rc;
         Py_BEGIN_ALLOW_THREADS
-        rc = g_api.forward(arr.data(), (uint32_t)L, x, B, ldx, y, ldy, ws.ptr, ws.bytes, s);
+        rc = g_api.forward(arr.data(), (uint32_t)L, x, B, ldx, y, ldy, ws.ptr, ws.bytes, on.handle);
         Py_END_ALLOW_THREADS
         check(rc, "hac_forward");
         if (a[2] != Py_None) { Py_INCREF(a[2]); return a[2]; }

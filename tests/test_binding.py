@@ -82,3 +82,42 @@ def test_out_of_memory_is_torchs_exception():
                 call()
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", ["hac_dot", "hac_forward"])
+def test_buffers_made_here_belong_to_the_stream_of_the_call(call):
+    """`stream` is not the current one: a copy of X neither waits for the current stream nor is its memory given to it early."""
+    import numpy as np
+    W = np.zeros((1000, 60), np.float32)
+    W[::7, ::3] = 0.5
+    db = hac.hac_encode(W).to_device("cuda:0")
+    other, busy = torch.cuda.Stream(), 20_000_000                                   # (10 to 200 ms of either stream)
+
+    def product(x):
+        return hac.hac_dot(db, x, stream=other) if call == "hac_dot" else hac.hac_forward([(db, None, False)], x, stream=other)
+
+    def nan_in_free_memory():
+        blocks = [torch.full((n,), float("nan"), device="cuda:0") for n in (48 * 1000, 48 * 1000, 64 * 1000, 64 * 60)]
+        del blocks
+    xt = torch.rand(1000, 48, device="cuda:0")                                      # rows of X are columns of it
+    ref = (xt.t().double().cpu() @ torch.from_numpy(W).double())
+    product(xt.t())
+    with torch.cuda.stream(other):
+        nan_in_free_memory()
+    nan_in_free_memory()
+    torch.cuda.synchronize()
+    print("[case] streams", flush=True)
+    torch.cuda._sleep(busy)                                                         # the current stream is late
+    y = product(xt.t())
+    other.synchronize()
+    with torch.cuda.stream(other):
+        got = y.cpu()
+    torch.cuda.synchronize()
+    assert torch.allclose(got.double(), ref, rtol=1e-5, atol=1e-5)                  # (143 terms of at most 0.5)
+    with torch.cuda.stream(other):
+        torch.cuda._sleep(busy)                                                     # the stream of the call is late
+    y = product(xt.t())
+    nan_in_free_memory()
+    torch.cuda.synchronize()
+    assert torch.allclose(y.cpu().double(), ref, rtol=1e-5, atol=1e-5)
