@@ -425,7 +425,7 @@ def _native():
         mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_hacbind", loader))
         loader.exec_module(mod)
         lib = load_library()
-        mod.bind(_check, *(C.cast(getattr(lib, f), C.c_void_p).value for f in (
+        mod.bind(_check, Desc, Launch, *(C.cast(getattr(lib, f), C.c_void_p).value for f in (
             "hac_dot", "shac_dot", "im_dot", "hac_dot_noalloc", "hac_workspace_bytes_for", "hac_forward", "hac_forward_workspace_bytes")))
         _bound = mod
     return _bound

@@ -30,6 +30,7 @@ struct Api {
 } g_api;
 PyObject* g_error = nullptr;             // called with (status, function name): raises HacError
 PyObject *g_desc, *g_tensor, *g_stream;  // attribute names
+PyObject *g_Desc = nullptr, *g_Launch = nullptr;             // the ctypes structures of the header and of a launch
 
 struct Raised {};                        // a Python exception is set
 
@@ -50,8 +51,12 @@ struct Ref {                             // owned reference
 // The bytes of a ctypes structure, looked up anew in every call.
 template <class T> struct Struct {
     Py_buffer view;
-    explicit Struct(PyObject* o)
+    Struct(PyObject* o, PyObject* type)
     {
+        if (!PyObject_TypeCheck(o, reinterpret_cast<PyTypeObject*>(type))) {
+            PyErr_Format(PyExc_TypeError, "expected %s, not %s", reinterpret_cast<PyTypeObject*>(type)->tp_name, Py_TYPE(o)->tp_name);
+            throw Raised{};
+        }
         if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE)) throw Raised{};
         if (view.len < (Py_ssize_t)sizeof(T)) { PyBuffer_Release(&view); raise(PyExc_TypeError, "not the expected ctypes structure"); }
     }
@@ -66,7 +71,7 @@ struct Blob {                            // a DeviceBlob: .desc and .tensor
     Struct<hac_desc_t> desc;
     void* data;
     explicit Blob(PyObject* o)
-        : desc_obj(PyObject_GetAttr(o, g_desc)), tensor_obj(PyObject_GetAttr(o, g_tensor)), desc(desc_obj.p)
+        : desc_obj(PyObject_GetAttr(o, g_desc)), tensor_obj(PyObject_GetAttr(o, g_tensor)), desc(desc_obj.p, g_Desc)
     {
         if (!THPVariable_Check(tensor_obj.p)) raise(PyExc_TypeError, "the blob's bytes must be a tensor");
         data = THPVariable_Unpack(tensor_obj.p).data_ptr();
@@ -200,7 +205,7 @@ template <class F> PyObject* guarded(F&& f)
 const hac_launch_t* launch_of(PyObject* launch, std::unique_ptr<Struct<hac_launch_t>>& keep)
 {
     if (launch == Py_None) return nullptr;
-    keep.reset(new Struct<hac_launch_t>(launch));
+    keep.reset(new Struct<hac_launch_t>(launch, g_Launch));
     return keep->get();
 }
 
@@ -333,15 +338,15 @@ PyObject* py_forward(PyObject*, PyObject* const* args, Py_ssize_t n, PyObject* k
     });
 }
 
-// bind(error, hac_dot, shac_dot, im_dot, hac_dot_noalloc, hac_workspace_bytes_for, hac_forward, hac_forward_workspace_bytes): addresses
+// bind(error, Desc, Launch, hac_dot, shac_dot, im_dot, hac_dot_noalloc, hac_workspace_bytes_for, hac_forward, hac_forward_workspace_bytes): addresses
 PyObject* py_bind(PyObject*, PyObject* args)
 {
-    PyObject* error;
+    PyObject *error, *desc, *launch;
     unsigned long long p[7];
-    if (!PyArg_ParseTuple(args, "OKKKKKKK", &error, p, p + 1, p + 2, p + 3, p + 4, p + 5, p + 6)) return nullptr;
-    Py_INCREF(error);
-    Py_XDECREF(g_error);
-    g_error = error;
+    if (!PyArg_ParseTuple(args, "OO!O!KKKKKKK", &error, &PyType_Type, &desc, &PyType_Type, &launch, p, p + 1, p + 2, p + 3, p + 4, p + 5, p + 6)) return nullptr;
+    Py_INCREF(error); Py_INCREF(desc); Py_INCREF(launch);
+    Py_XDECREF(g_error); Py_XDECREF(g_Desc); Py_XDECREF(g_Launch);
+    g_error = error; g_Desc = desc; g_Launch = launch;
     g_api.hac_dot = reinterpret_cast<decltype(g_api.hac_dot)>(p[0]);
     g_api.shac_dot = reinterpret_cast<decltype(g_api.shac_dot)>(p[1]);
     g_api.im_dot = reinterpret_cast<decltype(g_api.im_dot)>(p[2]);

@@ -53,6 +53,15 @@ def test_results_buffers_and_errors_on_the_gpu():
     for bad in (y[:5], y.double(), y.cpu(), torch.empty(40, 6, device="cuda:0").t()):
         with pytest.raises(TypeError, match="Y must be"):
             hac.hac_dot(db, x, Y=bad)
+    for bad in (bytes(64), bytearray(64), np.zeros(64, np.uint8), hac.Desc()):                  # bytes are no launch settings
+        with pytest.raises(TypeError, match="expected Launch"):
+            hac.hac_dot(db, x, launch=bad)
+        with pytest.raises(TypeError, match="expected Launch"):
+            hac.hac_dot_noalloc(db, x, y, launch=bad)
+    class Bytes:
+        desc, tensor = bytes(db.desc), db.tensor
+    with pytest.raises(TypeError, match="expected Desc"):
+        hac.hac_dot(Bytes, x)
     with pytest.raises(ValueError, match="X has the wrong width"):
         hac.hac_dot(db, x[:, 1:])
     with pytest.raises(hac.HacError) as e:
