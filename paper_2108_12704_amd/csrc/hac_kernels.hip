@@ -368,12 +368,46 @@ struct EntryGroup {
 };
 
 // Accumulate list entries with CSC positions [lo, hi) (list index = position - winbase).
-// OWN: kPipe entries have a sum of their own first, instead of one chain of all the list's entries.  With few lane groups a
-// chain is long (relative error against 64 bits: 4096 x 4096, 4 % non-zero, two groups 1.2e-7 -> 8.0e-8).
-template <int NB, int kPipe, bool OWN>
+// How a lane group adds its entries: one chain (kChain); the kPipe entries of a turn have a sum of their own first (kTurns); or two
+// of half as many, added in 64 bits (kHalves), where fewer than eight groups walk a column, so that chains are longer than those
+// of passes of 32 columns.  Relative error against 64 bits, passes of 32 columns and one chain a group -> wide pass with kTurns -> with
+// kHalves: 60 non-zeros a column 6.3e-8 -> 6.9e-8 -> 4.3e-8, 100 6.9e-8 -> 8.0e-8 -> 4.3e-8, 4096 x 4096, 4 %, 128 rows 8.0e-8 -> 8.0e-8 ->
+// 4.3e-8.  kHalves for kTurns costs 1.2 % of a call (geometric mean over 81 products of 34 to 256 rows; worst 5 %: 2000 x 4096, 5 %,
+// 80 rows 17.3 -> 18.2 us); halves added in 32 bits first, or no 64 bits at all, leave the error of kTurns or cost the same.
+enum { kChain, kTurns, kHalves };
+template <int SUMS> struct SumType { typedef float type; };
+template <> struct SumType<kHalves> { typedef double type; };
+
+template <int NB, int kPipe, int SUMS>
+__device__ __forceinline__ void add_group(EntryGroup<NB, kPipe>& G, typename SumType<SUMS>::type (&acc)[NB])
+{
+    constexpr int first = SUMS == kHalves ? kPipe / 2 : kPipe;             // entries of the (first) sum
+#pragma unroll
+    for (int k = 0; k < kPipe; ++k) {
+        const float wv = __uint_as_float(G.e[k].y);                        // 0.0 for an entry that does not exist
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            if constexpr (SUMS == kChain) acc[i] = fmaf(G.x[k][i], wv, acc[i]);
+            else {
+                float& sum = G.x[k < first ? 0 : first % kPipe][i];
+                sum = k == 0 || k == first ? G.x[k][i] * wv : fmaf(G.x[k][i], wv, sum);
+            }
+        }
+    }
+    if constexpr (SUMS == kTurns) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) acc[i] += G.x[0][i];
+    }
+    if constexpr (SUMS == kHalves) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) acc[i] += (double)G.x[0][i] + (double)G.x[first][i];
+    }
+}
+
+template <int NB, int kPipe, int SUMS>
 __device__ __forceinline__ void fma_entries(const uint2* list, uint32_t winbase, uint32_t lo, uint32_t hi,
                                             uint32_t ng, uint32_t grp, const float* xt, uint32_t Bp,
-                                            float (&acc)[NB])
+                                            typename SumType<SUMS>::type (&acc)[NB])
 {
     const uint32_t first = lo + grp;
     const uint32_t count = first < hi ? (hi - first + ng - 1) / ng : 0u;     // entries of this lane group
@@ -386,19 +420,7 @@ __device__ __forceinline__ void fma_entries(const uint2* list, uint32_t winbase,
         for (int k = 0; k < kPipe; ++k) G.e[k] = list[idx + k * ng];
 #pragma unroll
         for (int k = 0; k < kPipe; ++k) VecLoad<NB>::ld(xt + (uint64_t)G.e[k].x * Bp, G.x[k]);
-#pragma unroll
-        for (int k = 0; k < kPipe; ++k) {
-            const float wv = __uint_as_float(G.e[k].y);
-#pragma unroll
-            for (int i2 = 0; i2 < NB; ++i2) {
-                if (!OWN) acc[i2] = fmaf(G.x[k][i2], wv, acc[i2]);
-                else G.x[0][i2] = k ? fmaf(G.x[k][i2], wv, G.x[0][i2]) : G.x[0][i2] * wv;
-            }
-        }
-        if (OWN) {
-#pragma unroll
-            for (int i2 = 0; i2 < NB; ++i2) acc[i2] += G.x[0][i2];
-        }
+        add_group<NB, kPipe, SUMS>(G, acc);
     }
     // last, partial group: only the entries that exist are fetched (a lane that is switched off asks
     // the memory path for nothing; a repeated fetch of some valid row would cost it a line like any other)
@@ -415,19 +437,7 @@ __device__ __forceinline__ void fma_entries(const uint2* list, uint32_t winbase,
         for (int k = 0; k < kPipe; ++k) if ((uint32_t)k < rest) G.e[k] = list[idx + k * ng];
 #pragma unroll
         for (int k = 0; k < kPipe; ++k) if ((uint32_t)k < rest) VecLoad<NB>::ld(xt + (uint64_t)G.e[k].x * Bp, G.x[k]);
-#pragma unroll
-        for (int k = 0; k < kPipe; ++k) {
-            const float wv = __uint_as_float(G.e[k].y);          // 0.0 for an entry that does not exist
-#pragma unroll
-            for (int i2 = 0; i2 < NB; ++i2) {
-                if (!OWN) acc[i2] = fmaf(G.x[k][i2], wv, acc[i2]);
-                else G.x[0][i2] = k ? fmaf(G.x[k][i2], wv, G.x[0][i2]) : G.x[0][i2] * wv;
-            }
-        }
-        if (OWN) {
-#pragma unroll
-            for (int i2 = 0; i2 < NB; ++i2) acc[i2] += G.x[0][i2];
-        }
+        add_group<NB, kPipe, SUMS>(G, acc);
     }
 }
 
@@ -536,8 +546,8 @@ __device__ __forceinline__ void block_sync_lds()
 // MP: several passes (npass > 1); the single-pass variant has no pass loop and no barrier.
 // EPI: the epilogue (bias, max(., 0), feature-major output) is compiled in; a plain product runs
 // the variant without it, which needs fewer registers (the single-pass kernel would spill one).
-// OWN: see fma_entries (off for many passes of 32 batch columns: eight lane groups keep the chains short, and it costs 0.7 % at 256 rows).
-template <bool SHAC, int NB, bool MP, bool EPI, bool OWN>
+// SUMS: see fma_entries (kChain for many passes of 32 batch columns: eight lane groups keep the chains short, and kTurns costs 0.7 % at 256 rows).
+template <bool SHAC, int NB, bool MP, bool EPI, int SUMS>
 __global__ void __launch_bounds__((BatchTraits<NB>::kMaxThreads))
 dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t panel_w, uint32_t B,
                  float* __restrict__ Y, uint64_t ldy, uint32_t cpw, uint32_t gw, uint32_t npass,
@@ -638,7 +648,7 @@ dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t panel_w, uint
             // wave, no column split over windows).  The first pass starts without waiting: a wave
             // that has decoded its column early gathers while the others still decode.
             if (MP && sync_passes && p > 0) __syncthreads();
-            float a[NB];
+            typename SumType<SUMS>::type a[NB];
 #pragma unroll
             for (int i = 0; i < NB; ++i) a[i] = (carried && part_words) ? part[(p * NB + i) * kWave + lane] : 0.0f;
             // (the single-pass kernel with the epilogue compiled in spills with ten fetches in flight; without it, it takes
@@ -646,12 +656,13 @@ dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t panel_w, uint
             constexpr int kPipe = BatchTraits<NB>::kPipe - ((!MP && NB == 4) ? 1 : 0);
             // (a lane whose batch columns are all padding fetches nothing)
             const uint32_t b0 = boff + p * pass_w;             // (NB columns of one panel)
-            if (t < hi && b0 < B) fma_entries<NB, kPipe, OWN>(list, winbase, t, hi, ng, grp, XT + panel_offset(panel_w, d.n, b0), panel_w, a);
+            if (t < hi && b0 < B) fma_entries<NB, kPipe, SUMS>(list, winbase, t, hi, ng, grp, XT + panel_offset(panel_w, d.n, b0), panel_w, a);
             if (last) {
 #pragma unroll
                 for (int i = 0; i < NB; ++i) {
-                    float v = a[i];
-                    for (uint32_t off = 32; off >= gw; off >>= 1) v += __shfl_xor(v, (int)off, kWave);
+                    typename SumType<SUMS>::type sum = a[i];
+                    for (uint32_t off = 32; off >= gw; off >>= 1) sum += __shfl_xor(sum, (int)off, kWave);
+                    const float v = (float)sum;
                     const uint32_t b = b0 + i;
                     if (grp == 0) {
                         if constexpr (EPI) {
@@ -665,7 +676,7 @@ dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t panel_w, uint
                 }
             } else if (part_words) {                       // always true here: the host sizes `part` whenever a split can occur
 #pragma unroll
-                for (int i = 0; i < NB; ++i) part[(p * NB + i) * kWave + lane] = a[i];
+                for (int i = 0; i < NB; ++i) part[(p * NB + i) * kWave + lane] = (float)a[i];
             }
         }
     };
@@ -1131,12 +1142,12 @@ void launch_bias_act(float* d_Y, uint32_t B, uint32_t m, uint64_t ldy, const flo
 }
 
 template <bool SHAC, bool EPI>
-batch_kern_t pick_batch_kernel(uint32_t nb, bool multipass, bool own)
+batch_kern_t pick_batch_kernel(uint32_t nb, bool multipass, int sums)
 {
-    if (nb == 1) return dot_batch_kernel<SHAC, 1, false, EPI, true>;
-    if (nb == 2) return dot_batch_kernel<SHAC, 2, false, EPI, true>;
-    if (!multipass) return dot_batch_kernel<SHAC, 4, false, EPI, true>;
-    return own ? dot_batch_kernel<SHAC, 4, true, EPI, true> : dot_batch_kernel<SHAC, 4, true, EPI, false>;
+    if (nb == 1) return dot_batch_kernel<SHAC, 1, false, EPI, kTurns>;
+    if (nb == 2) return dot_batch_kernel<SHAC, 2, false, EPI, kTurns>;
+    if (!multipass) return sums == kHalves ? dot_batch_kernel<SHAC, 4, false, EPI, kHalves> : dot_batch_kernel<SHAC, 4, false, EPI, kTurns>;
+    return sums == kHalves ? dot_batch_kernel<SHAC, 4, true, EPI, kHalves> : dot_batch_kernel<SHAC, 4, true, EPI, kChain>;
 }
 
 // per-wave LDS words for the stream (and ri) words of a wave's columns
@@ -1559,10 +1570,10 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     if (items > 0x7ffffff0ull) return HAC_EINVAL;
     const uint32_t grid = (uint32_t)((items + 7) / 8 * 8);
     const bool with_epilogue = io->bias || io->relu || io->yt_out;
-    const bool own = bs.npass == 1 || bs.gw * bs.nb > 32;
+    const int sums = bs.gw * bs.nb > 32 ? kHalves : bs.npass == 1 ? kTurns : kChain;
     batch_kern_t k = with_epilogue
-        ? (shac ? pick_batch_kernel<true, true>(bs.nb, bs.npass > 1, own) : pick_batch_kernel<false, true>(bs.nb, bs.npass > 1, own))
-        : (shac ? pick_batch_kernel<true, false>(bs.nb, bs.npass > 1, own) : pick_batch_kernel<false, false>(bs.nb, bs.npass > 1, own));
+        ? (shac ? pick_batch_kernel<true, true>(bs.nb, bs.npass > 1, sums) : pick_batch_kernel<false, true>(bs.nb, bs.npass > 1, sums))
+        : (shac ? pick_batch_kernel<true, false>(bs.nb, bs.npass > 1, sums) : pick_batch_kernel<false, false>(bs.nb, bs.npass > 1, sums));
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1571,7 +1582,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     hipLaunchKernelGGL(k, dim3(grid), dim3(wpb * kWave), lds, stream,
                        d, XT, panel_w, (uint32_t)B, d_Y, (uint64_t)ldy, cpw, bs.gw, bs.npass, list_cap, sbuf_words, part_words, nblocks,
                        sync_passes, epi);
-    note_kernel("dot_batch_kernel<%s, %u, %s, %s, %s>", tf[shac], bs.nb, tf[bs.nb == 4 && bs.npass > 1], tf[with_epilogue], tf[own]);
+    note_kernel("dot_batch_kernel<%s, %u, %s, %s, %d>", tf[shac], bs.nb, tf[bs.nb == 4 && bs.npass > 1], tf[with_epilogue], sums);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? HAC_OK : hip_fail(e);
 }
