@@ -172,3 +172,23 @@ def test_long_columns_lose_nothing_in_a_wide_pass(hac, B, m, kernel):
     Y, kernels = run(hac, "hac", W, X)
     assert kernels[-1].startswith(kernel)
     assert bool((np.abs(Y.cpu().numpy().astype(np.float64) - odot.dense_dot(X, W)) <= 8 * 2.0 ** -24 * odot.abs_dot(X, W)).all())
+
+
+@pytest.mark.parametrize("fmt", sorted(ENCODERS))
+@pytest.mark.parametrize("B", [2, 6, 13, 20, 32, 70])
+def test_short_columns_are_rounded_once(hac, B, fmt):
+    """Products and sums of two that fp32 holds exactly: what is added after that, in 64 bits, leaves one rounding."""
+    rng = np.random.default_rng(B)
+    n, m = 600, 150
+    values = rng.choice(np.arange(1, 2048), 24, replace=False).astype(np.float32)
+    W = np.zeros((n, m), np.float32)
+    for j in range(m):                                        # at most one non-zero a lane
+        rows = rng.choice(n, rng.integers(1, 65), replace=False)
+        W[rows, j] = values[rng.integers(0, 24, rows.size)]
+    X = rng.integers(1, 4096, (B, n)).astype(np.float32)
+    print(f"[case] short columns {fmt} B={B}", flush=True)
+    Y, kernels = run(hac, fmt, W, X)
+    assert kernels[0].startswith("dot_split_kernel") and not kernels[0].endswith(" 0>")
+    exact = X.astype(np.int64) @ W.astype(np.int64)
+    assert exact.max() > 1 << 26
+    assert bool((Y.cpu().numpy() == exact.astype(np.float32)).all())
