@@ -1015,7 +1015,7 @@ uint32_t panel_width(int64_t B)
     return w;
 }
 
-// Batch columns that one pass over the list covers, from as many panels side by side: as many as the batch has (a power of
+// The widest pass over the list, in batch columns, from as many panels side by side: as many as the batch has (a power of
 // two, at most 256) while what a pass reads of X stays within the 4 MB of an XCD's L2.  A wider pass means fewer of them:
 // 4096 x 4096, 4 % non-zero, 128 rows 29.4 (32 columns) -> 25.3 (64) -> 23.4 us (128); 1000 x 4096, 10 %, 256 rows, sparse route
 // asked for, 43.4 -> 31.6 -> 26.2 us; but 25088 rows of W, 256 rows of X: 109.4 (32 columns, 3.2 MB), 115.5 (64), 155.9 us (256).
@@ -1023,12 +1023,29 @@ uint32_t panel_width(int64_t B)
 // worst 1.6 % slower).
 constexpr double kPassBytes = 3.4e6;
 
-uint32_t pass_columns(uint64_t n, int64_t B)
+uint32_t widest_pass(uint64_t n, int64_t B)
 {
     uint32_t w = 1;
     while (w < (uint32_t)(B < 256 ? B : 256)) w <<= 1;
     while (w > 32 && 4.0 * (double)n * w > kPassBytes) w >>= 1;
     return w;
+}
+
+// ... and the width that dot_batch_kernel takes: a narrower one where the last pass of a wide one would be mostly padding.  A
+// pass takes a column as long as another 4400 batch columns do one non-zero (fitted, with the widest pass, to passes of 32 to 256
+// columns, each forced, on 720 products: 900 to 25000 rows of W, 2 to 10 % non-zero, 40 to 512 rows of X).  6000 x 4096, 10 %, 144 rows:
+// two passes of 128 91.9 us, five of 32 71.1; 9000 x 4096, 10 %, 96 rows: two of 64 62.7, three of 32 55.5; but 1800 x 4096, 2 %, 160
+// rows: one of 256 instead of five of 32.  Against passes of 32 the choice gains 16 % (geometric mean; the widest pass always 15 %) and
+// loses up to 3.6 % (six products more than 1.5 %; the widest pass always up to 23 %, 82 products).
+uint32_t pass_columns(const hac_desc_t* desc, int64_t B)
+{
+    const uint32_t here = (uint32_t)(B < 256 ? B : 256);                   // of a block's tile
+    const double per_pass = 4400.0 * (double)desc->m / (double)(desc->nnz > 0 ? desc->nnz : 1);
+    auto cost = [&](uint32_t w) { const uint32_t p = (here + w - 1) / w; return (double)(p * w) + per_pass * p; };
+    uint32_t best = widest_pass(desc->n, B);
+    for (uint32_t w = best >> 1; w >= 32; w >>= 1)
+        if (cost(w) < cost(best)) best = w;
+    return best;
 }
 
 uint32_t round_up(uint32_t v, uint32_t q) { return (v + q - 1) / q * q; }
@@ -1222,7 +1239,7 @@ SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* laun
     const double l1_us = 1.0e-7 * (double)n * (double)m * (double)B;       // every column reads all lines of X
     s.direct = n * (uint64_t)B <= kDirectFloats && l1_us < 4.0;
     if (!s.direct && (B <= 4 || xlds_plan(desc, B, launch).use)) return s;
-    uint32_t width = pass_columns(n, B);
+    uint32_t width = widest_pass(n, B);
     if (s.direct) {                                                        // tiles of at most 32 batch columns, all about as wide
         const uint64_t each = ((uint64_t)B + ((uint64_t)B + 31) / 32 - 1) / (((uint64_t)B + 31) / 32);
         width = each <= 4 ? 4u : each <= 8 ? 8u : each <= 16 ? 16u : each <= 24 ? 24u : 32u;
@@ -1308,7 +1325,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     const uint32_t panel_w = panel_width(B);
     const Epilogue epi = { io->bias, io->yt_out, io->relu, panel_w };
     hipStream_t stream = static_cast<hipStream_t>(stream_);
-    uint32_t cpw = default_cpw(desc), wpb = 0, list_cap = 0, sbuf_words = 0, pass_w = pass_columns(desc->n, B), tile_b = kDefaultTile;
+    uint32_t cpw = default_cpw(desc), wpb = 0, list_cap = 0, sbuf_words = 0, pass_w = pass_columns(desc, B), tile_b = kDefaultTile;
     bool reuse_xt = false, list_kernel = false;
     if (pass_w < 32) pass_w = 32;
     if (launch) {

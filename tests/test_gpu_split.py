@@ -192,3 +192,19 @@ def test_short_columns_are_rounded_once(hac, B, fmt):
     exact = X.astype(np.int64) @ W.astype(np.int64)
     assert exact.max() > 1 << 26
     assert bool((Y.cpu().numpy() == exact.astype(np.float32)).all())
+
+
+# the last pass of the widest kind full, partly full, mostly padding; a dense and a sparse matrix, two tiles of the batch
+@pytest.mark.parametrize("density,kinds", [(0.1, {72: 0, 96: 0, 128: 2, 144: 0, 200: 2, 256: 2, 280: 2}), (0.01, {72: 2, 129: 2, 160: 2, 256: 2})])
+def test_passes_that_the_batch_fills(hac, density, kinds):
+    """The kernel's last parameter is 2 for passes of 64 columns or more, 0 for several of 32."""
+    n, m = 4500, 3200
+    W = matrix(n, m, density, 11)
+    W[:, 1] *= (np.arange(n) % 20 == 0)
+    rng = np.random.default_rng(12)
+    for B, kind in kinds.items():
+        X = rng.standard_normal((B, n)).astype(np.float32)
+        print(f"[case] passes {density} B={B}", flush=True)
+        Y, kernels = run(hac, "hac", W, X)
+        assert kernels[-1].startswith("dot_batch_kernel") and kernels[-1].endswith(f"{kind}>"), (B, kernels)
+        check(Y, X, W)
