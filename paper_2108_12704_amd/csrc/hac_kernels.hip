@@ -1239,19 +1239,31 @@ SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* laun
     const double l1_us = 1.0e-7 * (double)n * (double)m * (double)B;       // every column reads all lines of X
     s.direct = n * (uint64_t)B <= kDirectFloats && l1_us < 4.0;
     if (!s.direct && (B <= 4 || xlds_plan(desc, B, launch).use)) return s;
-    uint32_t width = widest_pass(n, B);
-    if (s.direct) {                                                        // tiles of at most 32 batch columns, all about as wide
-        const uint64_t each = ((uint64_t)B + ((uint64_t)B + 31) / 32 - 1) / (((uint64_t)B + 31) / 32);
-        width = each <= 4 ? 4u : each <= 8 ? 8u : each <= 16 ? 16u : each <= 24 ? 24u : 32u;
+    uint32_t width = 0, split_log2 = 0;
+    uint64_t tiles = 0, turn = 0;                                          // (turn: entries of a wavefront's)
+    for (;;) {
+        width = widest_pass(n, B);
+        if (s.direct) {                                                    // tiles of at most 32 batch columns, all about as wide
+            const uint64_t each = ((uint64_t)B + ((uint64_t)B + 31) / 32 - 1) / (((uint64_t)B + 31) / 32);
+            width = each <= 4 ? 4u : each <= 8 ? 8u : each <= 16 ? 16u : each <= 24 ? 24u : 32u;
+        }
+        tiles = ((uint64_t)B + width - 1) / width;
+        turn = s.direct ? 64u : 8u * 64u / (width / 4u);
+        // as many wavefronts per column as leave 16 to a CU, a second one up to 24 (6559 x 300, 28 % non-zero, 4 rows: 8 per column
+        // 11.5 us, 16 per column 20.2; 1719 x 2287, 28 %, 3 rows: one 12.1 us, two 9.3)
+        split_log2 = 0;
+        while (split_log2 < 4 && (m * tiles << (split_log2 + 1)) <= (split_log2 ? 4096u : 6144u) && (turn << split_log2) < desc->max_col_nnz) ++split_log2;
+        // many columns of many non-zeros: a lane's fetch of one value of each row of X costs more than the copy of X (778 x 1963,
+        // 35 %, 26 rows 16.9 us, 12.5 from the copy; 529 x 1762, 35 %, 25 rows, 8 million fetches, 12.9 and 10.6)
+        if (!s.direct || B <= 4 || split_log2 > 1 || (double)desc->nnz * (double)B <= (split_log2 ? 7.0e6 : 4.5e6)) break;
+        s.direct = false;
+        if (xlds_plan(desc, B, launch).use) return s;
     }
     s.copy = launch && (launch->variant & HAC_LAUNCH_NO_X_LDS);
     s.nbd = s.direct ? width : 0u;
-    const uint64_t tiles = ((uint64_t)B + width - 1) / width;
-    const uint64_t turn = s.direct ? 64u : 8u * 64u / (width / 4u);       // entries of a wavefront's turn
-    uint32_t split_log2 = 0;
-    // as many wavefronts per column as leave 16 to a CU, a second one up to 24 (6559 x 300, 28 % non-zero, 4 rows: 8 per column
-    // 11.5 us, 16 per column 20.2; 1719 x 2287, 28 %, 3 rows: one 12.1 us, two 9.3)
-    while (split_log2 < 4 && (m * tiles << (split_log2 + 1)) <= (split_log2 ? 4096u : 6144u) && (turn << split_log2) < desc->max_col_nnz) ++split_log2;
+    // two rows of X and many columns for two wavefronts each, or hardly more than three turns for the two: the other kernels are
+    // as quick or quicker (770 x 2872, 33 %, 2 rows 8.2 against 6.9 us; 3000 x 2000, 1.5 %, 32 rows 9.9 against 9.3)
+    if (split_log2 == 1 && (s.direct ? B == 2 && m >= 1536 : 2 * desc->max_col_nnz < 7 * turn)) return s;
     // one wavefront per column after all: the other kernels are as good or better, but for a few rows and short columns
     // (8 rows of X, 512 x 4096, 10 % non-zero: 9.9 -> 7.3 us; 2 rows, 4096 x 4096, 40 %: 17.7 against 36.1)
     if (split_log2 == 0 && (!s.direct || desc->max_col_nnz > 256)) return s;
@@ -1275,7 +1287,15 @@ SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* laun
     p.sbuf_words = round_up(std::max((uint32_t)words + 1u, 2u * p.waves * width), 4);
     p.list_cap = (uint32_t)desc->max_col_nnz * p.cols;
     s.lds = table_bytes_of(desc) + 4ull * p.sbuf_words + 8ull * p.list_cap;
-    s.use = s.lds <= kLdsLimit;
+    if (s.lds > kLdsLimit) return s;
+    // blocks that wait for LDS: a few rows of X (their other kernel keeps no list, so all columns are decoded at once; 10590 x 1502,
+    // 38 %, 2 rows 66.2 against 28.5 us), or more than five rounds of them (16841 x 1291, 26 %, 53 rows 195 against 121)
+    // (Of 10239 products of 2 to 128 rows that took this kernel, 357 were more than 2 % slower than with the others, up to 2.9 times; with
+    // these lines 103 of 8146 other ones, up to 1.4 times, where the blocks of a second round are few; it gains 43 % in the mean.)
+    const uint64_t resident = std::min<uint64_t>(kLdsLimit / s.lds, 32u / p.waves);
+    const double rounds = (double)(nblocks * tiles) / (256.0 * (double)resident);
+    if (s.direct && B <= 4 ? rounds > 0.95 || (resident * p.waves < 16 && rounds > 0.7) : rounds > 5.0) return s;
+    s.use = true;
     return s;
 }
 

@@ -208,3 +208,21 @@ def test_passes_that_the_batch_fills(hac, density, kinds):
         Y, kernels = run(hac, "hac", W, X)
         assert kernels[-1].startswith("dot_batch_kernel") and kernels[-1].endswith(f"{kind}>"), (B, kernels)
         check(Y, X, W)
+
+
+# where the other kernels are the quicker ones: blocks that wait for LDS (few rows of X, and five rounds of them), two rows of many
+# columns, dense columns over X as it is, short columns for two wavefronts; and the neighbours that stay
+@pytest.mark.parametrize("n,m,density,B,kernel", [
+    (10590, 1502, 0.38, 2, "dot_small_kernel<false, 2, false>"), (10590, 400, 0.05, 2, "dot_split_kernel<false, 4>"),
+    (770, 2872, 0.33, 2, "dot_small_kernel<false, 2, true>"), (770, 2872, 0.33, 3, "dot_split_kernel<false, 4>"),
+    (778, 1963, 0.35, 26, "dot_split_kernel<false, 0>"), (778, 1963, 0.1, 26, "dot_split_kernel<false, 32>"),
+    (529, 3100, 0.35, 8, "dot_batch_kernel<false, 4, false, false, 1>"), (16841, 1291, 0.26, 70, "dot_batch_kernel<false, 4, true, false, 0>"),
+    (3000, 2000, 0.015, 32, "dot_batch_kernel<false, 4, false, false, 1>"), (3000, 2000, 0.08, 32, "dot_split_kernel<false, 0>")])
+def test_which_products_take_it(hac, n, m, density, B, kernel):
+    W = matrix(n, m, density, n + B)
+    W[:, 1] *= (np.arange(n) % max(1, round(1 / density)) == 0)
+    X = np.random.default_rng(B).standard_normal((B, n)).astype(np.float32)
+    print(f"[case] which kernel {n}x{m} {density} B={B}", flush=True)
+    Y, kernels = run(hac, "hac", W, X)
+    assert kernels[-1] == kernel
+    check(Y, X, W)
