@@ -546,7 +546,8 @@ __device__ __forceinline__ void block_sync_lds()
 // MP: several passes (npass > 1); the single-pass variant has no pass loop and no barrier.
 // EPI: the epilogue (bias, max(., 0), feature-major output) is compiled in; a plain product runs
 // the variant without it, which needs fewer registers (the single-pass kernel would spill one).
-// SUMS: see fma_entries (kChain for many passes of 32 batch columns: eight lane groups keep the chains short, and kTurns costs 0.7 % at 256 rows).
+// SUMS: see fma_entries (kChain for passes of 32 batch columns over a tall X: eight lane groups keep the chains short, and kTurns costs 0.7 %
+// at 256 rows; kTurns where passes of 32 were chosen before wider ones that L2 would hold, whose sums are better than a chain's).
 template <bool SHAC, int NB, bool MP, bool EPI, int SUMS>
 __global__ void __launch_bounds__((BatchTraits<NB>::kMaxThreads))
 dot_batch_kernel(DevBlob d, const float* __restrict__ XT, uint32_t panel_w, uint32_t B,
@@ -1164,7 +1165,8 @@ batch_kern_t pick_batch_kernel(uint32_t nb, bool multipass, int sums)
     if (nb == 1) return dot_batch_kernel<SHAC, 1, false, EPI, kTurns>;
     if (nb == 2) return dot_batch_kernel<SHAC, 2, false, EPI, kTurns>;
     if (!multipass) return sums == kHalves ? dot_batch_kernel<SHAC, 4, false, EPI, kHalves> : dot_batch_kernel<SHAC, 4, false, EPI, kTurns>;
-    return sums == kHalves ? dot_batch_kernel<SHAC, 4, true, EPI, kHalves> : dot_batch_kernel<SHAC, 4, true, EPI, kChain>;
+    return sums == kHalves ? dot_batch_kernel<SHAC, 4, true, EPI, kHalves> : sums == kTurns ? dot_batch_kernel<SHAC, 4, true, EPI, kTurns>
+                                                                                      : dot_batch_kernel<SHAC, 4, true, EPI, kChain>;
 }
 
 // per-wave LDS words for the stream (and ri) words of a wave's columns
@@ -1261,9 +1263,9 @@ SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* laun
     }
     s.copy = launch && (launch->variant & HAC_LAUNCH_NO_X_LDS);
     s.nbd = s.direct ? width : 0u;
-    // two rows of X and many columns for two wavefronts each, or hardly more than three turns for the two: the other kernels are
+    // two rows of X and many columns for two wavefronts each, or hardly three turns for the two: the other kernels are
     // as quick or quicker (770 x 2872, 33 %, 2 rows 8.2 against 6.9 us; 3000 x 2000, 1.5 %, 32 rows 9.9 against 9.3)
-    if (split_log2 == 1 && (s.direct ? B == 2 && m >= 1536 : 2 * desc->max_col_nnz < 7 * turn)) return s;
+    if (split_log2 == 1 && (s.direct ? B == 2 && m >= 2048 : desc->max_col_nnz < 3 * turn)) return s;
     // one wavefront per column after all: the other kernels are as good or better, but for a few rows and short columns
     // (8 rows of X, 512 x 4096, 10 % non-zero: 9.9 -> 7.3 us; 2 rows, 4096 x 4096, 40 %: 17.7 against 36.1)
     if (split_log2 == 0 && (!s.direct || desc->max_col_nnz > 256)) return s;
@@ -1607,7 +1609,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     if (items > 0x7ffffff0ull) return HAC_EINVAL;
     const uint32_t grid = (uint32_t)((items + 7) / 8 * 8);
     const bool with_epilogue = io->bias || io->relu || io->yt_out;
-    const int sums = bs.gw * bs.nb > 32 ? kHalves : bs.npass == 1 ? kTurns : kChain;
+    const int sums = bs.gw * bs.nb > 32 ? kHalves : bs.npass == 1 || widest_pass(desc->n, B) > 32 ? kTurns : kChain;
     batch_kern_t k = with_epilogue
         ? (shac ? pick_batch_kernel<true, true>(bs.nb, bs.npass > 1, sums) : pick_batch_kernel<false, true>(bs.nb, bs.npass > 1, sums))
         : (shac ? pick_batch_kernel<true, false>(bs.nb, bs.npass > 1, sums) : pick_batch_kernel<false, false>(bs.nb, bs.npass > 1, sums));

@@ -195,9 +195,9 @@ def test_short_columns_are_rounded_once(hac, B, fmt):
 
 
 # the last pass of the widest kind full, partly full, mostly padding; a dense and a sparse matrix, two tiles of the batch
-@pytest.mark.parametrize("density,kinds", [(0.1, {72: 0, 96: 0, 128: 2, 144: 0, 200: 2, 256: 2, 280: 2}), (0.01, {72: 2, 129: 2, 160: 2, 256: 2})])
+@pytest.mark.parametrize("density,kinds", [(0.1, {72: 1, 96: 1, 128: 2, 144: 1, 200: 2, 256: 2, 280: 2}), (0.01, {72: 2, 129: 2, 160: 2, 256: 2})])
 def test_passes_that_the_batch_fills(hac, density, kinds):
-    """The kernel's last parameter is 2 for passes of 64 columns or more, 0 for several of 32."""
+    """The kernel's last parameter is 2 for passes of 64 columns or more, 1 for several of 32 that were chosen before them."""
     n, m = 4500, 3200
     W = matrix(n, m, density, 11)
     W[:, 1] *= (np.arange(n) % 20 == 0)
