@@ -283,6 +283,11 @@ __device__ __forceinline__ void hac_advance(const DevBlob& d, const Tables& tb, 
     }
 }
 
+// The loops below are short chains that every lane walks alone, and what they take depends on where their instructions fall in
+// the 32-byte pieces that are fetched: 17732 x 3387, 35 % non-zero, sHAC, 20 rows 376 or 389 us, 12000 x 30, 30 %, 8 rows 23.1 or 23.8,
+// by what the code in front of them happened to leave.  (Padding is a few s_nop in front of a loop.)
+#define ALIGN_DECODE_LOOP() asm volatile(".p2align 6")
+
 // HAC, zero symbol = the single bit 0, words staged in LDS.  One pass of the loop per
 // non-zero: 128 stream bits are fetched at once, a count-leading-zeros over the first
 // 64 skips the zero run, and the codeword is taken from the same fetch.  Only a run
@@ -303,6 +308,7 @@ __device__ __forceinline__ void hac_advance_zrun(const DevBlob& d, const Tables&
 {
     lds_cu32* sw = (lds_cu32*)src.w;
     int32_t rm1 = (int32_t)(st.bp - (src.wbase << 5)) - 1;
+    ALIGN_DECODE_LOOP();
     while (st.wpos < limit) {
         const int32_t q = rm1 >> 5;
         const uint32_t s = ~(uint32_t)rm1;
@@ -351,6 +357,7 @@ __device__ __forceinline__ void shac_advance(const DevBlob& d, const Tables& tb,
                                              ChunkState& st, uint32_t limit, Emit emit)
 {
     int32_t rm1 = (int32_t)(st.bp - (src.wbase << 5)) - 1;
+    ALIGN_DECODE_LOOP();
     while (st.wpos < limit) {
         const Decoded sy = decode_symbol(d, tb, src.peek32_rm1(rm1));
         rm1 += (int32_t)sy.len;
@@ -370,6 +377,7 @@ __device__ __forceinline__ void gap_advance(const DevBlob& d, const Tables& tb, 
 {
     lds_cu32* sw = (lds_cu32*)src.w;
     const uint32_t k = d.rice_k;
+    ALIGN_DECODE_LOOP();
     while (st.wpos < limit) {
         const uint32_t wi = (st.bp >> 5) - src.wbase, off = st.bp & 31;
         const uint32_t w0 = sw[wi], w1 = sw[wi + 1], w2 = sw[wi + 2], w3 = sw[wi + 3];
