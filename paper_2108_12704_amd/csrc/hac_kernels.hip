@@ -369,8 +369,9 @@ struct EntryGroup {
 
 // Accumulate list entries with CSC positions [lo, hi) (list index = position - winbase).
 // How a lane group adds its entries: one chain (kChain); the kPipe entries of a turn have a sum of their own first (kTurns); or two
-// of half as many, added in 64 bits (kHalves), where fewer than eight groups walk a column, so that chains are longer than those
-// of passes of 32 columns.  Relative error against 64 bits, passes of 32 columns and one chain a group -> wide pass with kTurns -> with
+// of half as many, added in 64 bits (kHalves), where fewer than eight groups walk a short column: chains of turns are longer than those
+// of entries in passes of 32 columns up to a few hundred non-zeros (from 600 on, kTurns rounds less: 6000 x 4096, 10 %, 160 rows 1.22e-7 ->
+// 1.17e-7; 12000 x 3387, 36 %, 40 rows, kHalves takes 354 us, kTurns 322).  Relative error against 64 bits, passes of 32 columns and one chain a group -> wide pass with kTurns -> with
 // kHalves: 60 non-zeros a column 6.3e-8 -> 6.9e-8 -> 4.3e-8, 100 6.9e-8 -> 8.0e-8 -> 4.3e-8, 4096 x 4096, 4 %, 128 rows 8.0e-8 -> 8.0e-8 ->
 // 4.3e-8.  kHalves for kTurns costs 1.2 % of a call (geometric mean over 81 products of 34 to 256 rows; worst 5 %: 2000 x 4096, 5 %,
 // 80 rows 17.3 -> 18.2 us); halves added in 32 bits first, or no 64 bits at all, leave the error of kTurns or cost the same.
@@ -1505,7 +1506,10 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         typedef void (*split_kern_t)(DevBlob, SplitParams, const float*, uint32_t, uint64_t, uint32_t, float*, uint64_t, float*, Epilogue);
         split_kern_t k;
         switch (sp.nbd) {
-        case 0: k = shac ? dot_split_kernel<true, 0> : dot_split_kernel<false, 0>; break;
+        case 0:                                               // (from 400 non-zeros a column on its wavefronts' groups keep the chains short)
+            if (desc->nnz < 400 * desc->m) k = shac ? dot_split_kernel<true, 0> : dot_split_kernel<false, 0>;
+            else k = shac ? dot_split_kernel<true, 0, kTurns> : dot_split_kernel<false, 0, kTurns>;
+            break;
         case 4: k = shac ? dot_split_kernel<true, 4> : dot_split_kernel<false, 4>; break;
         case 8: k = shac ? dot_split_kernel<true, 8> : dot_split_kernel<false, 8>; break;
         case 16: k = shac ? dot_split_kernel<true, 16> : dot_split_kernel<false, 16>; break;
@@ -1609,7 +1613,8 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     if (items > 0x7ffffff0ull) return HAC_EINVAL;
     const uint32_t grid = (uint32_t)((items + 7) / 8 * 8);
     const bool with_epilogue = io->bias || io->relu || io->yt_out;
-    const int sums = bs.gw * bs.nb > 32 ? kHalves : bs.npass == 1 || widest_pass(desc->n, B) > 32 ? kTurns : kChain;
+    const bool wide = bs.gw * bs.nb > 32;
+    const int sums = wide && desc->nnz < 600 * desc->m ? kHalves : wide || bs.npass == 1 || widest_pass(desc->n, B) > 32 ? kTurns : kChain;
     batch_kern_t k = with_epilogue
         ? (shac ? pick_batch_kernel<true, true>(bs.nb, bs.npass > 1, sums) : pick_batch_kernel<false, true>(bs.nb, bs.npass > 1, sums))
         : (shac ? pick_batch_kernel<true, false>(bs.nb, bs.npass > 1, sums) : pick_batch_kernel<false, false>(bs.nb, bs.npass > 1, sums));

@@ -88,7 +88,7 @@ __device__ __forceinline__ void leave_copy(uint32_t before, const float* __restr
     }
 }
 
-template <bool SHAC, int NBD>
+template <bool SHAC, int NBD, int SUMS = kHalves>             // SUMS: see fma_entries (NBD = 0)
 __global__ void __launch_bounds__(1024)
 dot_split_kernel(DevBlob d, SplitParams p, const float* __restrict__ X, uint32_t xrow, uint64_t xcol, uint32_t B,
                  float* __restrict__ Y, uint64_t ldy, float* __restrict__ copy, Epilogue epi)
@@ -214,10 +214,10 @@ dot_split_kernel(DevBlob d, SplitParams p, const float* __restrict__ X, uint32_t
     if constexpr (NBD == 0) {
         const uint32_t gw = p.width >> 2, ng = kWave / gw;                 // lanes per row of X, rows side by side
         const uint32_t grp = lane / gw, lig = lane & (gw - 1);
-        double a[4] = { 0.0, 0.0, 0.0, 0.0 };
+        typename SumType<SUMS>::type a[4] = { 0, 0, 0, 0 };
         // (lanes whose four batch columns are all padding fetch nothing)
         if (4 * lig < nb)
-            fma_entries<4, 10, kHalves>(list, 0u, lo, hi, ng * shares, share * ng + grp, X + panel_offset(xrow, d.n, b0 + 4 * lig), xrow, a);
+            fma_entries<4, 10, SUMS>(list, 0u, lo, hi, ng * shares, share * ng + grp, X + panel_offset(xrow, d.n, b0 + 4 * lig), xrow, a);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             for (uint32_t off = 32; off >= gw; off >>= 1) a[i] += __shfl_xor(a[i], (int)off, kWave);

@@ -161,17 +161,17 @@ def test_a_call_that_reads_x_as_it_is_leaves_the_copy_too(hac, B, n, fmt):
 # passes of 64, 128 and 256 batch columns (four, two and one lane group), one wavefront per column and several
 @pytest.mark.parametrize("m,kernel", [(3300, "dot_batch_kernel"), (300, "dot_split_kernel")])
 @pytest.mark.parametrize("B", [64, 100, 250])
-def test_long_columns_lose_nothing_in_a_wide_pass(hac, B, m, kernel):
-    """Sums of five products in fp32, those in 64 bits: (5 + 1 for the result + 1 for each of two list windows) 2^-24 |X| . |W|."""
+def test_columns_lose_nothing_in_a_wide_pass(hac, B, m, kernel):
+    """350 non-zeros a column: sums of five products in fp32, those in 64 bits: (5 + 1 for the result) 2^-24 |X| . |W|."""
     rng = np.random.default_rng(B + m)
     n = 2500
     values = rng.uniform(0.5, 1.0, 16).astype(np.float32)
-    W = np.where(rng.random((n, m)) < 0.6, values[rng.integers(0, 16, (n, m))], np.float32(0)).astype(np.float32)
+    W = np.where(rng.random((n, m)) < 0.14, values[rng.integers(0, 16, (n, m))], np.float32(0)).astype(np.float32)
     X = rng.uniform(0.5, 1.0, (B, n)).astype(np.float32)     # all of one sign: partial sums grow, and with them what a chain rounds away
     print(f"[case] wide pass {kernel} B={B}", flush=True)
     Y, kernels = run(hac, "hac", W, X)
     assert kernels[-1].startswith(kernel)
-    assert bool((np.abs(Y.cpu().numpy().astype(np.float64) - odot.dense_dot(X, W)) <= 8 * 2.0 ** -24 * odot.abs_dot(X, W)).all())
+    assert bool((np.abs(Y.cpu().numpy().astype(np.float64) - odot.dense_dot(X, W)) <= 6 * 2.0 ** -24 * odot.abs_dot(X, W)).all())
 
 
 @pytest.mark.parametrize("fmt", sorted(ENCODERS))
