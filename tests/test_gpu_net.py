@@ -269,3 +269,26 @@ def test_chain_full_size_vgg19_block(hac, B):
     torch.cuda.synchronize()
     check_chain(Y, X, Ws, bs, relu, f"B {B}")
     assert torch.equal(Y, _one_call_at_a_time(hac, fmts, dls, bs, relu, X))
+
+
+# neighbouring layers whose passes over their input are 256, 128 (or 32 and 64), 32 columns wide: what one writes feature-major the
+# next reads, and nothing is re-laid out between them
+@pytest.mark.parametrize("B", [40, 72, 129, 200, 300])
+@pytest.mark.parametrize("fmt", [HAC, SHAC])
+def test_chain_of_layers_of_very_different_heights(hac, fmt, B):
+    shapes, bs, relu = ((900, 6000), (6000, 700), (700, 26000), (26000, 60)), [], (True, True, True, False)
+    rng = np.random.default_rng(7)
+    values = np.linspace(-0.2, 0.19, 32, dtype=np.float32)
+    Ws = [np.where(rng.random((n, m)) < 0.02, values[rng.integers(0, 32, (n, m))], np.float32(0)).astype(np.float32) for n, m in shapes]
+    bs = [np.random.default_rng(i).standard_normal(m).astype(np.float32) for i, (_, m) in enumerate(shapes)]
+    X = workloads.make_batch(B, shapes[0][0], 5)
+    enc = hac.hac_encode if fmt == HAC else hac.shac_encode
+    layers = [(enc(W).to_device(dev()), torch.from_numpy(b).to(dev()), r) for W, b, r in zip(Ws, bs, relu)]
+    print(f"[case] chain of heights {fmt} B={B}", flush=True)
+    Xd = torch.from_numpy(X).to(dev())
+    (hac.hac_dot if fmt == HAC else hac.shac_dot)(layers[0][0], Xd)     # (a plain call begins the list of kernels anew)
+    before = len(hac.hac_last_kernels())
+    Y = hac.hac_forward(layers, Xd)
+    kernels = hac.hac_last_kernels()[before:]
+    assert [k.split("_")[0] for k in kernels] == ["transpose"] + ["dot"] * 4
+    check_chain(Y, X, Ws, bs, relu, f"B {B}")

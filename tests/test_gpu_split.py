@@ -24,11 +24,13 @@ def matrix(n, m, density, seed, k=24):
     rng = np.random.default_rng(seed)
     values = np.sort(rng.standard_normal(k)).astype(np.float32)
     W = np.where(rng.random((n, m)) < density, values[rng.integers(0, k, (n, m))], np.float32(0)).astype(np.float32)
-    W[:, 0] = 0                                              # an empty column first, one in the middle, one at the end
-    W[:, m // 2] = 0
-    W[:, -1] = 0
+    if m > 4:
+        W[:, 0] = 0                                          # an empty column first, one in the middle, one at the end
+        W[:, m // 2] = 0
+        W[:, -1] = 0
     if m > 3:
         W[:, 1] = values[rng.integers(0, k, n)]              # a column without a zero: the longest
+    assert np.count_nonzero(W) > 0
     return W
 
 
@@ -69,6 +71,14 @@ def test_x_as_it_is(hac, fmt, n, m, density, B, nbd):
     check(Y, X, W)
     Ys, _ = run(hac, fmt, W, X, strided=True)
     assert torch.equal(Ys, Y)
+
+
+def test_a_matrix_of_zeros(hac):
+    for m, B in ((1, 2), (3, 200), (300, 8)):
+        print(f"[case] split, zeros {m} B={B}", flush=True)
+        X = np.random.default_rng(B).standard_normal((B, 500)).astype(np.float32)
+        Y, _ = run(hac, "hac", np.zeros((500, m), np.float32), X)
+        assert not bool(Y.any())
 
 
 # batches whose last panel or quad of batch columns is not full; two, four and sixteen wavefronts per column
