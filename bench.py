@@ -85,9 +85,9 @@ class Call:
         need = hac.hac_workspace_bytes(blob.desc, B, launch)
         self.ws = [torch.empty(max(need, 256), dtype=torch.uint8, device=dev) for _ in range(rot)]
         self.rot = rot
-        # the dot kernel can be timed alone (X already feature-major in the workspace) only where a
-        # call re-lays X out first: not at B = 1, with a short X kept in LDS, or on the dense route
-        self.relayout = B > 1 and need > 0 and hac.hac_dot_route(blob.desc, B) == 0
+        # the dot kernel can be timed alone (X already feature-major in the workspace) only where a call
+        # re-lays X out first: not at B = 1, with X read as it is or kept in LDS, or on the dense route
+        self.relayout = any("transpose" in k for k in self.kernels(hac, launch))
 
     def run(self, i, launch=None):
         j = i % self.rot
