@@ -228,8 +228,8 @@ typedef struct {
     uint32_t staging_words;   /* words of the per-wavefront LDS buffer for stream (and ri)
                                  words, 16..16384, a multiple of 4 [from the header]       */
     uint32_t pass_width;      /* batch columns one pass over the list covers: 32 / 64 / 128 /
-                                 256 [the widest that the batch fills and whose share of X
-                                 stays in an L2]                                           */
+                                 256 [the least work for this batch and column length
+                                 among those whose share of X stays in an L2]              */
     uint32_t free_running;    /* 1 = do not hold a block's wavefronts on the same pass
                                  (measurement aid) [0]                                     */
     uint32_t tile_width;      /* batch columns one block covers: 32 / 64 / 128 / 256, not

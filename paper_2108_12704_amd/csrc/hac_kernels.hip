@@ -1075,6 +1075,10 @@ uint32_t default_cpw(const hac_desc_t* desc)
 // The route so chosen costs 1.9 % over the better one (geometric mean over the 755; worst 2.5 times) and 1.7 % on 200 other
 // layers (worst 1.5 times); the fp32 kernel's constants with its plan cost 18 % (8.3 times), with the plan of the
 // kernel on bf16 parts 15 % (7.6 times).
+// Both sides were timed while the sparse route passed over the list 32 columns at a time with one wavefront per column of W.
+// Since passes are wider (pass_columns) and several wavefronts share a column (plan_split) it is quicker than this estimate at
+// heights of W below about 8000: 4096 x 1000, 10 %, 64 rows 13.2 us (estimated 25), 1000 x 4096, 10 %, 256 rows 26.2 (52; the dense
+// route's estimate of 44 wins there).  What the rule costs over the better route now has not been measured.
 // Batches of 32 rows and less are one panel of the sparse route and too few for MFMA tiles; layers with one non-zero in
 // 40 entries or fewer take the sparse route as they always did (of 24 measured ones the dense route was more than
 // 15 % quicker on three, 25088 x 16 at 256 rows 46 against 63 us).

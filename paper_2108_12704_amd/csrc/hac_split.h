@@ -16,8 +16,8 @@
 //             columns are long a wavefront's fetch touches few lines, and no copy of X is written first: a launch
 //             less, which for small products is a third of the call (blocks behind those of the product leave the copy
 //             all the same, for a later call with HAC_LAUNCH_REUSE_XT);
-//   sums    : over the lanes of a wavefront, then over a column's wavefronts through LDS, always in the same order, the last
-//             of them in 64 bits.
+//   sums    : over the lanes of a wavefront, then over a column's wavefronts through LDS, always in the same order; in 64 bits,
+//             but for the first of the lanes' where X is read as it is, and for the lanes' where columns are long (kTurns).
 // Measured (MI355X, kernels back to back), one wavefront per column -> this kernel: 500 x 300, 30 % non-zero, 8 rows 8.3 -> 5.5 us;
 // 4096 x 1000, 10 %, 64 rows 18.4 -> 13.2; 9973 x 1511, 7 %, 37 rows 26.6 -> 21.6; 21516 x 34, 34 %, 19 rows 161 -> 65;
 // 4718 x 12, 6 %, 41 rows 16.7 -> 7.4.  What is left of the small ones is a launch, two trips to memory and the chain of one
