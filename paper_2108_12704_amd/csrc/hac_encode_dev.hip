@@ -2,34 +2,39 @@
 // that already lives in device memory, byte for byte the blob hac_encode / shac_encode would build
 // on the host.
 //
-// The steps of the host encoder, split between device and host:
-//   1. device  the one pass over W: per 32 rows of a column a word with a bit per non-zero, the
-//              non-zeros themselves packed column by column (where they are few), and a histogram
-//              of the distinct fp32 values (a hash table keyed by bit pattern, privatised in LDS
-//              per block); the occupied slots of the table are gathered into a list;
-//   2. host    alphabet in value order, Huffman lengths, canonical code, decode tables, and a
-//              small hash table from a value's bit pattern to its codeword;
-//   3. device  non-zeros and stream bits of every (row segment, column) from the words and the
-//              packed values; with Rice-coded row gaps also the gap bits for every parameter
-//              k = 0..15; then, per column, running sums over its segments and their totals;
-//   4. host    chunk size, prefix sums over the columns (first stream bit, CSC position, first
-//              chunk of every column), section offsets, header;
-//   5. device  one thread per (row segment, column) writes the codewords (and row-index fields or
-//              gap codewords) of its non-zeros, and the chunk entries.
+// The steps of the host encoder:
+//   1. the one pass over W: per 32 rows of a column a word with a bit per non-zero, the
+//      non-zeros themselves packed column by column (where they are few), and a histogram
+//      of the distinct fp32 values (a hash table keyed by bit pattern, privatised in LDS
+//      per block, and a list of its occupied slots);
+//   2. alphabet in value order, Huffman lengths, canonical code, decode tables, and a
+//      small hash table from a value's bit pattern to its codeword: one block, up to kDevSymbols
+//      values; a larger alphabet comes to the host, which then does this step;
+//   3. non-zeros and stream bits of every (row segment, column) from the words and the
+//      packed values; with Rice-coded row gaps also the gap bits for every parameter
+//      k = 0..15; then, per column, running sums over its segments and their totals;
+//   4. chunk size and prefix sums over the columns (first stream bit, CSC position, first
+//      chunk of every column); the host learns the counts, places the sections and asks for the
+//      blob's memory;
+//   5. header, tables and column arrays are copied into the blob and the rest of it cleared; one
+//      thread per (row segment, column) writes the codewords (and row-index fields or
+//      gap codewords) of its non-zeros, and the chunk entries.
 // W is far larger than everything else, so it is read once.  A word costs 1/32 of what it stands for
 // and a packed list is as long as the non-zeros, so steps 3 and 5 move a few per cent of W's bytes
 // on a pruned layer; where more than an eighth of a 32 x 64 tile is non-zero its values are not
 // packed but fetched from W again, by then mostly whole cache lines.
 // 25088 x 4096, 2 % non-zero: the three passes over W that this replaces took 0.25 + 0.36 + 0.40 ms.
-// What crosses the bus is of the size of the alphabet and of the number of columns, never of the
-// matrix.  The call synchronises the stream twice before its final wait (steps 2 and 4 need the
-// device's results).
+// The host waits once before step 5, for a few counts that the device writes into pinned memory, and
+// once at the end; steps 1 to 4 are launched one after the other without it.  With steps 2 and 4 on the host, which
+// took the histogram and the columns' sums over the bus and sent tables and column arrays back (three waits, six copies),
+// a call on a small matrix took 142 us (700 x 90) where its kernels run for 50.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -74,15 +79,24 @@ __global__ void fill_zero_kernel(uint32_t* p, uint64_t count)
     for (; i < count; i += stride) p[i] = 0u;
 }
 
-__device__ void table_add(uint32_t* keys, uint32_t* cnts, uint32_t* flags, uint32_t key, uint32_t add)
+// The histogram of the whole matrix: keys and counts, and the slots in use in the order in which they were taken
+// (flags[1] counts them; those past kListCap are dropped: more than 65536 values are refused anyway).
+constexpr uint32_t kListCap = 65536 + 64;          // one more than the largest alphabet is enough to see "too many"
+struct Histogram { uint32_t* keys; uint32_t* cnts; uint32_t* used; uint32_t* flags; };
+
+__device__ void table_add(const Histogram& t, uint32_t key, uint32_t add)
 {
     uint32_t h = mix32(key) & (kHashSlots - 1);
     for (uint32_t probe = 0; probe < kHashSlots; ++probe) {
-        const uint32_t old = atomicCAS(&keys[h], 0u, key);
-        if (old == 0u || old == key) { atomicAdd(&cnts[h], add); return; }
+        const uint32_t old = atomicCAS(&t.keys[h], 0u, key);
+        if (old == 0u) {
+            const uint32_t i = atomicAdd(&t.flags[1], 1u);
+            if (i < kListCap) t.used[i] = h;
+        }
+        if (old == 0u || old == key) { atomicAdd(&t.cnts[h], add); return; }
         h = (h + 1) & (kHashSlots - 1);
     }
-    atomicOr(flags, kFlagTableFull);
+    atomicOr(t.flags, kFlagTableFull);
 }
 
 // Step 1.  A wavefront takes tiles of 32 rows x 64 columns, all 32 loads of a tile in flight at once;
@@ -94,8 +108,7 @@ __device__ void table_add(uint32_t* keys, uint32_t* cnts, uint32_t* flags, uint3
 // mask, off: [rows / 32][m]; values: [rows / 32][m][kQuota], a tile's columns' room taken as one list.
 __global__ void __launch_bounds__(64 * kScanWaves)
 enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ldw, uint32_t col_groups, uint32_t tiles,
-                uint32_t* __restrict__ mask, uint16_t* __restrict__ off, uint32_t* __restrict__ values,
-                uint32_t* keys, uint32_t* cnts, uint32_t* flags)
+                uint32_t* __restrict__ mask, uint16_t* __restrict__ off, uint32_t* __restrict__ values, Histogram table)
 {
     __shared__ uint32_t lk[kLocalSlots], lc[kLocalSlots], queue[kScanWaves][kScanQueue];
     for (uint32_t i = threadIdx.x; i < kLocalSlots; i += 64 * kScanWaves) { lk[i] = 0u; lc[i] = 0u; }
@@ -112,7 +125,7 @@ enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ld
             if (cur == 0u || cur == key) { atomicAdd(&lc[h], 1u); return; }
             h = (h + 1) & (kLocalSlots - 1);
         }
-        table_add(keys, cnts, flags, key, 1u);                       // the block's table is crowded
+        table_add(table, key, 1u);                       // the block's table is crowded
     };
     for (uint32_t tile = blockIdx.x * kScanWaves + wave; tile < tiles; tile += gridDim.x * kScanWaves) {
         const uint32_t w = tile / col_groups, j = (tile - w * col_groups) * kTileCols + lane, r0 = w * kTileRows;
@@ -161,10 +174,258 @@ enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ld
                 if (word >> u & 1u) count_value(__float_as_uint(v[u]));
         }
     }
-    if (non_finite) atomicOr(flags, kFlagNonFinite);
+    if (non_finite) atomicOr(table.flags, kFlagNonFinite);
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < kLocalSlots; i += 64 * kScanWaves)
-        if (lk[i]) table_add(keys, cnts, flags, lk[i], lc[i]);
+        if (lk[i]) table_add(table, lk[i], lc[i]);
+}
+
+// ---------------------------------------------------------------------------
+// step 2
+// ---------------------------------------------------------------------------
+constexpr uint32_t kDevSymbols = 512;              // non-zero values of an alphabet whose code is built on the device
+constexpr uint32_t kDevSlots = 2 * kDevSymbols;    // its code table: at most half full
+constexpr uint32_t kCodeThreads = kDevSymbols + 64;   // of the block that builds it: a thread a symbol; idle wavefronts cost the others time
+constexpr uint32_t kPairUp = 64;                   // symbols from which all merges of a turn are made at once
+
+enum : uint32_t { kCodeOk, kCodeNonFinite, kCodeRange, kCodeOnHost };
+struct EncCode {
+    uint32_t status, values, k_sym, lmax, lut_bits, has_zero, zcode, zlen, slots;
+    uint64_t nnz, bits;                            // of the codewords of all symbols
+};
+// What the host waits for: the code and step 4's sums.
+struct EncResult {
+    EncCode code;
+    uint32_t chunk, rice_k;
+    uint64_t max_col_nnz, max_col_bits, col_bits, col_nnz, chunks, gap_bits;
+};
+// tables of the blob, as step 2 leaves them in the workspace (words)
+struct DevTables { uint32_t codebook[kDevSymbols + 4], codelen[(kDevSymbols + 4) / 4], canon[100], symsort[kDevSymbols + 4], lut[4096]; };
+
+// of the sorted w[from .. to): how many are less than `than`
+__device__ __forceinline__ uint32_t count_below(const uint32_t* w, uint32_t from, uint32_t to, uint32_t than)
+{
+    uint32_t lo = from, hi = to;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (w[mid] < than) lo = mid + 1; else hi = mid;
+    }
+    return lo - from;
+}
+
+// One block.  Symbols are numbered by counting smaller ones.  Huffman's merging: leaves in order of (count, symbol) and merged
+// nodes in the order of their making are two queues whose heads are the smallest left, the leaf first where they are
+// equal, which is the order that the host's heap gives (weight, then node number).  Two ways:
+//   one thread walks the queues, 0.2 us a merge, each a chain of reads from LDS (one wavefront with the heads of the queues in scalar
+//   registers, a chain of 50 instructions and no wait: 0.23 us);
+//   from kPairUp symbols on the block pairs off, in order and at once, everything that weighs up to s, the two smallest
+//   together: no node made from now on weighs less, and one of the same weight comes behind all there are.  8 to 22 turns of about 1 us
+//   for 16 to 256 values by k-means or equal bins (s grows like Fibonacci's numbers at least).
+// The kernel takes 13 us for 32 values in equal bins and 22 for 200 by k-means (one thread: 49).
+__global__ void __launch_bounds__(kCodeThreads)
+enc_code_kernel(Histogram h, uint64_t entries, uint32_t shac, uint32_t lut_opt, uint32_t* __restrict__ table, DevTables* __restrict__ out, EncCode* __restrict__ code)
+{
+    constexpr uint32_t K = kDevSymbols + 1;
+    __shared__ unsigned long long sum;
+    __shared__ __align__(16) uint32_t freq[K + 3];
+    __shared__ uint32_t leaf[kCodeThreads], node[kCodeThreads], merged[2 * K], upto[2][2], last_is_node;
+    __shared__ __align__(16) uint32_t order[(kDevSymbols + 3) / 4 * 4];
+    __shared__ __align__(16) uint32_t lens[(K + 3) / 4];
+    __shared__ uint32_t key_of[K], leaf_sym[K], parent[2 * K], sort[K], codes[K], count[33], first_code[33], first_index[33];
+    __shared__ uint32_t wave_count[kCodeThreads / 64][33];
+    __shared__ uint32_t tkey[kDevSlots], tcode[kDevSlots], tlen[kDevSlots];
+    __shared__ uint32_t bad;
+    const uint32_t t = threadIdx.x;
+    const uint32_t flags = h.flags[0], nv = h.flags[1];
+    if (flags || nv > kDevSymbols || entries >= 0xffffffffull) {           // (weights of 32 bits here)
+        if (t == 0) {
+            code->status = flags & kFlagNonFinite ? kCodeNonFinite : (flags || nv > 65536) ? kCodeRange : kCodeOnHost;
+            code->values = nv;
+        }
+        return;
+    }
+    uint8_t* len = reinterpret_cast<uint8_t*>(lens);
+    uint32_t key = 0, cnt = 0;
+    if (t < nv) { const uint32_t s = h.used[t]; key = h.keys[s]; cnt = h.cnts[s]; }
+    if (t == 0) { sum = 0; bad = 0; }
+    if (t < 33) count[t] = 0;
+    node[t] = ~0u;
+    const uint32_t ordered = key ^ (key >> 31 ? 0xffffffffu : 0x80000000u);     // unsigned order = order of the floats
+    if (t < (kDevSymbols + 3) / 4 * 4) order[t] = t < nv ? ordered : 0xffffffffu;   // (that is a NaN's: larger than any value here)
+    __syncthreads();
+    auto add_up = [&](unsigned long long v) {                              // of the block's threads, to `sum`
+        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
+        if ((t & 63u) == 0 && v) atomicAdd(&sum, v);
+    };
+    add_up(cnt);
+    uint32_t rank = 0;
+    if (t < nv)
+        for (uint32_t i = 0; i < nv; i += 4) {
+            const uint4 o = *reinterpret_cast<const uint4*>(&order[i]);
+            rank += (o.x < ordered ? 1u : 0u) + (o.y < ordered ? 1u : 0u) + (o.z < ordered ? 1u : 0u) + (o.w < ordered ? 1u : 0u);
+        }
+    __syncthreads();
+    const uint64_t nnz = sum;
+    const uint32_t shift = !shac && entries > nnz ? 1u : 0u, k = nv + shift;
+    if (t >= k && t < K + 3) freq[t] = ~0u;
+    if (t < nv) { freq[rank + shift] = cnt; key_of[rank + shift] = key; }
+    if (t == 0 && shift) { freq[0] = (uint32_t)(entries - nnz); key_of[0] = 0u; }
+    __syncthreads();
+    if (t < k) {
+        const uint32_t f = freq[t];
+        uint32_t r = 0;
+        for (uint32_t i = 0; i < k; i += 4) {                             // (past k: ~0, which no count reaches)
+            const uint4 g = *reinterpret_cast<const uint4*>(&freq[i]);
+            r += (g.x < f + (i < t ? 1u : 0u) ? 1u : 0u) + (g.y < f + (i + 1 < t ? 1u : 0u) ? 1u : 0u) +
+                 (g.z < f + (i + 2 < t ? 1u : 0u) ? 1u : 0u) + (g.w < f + (i + 3 < t ? 1u : 0u) ? 1u : 0u);
+        }
+        leaf[r] = f; leaf_sym[r] = t;
+    }
+    if (t >= k) leaf[t] = ~0u;
+    if (t == 0) sum = 0;
+    __syncthreads();
+    if (k >= kPairUp) {
+        // thread t holds leaf t and node t, and the weights behind them
+        uint32_t li = 0, ni = 0, wl = ~0u, wl_next = ~0u, wn = ~0u, wn_next = ~0u;
+        if (t < k) { wl = leaf[t]; wl_next = leaf[t + 1]; }
+        if (t == 0) upto[0][0] = upto[0][1] = 0;
+        __syncthreads();
+        for (uint32_t made = 0, turn = 0; made + 1 < k; ++turn) {
+            const uint32_t l0 = leaf[li], l1 = leaf[li + 1], n0 = node[ni], n1 = node[ni + 1];
+            const uint32_t s = l0 <= n0 ? l0 + (l1 <= n0 ? l1 : n0) : n0 + (l0 <= n1 ? l0 : n1);
+            uint32_t (&n_upto)[2] = upto[turn & 1u];
+            const bool in_l = t >= li && t < k && wl <= s, in_n = t >= ni && t < made && wn <= s;
+            if (in_l && (t + 1 == k || wl_next > s)) n_upto[0] = t + 1 - li;
+            if (in_n && (t + 1 == made || wn_next > s)) n_upto[1] = t + 1 - ni;
+            if (t == 0) upto[~turn & 1u][0] = upto[~turn & 1u][1] = 0;
+            __syncthreads();
+            const uint32_t nl = n_upto[0], nn = n_upto[1], pairs = (nl + nn) / 2, odd = (nl + nn) & 1u;
+            if (in_l) {
+                const uint32_t at = t - li + count_below(node, ni, ni + nn, wl);
+                merged[at] = wl;
+                if (at < 2 * pairs) parent[t] = made + at / 2; else last_is_node = 0;
+            }
+            if (in_n) {
+                const uint32_t at = t - ni + count_below(leaf, li, li + nl, wn + 1);
+                merged[at] = wn;
+                if (at < 2 * pairs) parent[K + t] = made + at / 2; else last_is_node = 1;
+            }
+            __syncthreads();
+            const uint32_t stays = odd ? 1u + last_is_node : 0u;           // the last one, if it has no partner
+            if (t + 1 >= made && t < made + pairs) {
+                const uint32_t q = t + 1 - made;                           // pair of the node behind this thread's
+                if (q) { wn = merged[2 * q - 2] + merged[2 * q - 1]; node[t] = wn; }
+                wn_next = q < pairs ? merged[2 * q] + merged[2 * q + 1] : ~0u;
+            }
+            li += nl - (stays == 1 ? 1u : 0u);
+            ni += nn - (stays == 2 ? 1u : 0u);
+            made += pairs;
+            __syncthreads();
+        }
+    } else if (t == 0) {
+        uint32_t li = 0, ni = 0;
+        for (uint32_t made = 0; made + 1 < k; ++made) {
+            const uint32_t l0 = leaf[li], l1 = leaf[li + 1], n0 = node[ni], n1 = node[ni + 1];   // (~0 past the end)
+            const bool a = l0 <= n0;                                       // the first is a leaf
+            const uint32_t lx = a ? l1 : l0, nx = a ? n0 : n1;
+            const bool b = lx <= nx;
+            node[made] = (a ? l0 : n0) + (b ? lx : nx);
+            parent[a ? li : K + ni] = made;
+            li += a ? 1u : 0u; ni += a ? 0u : 1u;
+            parent[b ? li : K + ni] = made;
+            li += b ? 1u : 0u; ni += b ? 0u : 1u;
+        }
+    }
+    __syncthreads();
+    unsigned long long my_bits = 0;
+    if (t < k) {
+        uint32_t l = 1;
+        if (k > 1)
+            for (uint32_t p = parent[t]; p + 2 != k && l <= 32; p = parent[K + p]) ++l;
+        if (l > 32) { bad = 1; l = 32; }
+        len[leaf_sym[t]] = (uint8_t)l;
+        atomicAdd(&count[l], 1u);
+        my_bits = (unsigned long long)leaf[t] * l;
+    }
+    add_up(my_bits);
+    __syncthreads();
+    uint32_t lmax = 32;
+    while (lmax && !count[lmax]) --lmax;
+    if (t == 0) {
+        uint64_t c = 0;
+        uint32_t idx = 0;
+        first_code[0] = first_index[0] = 0;
+        for (uint32_t l = 1; l <= 32; ++l) {
+            c <<= 1;
+            first_code[l] = (uint32_t)c; first_index[l] = idx;
+            c += count[l]; idx += count[l];
+        }
+    }
+    uint32_t slots = 64;
+    while (slots < 4 * nv && slots < kDevSlots) slots <<= 1;
+    for (uint32_t i = t; i < slots; i += kCodeThreads) tkey[i] = 0;
+    __syncthreads();
+    // a symbol's place among those of its length: lanes below in the wavefront, then the wavefronts before
+    const uint32_t my_len = t < k ? len[t] : 0u;
+    uint32_t below = 0;
+    for (uint32_t l = 1; l <= lmax; ++l) {
+        const uint64_t same = __ballot(my_len == l);
+        if (my_len == l) below = (uint32_t)__popcll(same & ((1ull << (t & 63u)) - 1u));
+        if ((t & 63u) == 0) wave_count[t >> 6][l] = (uint32_t)__popcll(same);
+    }
+    __syncthreads();
+    if (t < k) {
+        const uint32_t l = my_len;
+        uint32_t r = below;
+        for (uint32_t w = 0; w < t >> 6; ++w) r += wave_count[w][l];
+        codes[t] = first_code[l] + r;
+        sort[first_index[l] + r] = t;
+        if (t >= shift) {
+            const uint32_t key2 = key_of[t];
+            uint32_t s = mix32(key2) & (slots - 1);
+            while (atomicCAS(&tkey[s], 0u, key2) != 0u) s = (s + 1) & (slots - 1);   // (half of the slots stay empty)
+            tcode[s] = codes[t]; tlen[s] = l;
+        }
+    }
+    __syncthreads();
+    for (uint32_t i = t; i < slots; i += kCodeThreads) {
+        const bool any = tkey[i] != 0u;
+        table[i] = tkey[i]; table[slots + i] = any ? tcode[i] : 0u; table[2 * slots + i] = any ? tlen[i] : 0u;
+    }
+    const uint32_t T = lut_opt ? lut_opt : lmax < 1 ? 1u : lmax < 10 ? lmax : 10u;
+    for (uint32_t e = t; e < (1u << T); e += kCodeThreads) {
+        uint32_t v = 0;
+        for (uint32_t l = 1; l <= T && l <= lmax; ++l) {
+            const uint32_t r = (e >> (T - l)) - first_code[l];
+            if (r < count[l]) { v = sort[first_index[l] + r] << 6 | l; break; }
+        }
+        out->lut[e] = v;
+    }
+    if (t < k) { out->codebook[t] = key_of[t]; out->symsort[t] = sort[t]; }
+    if (t < (kDevSymbols + 4) / 4) {
+        uint32_t w = 0;
+        for (uint32_t i = 0; i < 4; ++i) if (4 * t + i < k) w |= (uint32_t)len[4 * t + i] << (8 * i);
+        out->codelen[t] = w;
+    }
+    if (t < 33) { out->canon[t] = first_code[t]; out->canon[33 + t] = count[t]; out->canon[66 + t] = first_index[t]; }
+    if (t == 0) {
+        EncCode c = {};
+        c.status = bad || nnz > 0xfffffff0ull || sum > 0xfffffff0ull ? kCodeRange : kCodeOk;
+        c.values = nv; c.k_sym = k; c.lmax = lmax; c.lut_bits = T;
+        c.has_zero = shift; c.zcode = shift ? codes[0] : 0u; c.zlen = shift ? len[0] : 0u; c.slots = slots;
+        c.nnz = nnz; c.bits = sum;
+        *code = c;
+    }
+}
+
+// an alphabet for the host: the occupied slots as a list of (key, count)
+__global__ void __launch_bounds__(256)
+enc_pairs_kernel(Histogram h, uint32_t nv, uint32_t* __restrict__ list)
+{
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= nv) return;
+    const uint32_t s = h.used[i];
+    list[2 * (uint64_t)i] = h.keys[s]; list[2 * (uint64_t)i + 1] = h.cnts[s];
 }
 
 // What step 1 leaves behind, and the code: three arrays of `slots` words (a power of two, at most half
@@ -182,6 +443,16 @@ __device__ __forceinline__ const uint32_t* code_table(const Survivors& s, uint32
 {
     if (!LDS_TABLE) return s.table;
     for (uint32_t i = threadIdx.x; i < 3 * s.slots; i += 256) lds[i] = s.table[i];
+    __syncthreads();
+    return lds;
+}
+
+// the same without the codewords: bit patterns, then lengths
+template <bool LDS_TABLE>
+__device__ __forceinline__ const uint32_t* length_table(const Survivors& s, uint32_t* lds)
+{
+    if (!LDS_TABLE) return s.table;
+    for (uint32_t i = threadIdx.x; i < 2 * s.slots; i += 256) lds[i] = s.table[i < s.slots ? i : i + s.slots];
     __syncthreads();
     return lds;
 }
@@ -233,21 +504,31 @@ __device__ __forceinline__ uint32_t load_segment(const Survivors& s, SegWords& s
     return total;
 }
 
-// f(row, bit pattern) for the segment's `total` non-zeros, in order
+// f(row, bit pattern) for the segment's `total` non-zeros, in order.  The patterns of four are requested together: one trip to
+// memory per non-zero was half of what the passes of steps 3 and 5 took.
 template <class F>
 __device__ __forceinline__ void for_survivors(const Survivors& s, const SegWords& sw, uint32_t j, uint32_t r0, uint32_t total, F f)
 {
     const uint32_t t = threadIdx.x;
     uint32_t w = 0, word = sw.mask[0][t], at = sw.off[0][t];
     const uint32_t* list = s.values + ((uint64_t)(r0 / 32) * s.m + (j - j % kTileCols)) * kQuota;   // of the segment's first tile
-    for (uint32_t i = 0; i < total; ++i) {
-        while (word == 0) { ++w; word = sw.mask[w][t]; at = sw.off[w][t]; }
-        const uint32_t r = r0 + 32 * w + (uint32_t)__builtin_ctz(word);
-        word &= word - 1;
-        uint32_t key;
-        if (at != kNotPacked) key = list[(uint64_t)w * s.m * kQuota + at++];
-        else key = __float_as_uint(s.W[(uint64_t)r * s.ldw + j]);
-        f(r, key);
+    for (uint32_t i = 0; i < total; i += 4) {
+        uint32_t r[4], key[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u) {
+            if (i + u < total) {
+                while (word == 0) { ++w; word = sw.mask[w][t]; at = sw.off[w][t]; }
+                r[u] = r0 + 32 * w + (uint32_t)__builtin_ctz(word);
+                word &= word - 1;
+                const uint32_t* from = at != kNotPacked ? list + (uint64_t)w * s.m * kQuota + at
+                                                        : reinterpret_cast<const uint32_t*>(s.W) + (uint64_t)r[u] * s.ldw + j;
+                at += at != kNotPacked ? 1u : 0u;
+                key[u] = *from;
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 4; ++u)
+            if (i + u < total) f(r[u], key[u]);
     }
 }
 
@@ -262,26 +543,30 @@ __device__ __forceinline__ uint32_t rice_len(uint32_t d, uint32_t k)
 // over the matrix (added up in the block first: the sums are 16 addresses for the whole chip).
 template <bool LDS_TABLE>
 __global__ void __launch_bounds__(256)
-enc_bits_kernel(Survivors s, uint32_t zlen, uint32_t* __restrict__ seg_nnz, uint32_t* __restrict__ seg_bits,
+enc_bits_kernel(Survivors s, const EncCode* __restrict__ code, uint32_t* __restrict__ seg_nnz, uint32_t* __restrict__ seg_bits,
                 uint32_t* __restrict__ gap_bits, unsigned long long* gap_total, uint64_t seg_cols)
 {
     extern __shared__ uint32_t table_lds[];
     __shared__ SegWords sw;
     __shared__ unsigned long long sums[kRiceKMax + 1];
-    if (threadIdx.x <= kRiceKMax) sums[threadIdx.x] = 0;
-    const uint32_t* table = code_table<LDS_TABLE>(s, table_lds);
     const uint32_t seg = blockIdx.x / s.col_blocks, j = (blockIdx.x - seg * s.col_blocks) * 256 + threadIdx.x;
     const uint32_t r0 = seg * s.seg_rows, r1 = r0 + s.seg_rows < s.n ? r0 + s.seg_rows : s.n;
     const uint64_t at = (uint64_t)seg * s.m + j;
+    const uint32_t total = j < s.m ? load_segment(s, sw, j, r0, r1) : 0u;      // (needs nothing of the code: on its way first)
+    if (code->status != kCodeOk) return;
+    const uint32_t zlen = code->zlen;
+    s.slots = code->slots;
+    if (threadIdx.x <= kRiceKMax) sums[threadIdx.x] = 0;
+    const uint32_t* table = length_table<LDS_TABLE>(s, table_lds);
+    const uint32_t* lengths = table + (LDS_TABLE ? 1u : 2u) * s.slots;
     uint32_t g[kRiceKMax + 1];
 #pragma unroll
     for (uint32_t k = 0; k <= kRiceKMax; ++k) g[k] = 0;
     if (j < s.m) {
         uint32_t bits = 0;
-        const uint32_t total = load_segment(s, sw, j, r0, r1);
         uint32_t next = gap_bits && total ? row_after_previous(s, j, r0) : 0u;   // the row the next gap counts from
         for_survivors(s, sw, j, r0, total, [&](uint32_t r, uint32_t key) {
-            bits += table[2 * s.slots + slot_of(table, s.slots, key)];
+            bits += lengths[slot_of(table, s.slots, key)];
             if (gap_bits) {
                 const uint32_t d = r - next;
 #pragma unroll
@@ -405,37 +690,29 @@ __global__ void __launch_bounds__(256) enc_emit_kernel(Survivors s, EmitArgs a)
     if (a.ri) rows.flush(true);
 }
 
-// step 1, second part: the occupied slots of the table as a list of (key, count), in no
-// particular order (the host sorts by value); *n_list counts them, entries past `cap` are dropped
-// (the host then sees n_list > cap and gives up: more than 65536 distinct values)
-__global__ void __launch_bounds__(256)
-enc_gather_kernel(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ cnts, uint32_t* list, uint32_t cap, uint32_t* n_list)
+// the parameter with the fewest gap bits, the smaller on ties (as on the host)
+__device__ __forceinline__ uint32_t best_rice_k(const unsigned long long* __restrict__ gap_total)
 {
-    const uint32_t h = blockIdx.x * 256 + threadIdx.x;
-    if (h >= kHashSlots) return;
-    const uint32_t key = keys[h];
-    if (!key) return;
-    const uint32_t i = atomicAdd(n_list, 1u);
-    if (i < cap) { list[2 * (uint64_t)i] = key; list[2 * (uint64_t)i + 1] = cnts[h]; }
+    uint32_t best = 0;
+#pragma unroll
+    for (uint32_t k = 1; k <= kRiceKMax; ++k) if (gap_total[k] < gap_total[best]) best = k;
+    return best;
 }
 
 // Step 3, second part: running sums over the segments of every column (in place: what stands above a
 // segment in its column) and the column's totals.  16 columns x 16 ranges of segments per block: a tall
 // and narrow matrix has hundreds of segments per column and few columns.
-// gap_bits: all 16 parameters; the one with the fewest bits counts, the smaller on ties (as on the host).
+// gap_bits: all 16 parameters; the best one counts.
 __global__ void __launch_bounds__(256)
-enc_col_scan_kernel(uint32_t m, uint32_t S, uint32_t* __restrict__ seg_nnz, uint32_t* __restrict__ seg_bits,
+enc_col_scan_kernel(const EncCode* __restrict__ code, uint32_t m, uint32_t S, uint32_t* __restrict__ seg_nnz, uint32_t* __restrict__ seg_bits,
                     const uint32_t* __restrict__ gap_bits, const unsigned long long* __restrict__ gap_total, uint64_t seg_cols,
                     uint32_t* __restrict__ col_nnz, unsigned long long* __restrict__ col_bits)
 {
     __shared__ uint32_t part_nnz[16][17];
     __shared__ unsigned long long part_bits[16][17];
     const uint32_t c = threadIdx.x & 15, g = threadIdx.x >> 4, j = blockIdx.x * 16 + c;
-    if (gap_bits) {
-        uint32_t best = 0;
-        for (uint32_t k = 1; k <= kRiceKMax; ++k) if (gap_total[k] < gap_total[best]) best = k;
-        gap_bits += best * seg_cols;
-    }
+    if (code->status != kCodeOk) return;
+    if (gap_bits) gap_bits += best_rice_k(gap_total) * seg_cols;
     const uint32_t per = (S + 15) / 16, s0 = g * per < S ? g * per : S, s1 = s0 + per < S ? s0 + per : S;
     uint32_t nnz = 0;
     unsigned long long bits = 0;
@@ -462,10 +739,108 @@ enc_col_scan_kernel(uint32_t m, uint32_t S, uint32_t* __restrict__ seg_nnz, uint
     }
 }
 
-constexpr uint32_t kListCap = 65536 + 64;          // one more than the largest alphabet is enough to see "too many"
+// Step 4.  One block: the longest column gives the chunk size, then running sums over the columns, a range of
+// columns per thread.  col_arrays: first chunk, CSC position and first stream bit of every column and one
+// past it, `stride` words apart.  The counts go to *result and, where the host waits for them in pinned memory, to *mailbox.
+__global__ void __launch_bounds__(1024)
+enc_columns_kernel(const EncCode* __restrict__ code, uint32_t m, const uint32_t* __restrict__ col_nnz, const unsigned long long* __restrict__ col_bits,
+                   uint32_t chunk_opt, const unsigned long long* __restrict__ gap_total, uint32_t* __restrict__ col_arrays, uint64_t stride,
+                   EncResult* __restrict__ result, EncResult* mailbox)
+{
+    __shared__ unsigned long long wave_bits[16];
+    __shared__ uint32_t wave_nnz[16], wave_chunks[16];
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    EncResult r = {};
+    r.code = *code;
+    if (r.code.status == kCodeOk) {
+        const uint32_t per = (m + 1023) / 1024, j0 = (uint64_t)t * per < m ? t * per : m, j1 = m - j0 < per ? m : j0 + per;
+        uint32_t most = 0, nnz = 0, chunks = 0;
+        unsigned long long longest = 0, bits = 0;
+        for (uint32_t j = j0; j < j1; j += 4) {                              // (four columns requested together)
+            uint32_t c[4];
+            unsigned long long b[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) { const uint32_t q = j + u < j1 ? j + u : j1 - 1; c[u] = col_nnz[q]; b[u] = col_bits[q]; }
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) {
+                if (j + u >= j1) { c[u] = 0; b[u] = 0; }
+                most = c[u] > most ? c[u] : most; longest = b[u] > longest ? b[u] : longest;
+                nnz += c[u]; bits += b[u];
+            }
+        }
+        for (int d = 32; d >= 1; d >>= 1) {
+            const uint32_t o = __shfl_xor(most, d, 64);
+            const unsigned long long p = __shfl_xor(longest, d, 64);
+            most = o > most ? o : most; longest = p > longest ? p : longest;
+        }
+        if (lane == 0) { wave_nnz[wave] = most; wave_bits[wave] = longest; }
+        __syncthreads();
+        for (uint32_t w = 0; w < 16; ++w) {
+            most = wave_nnz[w] > most ? wave_nnz[w] : most; longest = wave_bits[w] > longest ? wave_bits[w] : longest;
+        }
+        __syncthreads();
+        r.max_col_nnz = most; r.max_col_bits = longest;
+        r.chunk = hac_internal::chunk_for(chunk_opt, most);
+#pragma unroll 4
+        for (uint32_t j = j0; j < j1; ++j) {
+            const uint32_t c = col_nnz[j], cj = hac_internal::chunk_of_column(r.chunk, c);
+            chunks += (c + cj - 1) / cj;
+        }
+        // this thread's place among all: sums of the threads before it in its wavefront, and of the wavefronts before
+        uint32_t in = nnz, ic = chunks;
+        unsigned long long ib = bits;
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t a = __shfl_up(in, d, 64), b = __shfl_up(ic, d, 64);
+            const unsigned long long c = __shfl_up(ib, d, 64);
+            if ((int)lane >= d) { in += a; ic += b; ib += c; }
+        }
+        if (lane == 63) { wave_nnz[wave] = in; wave_chunks[wave] = ic; wave_bits[wave] = ib; }
+        __syncthreads();
+        uint64_t pos = in - nnz, chunk = ic - chunks, bit = ib - bits;
+        for (uint32_t w = 0; w < 16; ++w) {
+            if (w < wave) { pos += wave_nnz[w]; chunk += wave_chunks[w]; bit += wave_bits[w]; }
+            r.col_nnz += wave_nnz[w]; r.chunks += wave_chunks[w]; r.col_bits += wave_bits[w];
+        }
+        for (uint32_t j = j0; j < j1; ++j) {
+            col_arrays[j] = (uint32_t)chunk; col_arrays[stride + j] = (uint32_t)pos; col_arrays[2 * stride + j] = (uint32_t)bit;
+            const uint32_t c = col_nnz[j], cj = hac_internal::chunk_of_column(r.chunk, c);
+            pos += c; chunk += (c + cj - 1) / cj; bit += col_bits[j];
+        }
+        if (t == 0) {
+            col_arrays[m] = (uint32_t)r.chunks; col_arrays[stride + m] = (uint32_t)r.col_nnz; col_arrays[2 * stride + m] = (uint32_t)r.col_bits;
+        }
+        if (gap_total) { r.rice_k = best_rice_k(gap_total); r.gap_bits = gap_total[r.rice_k]; }
+    }
+    if (t == 0) { *result = r; if (mailbox) *mailbox = r; }
+}
+
+// Step 5, first part: the blob as the codewords find it.  `tables`: step 2's (nullptr: the host copies header and tables itself).
+__global__ void __launch_bounds__(256)
+enc_head_kernel(hac_desc_t d, const DevTables* __restrict__ tables, const uint32_t* __restrict__ col_arrays, uint32_t* __restrict__ blob)
+{
+    const uint64_t i0 = blockIdx.x * 256 + threadIdx.x, step = (uint64_t)gridDim.x * 256;
+    const uint64_t cols = d.off_col_chunk / 4, ents = d.off_chunk_ent / 4, stride = (d.off_col_pos - d.off_col_chunk) / 4;
+    if (tables) {
+        auto section = [&](uint64_t off, uint64_t end, const uint32_t* from, uint32_t words) {   // the words of one, zeros behind them
+            for (uint64_t i = i0; i < (end - off) / 4; i += step) blob[off / 4 + i] = i < words ? from[i] : 0u;
+        };
+        section(0, d.off_codebook, reinterpret_cast<const uint32_t*>(&d), (uint32_t)sizeof(hac_desc_t) / 4);
+        section(d.off_codebook, d.off_codelen, tables->codebook, d.k_sym);
+        section(d.off_codelen, d.off_canon, tables->codelen, (d.k_sym + 3) / 4);
+        section(d.off_canon, d.off_symsort, tables->canon, 99);
+        section(d.off_symsort, d.off_lut, tables->symsort, d.k_sym);
+        section(d.off_lut, d.off_stream, tables->lut, 1u << d.lut_bits);
+    }
+    for (uint64_t i = i0; i < ents - cols; i += step) blob[cols + i] = i % stride <= d.m ? col_arrays[i] : 0u;   // (three of them, laid out alike)
+    const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+    uint4* b4 = reinterpret_cast<uint4*>(blob);
+    for (uint64_t i = d.off_stream / 16 + i0; i < cols / 4; i += step) b4[i] = zero;
+    for (uint64_t i = ents / 4 + i0; i < d.blob_bytes / 16; i += step) b4[i] = zero;
+}
 
 struct WsLayout {
-    size_t keys, cnts, flags, list, mask, off, values, seg_nnz, seg_bits, gap_bits, table, col_bits, col_nnz, total;
+    size_t keys, cnts, flags, used, list, mask, off, values, seg_nnz, seg_bits, gap_bits, table, col_bits, col_nnz, code, result, tables, col_arrays, total;
+    size_t col_stride;                                               // words from one of the column arrays to the next, as in a blob
 };
 
 WsLayout ws_layout(uint64_t n, uint64_t m)
@@ -476,17 +851,56 @@ WsLayout ws_layout(uint64_t n, uint64_t m)
     size_t c = 0;
     auto take = [&](size_t bytes) { const size_t o = c; c = (c + bytes + 255) / 256 * 256; return o; };
     L.keys = take(4ull * kHashSlots); L.cnts = take(4ull * kHashSlots); L.flags = take(256);
-    L.list = take(8ull * kListCap);                                 // behind the flags: one copy to the host
+    L.used = take(4ull * kListCap);
+    L.list = take(8ull * kListCap);
     L.mask = take(4 * words * m); L.off = take(2 * words * m); L.values = take(4ull * kQuota * words * m);
     L.seg_nnz = take(4 * S * m); L.seg_bits = take(4 * S * m);
     L.gap_bits = take(4 * S * m * (kRiceKMax + 1));                  // used with Rice-coded gaps only
     L.table = take(12ull * kHashSlots);
-    L.col_bits = take(8 * m); L.col_nnz = take(4 * m);               // side by side: one copy to the host
+    L.col_bits = take(8 * m); L.col_nnz = take(4 * m);
+    L.code = take(sizeof(EncCode)); L.result = take(sizeof(EncResult)); L.tables = take(sizeof(DevTables));
+    L.col_stride = (4 * ((size_t)m + 1) + 255) / 256 * 256 / 4;
+    L.col_arrays = take(12 * L.col_stride);
     L.total = c;
     return L;
 }
 
 int hip_fail(hipError_t e) { hac_internal::set_last_hip_error((int)e); return HAC_EHIP; }
+
+// Pinned memory that the device leaves a call's counts in: kBoxes of them for the process, allocated with the first call (one costs more
+// than the call) and lent to a call until it has read them.  get() is nullptr where none is free, or none can be had: the counts are then copied.
+constexpr int kBoxes = 16;
+class Mailbox {
+    struct Pool { std::mutex lock; EncResult* base = nullptr; bool asked = false; uint32_t taken = 0; };
+    static Pool& pool() { static Pool* p = new Pool; return *p; }   // (never taken down: a call may run while the process ends)
+    int i = -1;
+    EncResult* p = nullptr;
+public:
+    Mailbox()
+    {
+        Pool& q = pool();
+        std::lock_guard<std::mutex> hold(q.lock);
+        if (!q.asked) {
+            q.asked = true;
+            void* mem = nullptr;
+            if (hipHostMalloc(&mem, sizeof(EncResult) * kBoxes, hipHostMallocPortable) == hipSuccess) q.base = static_cast<EncResult*>(mem);
+            else (void)hipGetLastError();
+        }
+        if (!q.base) return;
+        for (int k = 0; k < kBoxes && i < 0; ++k) if (!(q.taken >> k & 1u)) i = k;
+        if (i >= 0) { q.taken |= 1u << i; p = q.base + i; }
+    }
+    ~Mailbox()
+    {
+        if (i < 0) return;
+        Pool& q = pool();
+        std::lock_guard<std::mutex> hold(q.lock);
+        q.taken &= ~(1u << i);
+    }
+    Mailbox(const Mailbox&) = delete;
+    Mailbox& operator=(const Mailbox&) = delete;
+    EncResult* get() const { return p; }
+};
 
 } // namespace
 
@@ -534,148 +948,123 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
     const uint64_t tiles = ((uint64_t)n + kTileRows - 1) / kTileRows * col_groups;
     if (tiles > 0x7fffffffull || (uint64_t)sv.col_blocks * S > 0x7fffffffull) return HAC_ERANGE;   // terabytes of W
     const dim3 seg_grid(sv.col_blocks * S);
+    const Histogram hist = { dptr(L.keys), dptr(L.cnts), dptr(L.used), dptr(L.flags) };   // (gap totals 64 bytes behind the flags, zeroed with them)
+    unsigned long long* d_gap_total = rice ? reinterpret_cast<unsigned long long*>(ws + L.flags + 64) : static_cast<unsigned long long*>(nullptr);
+    uint32_t* d_gap_bits = rice ? dptr(L.gap_bits) : static_cast<uint32_t*>(nullptr);
+    unsigned long long* d_col_bits = reinterpret_cast<unsigned long long*>(ws + L.col_bits);
+    EncCode* d_code = reinterpret_cast<EncCode*>(ws + L.code);
+    EncResult* d_result = reinterpret_cast<EncResult*>(ws + L.result);
+    DevTables* d_tables = reinterpret_cast<DevTables*>(ws + L.tables);
+    // (code tables up to kCodeSlotsLds are read from LDS)
+    auto table_bytes = [](uint32_t slots) { return slots <= kCodeSlotsLds ? 12 * (size_t)slots : (size_t)0; };
     hipError_t e;
+    // steps 3 and 4 with a code of at most `slots` slots, and the wait for their sums
+    auto sums = [&](uint32_t slots, EncResult& r) -> hipError_t {
+        Mailbox box;
+        const size_t lds = table_bytes(slots) / 3 * 2;
+        hipLaunchKernelGGL(lds ? enc_bits_kernel<true> : enc_bits_kernel<false>, seg_grid, dim3(256), lds, stream, sv, d_code,
+                           dptr(L.seg_nnz), dptr(L.seg_bits), d_gap_bits, d_gap_total, SM);
+        hipLaunchKernelGGL(enc_col_scan_kernel, dim3((uint32_t)(((uint64_t)m + 15) / 16)), dim3(256), 0, stream, d_code, (uint32_t)m, S,
+                           dptr(L.seg_nnz), dptr(L.seg_bits), static_cast<const uint32_t*>(d_gap_bits),
+                           static_cast<const unsigned long long*>(d_gap_total), SM, dptr(L.col_nnz), d_col_bits);
+        hipLaunchKernelGGL(enc_columns_kernel, dim3(1), dim3(1024), 0, stream, d_code, (uint32_t)m, dptr(L.col_nnz), d_col_bits,
+                           opts ? opts->chunk_nnz : 0u, static_cast<const unsigned long long*>(d_gap_total), dptr(L.col_arrays),
+                           (uint64_t)L.col_stride, d_result, box.get());
+        hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+        if (!box.get() && (err = hipMemcpyAsync(&r, d_result, sizeof r, hipMemcpyDeviceToHost, stream)) != hipSuccess) return err;
+        err = hipStreamSynchronize(stream);
+        if (err == hipSuccess && box.get()) r = *box.get();
+        return err;
+    };
     try {
-        // ---- step 1 ----
-        uint32_t* d_flags = dptr(L.flags);                           // [0] flags, [1] length of the list, +64 bytes: gap totals
-        hipLaunchKernelGGL(fill_zero_kernel, dim3(512), dim3(256), 0, stream, dptr(L.keys), (uint64_t)(L.list - L.keys) / 4);
+        // ---- steps 1 to 4 ----
+        hipLaunchKernelGGL(fill_zero_kernel, dim3(512), dim3(256), 0, stream, dptr(L.keys), (uint64_t)(L.used - L.keys) / 4);
         const uint64_t scan_blocks = std::min<uint64_t>((tiles + kScanWaves - 1) / kScanWaves, kScanBlocks);
         hipLaunchKernelGGL(enc_scan_kernel, dim3((uint32_t)scan_blocks), dim3(64 * kScanWaves), 0, stream, d_W, (uint32_t)n, (uint32_t)m,
                            (uint64_t)ldw, col_groups, (uint32_t)tiles, dptr(L.mask), reinterpret_cast<uint16_t*>(ws + L.off),
-                           dptr(L.values), dptr(L.keys), dptr(L.cnts), d_flags);
-        hipLaunchKernelGGL(enc_gather_kernel, dim3(kHashSlots / 256), dim3(256), 0, stream, dptr(L.keys), dptr(L.cnts),
-                           dptr(L.list), kListCap, d_flags + 1);
-        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
-        // flags, the length of the list and its first entries (they sit side by side), then the rest of
-        // the list; a small alphabet arrives with the first copy
-        constexpr uint32_t kFirst = 1024, kHead = 64;                // words
-        std::vector<uint32_t> head(kHead + 2 * (size_t)kFirst);
-        if ((e = hipMemcpyAsync(head.data(), d_flags, 4 * head.size(), hipMemcpyDeviceToHost, stream)) != hipSuccess) return hip_fail(e);
-        if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e);
-        const uint32_t flags = head[0], n_list = head[1];
-        if (flags & kFlagNonFinite) return HAC_EINVAL;
-        if (flags & kFlagTableFull) return HAC_ERANGE;
-        if (n_list > 65536) return HAC_ERANGE;
-        if (n_list > kFirst) {
-            head.resize(kHead + 2 * (size_t)n_list);
-            if ((e = hipMemcpyAsync(head.data(), d_flags, 4 * head.size(), hipMemcpyDeviceToHost, stream)) != hipSuccess) return hip_fail(e);
-            if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e);
-        }
-        const uint32_t* list = head.data() + kHead;
+                           dptr(L.values), hist);
+        hipLaunchKernelGGL(enc_code_kernel, dim3(1), dim3(kCodeThreads), 0, stream, hist, (uint64_t)n * (uint64_t)m, shac ? 1u : 0u,
+                           opts ? opts->lut_bits : 0u, dptr(L.table), d_tables, d_code);
+        EncResult r;
+        if ((e = sums(kDevSlots, r)) != hipSuccess) return hip_fail(e);
+        if (r.code.status == kCodeNonFinite) return HAC_EINVAL;
+        if (r.code.status == kCodeRange) return HAC_ERANGE;
 
-        // ---- step 2 ----
-        struct Val { float v; uint32_t key; uint64_t f; };
-        std::vector<Val> vals(n_list);
-        uint64_t nnz = 0;
-        for (uint32_t i = 0; i < n_list; ++i) {
-            vals[i].key = list[2 * (size_t)i]; vals[i].f = list[2 * (size_t)i + 1];
-            std::memcpy(&vals[i].v, &vals[i].key, 4);
-            nnz += vals[i].f;
-        }
-        if (nnz > 0xfffffff0ull) return HAC_ERANGE;
-        std::sort(vals.begin(), vals.end(), [](const Val& a, const Val& b) { return a.v < b.v; });
-        const uint64_t zeros = (uint64_t)n * (uint64_t)m - nnz;
-        const bool has_zero = !shac && zeros > 0;
-        const uint32_t shift = has_zero ? 1u : 0u;
+        // ---- step 2 for a large alphabet ----
+        const bool on_host = r.code.status == kCodeOnHost;
         std::vector<float> codebook;
-        std::vector<uint64_t> freq;
-        if (has_zero) { codebook.push_back(0.0f); freq.push_back(zeros); }
-        for (const Val& x : vals) { codebook.push_back(x.v); freq.push_back(x.f); }
-        std::vector<uint8_t> len; uint32_t lmax = 0;
-        if (!huffman_lengths(freq, len, lmax)) return HAC_ERANGE;
-        CodeTables t; canonical_codes(len, t);
-        uint64_t total_bits = 0;
-        for (size_t i = 0; i < freq.size(); ++i) total_bits += freq[i] * len[i];
+        std::vector<uint8_t> len;
+        std::vector<uint32_t> lut, table;
+        CodeTables t;
+        EncCode c = {};
+        if (on_host) {
+            const uint32_t nv = r.code.values;
+            std::vector<uint32_t> list(2 * (size_t)nv);
+            hipLaunchKernelGGL(enc_pairs_kernel, dim3((nv + 255) / 256), dim3(256), 0, stream, hist, nv, dptr(L.list));
+            if ((e = hipMemcpyAsync(list.data(), dptr(L.list), 4 * list.size(), hipMemcpyDeviceToHost, stream)) != hipSuccess) return hip_fail(e);
+            if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e);
+            struct Val { float v; uint32_t key; uint64_t f; };
+            std::vector<Val> vals(nv);
+            for (uint32_t i = 0; i < nv; ++i) {
+                vals[i].key = list[2 * (size_t)i]; vals[i].f = list[2 * (size_t)i + 1];
+                std::memcpy(&vals[i].v, &vals[i].key, 4);
+                c.nnz += vals[i].f;
+            }
+            if (c.nnz > 0xfffffff0ull) return HAC_ERANGE;
+            std::sort(vals.begin(), vals.end(), [](const Val& a, const Val& b) { return a.v < b.v; });
+            const uint64_t zeros = (uint64_t)n * (uint64_t)m - c.nnz;
+            c.has_zero = !shac && zeros > 0 ? 1u : 0u;
+            std::vector<uint64_t> freq;
+            if (c.has_zero) { codebook.push_back(0.0f); freq.push_back(zeros); }
+            for (const Val& x : vals) { codebook.push_back(x.v); freq.push_back(x.f); }
+            if (!huffman_lengths(freq, len, c.lmax)) return HAC_ERANGE;
+            canonical_codes(len, t);
+            for (size_t i = 0; i < freq.size(); ++i) c.bits += freq[i] * len[i];
+            if (c.bits > 0xfffffff0ull) return HAC_ERANGE;
+            c.k_sym = (uint32_t)codebook.size(); c.lut_bits = pick_lut_bits(opts, c.lmax);
+            build_lut(len, t, c.lut_bits, lut);
+            c.zlen = c.has_zero ? len[0] : 0; c.zcode = c.has_zero ? t.code[0] : 0;
+            c.status = kCodeOk; c.values = nv;
+            // bit pattern -> codeword, at most a quarter full (half for the largest alphabets)
+            c.slots = 64;
+            while (c.slots < 4 * (uint64_t)nv && c.slots < kHashSlots) c.slots <<= 1;
+            table.assign(3 * (size_t)c.slots, 0);
+            for (size_t i = 0; i < vals.size(); ++i) {
+                uint32_t h = mix32(vals[i].key) & (c.slots - 1);
+                while (table[h]) h = (h + 1) & (c.slots - 1);
+                table[h] = vals[i].key; table[c.slots + h] = t.code[i + c.has_zero]; table[2 * (size_t)c.slots + h] = len[i + c.has_zero];
+            }
+            if ((e = hipMemcpyAsync(dptr(L.table), table.data(), 4 * table.size(), hipMemcpyHostToDevice, stream)) != hipSuccess) return hip_fail(e);
+            if ((e = hipMemcpyAsync(d_code, &c, sizeof c, hipMemcpyHostToDevice, stream)) != hipSuccess) return hip_fail(e);
+            if ((e = sums(c.slots, r)) != hipSuccess) return hip_fail(e);
+        }
+        c = r.code;
+        sv.slots = c.slots;
+        const uint64_t total_bits = c.bits + r.gap_bits, nnz = c.nnz;
         if (total_bits > 0xfffffff0ull) return HAC_ERANGE;
-        const uint32_t lut_bits = pick_lut_bits(opts, lmax);
-        if (lut_bits < 1 || lut_bits > 12) return HAC_EINVAL;
-        std::vector<uint32_t> lut; build_lut(len, t, lut_bits, lut);
-        const uint32_t zlen = has_zero ? len[0] : 0, zcode = has_zero ? t.code[0] : 0;
-
-        // bit pattern -> codeword, at most a quarter full (half for the largest alphabets)
-        uint32_t slots = 64;
-        while (slots < 4 * (uint64_t)n_list && slots < kHashSlots) slots <<= 1;
-        std::vector<uint32_t> table(3 * (size_t)slots, 0);
-        for (size_t i = 0; i < vals.size(); ++i) {
-            uint32_t h = mix32(vals[i].key) & (slots - 1);
-            while (table[h]) h = (h + 1) & (slots - 1);
-            table[h] = vals[i].key; table[slots + h] = t.code[i + shift]; table[2 * (size_t)slots + h] = len[i + shift];
-        }
-        if ((e = hipMemcpyAsync(dptr(L.table), table.data(), 4 * table.size(), hipMemcpyHostToDevice, stream)) != hipSuccess) return hip_fail(e);
-        sv.slots = slots;
-        const bool lds_table = slots <= kCodeSlotsLds;
-        const size_t table_lds = lds_table ? 12 * (size_t)slots : 0;
-
-        // ---- step 3 ----
-        unsigned long long* d_gap_total = reinterpret_cast<unsigned long long*>(ws + L.flags + 64);   // zeroed with the flags
-        uint32_t* d_gap_bits = rice ? dptr(L.gap_bits) : static_cast<uint32_t*>(nullptr);
-        hipLaunchKernelGGL(lds_table ? enc_bits_kernel<true> : enc_bits_kernel<false>, seg_grid, dim3(256), table_lds, stream, sv, zlen,
-                           dptr(L.seg_nnz), dptr(L.seg_bits), d_gap_bits, d_gap_total, SM);
-        unsigned long long* d_col_bits = reinterpret_cast<unsigned long long*>(ws + L.col_bits);
-        hipLaunchKernelGGL(enc_col_scan_kernel, dim3((uint32_t)(((uint64_t)m + 15) / 16)), dim3(256), 0, stream, (uint32_t)m, S,
-                           dptr(L.seg_nnz), dptr(L.seg_bits), static_cast<const uint32_t*>(d_gap_bits),
-                           static_cast<const unsigned long long*>(d_gap_total), SM, dptr(L.col_nnz), d_col_bits);
-        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
-        unsigned long long gap_total[kRiceKMax + 1] = { 0 };
-        if (rice && (e = hipMemcpyAsync(gap_total, d_gap_total, sizeof gap_total, hipMemcpyDeviceToHost, stream)) != hipSuccess) return hip_fail(e);
-        std::vector<uint8_t> col_sums(L.col_nnz - L.col_bits + 4 * (size_t)m);
-        if ((e = hipMemcpyAsync(col_sums.data(), d_col_bits, col_sums.size(), hipMemcpyDeviceToHost, stream)) != hipSuccess) return hip_fail(e);
-        if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e);
-        const unsigned long long* col_bits = reinterpret_cast<const unsigned long long*>(col_sums.data());
-        const uint32_t* col_nnz = reinterpret_cast<const uint32_t*>(col_sums.data() + (L.col_nnz - L.col_bits));
-        // the Rice parameter: fewest gap bits, the smaller k on ties
-        uint32_t rice_k = 0; uint64_t gap_bits = 0;
-        if (rice) {
-            for (uint32_t k = 1; k <= kRiceKMax; ++k) if (gap_total[k] < gap_total[rice_k]) rice_k = k;
-            gap_bits = gap_total[rice_k];
-            total_bits += gap_bits;
-            if (total_bits > 0xfffffff0ull) return HAC_ERANGE;
-        }
-
-        // ---- step 4 ----
-        uint64_t max_col_nnz = 0, max_col_bits = 0;
-        for (int64_t j = 0; j < m; ++j) {
-            max_col_nnz = std::max<uint64_t>(max_col_nnz, col_nnz[(size_t)j]);
-            max_col_bits = std::max<uint64_t>(max_col_bits, col_bits[(size_t)j]);
-        }
-        const uint32_t Cn = pick_chunk(opts, max_col_nnz);
-        // the three per-column arrays sit side by side in the blob (256-byte aligned sections): one
-        // host buffer with the same spacing, one copy
-        const size_t col_stride = (4 * ((size_t)m + 1) + 255) / 256 * 256 / 4;       // words from one array to the next
-        std::vector<uint32_t> col_arrays(3 * col_stride, 0);
-        uint32_t* col_chunk = col_arrays.data();
-        uint32_t* col_pos = col_chunk + col_stride;
-        uint32_t* col_bit = col_pos + col_stride;
-        uint64_t bit = 0, pos = 0, chunks = 0;
-        for (int64_t j = 0; j < m; ++j) {
-            col_bit[(size_t)j] = (uint32_t)bit; col_pos[(size_t)j] = (uint32_t)pos; col_chunk[(size_t)j] = (uint32_t)chunks;
-            bit += col_bits[(size_t)j]; pos += col_nnz[(size_t)j];
-            const uint32_t cj = chunk_of_column(Cn, col_nnz[(size_t)j]);
-            chunks += (col_nnz[(size_t)j] + cj - 1) / cj;
-        }
-        col_bit[(size_t)m] = (uint32_t)bit; col_pos[(size_t)m] = (uint32_t)pos; col_chunk[(size_t)m] = (uint32_t)chunks;
-        if (bit != total_bits || pos != nnz) return HAC_EFORMAT;
-        if (chunks > 0xfffffff0ull) return HAC_ERANGE;
+        if (r.col_bits != total_bits || r.col_nnz != nnz) return HAC_EFORMAT;
+        if (r.chunks > 0xfffffff0ull) return HAC_ERANGE;
 
         hac_desc_t d;
         std::memset(&d, 0, sizeof d);
         d.magic = kMagic; d.version = kVersion; d.format = format; d.header_bytes = 256;
         d.n = (uint64_t)n; d.m = (uint64_t)m; d.nnz = nnz; d.total_bits = total_bits; d.n_words = (total_bits + 31) / 32;
-        d.k_sym = (uint32_t)codebook.size(); d.lmax = lmax; d.lut_bits = lut_bits;
-        d.chunk = Cn; d.n_chunks = chunks; d.max_col_bits = max_col_bits; d.max_col_nnz = max_col_nnz;
+        d.k_sym = c.k_sym; d.lmax = c.lmax; d.lut_bits = c.lut_bits;
+        d.chunk = r.chunk; d.n_chunks = r.chunks; d.max_col_bits = r.max_col_bits; d.max_col_nnz = r.max_col_nnz;
         if (rice) {
-            const uint32_t brel_bits = std::max<uint32_t>(ceil_log2(max_col_bits + 1), 1);
+            const uint32_t brel_bits = std::max<uint32_t>(ceil_log2(r.max_col_bits + 1), 1);
             d.ent_bits = need_bits + brel_bits <= 32 ? 32 : 64;
             d.row_bits = d.ent_bits == 32 ? need_bits : 0;
-            d.ri_coding = HAC_RI_RICE; d.rice_k = rice_k; d.gap_bits = gap_bits;
+            d.ri_coding = HAC_RI_RICE; d.rice_k = r.rice_k; d.gap_bits = r.gap_bits;
         } else if (shac) {
             d.ri_bits = ri_bits;
-            d.ent_bits = max_col_bits < 65536 ? 16 : 32;
+            d.ent_bits = r.max_col_bits < 65536 ? 16 : 32;
             if (nnz * (uint64_t)ri_bits > 0xfffffff0ull * 32ull) return HAC_ERANGE;
         } else {
-            d.has_zero = has_zero ? 1 : 0;
-            d.zero_len = (has_zero && zcode == 0) ? zlen : 0;
-            const uint32_t brel_bits = std::max<uint32_t>(ceil_log2(max_col_bits + 1), 1);
+            d.has_zero = c.has_zero;
+            d.zero_len = (c.has_zero && c.zcode == 0) ? c.zlen : 0;
+            const uint32_t brel_bits = std::max<uint32_t>(ceil_log2(r.max_col_bits + 1), 1);
             d.ent_bits = need_bits + brel_bits <= 32 ? 32 : 64;
             d.row_bits = d.ent_bits == 32 ? need_bits : 0;
         }
@@ -684,20 +1073,19 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
         void* d_blob = place((size_t)d.blob_bytes);
         if (!d_blob) return HAC_EWORKSPACE;                                         // desc->blob_bytes says how much
         if (reinterpret_cast<uintptr_t>(d_blob) % 256) return HAC_EINVAL;
-
-        // head of the blob (header, tables, per-column arrays) is assembled here and copied over
-        const size_t head_bytes = (size_t)d.off_stream;
-        std::vector<uint8_t> blob_head(head_bytes, 0);
-        std::memcpy(blob_head.data(), &d, sizeof d);
-        write_tables(blob_head.data(), d, codebook, len, t, lut);
-        uint8_t* blob = static_cast<uint8_t*>(d_blob);
-        hipLaunchKernelGGL(fill_zero_kernel, dim3(1024), dim3(256), 0, stream, reinterpret_cast<uint32_t*>(blob + d.off_stream),
-                           (uint64_t)(d.blob_bytes - d.off_stream) / 4);
-        if ((e = hipMemcpyAsync(blob, blob_head.data(), head_bytes, hipMemcpyHostToDevice, stream)) != hipSuccess) return hip_fail(e);
-        if (d.off_col_pos - d.off_col_chunk != 4 * col_stride || d.off_col_bit - d.off_col_pos != 4 * col_stride) return HAC_EFORMAT;
-        if ((e = hipMemcpyAsync(blob + d.off_col_chunk, col_chunk, 4 * (2 * col_stride + (size_t)m + 1), hipMemcpyHostToDevice, stream)) != hipSuccess) return hip_fail(e);
+        if (d.off_col_pos - d.off_col_chunk != 4 * L.col_stride || d.off_chunk_ent - d.off_col_chunk != 12 * L.col_stride) return HAC_EFORMAT;
 
         // ---- step 5 ----
+        uint8_t* blob = static_cast<uint8_t*>(d_blob);
+        hipLaunchKernelGGL(enc_head_kernel, dim3(1024), dim3(256), 0, stream, d, static_cast<const DevTables*>(on_host ? nullptr : d_tables),
+                           static_cast<const uint32_t*>(dptr(L.col_arrays)), reinterpret_cast<uint32_t*>(blob));
+        std::vector<uint8_t> blob_head;
+        if (on_host) {
+            blob_head.assign((size_t)d.off_stream, 0);
+            std::memcpy(blob_head.data(), &d, sizeof d);
+            write_tables(blob_head.data(), d, codebook, len, t, lut);
+            if ((e = hipMemcpyAsync(blob, blob_head.data(), blob_head.size(), hipMemcpyHostToDevice, stream)) != hipSuccess) return hip_fail(e);
+        }
         EmitArgs a;
         a.seg_bit0 = dptr(L.seg_bits); a.seg_pos0 = dptr(L.seg_nnz);
         a.col_bit = reinterpret_cast<const uint32_t*>(blob + d.off_col_bit);
@@ -706,10 +1094,11 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
         a.stream = reinterpret_cast<uint32_t*>(blob + d.off_stream);
         a.ent = blob + d.off_chunk_ent;
         a.ri = (shac && !rice) ? reinterpret_cast<uint32_t*>(blob + d.off_ri) : nullptr;
-        a.rice = rice ? 1u : 0u; a.rice_k = rice_k;
-        a.shac = shac ? 1u : 0u; a.zcode = zcode; a.zlen = zlen;
-        a.chunk = Cn; a.ent_bits = d.ent_bits; a.row_bits = d.row_bits; a.ri_bits = ri_bits;
-        hipLaunchKernelGGL(lds_table ? enc_emit_kernel<true> : enc_emit_kernel<false>, seg_grid, dim3(256), table_lds, stream, sv, a);
+        a.rice = rice ? 1u : 0u; a.rice_k = r.rice_k;
+        a.shac = shac ? 1u : 0u; a.zcode = c.zcode; a.zlen = c.zlen;
+        a.chunk = r.chunk; a.ent_bits = d.ent_bits; a.row_bits = d.row_bits; a.ri_bits = ri_bits;
+        const size_t lds = table_bytes(c.slots);
+        hipLaunchKernelGGL(lds ? enc_emit_kernel<true> : enc_emit_kernel<false>, seg_grid, dim3(256), lds, stream, sv, a);
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
         // the host vectors above feed asynchronous copies: they must outlive them
         if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e);

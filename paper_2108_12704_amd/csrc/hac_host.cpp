@@ -457,10 +457,7 @@ uint32_t pick_lut_bits(const hac_opts_t* opts, uint32_t lmax)
 
 uint32_t pick_chunk(const hac_opts_t* opts, uint64_t max_col_nnz)
 {
-    if (opts && opts->chunk_nnz == HAC_CHUNK_PER_COLUMN) return kChunkPerColumn | kChunkPerColumnLeast;
-    if (opts && opts->chunk_nnz) return opts->chunk_nnz;
-    const uint64_t c = (max_col_nnz + 63) / 64;              // a 64-lane wavefront covers any column
-    return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(c, 4), 65536);
+    return chunk_for(opts ? opts->chunk_nnz : 0u, max_col_nnz);
 }
 
 int check_opts(const hac_opts_t* opts)

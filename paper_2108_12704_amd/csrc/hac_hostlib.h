@@ -58,6 +58,14 @@ HAC_HOST_DEVICE inline uint32_t chunk_of_column(uint32_t c, uint64_t col_nnz)
     const uint64_t per = (col_nnz + 63) / 64;
     return per > base ? (uint32_t)per : base;
 }
+// the header's chunk for hac_opts_t.chunk_nnz = asked
+HAC_HOST_DEVICE inline uint32_t chunk_for(uint32_t asked, uint64_t max_col_nnz)
+{
+    if (asked == HAC_CHUNK_PER_COLUMN) return kChunkPerColumn | kChunkPerColumnLeast;
+    if (asked) return asked;
+    const uint64_t c = (max_col_nnz + 63) / 64;              // a 64-lane wavefront covers any column
+    return c < 4 ? 4u : c > 65536 ? 65536u : (uint32_t)c;
+}
 int check_opts(const hac_opts_t* opts);
 uint32_t rice_length(uint32_t d, uint32_t k);
 

@@ -153,6 +153,53 @@ def test_device_blob_at_the_edges_of_the_tiles(hac, n, m, per_tile, k):
                           hac.shac_encode(W, ri_coding=hac.RI_RICE).data)
 
 
+def alphabet_matrix(k, counts, n, m):
+    """k values, the i-th of them counts(i) times, scattered over n x m zeros."""
+    rng = np.random.default_rng(k)
+    values = np.unique(rng.standard_normal(2 * k + 8).astype(np.float32))
+    values = rng.permutation(values[values != 0.0])[:k]
+    nz = np.repeat(values, [counts(i) for i in range(k)])
+    W = np.zeros(n * m, np.float32)
+    W[rng.permutation(n * m)[:nz.size]] = nz
+    return W.reshape(n, m)
+
+
+# alphabets around the largest one whose code is built on the device (512 values), the smallest ones, equal counts (ties at every
+# merge), counts that make the code as deep as 25 bits, and numbers of columns around a thread's share of one block
+@pytest.mark.parametrize("k,counts,n,m", [(0, None, 40, 3), (1, lambda i: 7, 40, 3), (2, lambda i: 1, 2, 1), (3, lambda i: 5, 64, 70),
+                                          (511, lambda i: 4, 300, 9), (512, lambda i: 1 + i % 3, 300, 9), (513, lambda i: 4, 300, 9),
+                                          (512, lambda i: 1 + i * i // 99, 1100, 1025), (256, lambda i: 16, 64, 64),
+                                          (25, lambda i: int(1.62 ** i), 700, 1023), (700, lambda i: 1 + i, 500, 1024),
+                                          (9, lambda i: 40, 3, 5000)])
+def test_device_blob_over_alphabets(hac, k, counts, n, m):
+    W = alphabet_matrix(k, counts, n, m)
+    Wd = torch.from_numpy(W).to(dev())
+    print(f"[case] encode_dev {n} x {m}, {k} values", flush=True)
+    for kw in (dict(), dict(chunk_nnz=hac.CHUNK_PER_COLUMN), dict(lut_bits=12)):
+        assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_HAC, **kw).tensor.cpu().numpy(), hac.hac_encode(W, **kw).data)
+        assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_SHAC, **kw).tensor.cpu().numpy(), hac.shac_encode(W, **kw).data)
+    assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_SHAC, ri_coding=hac.RI_RICE).tensor.cpu().numpy(),
+                          hac.shac_encode(W, ri_coding=hac.RI_RICE).data)
+
+
+def test_device_encodes_side_by_side(hac):
+    """More calls at once than there is pinned memory for, each on a stream of its own."""
+    import concurrent.futures as cf
+    Ws = [alphabet_matrix(5 + i, lambda j: 3 + j, 200 + i, 40) for i in range(24)]
+    Wd = [torch.from_numpy(W).to(dev()) for W in Ws]
+    torch.cuda.synchronize()
+
+    def one(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for _ in range(5):
+                got = hac.hac_encode_dev(Wd[i], hac.HAC_FORMAT_HAC).tensor.cpu().numpy()
+        return got
+    with cf.ThreadPoolExecutor(24) as pool:
+        for W, got in zip(Ws, pool.map(one, range(24))):
+            assert np.array_equal(got, hac.hac_encode(W).data)
+
+
 def gap_matrix(kind):
     """Columns that are empty over many segments of rows."""
     rng = np.random.default_rng(8)
