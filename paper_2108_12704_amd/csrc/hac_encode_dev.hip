@@ -79,9 +79,10 @@ __global__ void fill_zero_kernel(uint32_t* p, uint64_t count)
     for (; i < count; i += stride) p[i] = 0u;
 }
 
-// The histogram of the whole matrix: keys and counts, and the slots in use in the order in which they were taken
-// (flags[1] counts them; those past kListCap are dropped: more than 65536 values are refused anyway).
-constexpr uint32_t kListCap = 65536 + 64;          // one more than the largest alphabet is enough to see "too many"
+// The histogram of the whole matrix: keys and counts, and the slots in use in the order in which they were taken, as many
+// as step 2 takes on the device; flags[1] counts them until there are more (an alphabet of 40000 would add to that one word
+// 40000 times).
+constexpr uint32_t kDevSymbols = 512;              // non-zero values of an alphabet whose code is built on the device
 struct Histogram { uint32_t* keys; uint32_t* cnts; uint32_t* used; uint32_t* flags; };
 
 __device__ void table_add(const Histogram& t, uint32_t key, uint32_t add)
@@ -89,9 +90,9 @@ __device__ void table_add(const Histogram& t, uint32_t key, uint32_t add)
     uint32_t h = mix32(key) & (kHashSlots - 1);
     for (uint32_t probe = 0; probe < kHashSlots; ++probe) {
         const uint32_t old = atomicCAS(&t.keys[h], 0u, key);
-        if (old == 0u) {
+        if (old == 0u && __hip_atomic_load(&t.flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= kDevSymbols) {
             const uint32_t i = atomicAdd(&t.flags[1], 1u);
-            if (i < kListCap) t.used[i] = h;
+            if (i < kDevSymbols) t.used[i] = h;
         }
         if (old == 0u || old == key) { atomicAdd(&t.cnts[h], add); return; }
         h = (h + 1) & (kHashSlots - 1);
@@ -183,7 +184,6 @@ enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ld
 // ---------------------------------------------------------------------------
 // step 2
 // ---------------------------------------------------------------------------
-constexpr uint32_t kDevSymbols = 512;              // non-zero values of an alphabet whose code is built on the device
 constexpr uint32_t kDevSlots = 2 * kDevSymbols;    // its code table: at most half full
 constexpr uint32_t kCodeThreads = kDevSymbols + 64;   // of the block that builds it: a thread a symbol; idle wavefronts cost the others time
 constexpr uint32_t kPairUp = 64;                   // symbols from which all merges of a turn are made at once
@@ -239,8 +239,7 @@ enc_code_kernel(Histogram h, uint64_t entries, uint32_t shac, uint32_t lut_opt, 
     const uint32_t flags = h.flags[0], nv = h.flags[1];
     if (flags || nv > kDevSymbols || entries >= 0xffffffffull) {           // (weights of 32 bits here)
         if (t == 0) {
-            code->status = flags & kFlagNonFinite ? kCodeNonFinite : (flags || nv > 65536) ? kCodeRange : kCodeOnHost;
-            code->values = nv;
+            code->status = flags & kFlagNonFinite ? kCodeNonFinite : flags ? kCodeRange : kCodeOnHost;
         }
         return;
     }
@@ -418,14 +417,22 @@ enc_code_kernel(Histogram h, uint64_t entries, uint32_t shac, uint32_t lut_opt, 
     }
 }
 
-// an alphabet for the host: the occupied slots as a list of (key, count)
-__global__ void __launch_bounds__(256)
-enc_pairs_kernel(Histogram h, uint32_t nv, uint32_t* __restrict__ list)
+// An alphabet for the host: the occupied slots of the histogram as a list of (key, count) in no particular order (the host sorts by
+// value), by all threads of a grid.  flags[2] counts them; those past kListCap are dropped: more than 65536 values are refused.
+// `near`: the first kBoxPairs of them once more, in pinned memory (or nullptr).
+constexpr uint32_t kListCap = 65536 + 64;
+constexpr uint32_t kBoxPairs = 4096;
+struct PairList { uint32_t* list; uint32_t* near; };
+
+__device__ __forceinline__ void list_pairs(const Histogram& h, const PairList& to)
 {
-    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= nv) return;
-    const uint32_t s = h.used[i];
-    list[2 * (uint64_t)i] = h.keys[s]; list[2 * (uint64_t)i + 1] = h.cnts[s];
+    for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < kHashSlots; s += gridDim.x * blockDim.x) {
+        const uint32_t key = h.keys[s];
+        if (!key) continue;
+        const uint32_t i = atomicAdd(&h.flags[2], 1u), cnt = h.cnts[s];
+        if (i < kListCap) { to.list[2 * (uint64_t)i] = key; to.list[2 * (uint64_t)i + 1] = cnt; }
+        if (i < kBoxPairs && to.near) { to.near[2 * i] = key; to.near[2 * i + 1] = cnt; }
+    }
 }
 
 // What step 1 leaves behind, and the code: three arrays of `slots` words (a power of two, at most half
@@ -541,9 +548,10 @@ __device__ __forceinline__ uint32_t rice_len(uint32_t d, uint32_t k)
 // Step 3.  seg_bits: code bits and, in HAC, the zeros' codewords.  gap_bits (Rice-coded gaps only, else
 // nullptr): [k][segment][column] bits of the gap codewords for k = 0..15; gap_total: their 16 sums
 // over the matrix (added up in the block first: the sums are 16 addresses for the whole chip).
+// Where the code has to come from the host, its alphabet is listed instead.
 template <bool LDS_TABLE>
 __global__ void __launch_bounds__(256)
-enc_bits_kernel(Survivors s, const EncCode* __restrict__ code, uint32_t* __restrict__ seg_nnz, uint32_t* __restrict__ seg_bits,
+enc_bits_kernel(Survivors s, const EncCode* __restrict__ code, Histogram hist, PairList pairs, uint32_t* __restrict__ seg_nnz, uint32_t* __restrict__ seg_bits,
                 uint32_t* __restrict__ gap_bits, unsigned long long* gap_total, uint64_t seg_cols)
 {
     extern __shared__ uint32_t table_lds[];
@@ -553,7 +561,10 @@ enc_bits_kernel(Survivors s, const EncCode* __restrict__ code, uint32_t* __restr
     const uint32_t r0 = seg * s.seg_rows, r1 = r0 + s.seg_rows < s.n ? r0 + s.seg_rows : s.n;
     const uint64_t at = (uint64_t)seg * s.m + j;
     const uint32_t total = j < s.m ? load_segment(s, sw, j, r0, r1) : 0u;      // (needs nothing of the code: on its way first)
-    if (code->status != kCodeOk) return;
+    if (code->status != kCodeOk) {
+        if (code->status == kCodeOnHost) list_pairs(hist, pairs);
+        return;
+    }
     const uint32_t zlen = code->zlen;
     s.slots = code->slots;
     if (threadIdx.x <= kRiceKMax) sums[threadIdx.x] = 0;
@@ -744,7 +755,7 @@ enc_col_scan_kernel(const EncCode* __restrict__ code, uint32_t m, uint32_t S, ui
 // past it, `stride` words apart.  The counts go to *result and, where the host waits for them in pinned memory, to *mailbox.
 __global__ void __launch_bounds__(1024)
 enc_columns_kernel(const EncCode* __restrict__ code, uint32_t m, const uint32_t* __restrict__ col_nnz, const unsigned long long* __restrict__ col_bits,
-                   uint32_t chunk_opt, const unsigned long long* __restrict__ gap_total, uint32_t* __restrict__ col_arrays, uint64_t stride,
+                   const uint32_t* __restrict__ flags, uint32_t chunk_opt, const unsigned long long* __restrict__ gap_total, uint32_t* __restrict__ col_arrays, uint64_t stride,
                    EncResult* __restrict__ result, EncResult* mailbox)
 {
     __shared__ unsigned long long wave_bits[16];
@@ -811,6 +822,7 @@ enc_columns_kernel(const EncCode* __restrict__ code, uint32_t m, const uint32_t*
         }
         if (gap_total) { r.rice_k = best_rice_k(gap_total); r.gap_bits = gap_total[r.rice_k]; }
     }
+    if (r.code.status == kCodeOnHost) r.code.values = flags[2];
     if (t == 0) { *result = r; if (mailbox) *mailbox = r; }
 }
 
@@ -851,7 +863,7 @@ WsLayout ws_layout(uint64_t n, uint64_t m)
     size_t c = 0;
     auto take = [&](size_t bytes) { const size_t o = c; c = (c + bytes + 255) / 256 * 256; return o; };
     L.keys = take(4ull * kHashSlots); L.cnts = take(4ull * kHashSlots); L.flags = take(256);
-    L.used = take(4ull * kListCap);
+    L.used = take(4ull * kDevSymbols);
     L.list = take(8ull * kListCap);
     L.mask = take(4 * words * m); L.off = take(2 * words * m); L.values = take(4ull * kQuota * words * m);
     L.seg_nnz = take(4 * S * m); L.seg_bits = take(4 * S * m);
@@ -867,14 +879,16 @@ WsLayout ws_layout(uint64_t n, uint64_t m)
 
 int hip_fail(hipError_t e) { hac_internal::set_last_hip_error((int)e); return HAC_EHIP; }
 
-// Pinned memory that the device leaves a call's counts in: kBoxes of them for the process, allocated with the first call (one costs more
-// than the call) and lent to a call until it has read them.  get() is nullptr where none is free, or none can be had: the counts are then copied.
+// Pinned memory that the device leaves a call's counts in, and a list of up to kBoxPairs values: kBoxes of them for the process (512 KB),
+// allocated with the first call (one costs more than the call) and lent to a call until it has read them.  get() is nullptr where
+// none is free, or none can be had: what the host needs is then copied.
 constexpr int kBoxes = 16;
+struct Box { EncResult result; uint32_t pairs[2 * kBoxPairs]; };
 class Mailbox {
-    struct Pool { std::mutex lock; EncResult* base = nullptr; bool asked = false; uint32_t taken = 0; };
+    struct Pool { std::mutex lock; Box* base = nullptr; bool asked = false; uint32_t taken = 0; };
     static Pool& pool() { static Pool* p = new Pool; return *p; }   // (never taken down: a call may run while the process ends)
     int i = -1;
-    EncResult* p = nullptr;
+    Box* p = nullptr;
 public:
     Mailbox()
     {
@@ -883,7 +897,7 @@ public:
         if (!q.asked) {
             q.asked = true;
             void* mem = nullptr;
-            if (hipHostMalloc(&mem, sizeof(EncResult) * kBoxes, hipHostMallocPortable) == hipSuccess) q.base = static_cast<EncResult*>(mem);
+            if (hipHostMalloc(&mem, sizeof(Box) * kBoxes, hipHostMallocPortable) == hipSuccess) q.base = static_cast<Box*>(mem);
             else (void)hipGetLastError();
         }
         if (!q.base) return;
@@ -899,7 +913,7 @@ public:
     }
     Mailbox(const Mailbox&) = delete;
     Mailbox& operator=(const Mailbox&) = delete;
-    EncResult* get() const { return p; }
+    Box* get() const { return p; }
 };
 
 } // namespace
@@ -959,22 +973,29 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
     auto table_bytes = [](uint32_t slots) { return slots <= kCodeSlotsLds ? 12 * (size_t)slots : (size_t)0; };
     hipError_t e;
     // steps 3 and 4 with a code of at most `slots` slots, and the wait for their sums
+    std::vector<uint32_t> list;                        // of a code that the host has to build
     auto sums = [&](uint32_t slots, EncResult& r) -> hipError_t {
-        Mailbox box;
+        Mailbox mail;
+        Box* const box = mail.get();
+        const PairList to = { dptr(L.list), box ? box->pairs : nullptr };
         const size_t lds = table_bytes(slots) / 3 * 2;
-        hipLaunchKernelGGL(lds ? enc_bits_kernel<true> : enc_bits_kernel<false>, seg_grid, dim3(256), lds, stream, sv, d_code,
+        hipLaunchKernelGGL(lds ? enc_bits_kernel<true> : enc_bits_kernel<false>, seg_grid, dim3(256), lds, stream, sv, d_code, hist, to,
                            dptr(L.seg_nnz), dptr(L.seg_bits), d_gap_bits, d_gap_total, SM);
         hipLaunchKernelGGL(enc_col_scan_kernel, dim3((uint32_t)(((uint64_t)m + 15) / 16)), dim3(256), 0, stream, d_code, (uint32_t)m, S,
                            dptr(L.seg_nnz), dptr(L.seg_bits), static_cast<const uint32_t*>(d_gap_bits),
                            static_cast<const unsigned long long*>(d_gap_total), SM, dptr(L.col_nnz), d_col_bits);
         hipLaunchKernelGGL(enc_columns_kernel, dim3(1), dim3(1024), 0, stream, d_code, (uint32_t)m, dptr(L.col_nnz), d_col_bits,
-                           opts ? opts->chunk_nnz : 0u, static_cast<const unsigned long long*>(d_gap_total), dptr(L.col_arrays),
-                           (uint64_t)L.col_stride, d_result, box.get());
+                           dptr(L.flags), opts ? opts->chunk_nnz : 0u, static_cast<const unsigned long long*>(d_gap_total), dptr(L.col_arrays),
+                           (uint64_t)L.col_stride, d_result, box ? &box->result : nullptr);
         hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
-        if (!box.get() && (err = hipMemcpyAsync(&r, d_result, sizeof r, hipMemcpyDeviceToHost, stream)) != hipSuccess) return err;
-        err = hipStreamSynchronize(stream);
-        if (err == hipSuccess && box.get()) r = *box.get();
+        if (!box && (err = hipMemcpyAsync(&r, d_result, sizeof r, hipMemcpyDeviceToHost, stream)) != hipSuccess) return err;
+        if ((err = hipStreamSynchronize(stream)) != hipSuccess) return err;
+        if (box) r = box->result;
+        if (r.code.status != kCodeOnHost || r.code.values > 65536) return hipSuccess;
+        list.resize(2 * (size_t)r.code.values);
+        if (box && r.code.values <= kBoxPairs) std::memcpy(list.data(), box->pairs, 4 * list.size());
+        else if ((err = hipMemcpyAsync(list.data(), to.list, 4 * list.size(), hipMemcpyDeviceToHost, stream)) == hipSuccess) err = hipStreamSynchronize(stream);
         return err;
     };
     try {
@@ -1000,10 +1021,7 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
         EncCode c = {};
         if (on_host) {
             const uint32_t nv = r.code.values;
-            std::vector<uint32_t> list(2 * (size_t)nv);
-            hipLaunchKernelGGL(enc_pairs_kernel, dim3((nv + 255) / 256), dim3(256), 0, stream, hist, nv, dptr(L.list));
-            if ((e = hipMemcpyAsync(list.data(), dptr(L.list), 4 * list.size(), hipMemcpyDeviceToHost, stream)) != hipSuccess) return hip_fail(e);
-            if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e);
+            if (nv > 65536) return HAC_ERANGE;
             struct Val { float v; uint32_t key; uint64_t f; };
             std::vector<Val> vals(nv);
             for (uint32_t i = 0; i < nv; ++i) {
