@@ -45,8 +45,7 @@ namespace {
 using namespace hac_internal;
 
 constexpr uint32_t kHashSlots = 1u << 17;          // distinct values <= 65536 keep the load below 1/2
-constexpr uint32_t kSegRowsMax = 256, kSegRowsMin = 32;   // multiples of 32: a segment is whole words
-constexpr uint32_t kSegWordsMax = kSegRowsMax / 32;
+constexpr uint32_t kSegRowsMax = 512, kSegRowsMin = 32;   // multiples of 32: a segment is whole words
 constexpr uint64_t kMaxRows = 65535ull * 1024;
 constexpr uint32_t kTileCols = 64, kTileRows = 32;        // what a wavefront reads at a time in step 1
 constexpr uint32_t kQuota = 4;                            // packed values per column of a tile: an eighth of it
@@ -54,11 +53,14 @@ constexpr uint32_t kNotPacked = 0xffffu;
 constexpr uint32_t kScanWaves = 8, kScanQueue = 1024, kScanBlocks = 1024;   // 40 KB of LDS a block: four on a CU
 constexpr uint32_t kCodeSlotsLds = 2048;                  // code tables up to this size (24 KB) are copied to LDS
 
-// Rows per segment: 256 on a large matrix, fewer on a small one, so that there are about 512 K
-// (segment, column) threads (a thread's work is a chain of short trips to memory).
+// Rows per segment: 512 on a large matrix, fewer on a small one, so that there are about 256 K
+// (segment, column) threads.  What bounds the emission is the atomics on the words that two segments share (1.3 million with
+// segments of 256 rows at 25088 x 4096, 2 %; half the segments, half of them) and lanes that wait for the one with the most non-zeros
+// (12.5 turns for 5.1 non-zeros a lane, 17 for 10); whole calls with 512 K threads -> 256 K -> 128 K: that layer 245 -> 226 -> 245 us,
+// 12000 x 2000, 10 % 209 -> 183 -> 195, 4096 x 4096, 40 % 298 -> 287 -> 324.
 __host__ inline uint32_t seg_rows_for(uint64_t n, uint64_t m)
 {
-    const uint64_t want = (n * m + 524287) / 524288;
+    const uint64_t want = (n * m + 262143) / 262144;
     uint32_t r = kSegRowsMin;
     while (r < kSegRowsMax && r < want) r <<= 1;
     return r;
@@ -426,12 +428,19 @@ struct PairList { uint32_t* list; uint32_t* near; };
 
 __device__ __forceinline__ void list_pairs(const Histogram& h, const PairList& to)
 {
-    for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < kHashSlots; s += gridDim.x * blockDim.x) {
-        const uint32_t key = h.keys[s];
-        if (!key) continue;
-        const uint32_t i = atomicAdd(&h.flags[2], 1u), cnt = h.cnts[s];
-        if (i < kListCap) { to.list[2 * (uint64_t)i] = key; to.list[2 * (uint64_t)i + 1] = cnt; }
-        if (i < kBoxPairs && to.near) { to.near[2 * i] = key; to.near[2 * i + 1] = cnt; }
+    const uint32_t threads = gridDim.x * blockDim.x;
+    for (uint32_t s0 = blockIdx.x * blockDim.x + threadIdx.x; s0 < kHashSlots; s0 += 16 * threads) {
+        uint32_t keys[16];                             // requested together: a small matrix has few threads for its 131072 slots
+#pragma unroll
+        for (uint32_t u = 0; u < 16; ++u) { const uint64_t s = s0 + (uint64_t)u * threads; keys[u] = h.keys[s < kHashSlots ? s : kHashSlots - 1]; }
+#pragma unroll
+        for (uint32_t u = 0; u < 16; ++u) {
+            const uint64_t s = s0 + (uint64_t)u * threads;
+            if (!keys[u] || s >= kHashSlots) continue;
+            const uint32_t i = atomicAdd(&h.flags[2], 1u), cnt = h.cnts[s];
+            if (i < kListCap) { to.list[2 * (uint64_t)i] = keys[u]; to.list[2 * (uint64_t)i + 1] = cnt; }
+            if (i < kBoxPairs && to.near) { to.near[2 * i] = keys[u]; to.near[2 * i + 1] = cnt; }
+        }
     }
 }
 
@@ -492,21 +501,33 @@ __device__ __forceinline__ uint32_t row_after_previous(const Survivors& s, uint3
 // A thread's segment of a column: its words wait in LDS (each thread reads back only its own), so that the
 // lanes of a wavefront step through their words independently and it runs as long as the lane with the
 // most non-zeros in the whole segment, not the sum of the words' longest lanes.
-struct SegWords { uint32_t mask[kSegWordsMax][256]; uint16_t off[kSegWordsMax][256]; };
-
-__device__ __forceinline__ uint32_t load_segment(const Survivors& s, SegWords& sw, uint32_t j, uint32_t r0, uint32_t r1)
+struct SegWords {
+    uint32_t* mask_; uint16_t* off_;
+    __device__ __forceinline__ uint32_t& mask(uint32_t w) const { return mask_[256 * w + threadIdx.x]; }
+    __device__ __forceinline__ uint16_t& off(uint32_t w) const { return off_[256 * w + threadIdx.x]; }
+};
+__host__ __device__ inline uint32_t seg_words_lds(uint32_t seg_rows) { return (seg_rows / 32) * (256 + 128); }   // in words of 32 bits
+// a block's LDS: its segments' words, then the code table
+__device__ __forceinline__ SegWords seg_words(uint32_t* lds, uint32_t seg_rows)
 {
-    const uint32_t w0 = r0 / 32, words = (r1 - r0 + 31) / 32;
+    return SegWords{ lds, reinterpret_cast<uint16_t*>(lds + (seg_rows / 32) * 256) };
+}
+
+__device__ __forceinline__ uint32_t load_segment(const Survivors& s, const SegWords& sw, uint32_t j, uint32_t r0, uint32_t r1)
+{
+    const uint32_t words = (r1 - r0 + 31) / 32;
+    const uint64_t at = (uint64_t)(r0 / 32) * s.m + j;
     uint32_t total = 0;
+    for (uint32_t w0 = 0; w0 < words; w0 += 8) {                      // eight words' loads in flight; past the end: the last word again
+        uint32_t word[8], off[8];
 #pragma unroll
-    for (uint32_t w = 0; w < kSegWordsMax; ++w) {
-        if (w < words) {
-            const uint64_t at = (uint64_t)(w0 + w) * s.m + j;
-            const uint32_t word = s.mask[at];
-            sw.mask[w][threadIdx.x] = word;
-            sw.off[w][threadIdx.x] = s.off[at];
-            total += __popc(word);
+        for (uint32_t u = 0; u < 8; ++u) {
+            const uint64_t a = at + (uint64_t)(w0 + u < words ? w0 + u : words - 1) * s.m;
+            word[u] = s.mask[a]; off[u] = s.off[a];
         }
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u)
+            if (w0 + u < words) { sw.mask(w0 + u) = word[u]; sw.off(w0 + u) = (uint16_t)off[u]; total += __popc(word[u]); }
     }
     return total;
 }
@@ -516,15 +537,14 @@ __device__ __forceinline__ uint32_t load_segment(const Survivors& s, SegWords& s
 template <class F>
 __device__ __forceinline__ void for_survivors(const Survivors& s, const SegWords& sw, uint32_t j, uint32_t r0, uint32_t total, F f)
 {
-    const uint32_t t = threadIdx.x;
-    uint32_t w = 0, word = sw.mask[0][t], at = sw.off[0][t];
+    uint32_t w = 0, word = sw.mask(0), at = sw.off(0);
     const uint32_t* list = s.values + ((uint64_t)(r0 / 32) * s.m + (j - j % kTileCols)) * kQuota;   // of the segment's first tile
     for (uint32_t i = 0; i < total; i += 4) {
         uint32_t r[4], key[4];
 #pragma unroll
         for (uint32_t u = 0; u < 4; ++u) {
             if (i + u < total) {
-                while (word == 0) { ++w; word = sw.mask[w][t]; at = sw.off[w][t]; }
+                while (word == 0) { ++w; word = sw.mask(w); at = sw.off(w); }
                 r[u] = r0 + 32 * w + (uint32_t)__builtin_ctz(word);
                 word &= word - 1;
                 const uint32_t* from = at != kNotPacked ? list + (uint64_t)w * s.m * kQuota + at
@@ -554,8 +574,8 @@ __global__ void __launch_bounds__(256)
 enc_bits_kernel(Survivors s, const EncCode* __restrict__ code, Histogram hist, PairList pairs, uint32_t* __restrict__ seg_nnz, uint32_t* __restrict__ seg_bits,
                 uint32_t* __restrict__ gap_bits, unsigned long long* gap_total, uint64_t seg_cols)
 {
-    extern __shared__ uint32_t table_lds[];
-    __shared__ SegWords sw;
+    extern __shared__ uint32_t lds[];
+    const SegWords sw = seg_words(lds, s.seg_rows);
     __shared__ unsigned long long sums[kRiceKMax + 1];
     const uint32_t seg = blockIdx.x / s.col_blocks, j = (blockIdx.x - seg * s.col_blocks) * 256 + threadIdx.x;
     const uint32_t r0 = seg * s.seg_rows, r1 = r0 + s.seg_rows < s.n ? r0 + s.seg_rows : s.n;
@@ -568,7 +588,7 @@ enc_bits_kernel(Survivors s, const EncCode* __restrict__ code, Histogram hist, P
     const uint32_t zlen = code->zlen;
     s.slots = code->slots;
     if (threadIdx.x <= kRiceKMax) sums[threadIdx.x] = 0;
-    const uint32_t* table = length_table<LDS_TABLE>(s, table_lds);
+    const uint32_t* table = length_table<LDS_TABLE>(s, lds + seg_words_lds(s.seg_rows));
     const uint32_t* lengths = table + (LDS_TABLE ? 1u : 2u) * s.slots;
     uint32_t g[kRiceKMax + 1];
 #pragma unroll
@@ -636,9 +656,9 @@ struct EmitArgs {
 template <bool LDS_TABLE>
 __global__ void __launch_bounds__(256) enc_emit_kernel(Survivors s, EmitArgs a)
 {
-    extern __shared__ uint32_t table_lds[];
-    __shared__ SegWords sw;
-    const uint32_t* table = code_table<LDS_TABLE>(s, table_lds);
+    extern __shared__ uint32_t lds[];
+    const SegWords sw = seg_words(lds, s.seg_rows);
+    const uint32_t* table = code_table<LDS_TABLE>(s, lds + seg_words_lds(s.seg_rows));
     const uint32_t seg = blockIdx.x / s.col_blocks, j = (blockIdx.x - seg * s.col_blocks) * 256 + threadIdx.x;
     if (j >= s.m) return;
     const uint32_t r0 = seg * s.seg_rows, r1 = r0 + s.seg_rows < s.n ? r0 + s.seg_rows : s.n;
@@ -969,6 +989,7 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
     EncCode* d_code = reinterpret_cast<EncCode*>(ws + L.code);
     EncResult* d_result = reinterpret_cast<EncResult*>(ws + L.result);
     DevTables* d_tables = reinterpret_cast<DevTables*>(ws + L.tables);
+    const size_t words_lds = 4 * (size_t)seg_words_lds(seg_rows);
     // (code tables up to kCodeSlotsLds are read from LDS)
     auto table_bytes = [](uint32_t slots) { return slots <= kCodeSlotsLds ? 12 * (size_t)slots : (size_t)0; };
     hipError_t e;
@@ -979,7 +1000,7 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
         Box* const box = mail.get();
         const PairList to = { dptr(L.list), box ? box->pairs : nullptr };
         const size_t lds = table_bytes(slots) / 3 * 2;
-        hipLaunchKernelGGL(lds ? enc_bits_kernel<true> : enc_bits_kernel<false>, seg_grid, dim3(256), lds, stream, sv, d_code, hist, to,
+        hipLaunchKernelGGL(lds ? enc_bits_kernel<true> : enc_bits_kernel<false>, seg_grid, dim3(256), words_lds + lds, stream, sv, d_code, hist, to,
                            dptr(L.seg_nnz), dptr(L.seg_bits), d_gap_bits, d_gap_total, SM);
         hipLaunchKernelGGL(enc_col_scan_kernel, dim3((uint32_t)(((uint64_t)m + 15) / 16)), dim3(256), 0, stream, d_code, (uint32_t)m, S,
                            dptr(L.seg_nnz), dptr(L.seg_bits), static_cast<const uint32_t*>(d_gap_bits),
@@ -1116,7 +1137,7 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
         a.shac = shac ? 1u : 0u; a.zcode = c.zcode; a.zlen = c.zlen;
         a.chunk = r.chunk; a.ent_bits = d.ent_bits; a.row_bits = d.row_bits; a.ri_bits = ri_bits;
         const size_t lds = table_bytes(c.slots);
-        hipLaunchKernelGGL(lds ? enc_emit_kernel<true> : enc_emit_kernel<false>, seg_grid, dim3(256), lds, stream, sv, a);
+        hipLaunchKernelGGL(lds ? enc_emit_kernel<true> : enc_emit_kernel<false>, seg_grid, dim3(256), words_lds + lds, stream, sv, a);
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e);
         // the host vectors above feed asynchronous copies: they must outlive them
         if ((e = hipStreamSynchronize(stream)) != hipSuccess) return hip_fail(e);
