@@ -102,38 +102,45 @@ struct WordSrc {
 };
 
 // Decode tables of one block in LDS.  Layout (uint32 words):
-//   lut2[2^lut_bits][2] | canon[99] (+1 pad) | codebook[k4] | symsort[k4]     k4 = k_sym rounded up to 4
+//   lut2[2^lut_bits][2] | bound[40] base[40] (+20 pad) | long2[k4][2]     k4 = k_sym rounded up to 4
 // lut2 pairs the blob's first-level entry with the shared value of its symbol, so a short
-// codeword costs one 64-bit LDS read.  codebook / symsort sit in LDS only when
-// k_sym <= kCodebookLdsMax; otherwise the (rare) long codewords read them from the blob.
+// codeword costs one 64-bit LDS read.  A longer one is found by its length: bound[l], half of the first
+// 32 bits that belong to codewords longer than l, base[l], what its first l bits have to be moved by to
+// give its place in (length, symbol) order, and long2, symbol and value by that place.  long2 sits in LDS only when
+// k_sym <= kCodebookLdsMax; otherwise symbols and values are read from the blob.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) const u32x2 lds_cu2;
 
+constexpr uint32_t kBounds = 40;             // entries of bound and base: lengths to 32, read four at a time
+
 struct Tables {
     const uint2* lut2;          // LDS
-    const uint32_t* canon;      // LDS
-    const float* cb;            // LDS when small, else the blob's copy
-    const uint32_t* symsort;    // likewise
+    const uint32_t* bound;      // LDS; base behind it
+    const uint2* long2;         // LDS when small
     bool small;                 // k_sym <= kCodebookLdsMax (uniform)
 };
 
-// Code longer than the first-level table: canonical search by length.
-// Returns {(symbol << 6) | length, value bits}.
-__device__ __noinline__ uint2 decode_long(const uint32_t* canon_, const uint32_t* symsort, const float* cb, bool small,
-                                          uint32_t top, uint32_t lut_bits, uint32_t lmax)
+// Code longer than the first-level table: {(symbol << 6) | length, value bits}.  Its length is the number of bounds it has passed,
+// four of them read at once (all lanes the same words), then two reads.  Some lane of a wavefront is here at almost every step of a HAC
+// stream: one length after the other, two reads each, made that lane's search the longest part of the step.
+__device__ __forceinline__ uint2 decode_long(const DevBlob& d, const Tables& t, uint32_t top)
 {
-    lds_cu32* canon = (lds_cu32*)canon_;
-    for (uint32_t l = lut_bits + 1; l <= lmax; ++l) {
-        const uint32_t code = top >> (32 - l);
-        const uint32_t rel = code - canon[l];
-        if (rel < canon[33 + l]) {
-            const uint32_t idx = canon[66 + l] + rel;
-            const uint32_t sy = small ? ((lds_cu32*)symsort)[idx] : symsort[idx];
-            const float v = small ? ((lds_cf32*)cb)[sy] : cb[sy];
-            return make_uint2((sy << 6) | l, __float_as_uint(v));
-        }
+    if (d.lmax <= d.lut_bits) return make_uint2(d.lmax ? d.lmax : 1u, 0u);       // no such code: a damaged stream; still makes progress
+    lds_cu32* bound = (lds_cu32*)t.bound;
+    const uint32_t half = top >> 1;
+    uint32_t l = d.lut_bits + 1;
+    for (uint32_t u = d.lut_bits + 1; u < d.lmax; u += 4) {                     // (from lmax on no bound is passed)
+        const uint32_t b0 = bound[u], b1 = bound[u + 1], b2 = bound[u + 2], b3 = bound[u + 3];
+        l += (half >= b0 ? 1u : 0u) + (half >= b1 ? 1u : 0u) + (half >= b2 ? 1u : 0u) + (half >= b3 ? 1u : 0u);
     }
-    return make_uint2(lmax ? lmax : 1, 0u);   // unreachable for a validated blob; still makes progress
+    uint32_t at = bound[kBounds + l] + (top >> (32 - l));
+    at = at < d.k_sym ? at : d.k_sym - 1u;                                      // (of a damaged stream)
+    if (t.small) {
+        const u32x2 e = ((lds_cu2*)t.long2)[at];
+        return make_uint2(e.x << 6 | l, e.y);
+    }
+    const uint32_t sy = d.symsort[at];
+    return make_uint2(sy << 6 | l, __float_as_uint(d.codebook[sy]));
 }
 
 struct Decoded { uint32_t sym, len; float val; };
@@ -142,7 +149,7 @@ __device__ __forceinline__ Decoded decode_symbol(const DevBlob& d, const Tables&
 {
     const u32x2 raw = ((lds_cu2*)t.lut2)[top >> (32 - d.lut_bits)];
     uint2 e = make_uint2(raw.x, raw.y);
-    if ((e.x & 63u) == 0) e = decode_long(t.canon, t.symsort, t.cb, t.small, top, d.lut_bits, d.lmax);
+    if ((e.x & 63u) == 0) e = decode_long(d, t, top);
     Decoded r;
     r.len = e.x & 63u; r.sym = e.x >> 6; r.val = __uint_as_float(e.y);
     return r;
@@ -164,34 +171,35 @@ __device__ __forceinline__ uint32_t table_words_dev(const DevBlob& d)
 // first kTabTurns turns of every loop are issued from clamped, valid indices on every thread;
 // what a small block or a long table leaves over is copied the plain way.
 constexpr int kTabTurns = 4;                        // (the asm statement in store_tables names four values)
-struct TableRegs { uint32_t e[kTabTurns], v[kTabTurns]; uint32_t canon, cb, sort; };
+struct TableRegs { uint32_t e[kTabTurns], v[kTabTurns]; uint32_t first, count, index, cb, sort; };
 
 __device__ __forceinline__ TableRegs request_tables(const DevBlob& d)
 {
     TableRegs r;
     const uint32_t nl = 1u << d.lut_bits;
+    // What only codewords longer than the first-level table need, where there are any: requested before the others, so that the
+    // number of loads behind those a later wait is for is the same on both paths (and without branches beyond this uniform one:
+    // a guarded load would be moved down beside its use).
+    r.first = r.count = r.index = r.sort = r.cb = 0u;
+    if (d.lmax > d.lut_bits) {
+        const uint32_t l = threadIdx.x < 32u ? threadIdx.x : 32u;
+        r.first = d.canon[l]; r.count = d.canon[33 + l]; r.index = d.canon[66 + l];
+        r.sort = d.symsort[threadIdx.x < d.k_sym - 1u ? threadIdx.x : d.k_sym - 1u];   // (such a code has symbols)
+    }
 #pragma unroll
     for (int k = 0; k < kTabTurns; ++k) {
         const uint32_t i = threadIdx.x + k * blockDim.x;
         r.e[k] = d.lut[i < nl ? i : nl - 1u];
         r.v[k] = 0u;
     }
-    r.canon = d.canon[threadIdx.x < 99u ? threadIdx.x : 98u];
-    // no branch around a load: the number of loads in flight is then the same on every path, and a
-    // later wait for these can leave younger loads travelling.  Without symbols (an empty address
-    // map) the canonical table stands in as a valid address.
-    const uint32_t* cbp = d.k_sym ? reinterpret_cast<const uint32_t*>(d.codebook) : d.canon;
-    const uint32_t* sop = d.k_sym ? d.symsort : d.canon;
-    const uint32_t last = d.k_sym ? d.k_sym - 1u : 0u;
-    const uint32_t i = threadIdx.x < last ? threadIdx.x : last;
-    r.cb = cbp[i];
-    r.sort = sop[i];
     return r;
 }
 
 __device__ __forceinline__ void request_table_values(const DevBlob& d, TableRegs& r)
 {
+    // without symbols (an empty address map) the canonical table stands in as a valid address
     const uint32_t* cbp = d.k_sym ? reinterpret_cast<const uint32_t*>(d.codebook) : d.canon;
+    if (d.lmax > d.lut_bits) r.cb = cbp[r.sort < d.k_sym ? r.sort : 0u];
 #pragma unroll
     for (int k = 0; k < kTabTurns; ++k) r.v[k] = cbp[(r.e[k] & 63u) ? r.e[k] >> 6 : 0u];
 }
@@ -199,16 +207,14 @@ __device__ __forceinline__ void request_table_values(const DevBlob& d, TableRegs
 __device__ __forceinline__ Tables store_tables(const DevBlob& d, uint32_t* smem, TableRegs& r)
 {
     const uint32_t nl = 1u << d.lut_bits;
-    const uint32_t k4 = (d.k_sym + 3u) & ~3u;
     uint2* s_lut2 = reinterpret_cast<uint2*>(smem);
-    uint32_t* s_canon = smem + 2 * nl;
-    float* s_cb = reinterpret_cast<float*>(s_canon + 100);
-    uint32_t* s_sort = reinterpret_cast<uint32_t*>(s_cb) + k4;
+    uint32_t* s_bound = smem + 2 * nl;
+    uint2* s_long2 = reinterpret_cast<uint2*>(s_bound + 100);
     // The values pass through an empty asm statement first: their loads then stay where they were
     // issued (the compiler would otherwise move a load down beside the guarded store that uses it,
     // behind every load issued since).
     static_assert(kTabTurns == 4, "the asm statement below names four values");
-    asm volatile("" : "+v"(r.v[0]), "+v"(r.v[1]), "+v"(r.v[2]), "+v"(r.v[3]));
+    asm volatile("" : "+v"(r.v[0]), "+v"(r.v[1]), "+v"(r.v[2]), "+v"(r.v[3]), "+v"(r.cb));
 #pragma unroll
     for (int k = 0; k < kTabTurns; ++k) {
         const uint32_t i = threadIdx.x + k * blockDim.x;
@@ -218,16 +224,20 @@ __device__ __forceinline__ Tables store_tables(const DevBlob& d, uint32_t* smem,
         const uint32_t e = d.lut[i];
         s_lut2[i] = make_uint2(e, (e & 63u) ? __float_as_uint(d.codebook[e >> 6]) : 0u);
     }
-    if (threadIdx.x < 99u) s_canon[threadIdx.x] = r.canon;
-    for (uint32_t i = threadIdx.x + blockDim.x; i < 99u; i += blockDim.x) s_canon[i] = d.canon[i];
+    const bool longer = d.lmax > d.lut_bits;
+    if (longer && threadIdx.x < kBounds) {                                      // (blocks have at least a wavefront)
+        const uint32_t l = threadIdx.x;
+        s_bound[l] = l < d.lmax && l < 32u ? (r.first + r.count) << (31u - l) : 0x80000000u;
+        s_bound[kBounds + l] = r.index - r.first;
+    }
     Tables t;
-    t.lut2 = s_lut2; t.canon = s_canon; t.small = d.k_sym <= kCodebookLdsMax;
-    if (t.small) {
-        if (threadIdx.x < d.k_sym) { s_cb[threadIdx.x] = __uint_as_float(r.cb); s_sort[threadIdx.x] = r.sort; }
-        for (uint32_t i = threadIdx.x + blockDim.x; i < d.k_sym; i += blockDim.x) { s_cb[i] = d.codebook[i]; s_sort[i] = d.symsort[i]; }
-        t.cb = s_cb; t.symsort = s_sort;
-    } else {
-        t.cb = d.codebook; t.symsort = d.symsort;
+    t.lut2 = s_lut2; t.bound = s_bound; t.long2 = s_long2; t.small = d.k_sym <= kCodebookLdsMax;
+    if (longer && t.small) {
+        if (threadIdx.x < d.k_sym) s_long2[threadIdx.x] = make_uint2(r.sort, r.cb);
+        for (uint32_t i = threadIdx.x + blockDim.x; i < d.k_sym; i += blockDim.x) {
+            const uint32_t sy = d.symsort[i];
+            s_long2[i] = make_uint2(sy, __float_as_uint(d.codebook[sy < d.k_sym ? sy : 0u]));
+        }
     }
     return t;
 }
@@ -351,20 +361,29 @@ __device__ __forceinline__ void shac_advance(const DevBlob& d, const Tables& tb,
     }
 }
 
-// The same over the staged copy: one funnel shift per codeword.
+// The same over the staged copy.  The two words around the position and the one behind them stay in registers, the bits still
+// ahead in the first counted from 31 down, so that what one codeword waits for is a funnel shift and the table's entry; the next
+// word is read beside that.  (Reading both words at every codeword put a second LDS latency into the chain.)
 template <class Emit>
 __device__ __forceinline__ void shac_advance(const DevBlob& d, const Tables& tb, const WordSrc<true>& src,
                                              ChunkState& st, uint32_t limit, Emit emit)
 {
-    int32_t rm1 = (int32_t)(st.bp - (src.wbase << 5)) - 1;
+    lds_cu32* sw = (lds_cu32*)src.w;
+    const int32_t rm1 = (int32_t)(st.bp - (src.wbase << 5)) - 1;
+    int32_t q = (rm1 >> 5) + 2, s = 31 - (rm1 & 31);                       // word q waits in w2
+    uint32_t w0 = sw[q - 2], w1 = sw[q - 1], w2 = sw[q];
     ALIGN_DECODE_LOOP();
     while (st.wpos < limit) {
-        const Decoded sy = decode_symbol(d, tb, src.peek32_rm1(rm1));
-        rm1 += (int32_t)sy.len;
+        const Decoded sy = decode_symbol(d, tb, __builtin_amdgcn_alignbit(w0, w1, (uint32_t)s));
+        s -= (int32_t)sy.len;
+        const bool on = s < 0;                                             // into the next word
+        w0 = on ? w1 : w0; w1 = on ? w2 : w1;
+        q += on ? 1 : 0; s &= 31;
+        w2 = sw[q];
         emit(st.wpos, 0u, sy.sym, sy.val);
         st.wpos++;
     }
-    st.bp = (uint32_t)(rm1 + 1) + (src.wbase << 5);
+    st.bp = (uint32_t)(32 * (q - 2) + 32 - s) + (src.wbase << 5);
 }
 
 // sHAC with Rice-coded row gaps: gap codeword, then the value's codeword.  Gap d with
@@ -377,33 +396,34 @@ __device__ __forceinline__ void gap_advance(const DevBlob& d, const Tables& tb, 
 {
     lds_cu32* sw = (lds_cu32*)src.w;
     const uint32_t k = d.rice_k;
+    int32_t rm1 = (int32_t)(st.bp - (src.wbase << 5)) - 1;                 // as in hac_advance_zrun: funnel shifts only
     ALIGN_DECODE_LOOP();
     while (st.wpos < limit) {
-        const uint32_t wi = (st.bp >> 5) - src.wbase, off = st.bp & 31;
-        const uint32_t w0 = sw[wi], w1 = sw[wi + 1], w2 = sw[wi + 2], w3 = sw[wi + 3];
-        const uint32_t hi = (uint32_t)(((((uint64_t)w0 << 32) | w1) << off) >> 32);
-        const uint32_t mid = (uint32_t)(((((uint64_t)w1 << 32) | w2) << off) >> 32);
-        const uint32_t lo = (uint32_t)(((((uint64_t)w2 << 32) | w3) << off) >> 32);
-        const uint32_t z = hi ? (uint32_t)__builtin_clz(hi) : 31u;        // a valid stream has a one within 32 bits
-        const uint32_t s1 = z + 1;                                        // 1..32
-        const uint32_t p0 = (uint32_t)(((((uint64_t)hi << 32) | mid) << s1) >> 32);
-        const uint32_t p1 = (uint32_t)(((((uint64_t)mid << 32) | lo) << s1) >> 32);
+        const int32_t q = rm1 >> 5;
+        const uint32_t s = ~(uint32_t)rm1;
+        const uint32_t w0 = sw[q], w1 = sw[q + 1], w2 = sw[q + 2], w3 = sw[q + 3];
+        const uint32_t hi = __builtin_amdgcn_alignbit(w0, w1, s);
+        const uint32_t mid = __builtin_amdgcn_alignbit(w1, w2, s);
+        const uint32_t lo = __builtin_amdgcn_alignbit(w2, w3, s);
+        const uint32_t z0 = leading_zeros_raw(hi), z = z0 < 31u ? z0 : 31u;   // a valid stream has a one within 32 bits
         uint32_t gapv, top, used;
         if (z < 31) {
-            const uint64_t w = (((uint64_t)p0 << 32) | p1) << k;          // k <= 15
-            gapv = (z << k) | (uint32_t)(((uint64_t)p0 << k) >> 32);
-            top = (uint32_t)(w >> 32);
-            used = s1 + k;
+            const uint32_t low = __builtin_amdgcn_alignbit(hi, mid, 31u - z);     // the 32 bits behind the one
+            used = z + 1 + k;                                              // 1 .. 46
+            gapv = (z << k) | ((low >> 1) >> (31u - k));
+            const uint32_t x0 = used < 32u ? hi : mid, x1 = used < 32u ? mid : lo, u = used & 31u;
+            top = (x0 << u) | ((x1 >> 1) >> (u ^ 31u));
         } else {
-            gapv = p0; top = p1; used = s1 + 32;
+            gapv = mid; top = lo; used = 64;
         }
-        const Decoded q = decode_symbol(d, tb, top);
+        const Decoded sy = decode_symbol(d, tb, top);
         const uint32_t row = st.row + gapv;
-        st.bp += used + q.len;
+        rm1 += (int32_t)(used + sy.len);
         st.row = row + 1;
-        emit(st.wpos, row, q.sym, q.val);
+        emit(st.wpos, row, sy.sym, sy.val);
         st.wpos++;
     }
+    st.bp = (uint32_t)(rm1 + 1) + (src.wbase << 5);
 }
 
 // The same from any word source, one field at a time (streams too long to stage, and the

@@ -207,24 +207,24 @@ decode_to_index_kernel(DevBlob d, IdxT* idx, uint64_t pitch, uint32_t shac, uint
     }
     __syncthreads();
     if (!live) return;
-    auto walk = [&](auto src, auto rsrc) {
-        if (shac && d.rice) {
-            gap_advance_slow(d, tb, src, st, st.wend, [&](uint32_t, uint32_t row, uint32_t s, float) {
-                idx[(uint64_t)row * pitch + col] = (IdxT)(s + 1);
-            });
-        } else if (shac) {
-            shac_advance(d, tb, src, st, st.wend, [&](uint32_t p, uint32_t, uint32_t s, float) {
-                const uint32_t row = rsrc.field((uint64_t)p * d.ri_bits, d.ri_bits);
-                idx[(uint64_t)row * pitch + col] = (IdxT)(s + 1);
-            });
-        } else {
-            hac_advance(d, tb, src, st, st.wend, [&](uint32_t, uint32_t row, uint32_t s, float) {
-                idx[(uint64_t)row * pitch + col] = (IdxT)s;
-            });
-        }
-    };
-    if (staged) walk(WordSrc<true>{ sstage, wlo }, WordSrc<true>{ rstage, rwlo });
-    else walk(WordSrc<false>{ d.stream, 0 }, WordSrc<false>{ d.ri, 0 });
+    auto gap = [&](uint32_t, uint32_t row, uint32_t s, float) { idx[(uint64_t)row * pitch + col] = (IdxT)(s + 1); };
+    auto entry = [&](uint32_t, uint32_t row, uint32_t s, float) { idx[(uint64_t)row * pitch + col] = (IdxT)s; };
+    const WordSrc<true> src = { sstage, wlo }, rsrc = { rstage, rwlo };
+    const WordSrc<false> gsrc = { d.stream, 0 }, grsrc = { d.ri, 0 };
+    if (fields) {
+        auto field = [&](auto rs) {
+            return [&, rs](uint32_t p, uint32_t, uint32_t s, float) { idx[(uint64_t)rs.field((uint64_t)p * d.ri_bits, d.ri_bits) * pitch + col] = (IdxT)(s + 1); };
+        };
+        if (staged) shac_advance(d, tb, src, st, st.wend, field(rsrc));
+        else shac_advance(d, tb, gsrc, st, st.wend, field(grsrc));
+    } else if (shac) {
+        if (staged) gap_advance(d, tb, src, st, st.wend, gap);
+        else gap_advance_slow(d, tb, gsrc, st, st.wend, gap);
+    } else {
+        if (staged && d.zero_len == 1) hac_advance_zrun(d, tb, src, st, st.wend, entry);
+        else if (staged) hac_advance(d, tb, src, st, st.wend, entry);
+        else hac_advance(d, tb, gsrc, st, st.wend, entry);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -256,54 +256,58 @@ transpose_pad_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64
     }
 }
 
-// Same re-layout for panels of exactly 32 batch columns: a block turns 32 batch rows x 128
-// features into one contiguous 16 KB piece of a panel.  With X 16-byte aligned (vec = 1) the
-// reads are 128-bit (512 bytes per batch row) and so are the writes.
+// Same re-layout for panels of exactly 32 batch columns: a block turns 32 batch rows x F features into one contiguous piece of a
+// panel (F = 128: 16 KB).  With X 16-byte aligned (vec = 1) the reads are 128-bit (4 F bytes per batch row) and so are the
+// writes.  A small X is a matter of latency, and of CUs that have nothing to do: F = 32 where 128 would leave fewer than kTurnBlocks blocks
+// (4096 features, 64 rows 13.5 -> 13.2 us for the whole product; 25088, 32 rows 23.0 -> 22.7; but 256 rows 109.5 and 110.7).
+constexpr uint32_t kTurnBlocks = 512;
+template <uint32_t F>
 __global__ void __launch_bounds__(256)
 transpose_panel32_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64_t ldx,
                          float* __restrict__ XT, uint32_t vec)
 {
-    __shared__ float tile[32][129];
-    const uint32_t r0 = blockIdx.x * 128, b0 = blockIdx.y * 32;
+    constexpr uint32_t Q = F / 4, N4 = F / 32, N1 = F / 8;
+    __shared__ float tile[32][F + 1];
+    const uint32_t r0 = blockIdx.x * F, b0 = blockIdx.y * 32;
     // All loads of a thread are issued before the first is used: rows past B and features past n
     // are read from a clamped, valid address and replaced by zero afterwards (a guarded load would
     // be compiled into load / wait / store turns, one trip to memory each).
-    if (vec && r0 + 128 <= n) {
-        float4 v[4];
+    if (vec && r0 + F <= n) {
+        float4 v[N4];
 #pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) {
-            const uint32_t idx = threadIdx.x + 256 * i;          // float4 index: 32 rows x 32 quads
-            const uint32_t b = b0 + (idx >> 5), q = idx & 31;
+        for (uint32_t i = 0; i < N4; ++i) {
+            const uint32_t idx = threadIdx.x + 256 * i;          // float4 index: 32 rows x Q quads
+            const uint32_t b = b0 + idx / Q, q = idx % Q;
             v[i] = *reinterpret_cast<const float4*>(X + (uint64_t)(b < B ? b : B - 1) * ldx + r0 + 4 * q);
         }
 #pragma unroll
-        for (uint32_t i = 0; i < 4; ++i) {
+        for (uint32_t i = 0; i < N4; ++i) {
             const uint32_t idx = threadIdx.x + 256 * i;
-            const uint32_t b = idx >> 5, q = idx & 31;
+            const uint32_t b = idx / Q, q = idx % Q;
             const bool ok = b0 + b < B;
             tile[b][4 * q + 0] = ok ? v[i].x : 0.0f; tile[b][4 * q + 1] = ok ? v[i].y : 0.0f;
             tile[b][4 * q + 2] = ok ? v[i].z : 0.0f; tile[b][4 * q + 3] = ok ? v[i].w : 0.0f;
         }
     } else {
-        float v[16];
+        float v[N1];
 #pragma unroll
-        for (uint32_t i = 0; i < 16; ++i) {
+        for (uint32_t i = 0; i < N1; ++i) {
             const uint32_t idx = threadIdx.x + 256 * i;
-            const uint32_t b = b0 + (idx >> 7), r = r0 + (idx & 127);
+            const uint32_t b = b0 + idx / F, r = r0 + idx % F;
             v[i] = X[(uint64_t)(b < B ? b : B - 1) * ldx + (r < n ? r : n - 1)];
         }
 #pragma unroll
-        for (uint32_t i = 0; i < 16; ++i) {
+        for (uint32_t i = 0; i < N1; ++i) {
             const uint32_t idx = threadIdx.x + 256 * i;
-            const uint32_t b = idx >> 7, r = idx & 127;
+            const uint32_t b = idx / F, r = idx % F;
             tile[b][r] = (b0 + b < B && r0 + r < n) ? v[i] : 0.0f;
         }
     }
     __syncthreads();
     float* out = XT + (uint64_t)blockIdx.y * n * 32 + (uint64_t)r0 * 32;
 #pragma unroll
-    for (uint32_t i = 0; i < 4; ++i) {
-        const uint32_t idx = threadIdx.x + 256 * i;              // float4 index: 128 features x 8 quads of batch
+    for (uint32_t i = 0; i < N4; ++i) {
+        const uint32_t idx = threadIdx.x + 256 * i;              // float4 index: F features x 8 quads of batch
         const uint32_t r = idx >> 3, bq = (idx & 7) * 4;
         if (r0 + r < n) {
             const float4 v = make_float4(tile[bq][r], tile[bq + 1][r], tile[bq + 2][r], tile[bq + 3][r]);
@@ -1491,11 +1495,13 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         XT = xt;
         if (!reuse_xt) {
             if (panel_w == 32) {
-                dim3 grid((d.n + 127) / 128, (uint32_t)((B + 31) / 32));     // what lies past the batch is never read
+                const uint32_t panels = (uint32_t)((B + 31) / 32);               // what lies past the batch is never read
+                const uint32_t features = (uint64_t)(d.n + 127) / 128 * panels < kTurnBlocks ? 32u : 128u;
+                const dim3 grid((d.n + features - 1) / features, panels);
                 const uint32_t vec = (reinterpret_cast<uintptr_t>(d_X) % 16 == 0 && ldx % 4 == 0) ? 1u : 0u;
-                hipLaunchKernelGGL(transpose_panel32_kernel, grid, dim3(256), 0, stream,
+                hipLaunchKernelGGL(features == 32 ? transpose_panel32_kernel<32> : transpose_panel32_kernel<128>, grid, dim3(256), 0, stream,
                                    d_X, (uint32_t)B, d.n, (uint64_t)ldx, xt, vec);
-                note_kernel("transpose_panel32_kernel");
+                note_kernel("transpose_panel32_kernel<%u>", features);
             } else {
                 dim3 grid((d.n + 31) / 32, (bs.Bp + 31) / 32);
                 hipLaunchKernelGGL(transpose_pad_kernel, grid, dim3(256), 0, stream,
