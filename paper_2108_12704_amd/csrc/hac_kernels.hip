@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 
@@ -1068,25 +1069,7 @@ uint32_t default_cpw(const hac_desc_t* desc)
     return cpw;
 }
 
-// Dense route (decode to an index map, then MFMA tiles) or sparse route (vector FMAs per non-zero)?  The shorter of
-// two time estimates whose constants are fitted to both routes' times, forced, on 755 layers (200 x 10 to 25088 x 4096,
-// 50 to 99 % pruned, 33 to 8192 rows):
-//   sparse: 12.8 us, the re-layout of X (4.3 TB/s), 4 bytes gathered per non-zero and batch column (35 TB/s; batch
-//           columns in panels of 32), 9 ns per non-zero of a column and panel (a wavefront walks its columns' lists
-//           one after the other), and Y, written a few columns at a time (0.21 TB/s);
-//   dense : 5.6 us, the map cleared and read (1.2 TB/s), 9 ns per thousand non-zeros scattered into it, half a us per
-//           symbol of a chunk (one lane decodes a chunk), and the product as its plan estimates it.
-// The route so chosen costs 1.9 % over the better one (geometric mean over the 755; worst 2.5 times) and 1.7 % on 200 other
-// layers (worst 1.5 times); the fp32 kernel's constants with its plan cost 18 % (8.3 times), with the plan of the
-// kernel on bf16 parts 15 % (7.6 times).
-// Both sides were timed while the sparse route passed over the list 32 columns at a time with one wavefront per column of W.
-// Since passes are wider (pass_columns) and several wavefronts share a column (plan_split) it is quicker than this estimate at
-// heights of W below about 8000: 4096 x 1000, 10 %, 64 rows 13.2 us (estimated 25), 1000 x 4096, 10 %, 256 rows 26.2 (52; the dense
-// route's estimate of 44 wins there).  What the rule costs over the better route now has not been measured.
-// Batches of 32 rows and less are one panel of the sparse route and too few for MFMA tiles; layers with one non-zero in
-// 40 entries or fewer take the sparse route as they always did (of 24 measured ones the dense route was more than
-// 15 % quicker on three, 25088 x 16 at 256 rows 46 against 63 us).
-// `room`: bytes of workspace there are, for hac_dot_noalloc; the plan then splits K only as far as the parts fit.
+// `bytes` of workspace, the index map in the first idx_bytes of them.
 struct DenseRoute { bool use; uint32_t idx_bits; uint64_t pitch; size_t idx_bytes, bytes; hac_internal::GemmPlan plan; };
 
 bool size_index_map(const hac_desc_t* desc, DenseRoute& r)
@@ -1097,27 +1080,6 @@ bool size_index_map(const hac_desc_t* desc, DenseRoute& r)
     r.pitch = (desc->m + 15) / 16 * 16;
     r.idx_bytes = (size_t)((desc->n * r.pitch * (r.idx_bits / 8) + 255) / 256 * 256);
     return true;
-}
-
-DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room = ~(size_t)0)
-{
-    DenseRoute r = {};
-    const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
-    if (B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && (B <= 32 || desc->nnz <= desc->n * desc->m / 40)) || !size_index_map(desc, r)) return r;
-    const hac_internal::GemmPlan plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m,
-                                                                      room > r.idx_bytes ? room - r.idx_bytes : 0);
-    r.plan = plan;
-    r.bytes = r.idx_bytes + ((plan.part_bytes + 255) / 256 * 256);
-    if (force == HAC_LAUNCH_DENSE_ROUTE) { r.use = true; return r; }
-    if (force == HAC_LAUNCH_SPARSE_ROUTE) return r;
-    const double nnz = (double)desc->nnz, n = (double)desc->n, m = (double)desc->m, b = (double)B;
-    const double bp = (double)((B + 31) / 32 * 32), panels = std::min(bp / 32.0, 8.0);      // of a block of the sparse route
-    const double sparse_us = 12.8 + 1.85e-6 * n * bp + nnz * bp * 1.15e-7 + 8.9e-3 * panels * nnz / m + 1.87e-5 * b * m;
-    double chunk = (double)hac_internal::chunk_base(desc->chunk);
-    if (desc->chunk & hac_internal::kChunkPerColumn) chunk = std::max(chunk, (double)desc->max_col_nnz / 64.0);
-    const double dense_us = 5.6 + 0.8e-6 * (double)r.idx_bytes + 9e-6 * nnz + 0.49 * chunk + plan.us;
-    r.use = dense_us < sparse_us;
-    return r;
 }
 
 } // namespace
@@ -1187,6 +1149,17 @@ uint32_t default_staging_words(const hac_desc_t* desc, uint32_t cpw)
     return round_up((uint32_t)(est < 8192.0 ? est : 8192.0), 16);
 }
 
+// the list of one batch's non-zeros, of a wavefront
+uint32_t default_list_entries(const hac_desc_t* desc, uint32_t cpw)
+{
+    double est = (double)desc->max_col_nnz * cpw;
+    // (with chunk sizes per column a column has at most 64 chunks: a batch then never holds more than the longest column)
+    const double one_batch = (desc->chunk & hac_internal::kChunkPerColumn) ? (double)desc->max_col_nnz * cpw
+                                                                           : 64.0 * desc->chunk;
+    if (est > one_batch) est = one_batch;
+    return round_up((uint32_t)(est < 2048.0 ? (est > 1.0 ? est : 1.0) : 2048.0), 64);
+}
+
 // Batches of 2 to 8 rows and a short X (at most 32 KB once padded to a power of two of rows):
 // every block keeps its own feature-major copy of X in LDS, so there is no re-layout launch and
 // no workspace.  Measured on 512 x 4096 layers: 7-8 us against 9-10 (4 rows), 10 against 13-14
@@ -1229,7 +1202,8 @@ XldsPlan xlds_plan(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch
 
 // Several wavefronts per column (hac_split.h)?  `direct`: a lane takes a non-zero and reads X as it is (`copy`: from the
 // feature-major copy all the same, because the caller asked for one), else lanes take batch columns of the copy.
-struct SplitPlan { bool use, direct, copy; uint32_t nbd; size_t lds; SplitParams p; };
+// turn: list entries that a wavefront takes side by side; rounds: how many times over the blocks fill the chip.
+struct SplitPlan { bool use, direct, copy; uint32_t nbd; size_t lds; uint64_t turn; double rounds; SplitParams p; };
 
 constexpr uint64_t kDirectFloats = 1u << 19;     // of X; a larger one is always re-laid out
 
@@ -1305,9 +1279,82 @@ SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* laun
     // these lines 103 of 8146 other ones, up to 1.4 times, where the blocks of a second round are few; it gains 43 % in the mean.)
     const uint64_t resident = std::min<uint64_t>(kLdsLimit / s.lds, 32u / p.waves);
     const double rounds = (double)(nblocks * tiles) / (256.0 * (double)resident);
+    s.turn = turn; s.rounds = rounds;
     if (s.direct && B <= 4 ? rounds > 0.95 || (resident * p.waves < 16 && rounds > 0.7) : rounds > 5.0) return s;
     s.use = true;
     return s;
+}
+
+// Estimated times of the two routes, for the choice between them; B > 32.  Each kernel's constants are fitted to its times, the route
+// forced, on 13000 products (300 x 10 to 25088 x 4096, 45 to 98.5 % pruned, 16 to 256 values, 33 to 4000 rows, both formats and
+// Rice-coded gaps).  `chunk`: codewords that a lane decodes one after the other; blocks that do not fit the chip at once go in rounds.
+//   several wavefronts per column, X as it is: 4.8 us a round, 0.35 us a codeword, 0.014 us a lane's turn and row of X, the values
+//       of X fetched, and lines of X (95 % of the products within 12 %);
+//   ... from the copy: 8.4 us, the copy's two passes, 0.24 us a codeword, 0.28 us a turn of ten entries, 4 bytes gathered per
+//       non-zero and batch column at 36 TB/s (-21 .. +16 %);
+//   one wavefront per column: the same, as its passes and the wavefronts that LDS leaves a CU make it (-30 .. +16 %);
+//   dense: 3.7 us, the map cleared, written and read (2.1 TB/s), 9 ns per thousand non-zeros scattered into it, 0.28 us a codeword, the
+//       product as its plan estimates it and the launch that adds its parts (-15 .. +12 %).
+// What a product takes on the route so chosen, over the better one, 4500 other products of more than one non-zero in 40 entries: 1.003
+// (geometric mean; worst 1.65).  The estimate before, fitted while passes were 32 columns wide and a column had one wavefront, took
+// the dense route twice as often as it was the quicker one: 1.21, worst 3.0 (929 x 11, 285 rows 17.7 us, 6.5 on the other route; 24391 x 100,
+// 50 %, 46 rows 153 and 51).
+double sparse_us(const hac_desc_t* desc, int64_t B)
+{
+    const double n = (double)desc->n, m = (double)desc->m, b = (double)B, nnz = (double)desc->nnz;
+    const double bp = (double)((B + 31) / 32 * 32);
+    double chunk = (double)hac_internal::chunk_base(desc->chunk);
+    if (desc->chunk & hac_internal::kChunkPerColumn) chunk = std::max(chunk, (double)desc->max_col_nnz / 64.0);
+    const SplitPlan sp = plan_split(desc, B, nullptr);
+    if (sp.use) {
+        const double rounds = std::max(1.0, std::ceil(sp.rounds)), shares = (double)(1u << sp.p.split_log2);
+        if (sp.direct) {
+            const double turns = std::ceil((double)desc->max_col_nnz / (64.0 * shares));
+            return rounds * (4.77 + 0.348 * chunk + 0.014 * turns * (double)sp.p.width) + 3.44e-7 * nnz * b + 6.1e-8 * n * m * b;
+        }
+        const double turns = std::ceil((double)desc->max_col_nnz / ((double)(sp.turn / 8 * 10) * shares));
+        return 8.37 + 1.77e-6 * n * bp + rounds * (0.24 * chunk + 0.283 * turns) + 1.096e-7 * nnz * bp;
+    }
+    const uint32_t cpw = default_cpw(desc), width = std::max(32u, pass_columns(desc, B));
+    const BatchShape bs = batch_shape(B, width, kDefaultTile);
+    const uint64_t here = (uint64_t)std::min<int64_t>(B, kDefaultTile), passes = (here + width - 1) / width;
+    const uint32_t list_cap = default_list_entries(desc, cpw), chunk_least = hac_internal::chunk_base(desc->chunk);
+    const uint64_t chunks = (desc->max_col_nnz + chunk_least - 1) / chunk_least;
+    const bool split = cpw * chunks > 64 || cpw * desc->max_col_nnz > list_cap;
+    const size_t per_wave = 4ull * default_staging_words(desc, cpw) + 8ull * list_cap + (split ? 4ull * bs.npass * bs.nb * 64u : 0u);
+    uint64_t waves = 1;
+    for (uint64_t w = 16; w >= 1; w >>= 1) {
+        const size_t block = table_bytes_of(desc) + w * per_wave;
+        if (block <= kLdsLimit) waves = std::max(waves, std::min<uint64_t>(16, kLdsLimit / block * w));
+    }
+    const double rounds = std::max(1.0, std::ceil(m * (double)((B + 255) / 256) / ((double)cpw * 256.0 * (double)waves)));
+    const double column = nnz / m;
+    return 7.77 + 2.37e-6 * n * bp + 7.92e-8 * nnz * bp + 5.2e-6 * m * b +
+           rounds * (0.155 * chunk * cpw + (double)passes * (0.714 + 1.334e-3 * column + 1.47e-4 * column * (double)width));
+}
+
+double dense_us(const hac_desc_t* desc, const DenseRoute& r)
+{
+    double chunk = (double)hac_internal::chunk_base(desc->chunk);
+    if (desc->chunk & hac_internal::kChunkPerColumn) chunk = std::max(chunk, (double)desc->max_col_nnz / 64.0);
+    return 3.72 + 4.8e-7 * (double)r.idx_bytes + 9.25e-6 * (double)desc->nnz + 0.282 * chunk + 0.929 * r.plan.us + (r.plan.splits > 1 ? 1.9 : 0.0);
+}
+
+// Dense route (decode to an index map, then MFMA tiles) or sparse route (vector FMAs per non-zero)?  The shorter of the two
+// estimates.  Batches of 32 rows and less are one panel of the sparse route and too few for MFMA tiles; layers with one non-zero in
+// 40 entries or fewer take the sparse route as they always did (of 24 measured ones the dense route was more than
+// 15 % quicker on three, 25088 x 16 at 256 rows 46 against 63 us).
+// `room`: bytes of workspace there are, for hac_dot_noalloc; the plan then splits K only as far as the parts fit.
+DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room = ~(size_t)0)
+{
+    DenseRoute r = {};
+    const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
+    if (B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && (B <= 32 || desc->nnz <= desc->n * desc->m / 40)) || !size_index_map(desc, r)) return r;
+    r.plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m, room > r.idx_bytes ? room - r.idx_bytes : 0);
+    r.bytes = r.idx_bytes + ((r.plan.part_bytes + 255) / 256 * 256);
+    if (force) { r.use = force == HAC_LAUNCH_DENSE_ROUTE; return r; }
+    r.use = dense_us(desc, r) < sparse_us(desc, B);
+    return r;
 }
 
 // bytes of workspace the sparse route needs: partial sums of the row-blocked kernel, or the feature-major copy of X
@@ -1396,9 +1443,16 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
                            (uint64_t)(dr.idx_bytes / 4), 0u);
         note_kernel("fill_u32_kernel");
         note_kernel("decode_to_index_kernel<unsigned %s>", dr.idx_bits == 8 ? "char" : "short");
-        // LDS beside the tables: room for the stream words (and ri fields) of a block's chunks
-        const uint32_t s_words = 6144, r_words = (format == HAC_FORMAT_SHAC && !d.rice) ? 6144u : 0u;
+        // LDS beside the tables: room for the stream words (a quarter more than a block's chunks have on average) and ri fields of a
+        // block's chunks.  A block whose words do not fit reads them from the blob, a trip to memory per codeword (9402 x 2297, 46 %, sHAC, 34 rows,
+        // with 6144 words for each: 327 us); with no more than is needed more blocks share a CU.
+        const double chunk_words = d.n_chunks ? 256.0 / 32.0 * (double)desc->total_bits / (double)d.n_chunks : 0.0;
+        const uint64_t chunk_nnz = std::min<uint64_t>(std::max<uint64_t>(hac_internal::chunk_base(desc->chunk),
+                                                      desc->chunk & hac_internal::kChunkPerColumn ? (desc->max_col_nnz + 63) / 64 : 0), desc->max_col_nnz);
+        uint32_t s_words = round_up((uint32_t)std::min(1.25 * chunk_words + 64.0, 20480.0), 4), r_words = 0;
+        if (format == HAC_FORMAT_SHAC && !d.rice) r_words = round_up((uint32_t)std::min<uint64_t>(256 * chunk_nnz * d.ri_bits / 32 + 16, 28672), 4);
         const uint32_t c_words = d.m + 1 <= 8192 ? round_up(d.m + 1, 4) : 0u;       // colchunk, for the owner search
+        if (4ull * (table_words(d) + s_words + r_words + c_words) > kLdsLimit - 64) { s_words = std::min(s_words, 6144u); r_words = std::min(r_words, 6144u); }
         const size_t lds = 4ull * (table_words(d) + s_words + r_words + c_words);
         const uint32_t grid = (d.n_chunks + 255) / 256;
         const uint32_t is_shac = format == HAC_FORMAT_SHAC ? 1u : 0u;
@@ -1544,14 +1598,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     }
     // per-wave LDS: the stream (and ri) words of the wave's columns, and the list of one batch's non-zeros
     if (!sbuf_words) sbuf_words = default_staging_words(desc, cpw);
-    if (!list_cap) {
-        double est = (double)desc->max_col_nnz * cpw;
-        // (with chunk sizes per column a column has at most 64 chunks: a batch then never holds more than the longest column)
-        const double one_batch = (desc->chunk & hac_internal::kChunkPerColumn) ? (double)desc->max_col_nnz * cpw
-                                                                               : 64.0 * desc->chunk;
-        if (est > one_batch) est = one_batch;
-        list_cap = round_up((uint32_t)(est < 2048.0 ? (est > 1.0 ? est : 1.0) : 2048.0), 64);
-    }
+    if (!list_cap) list_cap = default_list_entries(desc, cpw);
     if (bs.gw == 1 && bs.npass == 1 && !list_kernel) {
         // at most 4 batch columns: lanes multiply what they decode, no list
         const uint32_t sum_words = round_up(cpw * bs.nb, 4);

@@ -81,6 +81,20 @@ def test_the_quicker_route_is_taken(n, m, prune, B, sparse_us, dense_us):
     assert hac.hac_dot_route(d, B) == (1 if dense_us < sparse_us else 0)
 
 
+# the same with the kernels that run now, longest column and its bits as they were: several wavefronts per column with X as it is or
+# from its copy, one wavefront per column with wide and narrow passes, lists in several windows
+@pytest.mark.parametrize("n,m,prune,B,k,most,bits,sparse_us,dense_us",
+                         [(497, 908, 0.814, 61, 118, 121, 1333, 10, 19), (929, 11, 0.85, 285, 86, 170, 1800, 7, 18), (1424, 1275, 0.874, 36, 25, 223, 1923, 11, 23),
+                          (3181, 1825, 0.86, 51, 102, 509, 4419, 17, 39), (529, 243, 0.95, 417, 219, 41, 465, 10, 20), (24391, 100, 0.5, 46, 24, 12300, 60000, 51, 153),
+                          (362, 4012, 0.671, 341, 26, 158, 890, 44, 29), (6818, 765, 0.555, 333, 65, 3148, 20747, 366, 75),
+                          (4962, 123, 0.617, 3884, 150, 1971, 19240, 160, 59), (22466, 1346, 0.867, 183, 58, 3147, 25129, 338, 140)])
+def test_the_quicker_route_with_several_wavefronts_per_column(n, m, prune, B, k, most, bits, sparse_us, dense_us):
+    nnz = int(n * m * (1 - prune))
+    d = header(hac.HAC_FORMAT_HAC, n, m, nnz, k, max(4, -(-most // 64)))
+    d.max_col_nnz, d.max_col_bits = most, bits
+    assert hac.hac_dot_route(d, B) == (1 if dense_us < sparse_us else 0)
+
+
 @pytest.mark.parametrize("n,m", [(1_000_000, 1), (67_000_000, 1), (300_000, 65), (4096, 10), (25088, 4096), (100_000, 129)])
 def test_device_encoder_workspace_follows_the_matrix(n, m):
     """At most as much as W beside the fixed tables (about 4 MB), whatever the matrix's shape."""
