@@ -50,7 +50,8 @@ constexpr uint64_t kMaxRows = 65535ull * 1024;
 constexpr uint32_t kTileCols = 64, kTileRows = 32;        // what a wavefront reads at a time in step 1
 constexpr uint32_t kQuota = 4;                            // packed values per column of a tile: an eighth of it
 constexpr uint32_t kNotPacked = 0xffffu;
-constexpr uint32_t kScanWaves = 8, kScanQueue = 1024, kScanBlocks = 1024;   // 40 KB of LDS a block: four on a CU
+constexpr uint32_t kScanWaves = 8, kScanQueue = 1024, kScanBlocks = 512;   // two blocks a CU: their registers fill it
+constexpr uint64_t kCachedEntries = 64u << 20;            // 256 MB of W, the size of the memory-side cache
 constexpr uint32_t kCodeSlotsLds = 2048;                  // code tables up to this size (24 KB) are copied to LDS
 
 // Rows per segment: 512 on a large matrix, fewer on a small one, so that there are about 256 K
@@ -106,9 +107,13 @@ __device__ void table_add(const Histogram& t, uint32_t key, uint32_t add)
 // lane l owns column l, so the bit of every row falls into the lane's own word.  A prefix sum of the
 // lanes' counts gives every lane its place in the tile's list; the list is put together in LDS, from
 // where the wavefront counts it (64 values at a time, whatever the density) and copies it out.  Tiles
-// are dealt over a grid that fits the chip once, so that a block merges its histogram only once.
+// are dealt over a grid that fits the chip once, so that a block merges its histogram only once (4096 x 4096, 40 %, with twice as
+// many blocks 286 us for the whole call, 274 so; a W that comes from memory is read more evenly by twice as many: 220.5 and 218.5).
 // The words and the room per tile need no atomics; what bounds it is reading W.
+// ONCE: W does not stay in any cache until the emission may ask for some of it again, and is read past them (25088 x 4096, 411 MB:
+// 227 -> 218 us for the whole call; but 4096 x 4096, 40 %, 286 -> 292).
 // mask, off: [rows / 32][m]; values: [rows / 32][m][kQuota], a tile's columns' room taken as one list.
+template <bool ONCE>
 __global__ void __launch_bounds__(64 * kScanWaves)
 enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ldw, uint32_t col_groups, uint32_t tiles,
                 uint32_t* __restrict__ mask, uint16_t* __restrict__ off, uint32_t* __restrict__ values, Histogram table)
@@ -137,7 +142,7 @@ enc_scan_kernel(const float* __restrict__ W, uint32_t n, uint32_t m, uint64_t ld
         float v[kTileRows];
         if (rows == kTileRows) {
 #pragma unroll
-            for (uint32_t u = 0; u < kTileRows; ++u) v[u] = col[u * ldw];
+            for (uint32_t u = 0; u < kTileRows; ++u) v[u] = ONCE ? __builtin_nontemporal_load(col + u * ldw) : col[u * ldw];
         } else {
 #pragma unroll
             for (uint32_t u = 0; u < kTileRows; ++u) v[u] = u < rows ? col[u * ldw] : 0.0f;
@@ -771,7 +776,7 @@ enc_col_scan_kernel(const EncCode* __restrict__ code, uint32_t m, uint32_t S, ui
 }
 
 // Step 4.  One block: the longest column gives the chunk size, then running sums over the columns, a range of
-// columns per thread.  col_arrays: first chunk, CSC position and first stream bit of every column and one
+// columns per thread (few columns: fewer wavefronts, which wait for each other).  col_arrays: first chunk, CSC position and first stream bit of every column and one
 // past it, `stride` words apart.  The counts go to *result and, where the host waits for them in pinned memory, to *mailbox.
 __global__ void __launch_bounds__(1024)
 enc_columns_kernel(const EncCode* __restrict__ code, uint32_t m, const uint32_t* __restrict__ col_nnz, const unsigned long long* __restrict__ col_bits,
@@ -784,7 +789,7 @@ enc_columns_kernel(const EncCode* __restrict__ code, uint32_t m, const uint32_t*
     EncResult r = {};
     r.code = *code;
     if (r.code.status == kCodeOk) {
-        const uint32_t per = (m + 1023) / 1024, j0 = (uint64_t)t * per < m ? t * per : m, j1 = m - j0 < per ? m : j0 + per;
+        const uint32_t per = (m + blockDim.x - 1) / blockDim.x, j0 = (uint64_t)t * per < m ? t * per : m, j1 = m - j0 < per ? m : j0 + per;
         uint32_t most = 0, nnz = 0, chunks = 0;
         unsigned long long longest = 0, bits = 0;
         for (uint32_t j = j0; j < j1; j += 4) {                              // (four columns requested together)
@@ -806,7 +811,7 @@ enc_columns_kernel(const EncCode* __restrict__ code, uint32_t m, const uint32_t*
         }
         if (lane == 0) { wave_nnz[wave] = most; wave_bits[wave] = longest; }
         __syncthreads();
-        for (uint32_t w = 0; w < 16; ++w) {
+        for (uint32_t w = 0; w < blockDim.x / 64; ++w) {
             most = wave_nnz[w] > most ? wave_nnz[w] : most; longest = wave_bits[w] > longest ? wave_bits[w] : longest;
         }
         __syncthreads();
@@ -828,7 +833,7 @@ enc_columns_kernel(const EncCode* __restrict__ code, uint32_t m, const uint32_t*
         if (lane == 63) { wave_nnz[wave] = in; wave_chunks[wave] = ic; wave_bits[wave] = ib; }
         __syncthreads();
         uint64_t pos = in - nnz, chunk = ic - chunks, bit = ib - bits;
-        for (uint32_t w = 0; w < 16; ++w) {
+        for (uint32_t w = 0; w < blockDim.x / 64; ++w) {
             if (w < wave) { pos += wave_nnz[w]; chunk += wave_chunks[w]; bit += wave_bits[w]; }
             r.col_nnz += wave_nnz[w]; r.chunks += wave_chunks[w]; r.col_bits += wave_bits[w];
         }
@@ -1005,7 +1010,7 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
         hipLaunchKernelGGL(enc_col_scan_kernel, dim3((uint32_t)(((uint64_t)m + 15) / 16)), dim3(256), 0, stream, d_code, (uint32_t)m, S,
                            dptr(L.seg_nnz), dptr(L.seg_bits), static_cast<const uint32_t*>(d_gap_bits),
                            static_cast<const unsigned long long*>(d_gap_total), SM, dptr(L.col_nnz), d_col_bits);
-        hipLaunchKernelGGL(enc_columns_kernel, dim3(1), dim3(1024), 0, stream, d_code, (uint32_t)m, dptr(L.col_nnz), d_col_bits,
+        hipLaunchKernelGGL(enc_columns_kernel, dim3(1), dim3(m <= 1024 ? 256 : 1024), 0, stream, d_code, (uint32_t)m, dptr(L.col_nnz), d_col_bits,
                            dptr(L.flags), opts ? opts->chunk_nnz : 0u, static_cast<const unsigned long long*>(d_gap_total), dptr(L.col_arrays),
                            (uint64_t)L.col_stride, d_result, box ? &box->result : nullptr);
         hipError_t err = hipGetLastError();
@@ -1022,8 +1027,9 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
     try {
         // ---- steps 1 to 4 ----
         hipLaunchKernelGGL(fill_zero_kernel, dim3(512), dim3(256), 0, stream, dptr(L.keys), (uint64_t)(L.used - L.keys) / 4);
-        const uint64_t scan_blocks = std::min<uint64_t>((tiles + kScanWaves - 1) / kScanWaves, kScanBlocks);
-        hipLaunchKernelGGL(enc_scan_kernel, dim3((uint32_t)scan_blocks), dim3(64 * kScanWaves), 0, stream, d_W, (uint32_t)n, (uint32_t)m,
+        const bool once = (uint64_t)n * (uint64_t)m > kCachedEntries;
+        const uint64_t scan_blocks = std::min<uint64_t>((tiles + kScanWaves - 1) / kScanWaves, once ? 2 * kScanBlocks : kScanBlocks);
+        hipLaunchKernelGGL(once ? enc_scan_kernel<true> : enc_scan_kernel<false>, dim3((uint32_t)scan_blocks), dim3(64 * kScanWaves), 0, stream, d_W, (uint32_t)n, (uint32_t)m,
                            (uint64_t)ldw, col_groups, (uint32_t)tiles, dptr(L.mask), reinterpret_cast<uint16_t*>(ws + L.off),
                            dptr(L.values), hist);
         hipLaunchKernelGGL(enc_code_kernel, dim3(1), dim3(kCodeThreads), 0, stream, hist, (uint64_t)n * (uint64_t)m, shac ? 1u : 0u,

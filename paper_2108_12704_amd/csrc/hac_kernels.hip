@@ -1444,8 +1444,8 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         note_kernel("fill_u32_kernel");
         note_kernel("decode_to_index_kernel<unsigned %s>", dr.idx_bits == 8 ? "char" : "short");
         // LDS beside the tables: room for the stream words (a quarter more than a block's chunks have on average) and ri fields of a
-        // block's chunks.  A block whose words do not fit reads them from the blob, a trip to memory per codeword (9402 x 2297, 46 %, sHAC, 34 rows,
-        // with 6144 words for each: 327 us); with no more than is needed more blocks share a CU.
+        // block's chunks.  A block whose words do not fit reads them from the blob, a trip to memory per codeword (9402 x 2297, 46 %, sHAC, 34 rows, this route
+        // asked for, with 6144 words for each 356 us, 190 so); with no more than is needed more blocks share a CU.
         const double chunk_words = d.n_chunks ? 256.0 / 32.0 * (double)desc->total_bits / (double)d.n_chunks : 0.0;
         const uint64_t chunk_nnz = std::min<uint64_t>(std::max<uint64_t>(hac_internal::chunk_base(desc->chunk),
                                                       desc->chunk & hac_internal::kChunkPerColumn ? (desc->max_col_nnz + 63) / 64 : 0), desc->max_col_nnz);
