@@ -408,11 +408,10 @@ __device__ __forceinline__ void gap_advance(const DevBlob& d, const Tables& tb, 
         const uint32_t z0 = leading_zeros_raw(hi), z = z0 < 31u ? z0 : 31u;   // a valid stream has a one within 32 bits
         uint32_t gapv, top, used;
         if (z < 31) {
-            const uint32_t low = __builtin_amdgcn_alignbit(hi, mid, 31u - z);     // the 32 bits behind the one
-            used = z + 1 + k;                                              // 1 .. 46
-            gapv = (z << k) | ((low >> 1) >> (31u - k));
-            const uint32_t x0 = used < 32u ? hi : mid, x1 = used < 32u ? mid : lo, u = used & 31u;
-            top = (x0 << u) | ((x1 >> 1) >> (u ^ 31u));
+            const uint32_t p0 = __builtin_amdgcn_alignbit(hi, mid, 31u - z), p1 = __builtin_amdgcn_alignbit(mid, lo, 31u - z);   // behind the one
+            used = z + 1 + k;
+            gapv = (z << k) | ((p0 >> 1) >> (31u - k));
+            top = k ? __builtin_amdgcn_alignbit(p0, p1, 32u - k) : p0;
         } else {
             gapv = mid; top = lo; used = 64;
         }

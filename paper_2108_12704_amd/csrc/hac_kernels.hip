@@ -230,7 +230,8 @@ decode_to_index_kernel(DevBlob d, IdxT* idx, uint64_t pitch, uint32_t shac, uint
 
 // ---------------------------------------------------------------------------
 // X (B x n, row-major) -> XT, feature-major in panels of `wp` batch columns:
-// XT[(b / wp) * n * wp + r * wp + b % wp] = X[b][r], zero for B <= b < Bp (see panel_width).
+// XT[(b / wp) * n * wp + r * wp + b % wp] = X[b][r] (see panel_width).  What it holds past the batch is not read, or goes into sums
+// that are not stored; four columns of padding are not written (9973 x 1511, 7 %, 37 rows 21.7 -> 20.9 us for the whole product).
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 transpose_pad_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64_t ldx,
@@ -310,7 +311,7 @@ transpose_panel32_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, ui
     for (uint32_t i = 0; i < N4; ++i) {
         const uint32_t idx = threadIdx.x + 256 * i;              // float4 index: F features x 8 quads of batch
         const uint32_t r = idx >> 3, bq = (idx & 7) * 4;
-        if (r0 + r < n) {
+        if (r0 + r < n && b0 + bq < B) {                         // (four columns of padding are never read)
             const float4 v = make_float4(tile[bq][r], tile[bq + 1][r], tile[bq + 2][r], tile[bq + 3][r]);
             *reinterpret_cast<float4*>(out + (uint64_t)r * 32 + bq) = v;
         }
