@@ -1556,7 +1556,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
                 const uint32_t vec = (reinterpret_cast<uintptr_t>(d_X) % 16 == 0 && ldx % 4 == 0) ? 1u : 0u;
                 hipLaunchKernelGGL(features == 32 ? transpose_panel32_kernel<32> : transpose_panel32_kernel<128>, grid, dim3(256), 0, stream,
                                    d_X, (uint32_t)B, d.n, (uint64_t)ldx, xt, vec);
-                note_kernel("transpose_panel32_kernel<%u>", features);
+                note_kernel("transpose_panel32_kernel<%uu>", features);
             } else {
                 dim3 grid((d.n + 31) / 32, (bs.Bp + 31) / 32);
                 hipLaunchKernelGGL(transpose_pad_kernel, grid, dim3(256), 0, stream,
