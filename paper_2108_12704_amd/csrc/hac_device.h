@@ -120,12 +120,15 @@ struct Tables {
     bool small;                 // k_sym <= kCodebookLdsMax (uniform)
 };
 
+// codewords longer than the first-level table (none without symbols, whatever the rest of the header says)
+__device__ __forceinline__ bool longer_codes(const DevBlob& d) { return d.lmax > d.lut_bits && d.k_sym != 0; }
+
 // Code longer than the first-level table: {(symbol << 6) | length, value bits}.  Its length is the number of bounds it has passed,
 // four of them read at once (all lanes the same words), then two reads.  Some lane of a wavefront is here at almost every step of a HAC
 // stream: one length after the other, two reads each, made that lane's search the longest part of the step.
 __device__ __forceinline__ uint2 decode_long(const DevBlob& d, const Tables& t, uint32_t top)
 {
-    if (d.lmax <= d.lut_bits) return make_uint2(d.lmax ? d.lmax : 1u, 0u);       // no such code: a damaged stream; still makes progress
+    if (!longer_codes(d)) return make_uint2(d.lmax ? d.lmax : 1u, 0u);       // no such code: a damaged stream; still makes progress
     lds_cu32* bound = (lds_cu32*)t.bound;
     const uint32_t half = top >> 1;
     uint32_t l = d.lut_bits + 1;
@@ -181,10 +184,10 @@ __device__ __forceinline__ TableRegs request_tables(const DevBlob& d)
     // number of loads behind those a later wait is for is the same on both paths (and without branches beyond this uniform one:
     // a guarded load would be moved down beside its use).
     r.first = r.count = r.index = r.sort = r.cb = 0u;
-    if (d.lmax > d.lut_bits) {
+    if (longer_codes(d)) {
         const uint32_t l = threadIdx.x < 32u ? threadIdx.x : 32u;
         r.first = d.canon[l]; r.count = d.canon[33 + l]; r.index = d.canon[66 + l];
-        r.sort = d.symsort[threadIdx.x < d.k_sym - 1u ? threadIdx.x : d.k_sym - 1u];   // (such a code has symbols)
+        r.sort = d.symsort[threadIdx.x < d.k_sym - 1u ? threadIdx.x : d.k_sym - 1u];
     }
 #pragma unroll
     for (int k = 0; k < kTabTurns; ++k) {
@@ -199,7 +202,7 @@ __device__ __forceinline__ void request_table_values(const DevBlob& d, TableRegs
 {
     // without symbols (an empty address map) the canonical table stands in as a valid address
     const uint32_t* cbp = d.k_sym ? reinterpret_cast<const uint32_t*>(d.codebook) : d.canon;
-    if (d.lmax > d.lut_bits) r.cb = cbp[r.sort < d.k_sym ? r.sort : 0u];
+    if (longer_codes(d)) r.cb = cbp[r.sort < d.k_sym ? r.sort : 0u];
 #pragma unroll
     for (int k = 0; k < kTabTurns; ++k) r.v[k] = cbp[(r.e[k] & 63u) ? r.e[k] >> 6 : 0u];
 }
@@ -224,7 +227,7 @@ __device__ __forceinline__ Tables store_tables(const DevBlob& d, uint32_t* smem,
         const uint32_t e = d.lut[i];
         s_lut2[i] = make_uint2(e, (e & 63u) ? __float_as_uint(d.codebook[e >> 6]) : 0u);
     }
-    const bool longer = d.lmax > d.lut_bits;
+    const bool longer = longer_codes(d);
     if (longer && threadIdx.x < kBounds) {                                      // (blocks have at least a wavefront)
         const uint32_t l = threadIdx.x;
         s_bound[l] = l < d.lmax && l < 32u ? (r.first + r.count) << (31u - l) : 0x80000000u;
