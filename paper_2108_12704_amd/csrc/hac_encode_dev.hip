@@ -906,7 +906,9 @@ int hip_fail(hipError_t e) { hac_internal::set_last_hip_error((int)e); return HA
 
 // Pinned memory that the device leaves a call's counts in, and a list of up to kBoxPairs values: kBoxes of them for the process (512 KB),
 // allocated with the first call (one costs more than the call) and lent to a call until it has read them.  get() is nullptr where
-// none is free, or none can be had: what the host needs is then copied.
+// none is free, or none can be had: what the host needs is then copied.  From sent() on kernels of the call's stream may write to the box: it
+// goes back only once the stream has been waited for, by the call (arrived()) or, where an error ended that early, by the destructor, and never if that
+// wait fails.
 constexpr int kBoxes = 16;
 struct Box { EncResult result; uint32_t pairs[2 * kBoxPairs]; };
 class Mailbox {
@@ -914,8 +916,10 @@ class Mailbox {
     static Pool& pool() { static Pool* p = new Pool; return *p; }   // (never taken down: a call may run while the process ends)
     int i = -1;
     Box* p = nullptr;
+    hipStream_t stream;
+    bool written = false;                              // or about to be
 public:
-    Mailbox()
+    explicit Mailbox(hipStream_t s) : stream(s)
     {
         Pool& q = pool();
         std::lock_guard<std::mutex> hold(q.lock);
@@ -931,7 +935,7 @@ public:
     }
     ~Mailbox()
     {
-        if (i < 0) return;
+        if (i < 0 || (written && hipStreamSynchronize(stream) != hipSuccess)) return;
         Pool& q = pool();
         std::lock_guard<std::mutex> hold(q.lock);
         q.taken &= ~(1u << i);
@@ -939,6 +943,8 @@ public:
     Mailbox(const Mailbox&) = delete;
     Mailbox& operator=(const Mailbox&) = delete;
     Box* get() const { return p; }
+    void sent() { written = true; }
+    void arrived() { written = false; }
 };
 
 } // namespace
@@ -1001,8 +1007,9 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
     // steps 3 and 4 with a code of at most `slots` slots, and the wait for their sums
     std::vector<uint32_t> list;                        // of a code that the host has to build
     auto sums = [&](uint32_t slots, EncResult& r) -> hipError_t {
-        Mailbox mail;
+        Mailbox mail(stream);
         Box* const box = mail.get();
+        mail.sent();
         const PairList to = { dptr(L.list), box ? box->pairs : nullptr };
         const size_t lds = table_bytes(slots) / 3 * 2;
         hipLaunchKernelGGL(lds ? enc_bits_kernel<true> : enc_bits_kernel<false>, seg_grid, dim3(256), words_lds + lds, stream, sv, d_code, hist, to,
@@ -1017,6 +1024,7 @@ int encode_on_device(uint32_t format, const float* d_W, int64_t n, int64_t m, in
         if (err != hipSuccess) return err;
         if (!box && (err = hipMemcpyAsync(&r, d_result, sizeof r, hipMemcpyDeviceToHost, stream)) != hipSuccess) return err;
         if ((err = hipStreamSynchronize(stream)) != hipSuccess) return err;
+        mail.arrived();
         if (box) r = box->result;
         if (r.code.status != kCodeOnHost || r.code.values > 65536) return hipSuccess;
         list.resize(2 * (size_t)r.code.values);
