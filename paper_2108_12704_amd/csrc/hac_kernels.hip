@@ -1358,6 +1358,38 @@ DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* la
     return r;
 }
 
+// LDS of decode_to_index_kernel's blocks: the tables, the index of the columns, and room for the stream words and ri fields of a block's
+// chunks.  A block whose words do not fit reads them from the blob, a trip to memory per codeword, and the launch lasts as long as its
+// slowest block; how many words the fullest block has is not in the header.  A quarter more than a block's chunks have on average
+// (9402 x 2297, 54 % non-zero, sHAC, 48 rows, forced 403 -> 204 us against 6144 words each for stream and fields), and what a CU's LDS has left over
+// beside the blocks that run there at once, as far as a launch takes it without an attribute set first.  HAC and Rice-coded gaps: no less than
+// 6144, because chunks have as many non-zeros each, so that those of the emptier columns have more words than the average (4608 x 512, columns
+// from 70 to 10 % full, 48 rows, forced: room for the average and a quarter 53.3 us, so 40.9; equally full ones as quick or within 5 %).
+struct DecodeLds { uint32_t s_words, r_words, c_words, grid; size_t bytes; };
+
+DecodeLds decode_lds(const hac_desc_t* desc, const DevBlob& d)
+{
+    constexpr uint64_t kGranule = 1280, kStatic = 16, kNoAttribute = 64 * 1024;
+    DecodeLds p;
+    p.grid = (d.n_chunks + 255) / 256;
+    const double chunk_words = d.n_chunks ? 256.0 / 32.0 * (double)desc->total_bits / (double)d.n_chunks : 0.0;
+    const uint64_t chunk_nnz = std::min<uint64_t>(std::max<uint64_t>(hac_internal::chunk_base(desc->chunk),
+                                                  desc->chunk & hac_internal::kChunkPerColumn ? (desc->max_col_nnz + 63) / 64 : 0), desc->max_col_nnz);
+    const bool fields = desc->format == HAC_FORMAT_SHAC && !d.rice;
+    p.s_words = round_up(std::max(fields ? 0u : 6144u, (uint32_t)std::min(1.25 * chunk_words + 64.0, 20480.0)), 4);
+    p.r_words = 0;
+    if (fields) p.r_words = round_up((uint32_t)std::min<uint64_t>(256 * chunk_nnz * d.ri_bits / 32 + 16, 28672), 4);
+    p.c_words = d.m + 1 <= 8192 ? round_up(d.m + 1, 4) : 0u;               // colchunk, for the owner search
+    const uint64_t others = 4ull * (table_words(d) + p.c_words) + kStatic;
+    if (others + 4ull * (p.s_words + p.r_words) > kLdsLimit) { p.s_words = std::min(p.s_words, 6144u); p.r_words = std::min(p.r_words, 6144u); }
+    const uint64_t need = others + 4ull * (p.s_words + p.r_words);
+    const uint64_t fit = std::max<uint64_t>(1, kLdsLimit / ((need + kGranule - 1) / kGranule * kGranule));
+    const uint64_t share = std::min(kLdsLimit / std::min<uint64_t>(fit, std::max(1u, (p.grid + 255) / 256)) / kGranule * kGranule, kNoAttribute);
+    if (share > need) p.s_words += (uint32_t)((share - need) / 16) * 4;
+    p.bytes = others - kStatic + 4ull * (p.s_words + p.r_words);
+    return p;
+}
+
 // bytes of workspace the sparse route needs: partial sums of the row-blocked kernel, or the feature-major copy of X
 size_t sparse_need(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch)
 {
@@ -1444,18 +1476,9 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
                            (uint64_t)(dr.idx_bytes / 4), 0u);
         note_kernel("fill_u32_kernel");
         note_kernel("decode_to_index_kernel<unsigned %s>", dr.idx_bits == 8 ? "char" : "short");
-        // LDS beside the tables: room for the stream words (a quarter more than a block's chunks have on average) and ri fields of a
-        // block's chunks.  A block whose words do not fit reads them from the blob, a trip to memory per codeword (9402 x 2297, 46 %, sHAC, 34 rows, this route
-        // asked for, with 6144 words for each 356 us, 190 so); with no more than is needed more blocks share a CU.
-        const double chunk_words = d.n_chunks ? 256.0 / 32.0 * (double)desc->total_bits / (double)d.n_chunks : 0.0;
-        const uint64_t chunk_nnz = std::min<uint64_t>(std::max<uint64_t>(hac_internal::chunk_base(desc->chunk),
-                                                      desc->chunk & hac_internal::kChunkPerColumn ? (desc->max_col_nnz + 63) / 64 : 0), desc->max_col_nnz);
-        uint32_t s_words = round_up((uint32_t)std::min(1.25 * chunk_words + 64.0, 20480.0), 4), r_words = 0;
-        if (format == HAC_FORMAT_SHAC && !d.rice) r_words = round_up((uint32_t)std::min<uint64_t>(256 * chunk_nnz * d.ri_bits / 32 + 16, 28672), 4);
-        const uint32_t c_words = d.m + 1 <= 8192 ? round_up(d.m + 1, 4) : 0u;       // colchunk, for the owner search
-        if (4ull * (table_words(d) + s_words + r_words + c_words) > kLdsLimit - 64) { s_words = std::min(s_words, 6144u); r_words = std::min(r_words, 6144u); }
-        const size_t lds = 4ull * (table_words(d) + s_words + r_words + c_words);
-        const uint32_t grid = (d.n_chunks + 255) / 256;
+        const DecodeLds dl = decode_lds(desc, d);
+        const uint32_t s_words = dl.s_words, r_words = dl.r_words, c_words = dl.c_words, grid = dl.grid;
+        const size_t lds = dl.bytes;
         const uint32_t is_shac = format == HAC_FORMAT_SHAC ? 1u : 0u;
         if (grid) {
             if (lds > 64 * 1024) {

@@ -2,6 +2,11 @@
 import os
 import sys
 
+import numpy as np
+import pytest
+
+import paper_2108_12704_amd as hac
+
 sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import hip_stub
 
@@ -36,3 +41,49 @@ def test_calls_without_a_pinned_box_copy_the_counts(tmp_path):
     runs = hip_stub.run(tmp_path, ENCODE.replace("{how}", "[(1, 1)] * 16 + [(0, 0)]"))
     assert len({box for _, box in runs[:16]}) == 16 and 0 not in {box for _, box in runs[:16]}
     assert runs[16][1] == 0 and runs[16][0].startswith("LLLLLLMS")
+
+
+def uneven(n, m, most, least, k):
+    """Columns from `most` full to `least` full, values used as equal bins of a Gaussian are."""
+    rng = np.random.default_rng(n + m + k)
+    at = np.clip(np.round(rng.standard_normal((n, m)) * k / 6 + k / 2), 0, k - 1).astype(np.int64)
+    values = ((np.arange(k) - k / 2 + 0.3) * 0.01).astype(np.float32)
+    return np.where(rng.random((n, m)) < np.linspace(most, least, m), values[at], np.float32(0))
+
+
+def words_of_the_fullest_block(blob):
+    """Stream words from the first to the last of 256 chunks that follow one another, as decode_to_index_kernel copies them."""
+    d, data = blob.desc, blob.data
+    section = lambda off, count: data[off:off + 4 * count].view(np.uint32).astype(np.int64)
+    first, start = section(d.off_col_chunk, d.m + 1), section(d.off_col_bit, d.m + 1)
+    entry = section(d.off_chunk_ent, d.n_chunks)
+    assert d.ent_bits == 32
+    begin = start[np.searchsorted(first, np.arange(d.n_chunks), side="right") - 1] + (entry >> d.row_bits)
+    begin = np.append(begin, start[-1])
+    blocks = np.arange(0, d.n_chunks, 256)
+    ends = begin[np.minimum(blocks + 256, d.n_chunks)]
+    return int(((ends + 31) // 32 - (begin[blocks] // 32 & ~3)).max()) + 8
+
+
+# (the dense route's launches: the map cleared, the decode, whose fifth argument is the room for stream words, the product)
+DECODE = """
+d = hac.Desc.from_buffer_copy(bytes.fromhex({head!r}))
+launch = hac.Launch(variant=0x800)
+stub.stub_copy_arg(1, 4, 4)
+at = lambda x: C.c_void_p(x << 32)
+rc = lib.{call}(C.byref(d), at(1), at(2), 48, d.n, at(3), d.m, at(4), hac.hac_workspace_bytes(d, 48, launch), C.byref(launch), None)
+seen = events()
+print(json.dumps([rc, seen[1][2], seen[1][3]]))
+"""
+
+
+@pytest.mark.parametrize("n,m,most,least,k", [(2048, 1024, 0.5, 0.05, 32), (2048, 1024, 0.5, 0.05, 250), (4096, 1000, 0.5, 0.1, 32),
+                                              (4608, 512, 0.7, 0.1, 32), (1000, 4000, 0.5, 0.05, 32)])
+@pytest.mark.parametrize("fmt", ["hac", "rice"])
+def test_decode_of_uneven_columns_runs_on_words_in_lds(tmp_path, fmt, n, m, most, least, k):
+    """Chunks have as many non-zeros each, so those of emptier columns are longer than the average; all blocks' words fit all the same."""
+    W = uneven(n, m, most, least, k)
+    blob = hac.hac_encode(W) if fmt == "hac" else hac.shac_encode(W, ri_coding=hac.RI_RICE)
+    rc, lds, room = hip_stub.run(tmp_path, DECODE.format(head=bytes(blob.desc).hex(), call="hac_dot" if fmt == "hac" else "shac_dot"))
+    assert rc == 0 and lds <= 160 * 1024
+    assert room >= words_of_the_fullest_block(blob)
