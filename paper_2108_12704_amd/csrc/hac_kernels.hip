@@ -212,18 +212,23 @@ decode_to_index_kernel(DevBlob d, IdxT* idx, uint64_t pitch, uint32_t shac, uint
     auto entry = [&](uint32_t, uint32_t row, uint32_t s, float) { idx[(uint64_t)row * pitch + col] = (IdxT)s; };
     const WordSrc<true> src = { sstage, wlo }, rsrc = { rstage, rwlo };
     const WordSrc<false> gsrc = { d.stream, 0 }, grsrc = { d.ri, 0 };
+    // A loop that loads may be on their way into, from before it or, as the compiler sees it, from another branch's loop, begins every turn with a
+    // wait for all memory accesses, its own store of the turn before among them.  So that wait is made here, where there is nothing left to wait
+    // for (vmcnt 0, the other counters as they are).  48 rows, this route asked for: 4608 x 512, 40 % non-zero, 32 values, HAC 34.3 -> 30.9 us,
+    // Rice-coded gaps 34.9 -> 30.9; 512 x 20000, 35 %, 78.0 -> 68.1.
+    auto settle = [] { __builtin_amdgcn_s_waitcnt(0x0f70); };
     if (fields) {
         auto field = [&](auto rs) {
             return [&, rs](uint32_t p, uint32_t, uint32_t s, float) { idx[(uint64_t)rs.field((uint64_t)p * d.ri_bits, d.ri_bits) * pitch + col] = (IdxT)(s + 1); };
         };
-        if (staged) shac_advance(d, tb, src, st, st.wend, field(rsrc));
+        if (staged) { settle(); shac_advance(d, tb, src, st, st.wend, field(rsrc)); }
         else shac_advance(d, tb, gsrc, st, st.wend, field(grsrc));
     } else if (shac) {
-        if (staged) gap_advance(d, tb, src, st, st.wend, gap);
+        if (staged) { settle(); gap_advance(d, tb, src, st, st.wend, gap); }
         else gap_advance_slow(d, tb, gsrc, st, st.wend, gap);
     } else {
-        if (staged && d.zero_len == 1) hac_advance_zrun(d, tb, src, st, st.wend, entry);
-        else if (staged) hac_advance(d, tb, src, st, st.wend, entry);
+        if (staged && d.zero_len == 1) { settle(); hac_advance_zrun(d, tb, src, st, st.wend, entry); }
+        else if (staged) { settle(); hac_advance(d, tb, src, st, st.wend, entry); }
         else hac_advance(d, tb, gsrc, st, st.wend, entry);
     }
 }
