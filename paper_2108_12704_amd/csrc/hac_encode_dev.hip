@@ -775,80 +775,116 @@ enc_col_scan_kernel(const EncCode* __restrict__ code, uint32_t m, uint32_t S, ui
     }
 }
 
-// Step 4.  One block: the longest column gives the chunk size, then running sums over the columns, a range of
-// columns per thread (few columns: fewer wavefronts, which wait for each other).  col_arrays: first chunk, CSC position and first stream bit of every column and one
-// past it, `stride` words apart.  The counts go to *result and, where the host waits for them in pinned memory, to *mailbox.
+// Step 4.  One block: the longest column gives the chunk size, then running sums over the columns, four neighbouring ones per thread and a
+// strip of 4 blockDim.x at a time (few columns: fewer wavefronts, which wait for each other).  What bounds it is the chain of trips to memory, so a
+// strip's columns are requested while the one before is added up; matrices of one strip are read once.  (A range of columns per thread
+// instead, a line of memory for every column and lane: 64 x 500 000 3120 us for the whole call, 640 so; 64 x 4096 87 and 81.)
+// col_arrays: first chunk, CSC position and first stream bit of every column and one past it, `stride` words apart; what lies behind a multiple of
+// four past the last column is the sums once more.  The counts go to *result and, where the host waits for them in pinned memory, to *mailbox.
+struct ColumnQuad { uint32_t nnz[4]; unsigned long long bits[4]; };
+
+// (the arrays have room for whole quads; columns past m count as empty)
+__device__ __forceinline__ ColumnQuad load_quad(const uint32_t* __restrict__ col_nnz, const unsigned long long* __restrict__ col_bits, uint32_t j, uint32_t m)
+{
+    ColumnQuad q = {};
+    if (j >= m) return q;
+    const uint4 c = *reinterpret_cast<const uint4*>(col_nnz + j);
+    const ulonglong2 b0 = *reinterpret_cast<const ulonglong2*>(col_bits + j), b1 = *reinterpret_cast<const ulonglong2*>(col_bits + j + 2);
+    const uint32_t left = m - j;
+    q.nnz[0] = c.x; q.nnz[1] = left > 1 ? c.y : 0u; q.nnz[2] = left > 2 ? c.z : 0u; q.nnz[3] = left > 3 ? c.w : 0u;
+    q.bits[0] = b0.x; q.bits[1] = left > 1 ? b0.y : 0ull; q.bits[2] = left > 2 ? b1.x : 0ull; q.bits[3] = left > 3 ? b1.y : 0ull;
+    return q;
+}
+
 __global__ void __launch_bounds__(1024)
 enc_columns_kernel(const EncCode* __restrict__ code, uint32_t m, const uint32_t* __restrict__ col_nnz, const unsigned long long* __restrict__ col_bits,
                    const uint32_t* __restrict__ flags, uint32_t chunk_opt, const unsigned long long* __restrict__ gap_total, uint32_t* __restrict__ col_arrays, uint64_t stride,
                    EncResult* __restrict__ result, EncResult* mailbox)
 {
-    __shared__ unsigned long long wave_bits[16];
-    __shared__ uint32_t wave_nnz[16], wave_chunks[16];
-    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    EncResult r = {};
-    r.code = *code;
-    if (r.code.status == kCodeOk) {
-        const uint32_t per = (m + blockDim.x - 1) / blockDim.x, j0 = (uint64_t)t * per < m ? t * per : m, j1 = m - j0 < per ? m : j0 + per;
-        uint32_t most = 0, nnz = 0, chunks = 0;
-        unsigned long long longest = 0, bits = 0;
-        for (uint32_t j = j0; j < j1; j += 4) {                              // (four columns requested together)
-            uint32_t c[4];
-            unsigned long long b[4];
+    __shared__ unsigned long long wave_bits[2][16];
+    __shared__ uint32_t wave_nnz[2][16], wave_chunks[2][16];
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6, waves = blockDim.x / 64, strip = 4 * blockDim.x;
+    const uint32_t status = code->status;
+    uint32_t most = 0, chunk = 0, k = 0;
+    unsigned long long longest = 0, all_nnz = 0, all_chunks = 0, all_bits = 0, gap_bits = 0;
+    if (status == kCodeOk) {                                                // (uniform)
+        const ColumnQuad first = load_quad(col_nnz, col_bits, 4 * t, m);
+        ColumnQuad q = first;
+        for (uint64_t j0 = 0; j0 < m; j0 += strip) {
+            const uint64_t next = j0 + strip + 4 * t;
+            const ColumnQuad ahead = load_quad(col_nnz, col_bits, next < m ? (uint32_t)next : m, m);
 #pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) { const uint32_t q = j + u < j1 ? j + u : j1 - 1; c[u] = col_nnz[q]; b[u] = col_bits[q]; }
-#pragma unroll
-            for (uint32_t u = 0; u < 4; ++u) {
-                if (j + u >= j1) { c[u] = 0; b[u] = 0; }
-                most = c[u] > most ? c[u] : most; longest = b[u] > longest ? b[u] : longest;
-                nnz += c[u]; bits += b[u];
+            for (int u = 0; u < 4; ++u) {
+                most = q.nnz[u] > most ? q.nnz[u] : most;
+                longest = q.bits[u] > longest ? q.bits[u] : longest;
             }
+            q = ahead;
         }
         for (int d = 32; d >= 1; d >>= 1) {
             const uint32_t o = __shfl_xor(most, d, 64);
             const unsigned long long p = __shfl_xor(longest, d, 64);
             most = o > most ? o : most; longest = p > longest ? p : longest;
         }
-        if (lane == 0) { wave_nnz[wave] = most; wave_bits[wave] = longest; }
+        if (lane == 0) { wave_nnz[1][wave] = most; wave_bits[1][wave] = longest; }
         __syncthreads();
-        for (uint32_t w = 0; w < blockDim.x / 64; ++w) {
-            most = wave_nnz[w] > most ? wave_nnz[w] : most; longest = wave_bits[w] > longest ? wave_bits[w] : longest;
+        for (uint32_t w = 0; w < waves; ++w) {
+            most = wave_nnz[1][w] > most ? wave_nnz[1][w] : most; longest = wave_bits[1][w] > longest ? wave_bits[1][w] : longest;
         }
-        __syncthreads();
-        r.max_col_nnz = most; r.max_col_bits = longest;
-        r.chunk = hac_internal::chunk_for(chunk_opt, most);
-#pragma unroll 4
-        for (uint32_t j = j0; j < j1; ++j) {
-            const uint32_t c = col_nnz[j], cj = hac_internal::chunk_of_column(r.chunk, c);
-            chunks += (c + cj - 1) / cj;
+        chunk = hac_internal::chunk_for(chunk_opt, most);
+        q = first;
+        uint32_t side = 0;                                                  // of the wavefronts' sums: one barrier a strip
+        for (uint64_t j0 = 0; j0 < m; j0 += strip, side ^= 1u) {
+            const uint64_t j = j0 + 4 * t, next = j + strip;
+            const ColumnQuad ahead = load_quad(col_nnz, col_bits, next < m ? (uint32_t)next : m, m);
+            uint32_t chunks[4], nnz = 0, ch = 0;
+            unsigned long long bits = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t cj = hac_internal::chunk_of_column(chunk, q.nnz[u]);
+                chunks[u] = (q.nnz[u] + cj - 1) / cj;
+                nnz += q.nnz[u]; ch += chunks[u]; bits += q.bits[u];
+            }
+            // this thread's place among all: sums of the threads before it in its wavefront, and of the wavefronts before
+            uint32_t in = nnz, ic = ch;
+            unsigned long long ib = bits;
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t a = __shfl_up(in, d, 64), b = __shfl_up(ic, d, 64);
+                const unsigned long long c = __shfl_up(ib, d, 64);
+                if ((int)lane >= d) { in += a; ic += b; ib += c; }
+            }
+            if (lane == 63) { wave_nnz[side][wave] = in; wave_chunks[side][wave] = ic; wave_bits[side][wave] = ib; }
+            __syncthreads();
+            unsigned long long pos = all_nnz + in - nnz, at = all_chunks + ic - ch, bit = all_bits + ib - bits;
+            for (uint32_t w = 0; w < waves; ++w) {
+                const uint32_t wn = wave_nnz[side][w], wc = wave_chunks[side][w];
+                const unsigned long long wb = wave_bits[side][w];
+                if (w < wave) { pos += wn; at += wc; bit += wb; }
+                all_nnz += wn; all_chunks += wc; all_bits += wb;
+            }
+            if (j < m) {
+                uint32_t o[3][4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    o[0][u] = (uint32_t)at; o[1][u] = (uint32_t)pos; o[2][u] = (uint32_t)bit;
+                    at += chunks[u]; pos += q.nnz[u]; bit += q.bits[u];
+                }
+#pragma unroll
+                for (int s = 0; s < 3; ++s) *reinterpret_cast<uint4*>(col_arrays + s * stride + j) = make_uint4(o[s][0], o[s][1], o[s][2], o[s][3]);
+            }
+            q = ahead;
         }
-        // this thread's place among all: sums of the threads before it in its wavefront, and of the wavefronts before
-        uint32_t in = nnz, ic = chunks;
-        unsigned long long ib = bits;
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t a = __shfl_up(in, d, 64), b = __shfl_up(ic, d, 64);
-            const unsigned long long c = __shfl_up(ib, d, 64);
-            if ((int)lane >= d) { in += a; ic += b; ib += c; }
-        }
-        if (lane == 63) { wave_nnz[wave] = in; wave_chunks[wave] = ic; wave_bits[wave] = ib; }
-        __syncthreads();
-        uint64_t pos = in - nnz, chunk = ic - chunks, bit = ib - bits;
-        for (uint32_t w = 0; w < blockDim.x / 64; ++w) {
-            if (w < wave) { pos += wave_nnz[w]; chunk += wave_chunks[w]; bit += wave_bits[w]; }
-            r.col_nnz += wave_nnz[w]; r.chunks += wave_chunks[w]; r.col_bits += wave_bits[w];
-        }
-        for (uint32_t j = j0; j < j1; ++j) {
-            col_arrays[j] = (uint32_t)chunk; col_arrays[stride + j] = (uint32_t)pos; col_arrays[2 * stride + j] = (uint32_t)bit;
-            const uint32_t c = col_nnz[j], cj = hac_internal::chunk_of_column(r.chunk, c);
-            pos += c; chunk += (c + cj - 1) / cj; bit += col_bits[j];
-        }
-        if (t == 0) {
-            col_arrays[m] = (uint32_t)r.chunks; col_arrays[stride + m] = (uint32_t)r.col_nnz; col_arrays[2 * stride + m] = (uint32_t)r.col_bits;
-        }
-        if (gap_total) { r.rice_k = best_rice_k(gap_total); r.gap_bits = gap_total[r.rice_k]; }
+        if (gap_total) { k = best_rice_k(gap_total); gap_bits = gap_total[k]; }
     }
-    if (r.code.status == kCodeOnHost) r.code.values = flags[2];
-    if (t == 0) { *result = r; if (mailbox) *mailbox = r; }
+    if (t != 0) return;
+    if (status == kCodeOk) { col_arrays[m] = (uint32_t)all_chunks; col_arrays[stride + m] = (uint32_t)all_nnz; col_arrays[2 * stride + m] = (uint32_t)all_bits; }
+    for (EncResult* r : { result, mailbox }) {
+        if (!r) continue;
+        r->code = *code;
+        if (status == kCodeOnHost) r->code.values = flags[2];
+        r->chunk = chunk; r->rice_k = k;
+        r->max_col_nnz = most; r->max_col_bits = longest;
+        r->col_bits = all_bits; r->col_nnz = all_nnz; r->chunks = all_chunks; r->gap_bits = gap_bits;
+    }
 }
 
 // Step 5, first part: the blob as the codewords find it.  `tables`: step 2's (nullptr: the host copies header and tables itself).

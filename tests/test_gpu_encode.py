@@ -182,6 +182,21 @@ def test_device_blob_over_alphabets(hac, k, counts, n, m):
                           hac.shac_encode(W, ri_coding=hac.RI_RICE).data)
 
 
+# a block adds up the columns four to a thread, 1024 or 4096 at a time: one column, parts of a thread's four, the edges of one and two
+# strips, and many strips whose sums pass through one another
+@pytest.mark.parametrize("n,m", [(40, 1), (40, 2), (40, 7), (5, 1021), (5, 1024), (5, 4093), (5, 4096), (5, 4097), (4, 8192), (4, 8195), (3, 100003), (2, 300000)])
+def test_device_blob_over_columns(hac, n, m):
+    W = alphabet_matrix(30, lambda i: 1 + n * m // 200, n, m) if n * m > 400 else alphabet_matrix(5, lambda i: 2, n, m)
+    W[:, m // 3:m // 2] = 0.0                                              # empty columns among them
+    Wd = torch.from_numpy(W).to(dev())
+    print(f"[case] encode_dev {n} x {m}", flush=True)
+    for kw in (dict(), dict(chunk_nnz=hac.CHUNK_PER_COLUMN), dict(chunk_nnz=1)):
+        assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_HAC, **kw).tensor.cpu().numpy(), hac.hac_encode(W, **kw).data)
+        assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_SHAC, **kw).tensor.cpu().numpy(), hac.shac_encode(W, **kw).data)
+    assert np.array_equal(hac.hac_encode_dev(Wd, hac.HAC_FORMAT_SHAC, ri_coding=hac.RI_RICE).tensor.cpu().numpy(),
+                          hac.shac_encode(W, ri_coding=hac.RI_RICE).data)
+
+
 def test_device_encodes_side_by_side(hac):
     """More calls at once than there is pinned memory for, each on a stream of its own."""
     import concurrent.futures as cf
