@@ -391,9 +391,14 @@ struct EntryGroup {
 // kHalves: 60 non-zeros a column 6.3e-8 -> 6.9e-8 -> 4.3e-8, 100 6.9e-8 -> 8.0e-8 -> 4.3e-8, 4096 x 4096, 4 %, 128 rows 8.0e-8 -> 8.0e-8 ->
 // 4.3e-8.  kHalves for kTurns costs 1.2 % of a call (geometric mean over 81 products of 34 to 256 rows; worst 5 %: 2000 x 4096, 5 %,
 // 80 rows 17.3 -> 18.2 us); halves added in 32 bits first, or no 64 bits at all, leave the error of kTurns or cost the same.
-enum { kChain, kTurns, kHalves };
+// kTurns64 is kTurns with the turns' sums added in 64 bits, for long columns of products that the dense route had before (see dense_route): error
+// 5.0 to 5.8e-8 whatever the column's length, where the dense route's is 6 to 13e-8 and that of kTurns 5.5 to 49e-8.  It costs 0.1 to 0.5 % of a call of
+// dot_split_kernel, 0.2 to 4 % of one of dot_batch_kernel (12000 x 3387, 36 %, 40 rows 295 -> 307 us); two to eight turns added in 32 bits first leave
+// 5.8 to 7.5e-8 and are quicker above 2000 non-zeros a column only.
+enum { kChain, kTurns, kHalves, kTurns64 };
 template <int SUMS> struct SumType { typedef float type; };
 template <> struct SumType<kHalves> { typedef double type; };
+template <> struct SumType<kTurns64> { typedef double type; };
 
 template <int NB, int kPipe, int SUMS>
 __device__ __forceinline__ void add_group(EntryGroup<NB, kPipe>& G, typename SumType<SUMS>::type (&acc)[NB])
@@ -411,7 +416,7 @@ __device__ __forceinline__ void add_group(EntryGroup<NB, kPipe>& G, typename Sum
             }
         }
     }
-    if constexpr (SUMS == kTurns) {
+    if constexpr (SUMS == kTurns || SUMS == kTurns64) {
 #pragma unroll
         for (int i = 0; i < NB; ++i) acc[i] += G.x[0][i];
     }
@@ -1081,7 +1086,8 @@ uint32_t default_cpw(const hac_desc_t* desc)
 }
 
 // `bytes` of workspace, the index map in the first idx_bytes of them.
-struct DenseRoute { bool use; uint32_t idx_bits; uint64_t pitch; size_t idx_bytes, bytes; hac_internal::GemmPlan plan; };
+// careful: on the sparse route with sums of long columns in 64 bits (see dense_route)
+struct DenseRoute { bool use, careful; uint32_t idx_bits; uint64_t pitch; size_t idx_bytes, bytes; hac_internal::GemmPlan plan; };
 
 bool size_index_map(const hac_desc_t* desc, DenseRoute& r)
 {
@@ -1146,9 +1152,10 @@ batch_kern_t pick_batch_kernel(uint32_t nb, bool multipass, int sums)
 {
     if (nb == 1) return dot_batch_kernel<SHAC, 1, false, EPI, kTurns>;
     if (nb == 2) return dot_batch_kernel<SHAC, 2, false, EPI, kTurns>;
-    if (!multipass) return sums == kHalves ? dot_batch_kernel<SHAC, 4, false, EPI, kHalves> : dot_batch_kernel<SHAC, 4, false, EPI, kTurns>;
-    return sums == kHalves ? dot_batch_kernel<SHAC, 4, true, EPI, kHalves> : sums == kTurns ? dot_batch_kernel<SHAC, 4, true, EPI, kTurns>
-                                                                                      : dot_batch_kernel<SHAC, 4, true, EPI, kChain>;
+    if (!multipass) return sums == kHalves ? dot_batch_kernel<SHAC, 4, false, EPI, kHalves> : sums == kTurns64 ? dot_batch_kernel<SHAC, 4, false, EPI, kTurns64>
+                                                                                                               : dot_batch_kernel<SHAC, 4, false, EPI, kTurns>;
+    return sums == kHalves ? dot_batch_kernel<SHAC, 4, true, EPI, kHalves> : sums == kTurns64 ? dot_batch_kernel<SHAC, 4, true, EPI, kTurns64>
+         : sums == kTurns ? dot_batch_kernel<SHAC, 4, true, EPI, kTurns> : dot_batch_kernel<SHAC, 4, true, EPI, kChain>;
 }
 
 // per-wave LDS words for the stream (and ri) words of a wave's columns
@@ -1296,6 +1303,13 @@ SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* laun
     return s;
 }
 
+// which sums dot_batch_kernel takes (see fma_entries)
+int batch_sums(const hac_desc_t* desc, int64_t B, const BatchShape& bs)
+{
+    const bool wide = bs.gw * bs.nb > 32;
+    return wide && desc->nnz < 600 * desc->m ? kHalves : wide || bs.npass == 1 || widest_pass(desc->n, B) > 32 ? kTurns : kChain;
+}
+
 // Estimated times of the two routes, for the choice between them; B > 32.  Each kernel's constants are fitted to its times, the route
 // forced, on 13000 products (300 x 10 to 25088 x 4096, 45 to 98.5 % pruned, 16 to 256 values, 33 to 4000 rows, both formats and
 // Rice-coded gaps).  `chunk`: codewords that a lane decodes one after the other; blocks that do not fit the chip at once go in rounds.
@@ -1351,20 +1365,38 @@ double dense_us(const hac_desc_t* desc, const DenseRoute& r)
     return 3.72 + 4.8e-7 * (double)r.idx_bytes + 9.25e-6 * (double)desc->nnz + 0.282 * chunk + 0.929 * r.plan.us + (r.plan.splits > 1 ? 1.9 : 0.0);
 }
 
+// Whether the dense route had a product while the sparse route's passes were 32 columns wide and a column had one wavefront (the two estimates of
+// that time).  A caller's sums did not round more than that route's then, and do not now: see dense_route.
+bool dense_before(const hac_desc_t* desc, int64_t B, const DenseRoute& r)
+{
+    const double nnz = (double)desc->nnz, n = (double)desc->n, m = (double)desc->m, b = (double)B;
+    const double bp = (double)((B + 31) / 32 * 32), panels = std::min(bp / 32.0, 8.0);
+    double chunk = (double)hac_internal::chunk_base(desc->chunk);
+    if (desc->chunk & hac_internal::kChunkPerColumn) chunk = std::max(chunk, (double)desc->max_col_nnz / 64.0);
+    return 5.6 + 0.8e-6 * (double)r.idx_bytes + 9e-6 * nnz + 0.49 * chunk + r.plan.us <
+           12.8 + 1.85e-6 * n * bp + nnz * bp * 1.15e-7 + 8.9e-3 * panels * nnz / m + 1.87e-5 * b * m;
+}
+
 // Dense route (decode to an index map, then MFMA tiles) or sparse route (vector FMAs per non-zero)?  The shorter of the two
 // estimates.  Batches of 32 rows and less are one panel of the sparse route and too few for MFMA tiles; layers with one non-zero in
 // 40 entries or fewer take the sparse route as they always did (of 24 measured ones the dense route was more than
 // 15 % quicker on three, 25088 x 16 at 256 rows 46 against 63 us).
+// The routes round differently (relative error against 64 bits: dense 4.4 to 13e-8, 2.6 to 4.0e-8 for columns of up to 120 non-zeros and one K split; sparse 3 to
+// 5.2e-8 but for sums of long columns in 32 bits, 5.5 to 49e-8), so a product that the dense route had before takes the sparse one with `careful` sums, and not
+// where the dense route's are closer still.
 // `room`: bytes of workspace there are, for hac_dot_noalloc; the plan then splits K only as far as the parts fit.
 DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room = ~(size_t)0)
 {
     DenseRoute r = {};
     const uint32_t force = launch ? launch->variant & (HAC_LAUNCH_SPARSE_ROUTE | HAC_LAUNCH_DENSE_ROUTE) : 0u;
-    if (B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && (B <= 32 || desc->nnz <= desc->n * desc->m / 40)) || !size_index_map(desc, r)) return r;
+    const bool choice = B > 32 && desc->nnz > desc->n * desc->m / 40;
+    if (B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && !choice) || !size_index_map(desc, r)) return r;
     r.plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m, room > r.idx_bytes ? room - r.idx_bytes : 0);
     r.bytes = r.idx_bytes + ((r.plan.part_bytes + 255) / 256 * 256);
-    if (force) { r.use = force == HAC_LAUNCH_DENSE_ROUTE; return r; }
-    r.use = dense_us(desc, r) < sparse_us(desc, B);
+    const bool before = choice && dense_before(desc, B, r);
+    r.use = choice && (dense_us(desc, r) < sparse_us(desc, B) || (before && r.plan.splits == 1 && desc->nnz < 125 * desc->m));
+    r.careful = before && !r.use;
+    if (force) r.use = force == HAC_LAUNCH_DENSE_ROUTE;
     return r;
 }
 
@@ -1606,7 +1638,8 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
         switch (sp.nbd) {
         case 0:                                               // (from 400 non-zeros a column on its wavefronts' groups keep the chains short)
             if (desc->nnz < 400 * desc->m) k = shac ? dot_split_kernel<true, 0> : dot_split_kernel<false, 0>;
-            else k = shac ? dot_split_kernel<true, 0, kTurns> : dot_split_kernel<false, 0, kTurns>;
+            else if (!dr.careful) k = shac ? dot_split_kernel<true, 0, kTurns> : dot_split_kernel<false, 0, kTurns>;
+            else k = shac ? dot_split_kernel<true, 0, kTurns64> : dot_split_kernel<false, 0, kTurns64>;
             break;
         case 4: k = shac ? dot_split_kernel<true, 4> : dot_split_kernel<false, 4>; break;
         case 8: k = shac ? dot_split_kernel<true, 8> : dot_split_kernel<false, 8>; break;
@@ -1704,8 +1737,8 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
     if (items > 0x7ffffff0ull) return HAC_EINVAL;
     const uint32_t grid = (uint32_t)((items + 7) / 8 * 8);
     const bool with_epilogue = io->bias || io->relu || io->yt_out;
-    const bool wide = bs.gw * bs.nb > 32;
-    const int sums = wide && desc->nnz < 600 * desc->m ? kHalves : wide || bs.npass == 1 || widest_pass(desc->n, B) > 32 ? kTurns : kChain;
+    int sums = batch_sums(desc, B, bs);
+    if (dr.careful && sums != kHalves) sums = kTurns64;
     batch_kern_t k = with_epilogue
         ? (shac ? pick_batch_kernel<true, true>(bs.nb, bs.npass > 1, sums) : pick_batch_kernel<false, true>(bs.nb, bs.npass > 1, sums))
         : (shac ? pick_batch_kernel<true, false>(bs.nb, bs.npass > 1, sums) : pick_batch_kernel<false, false>(bs.nb, bs.npass > 1, sums));

@@ -370,3 +370,28 @@ def test_sums_of_few_terms(hac, n, terms):
     assert (err <= product_bound(X, W, terms + 1)).all()
     if n == 1:
         assert np.array_equal(Y, X * W)
+
+
+# products that the sparse route took from the dense one: long columns of dot_split_kernel and of dot_batch_kernel (one pass, several, passes of 32 columns),
+# and short ones whose dense sums, in one K split, are closer than any of the sparse kernels'
+@pytest.mark.parametrize("n,m,pruned,k,B,fmt", [(2772, 2179, 0.784, 60, 134, "rice"), (1425, 1511, 0.695, 32, 146, "hac"), (3783, 1654, 0.711, 32, 72, "shac"),
+                                                (4644, 1247, 0.624, 32, 93, "hac"), (9473, 1555, 0.869, 32, 105, "hac"), (1302, 3332, 0.67, 32, 77, "hac"),
+                                                (3481, 3811, 0.773, 32, 116, "shac"), (511, 2009, 0.967, 32, 415, "rice"), (661, 2914, 0.967, 32, 512, "hac")])
+def test_a_change_of_route_does_not_round_more(hac, n, m, pruned, k, B, fmt):
+    """Relative error against 64 bits of the route that runs, at most that of the dense route that had the product before (the
+    two differ by a quarter and more where the sums are not as careful, and by the share of rounding errors that happen to agree, 1 %, where they are)."""
+    print(f"[case] route error {fmt} {n} x {m}, {B} rows", flush=True)
+    rng = np.random.default_rng(n + m)
+    at = np.clip(np.round(rng.standard_normal((n, m)) * k / 6 + k / 2), 0, k - 1).astype(np.int64)
+    values = ((np.arange(k) - (k - 1) / 2) * 0.01).astype(np.float32)
+    W = np.where(rng.random((n, m)) < pruned, np.float32(0), values[at]).astype(np.float32)
+    X = np.maximum(rng.standard_normal((B, n)), 0).astype(np.float32)
+    Wd, Xd = torch.from_numpy(W).to(dev()), torch.from_numpy(X).to(dev())
+    blob = hac.hac_encode_dev(Wd, hac.HAC_FORMAT_HAC if fmt == "hac" else hac.HAC_FORMAT_SHAC, ri_coding=hac.RI_RICE if fmt == "rice" else hac.RI_FIELDS)
+    call = hac.hac_dot if fmt == "hac" else hac.shac_dot
+    ref = Xd.double() @ Wd.double()
+
+    def error(Y):
+        return float((Y.double() - ref).norm() / ref.norm())
+    now, dense = error(call(blob, Xd)), error(call(blob, Xd, launch=hac.Launch(variant=DENSE)))
+    assert now <= 1.01 * dense, (now, dense)
