@@ -1303,6 +1303,38 @@ SplitPlan plan_split(const hac_desc_t* desc, int64_t B, const hac_launch_t* laun
     return s;
 }
 
+// LDS of decode_to_index_kernel's blocks: the tables, the index of the columns, and room for the stream words and ri fields of a block's
+// chunks.  A block whose words do not fit reads them from the blob, a trip to memory per codeword, and the launch lasts as long as its
+// slowest block; how many words the fullest block has is not in the header.  A quarter more than a block's chunks have on average
+// (9402 x 2297, 54 % non-zero, sHAC, 48 rows, forced 403 -> 204 us against 6144 words each for stream and fields), and what a CU's LDS has left over
+// beside the blocks that run there at once, as far as a launch takes it without an attribute set first.  HAC and Rice-coded gaps: no less than
+// 6144, because chunks have as many non-zeros each, so that those of the emptier columns have more words than the average (4608 x 512, columns
+// from 70 to 10 % full, 48 rows, forced: room for the average and a quarter 53.3 us, so 40.9; equally full ones as quick or within 5 %).
+struct DecodeLds { uint32_t s_words, r_words, c_words, grid; size_t bytes; };
+
+DecodeLds decode_lds(const hac_desc_t* desc)
+{
+    constexpr uint64_t kGranule = 1280, kStatic = 16, kNoAttribute = 64 * 1024;
+    DecodeLds p;
+    p.grid = (uint32_t)((desc->n_chunks + 255) / 256);
+    const double chunk_words = desc->n_chunks ? 256.0 / 32.0 * (double)desc->total_bits / (double)desc->n_chunks : 0.0;
+    const uint64_t chunk_nnz = std::min<uint64_t>(std::max<uint64_t>(hac_internal::chunk_base(desc->chunk),
+                                                  desc->chunk & hac_internal::kChunkPerColumn ? (desc->max_col_nnz + 63) / 64 : 0), desc->max_col_nnz);
+    const bool fields = desc->format == HAC_FORMAT_SHAC && desc->ri_coding == HAC_RI_FIELDS;
+    p.s_words = round_up(std::max(fields ? 0u : 6144u, (uint32_t)std::min(1.25 * chunk_words + 64.0, 20480.0)), 4);
+    p.r_words = 0;
+    if (fields) p.r_words = round_up((uint32_t)std::min<uint64_t>(256 * chunk_nnz * desc->ri_bits / 32 + 16, 28672), 4);
+    p.c_words = desc->m + 1 <= 8192 ? round_up((uint32_t)desc->m + 1, 4) : 0u;   // colchunk, for the owner search
+    const uint64_t others = table_bytes_of(desc) + 4ull * p.c_words + kStatic;
+    if (others + 4ull * (p.s_words + p.r_words) > kLdsLimit) { p.s_words = std::min(p.s_words, 6144u); p.r_words = std::min(p.r_words, 6144u); }
+    const uint64_t need = others + 4ull * (p.s_words + p.r_words);
+    const uint64_t fit = std::max<uint64_t>(1, kLdsLimit / ((need + kGranule - 1) / kGranule * kGranule));
+    const uint64_t share = std::min(kLdsLimit / std::min<uint64_t>(fit, std::max(1u, (p.grid + 255) / 256)) / kGranule * kGranule, kNoAttribute);
+    if (share > need) p.s_words += (uint32_t)((share - need) / 16) * 4;
+    p.bytes = others - kStatic + 4ull * (p.s_words + p.r_words);
+    return p;
+}
+
 // which sums dot_batch_kernel takes (see fma_entries)
 int batch_sums(const hac_desc_t* desc, int64_t B, const BatchShape& bs)
 {
@@ -1310,39 +1342,46 @@ int batch_sums(const hac_desc_t* desc, int64_t B, const BatchShape& bs)
     return wide && desc->nnz < 600 * desc->m ? kHalves : wide || bs.npass == 1 || widest_pass(desc->n, B) > 32 ? kTurns : kChain;
 }
 
+// Non-zeros of a column that most reach.  Where the longest has no more, columns are about equally full.
+double usual_column(const hac_desc_t* desc) { return std::min((double)desc->max_col_nnz, 1.25 * (double)desc->nnz / (double)desc->m + 32.0); }
+
 // Estimated times of the two routes, for the choice between them; B > 32.  Each kernel's constants are fitted to its times, the route
-// forced, on 13000 products (300 x 10 to 25088 x 4096, 45 to 98.5 % pruned, 16 to 256 values, 33 to 4000 rows, both formats and
-// Rice-coded gaps).  `chunk`: codewords that a lane decodes one after the other; blocks that do not fit the chip at once go in rounds.
+// forced: those of several wavefronts per column on 13000 products whose columns are equally full (300 x 10 to 25088 x 4096, 45 to 98.5 % pruned, 16 to
+// 256 values, 33 to 4000 rows, both formats and Rice-coded gaps), the others on 15600 of 26055 (500 x 10 to 25088 x 4096, 50 to 97.5 % pruned, 33 to 512 rows, a
+// quarter with equally full columns, the others from full to 50, 20 or 5 % of that).  90 % of the estimates of the 10300 others lie within the range given,
+// equally full columns / others.
+// `chunk`: codewords that a lane decodes one after the other; blocks that do not fit the chip at once go in rounds, the longest column in one of them.
 //   several wavefronts per column, X as it is: 4.8 us a round, 0.35 us a codeword, 0.014 us a lane's turn and row of X, the values
-//       of X fetched, and lines of X (95 % of the products within 12 %);
+//       of X fetched, and lines of X (-15 .. +7 / -15 .. +5 %);
 //   ... from the copy: 8.4 us, the copy's two passes, 0.24 us a codeword, 0.28 us a turn of ten entries, 4 bytes gathered per
-//       non-zero and batch column at 36 TB/s (-21 .. +16 %);
-//   one wavefront per column: the same, as its passes and the wavefronts that LDS leaves a CU make it (-30 .. +16 %);
-//   dense: 3.7 us, the map cleared, written and read (2.1 TB/s), 9 ns per thousand non-zeros scattered into it, 0.28 us a codeword, the
-//       product as its plan estimates it and the launch that adds its parts (-15 .. +12 %).
-// What a product takes on the route so chosen, over the better one, 4500 other products of more than one non-zero in 40 entries: 1.003
-// (geometric mean; worst 1.65).  The estimate before, fitted while passes were 32 columns wide and a column had one wavefront, took
-// the dense route twice as often as it was the quicker one: 1.21, worst 3.0 (929 x 11, 285 rows 17.7 us, 6.5 on the other route; 24391 x 100,
-// 50 %, 46 rows 153 and 51).
-double sparse_us(const hac_desc_t* desc, int64_t B)
+//       non-zero and batch column at 36 TB/s (-24 .. +11 / -27 .. +10 %);
+//   one wavefront per column: the same, as its passes and the wavefronts that LDS leaves a CU make it, and what the longest column has more than most
+//       (-23 .. +24 / -30 .. +21 %);
+//   dense: 6.4 us, the map cleared, written and read (1.2 TB/s), 4 ns per thousand non-zeros scattered into it, 0.26 us a codeword, the
+//       product as its plan estimates it (-13 .. +13 / -20 .. +11 %).
+// sums32: a column's sums are of 32 bits and long enough (for dot_split_kernel 16 turns: 8.7e-8 with 6, 1.1e-7 with 20 at 16000 rows) to round about as much
+// as the dense route's or more
+struct SparseEstimate { double us; bool sums32; };
+
+SparseEstimate sparse_us(const hac_desc_t* desc, int64_t B)
 {
     const double n = (double)desc->n, m = (double)desc->m, b = (double)B, nnz = (double)desc->nnz;
-    const double bp = (double)((B + 31) / 32 * 32);
+    const double bp = (double)((B + 31) / 32 * 32), most = (double)desc->max_col_nnz, usual = usual_column(desc);
     double chunk = (double)hac_internal::chunk_base(desc->chunk);
     if (desc->chunk & hac_internal::kChunkPerColumn) chunk = std::max(chunk, (double)desc->max_col_nnz / 64.0);
     const SplitPlan sp = plan_split(desc, B, nullptr);
     if (sp.use) {
         const double rounds = std::max(1.0, std::ceil(sp.rounds)), shares = (double)(1u << sp.p.split_log2);
-        if (sp.direct) {
-            const double turns = std::ceil((double)desc->max_col_nnz / (64.0 * shares));
-            return rounds * (4.77 + 0.348 * chunk + 0.014 * turns * (double)sp.p.width) + 3.44e-7 * nnz * b + 6.1e-8 * n * m * b;
-        }
-        const double turns = std::ceil((double)desc->max_col_nnz / ((double)(sp.turn / 8 * 10) * shares));
-        return 8.37 + 1.77e-6 * n * bp + rounds * (0.24 * chunk + 0.283 * turns) + 1.096e-7 * nnz * bp;
+        const double entries = (sp.direct ? 64.0 : (double)(sp.turn / 8 * 10)) * shares;   // of a column, in a turn
+        const double turns = std::ceil(most / entries) + (rounds - 1.0) * std::ceil(usual / entries);
+        if (sp.direct) return { rounds * (4.77 + 0.348 * chunk) + 0.014 * turns * (double)sp.p.width + 3.44e-7 * nnz * b + 6.1e-8 * n * m * b, false };
+        return { 8.37 + 1.77e-6 * n * bp + rounds * 0.24 * chunk + 0.283 * turns + 1.096e-7 * nnz * bp,
+                 desc->nnz >= 400 * desc->m && nnz >= 16.0 * entries * m };
     }
     const uint32_t cpw = default_cpw(desc), width = std::max(32u, pass_columns(desc, B));
     const BatchShape bs = batch_shape(B, width, kDefaultTile);
-    const uint64_t here = (uint64_t)std::min<int64_t>(B, kDefaultTile), passes = (here + width - 1) / width;
+    const uint64_t here = (uint64_t)std::min<int64_t>(B, kDefaultTile);
+    const double passes = (double)((here + width - 1) / width);
     const uint32_t list_cap = default_list_entries(desc, cpw), chunk_least = hac_internal::chunk_base(desc->chunk);
     const uint64_t chunks = (desc->max_col_nnz + chunk_least - 1) / chunk_least;
     const bool split = cpw * chunks > 64 || cpw * desc->max_col_nnz > list_cap;
@@ -1354,15 +1393,15 @@ double sparse_us(const hac_desc_t* desc, int64_t B)
     }
     const double rounds = std::max(1.0, std::ceil(m * (double)((B + 255) / 256) / ((double)cpw * 256.0 * (double)waves)));
     const double column = nnz / m;
-    return 7.77 + 2.37e-6 * n * bp + 7.92e-8 * nnz * bp + 5.2e-6 * m * b +
-           rounds * (0.155 * chunk * cpw + (double)passes * (0.714 + 1.334e-3 * column + 1.47e-4 * column * (double)width));
+    return { 6.42 + 3.58e-6 * n * bp + 7.84e-8 * nnz * bp + 9.85e-6 * m * b + rounds * (0.416 * chunk * cpw + passes * column * (4.27e-4 + 1.81e-4 * (double)width)) +
+             passes * (most - usual) * (3.71e-3 + 1.7e-4 * (double)width), batch_sums(desc, B, bs) != kHalves };
 }
 
 double dense_us(const hac_desc_t* desc, const DenseRoute& r)
 {
     double chunk = (double)hac_internal::chunk_base(desc->chunk);
     if (desc->chunk & hac_internal::kChunkPerColumn) chunk = std::max(chunk, (double)desc->max_col_nnz / 64.0);
-    return 3.72 + 4.8e-7 * (double)r.idx_bytes + 9.25e-6 * (double)desc->nnz + 0.282 * chunk + 0.929 * r.plan.us + (r.plan.splits > 1 ? 1.9 : 0.0);
+    return 6.4 + 8.5e-7 * (double)r.idx_bytes + 4.1e-6 * (double)desc->nnz + 0.256 * chunk + 0.908 * r.plan.us;
 }
 
 // Whether the dense route had a product while the sparse route's passes were 32 columns wide and a column had one wavefront (the two estimates of
@@ -1377,13 +1416,31 @@ bool dense_before(const hac_desc_t* desc, int64_t B, const DenseRoute& r)
            12.8 + 1.85e-6 * n * bp + nnz * bp * 1.15e-7 + 8.9e-3 * panels * nnz / m + 1.87e-5 * b * m;
 }
 
+// Whether all blocks of the decode to an index map have their words in LDS, as far as the header tells: the emptiest columns are taken to be as far below
+// the average as the fullest is above it.  A block of a HAC stream that reads its words from the blob takes a trip to memory per 32 zeros
+// (19745 x 706, 28 to 1 % full, 51 rows 540 us, 158 on the sparse route).
+bool decode_in_lds(const hac_desc_t* desc)
+{
+    if (desc->format != HAC_FORMAT_HAC || !desc->nnz) return true;
+    const double n = (double)desc->n, m = (double)desc->m, column = (double)desc->nnz / m, zero = std::max<double>(1.0, desc->zero_len);
+    const double code = ((double)desc->total_bits - (n - column) * m * zero) / (double)desc->nnz;   // bits of a non-zero's codeword
+    const double emptiest = column * std::max(0.05, 2.0 - (double)desc->max_col_nnz / column);
+    return 8.0 * (double)hac_internal::chunk_base(desc->chunk) * (code + (n / emptiest - 1.0) * zero) <= (double)decode_lds(desc).s_words;
+}
+
 // Dense route (decode to an index map, then MFMA tiles) or sparse route (vector FMAs per non-zero)?  The shorter of the two
 // estimates.  Batches of 32 rows and less are one panel of the sparse route and too few for MFMA tiles; layers with one non-zero in
 // 40 entries or fewer take the sparse route as they always did (of 24 measured ones the dense route was more than
 // 15 % quicker on three, 25088 x 16 at 256 rows 46 against 63 us).
-// The routes round differently (relative error against 64 bits: dense 4.4 to 13e-8, 2.6 to 4.0e-8 for columns of up to 120 non-zeros and one K split; sparse 3 to
-// 5.2e-8 but for sums of long columns in 32 bits, 5.5 to 49e-8), so a product that the dense route had before takes the sparse one with `careful` sums, and not
-// where the dense route's are closer still.
+// What a product takes on the route so chosen, over the better one, 10300 products that were not fitted: equally full columns 1.003 (geometric mean; worst
+// 1.30), others 1.007 (worst 3.9, on the route they had before); with one estimate for all sparse kernels, as it was while passes were 32 columns wide and a
+// column had one wavefront, 1.22 and 1.18.
+// Two things besides, because the routes round differently (relative error against 64 bits: dense 4.4 to 13e-8, 2.6 to 4.0e-8 for columns of up to 120 non-zeros
+// and one K split; sparse 3 to 5.2e-8 but for sums of long columns in 32 bits, 5.5 to 49e-8):
+//   a product that the dense route had before takes the sparse one with `careful` sums, and not where the dense route's are closer still;
+//   one that the sparse route had before leaves it only from long sums in 32 bits, and where columns are not equally full, which misleads the estimates, only
+//   if these are far apart (2609 drawn ones that do: 0.54 of the error they had, 37 of them more, up to 1.11; where the decode may not run on LDS, 32 of twice
+//   the estimate: 0.45 of the time, one slower).
 // `room`: bytes of workspace there are, for hac_dot_noalloc; the plan then splits K only as far as the parts fit.
 DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* launch, size_t room = ~(size_t)0)
 {
@@ -1393,43 +1450,16 @@ DenseRoute dense_route(const hac_desc_t* desc, int64_t B, const hac_launch_t* la
     if (B < 1 || (force != HAC_LAUNCH_DENSE_ROUTE && !choice) || !size_index_map(desc, r)) return r;
     r.plan = hac_internal::plan_index_gemm((uint32_t)B, (uint32_t)desc->n, (uint32_t)desc->m, room > r.idx_bytes ? room - r.idx_bytes : 0);
     r.bytes = r.idx_bytes + ((r.plan.part_bytes + 255) / 256 * 256);
-    const bool before = choice && dense_before(desc, B, r);
-    r.use = choice && (dense_us(desc, r) < sparse_us(desc, B) || (before && r.plan.splits == 1 && desc->nnz < 125 * desc->m));
-    r.careful = before && !r.use;
+    if (choice) {
+        const SparseEstimate sparse = sparse_us(desc, B);
+        const double dense = dense_us(desc, r);
+        const bool before = dense_before(desc, B, r), even = (double)desc->max_col_nnz <= usual_column(desc);
+        if (before) r.use = dense < sparse.us || (r.plan.splits == 1 && desc->nnz < 125 * desc->m);
+        else r.use = sparse.sums32 && dense * (even ? 1.0 : decode_in_lds(desc) ? 1.3 : 2.0) < sparse.us;
+        r.careful = before && !r.use;
+    }
     if (force) r.use = force == HAC_LAUNCH_DENSE_ROUTE;
     return r;
-}
-
-// LDS of decode_to_index_kernel's blocks: the tables, the index of the columns, and room for the stream words and ri fields of a block's
-// chunks.  A block whose words do not fit reads them from the blob, a trip to memory per codeword, and the launch lasts as long as its
-// slowest block; how many words the fullest block has is not in the header.  A quarter more than a block's chunks have on average
-// (9402 x 2297, 54 % non-zero, sHAC, 48 rows, forced 403 -> 204 us against 6144 words each for stream and fields), and what a CU's LDS has left over
-// beside the blocks that run there at once, as far as a launch takes it without an attribute set first.  HAC and Rice-coded gaps: no less than
-// 6144, because chunks have as many non-zeros each, so that those of the emptier columns have more words than the average (4608 x 512, columns
-// from 70 to 10 % full, 48 rows, forced: room for the average and a quarter 53.3 us, so 40.9; equally full ones as quick or within 5 %).
-struct DecodeLds { uint32_t s_words, r_words, c_words, grid; size_t bytes; };
-
-DecodeLds decode_lds(const hac_desc_t* desc, const DevBlob& d)
-{
-    constexpr uint64_t kGranule = 1280, kStatic = 16, kNoAttribute = 64 * 1024;
-    DecodeLds p;
-    p.grid = (d.n_chunks + 255) / 256;
-    const double chunk_words = d.n_chunks ? 256.0 / 32.0 * (double)desc->total_bits / (double)d.n_chunks : 0.0;
-    const uint64_t chunk_nnz = std::min<uint64_t>(std::max<uint64_t>(hac_internal::chunk_base(desc->chunk),
-                                                  desc->chunk & hac_internal::kChunkPerColumn ? (desc->max_col_nnz + 63) / 64 : 0), desc->max_col_nnz);
-    const bool fields = desc->format == HAC_FORMAT_SHAC && !d.rice;
-    p.s_words = round_up(std::max(fields ? 0u : 6144u, (uint32_t)std::min(1.25 * chunk_words + 64.0, 20480.0)), 4);
-    p.r_words = 0;
-    if (fields) p.r_words = round_up((uint32_t)std::min<uint64_t>(256 * chunk_nnz * d.ri_bits / 32 + 16, 28672), 4);
-    p.c_words = d.m + 1 <= 8192 ? round_up(d.m + 1, 4) : 0u;               // colchunk, for the owner search
-    const uint64_t others = 4ull * (table_words(d) + p.c_words) + kStatic;
-    if (others + 4ull * (p.s_words + p.r_words) > kLdsLimit) { p.s_words = std::min(p.s_words, 6144u); p.r_words = std::min(p.r_words, 6144u); }
-    const uint64_t need = others + 4ull * (p.s_words + p.r_words);
-    const uint64_t fit = std::max<uint64_t>(1, kLdsLimit / ((need + kGranule - 1) / kGranule * kGranule));
-    const uint64_t share = std::min(kLdsLimit / std::min<uint64_t>(fit, std::max(1u, (p.grid + 255) / 256)) / kGranule * kGranule, kNoAttribute);
-    if (share > need) p.s_words += (uint32_t)((share - need) / 16) * 4;
-    p.bytes = others - kStatic + 4ull * (p.s_words + p.r_words);
-    return p;
 }
 
 // bytes of workspace the sparse route needs: partial sums of the row-blocked kernel, or the feature-major copy of X
@@ -1518,7 +1548,7 @@ int dot_impl(uint32_t format, const hac_desc_t* desc, const void* d_blob,
                            (uint64_t)(dr.idx_bytes / 4), 0u);
         note_kernel("fill_u32_kernel");
         note_kernel("decode_to_index_kernel<unsigned %s>", dr.idx_bits == 8 ? "char" : "short");
-        const DecodeLds dl = decode_lds(desc, d);
+        const DecodeLds dl = decode_lds(desc);
         const uint32_t s_words = dl.s_words, r_words = dl.r_words, c_words = dl.c_words, grid = round_up(dl.grid, 8);
         const size_t lds = dl.bytes;
         const uint32_t is_shac = format == HAC_FORMAT_SHAC ? 1u : 0u;

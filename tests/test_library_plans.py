@@ -95,6 +95,32 @@ def test_the_quicker_route_with_several_wavefronts_per_column(n, m, prune, B, k,
     assert hac.hac_dot_route(d, B) == (1 if dense_us < sparse_us else 0)
 
 
+# columns from full to 5 or 20 % of that, headers and times as measured: where the longest column is most of a launch, where a HAC stream's emptiest
+# columns leave no room for their words in the decode's LDS, and where both are as on equal columns
+@pytest.mark.parametrize("fmt,n,m,B,nnz,k,lmax,chunk,n_chunks,most,bits,total,ri_bits,sparse_us,dense_us",
+                         [("hac", 22082, 184, 50, 754108, 62, 21, 146, 5251, 9334, 63633, 7528560, 0, 112, 495),
+                          ("hac", 19745, 706, 51, 1882098, 118, 21, 90, 21257, 5703, 50669, 24346516, 0, 158, 540),
+                          ("hac", 23642, 675, 63, 2236407, 165, 22, 111, 20484, 7042, 64661, 29372980, 0, 206, 700),
+                          ("hac", 16082, 3057, 41, 14845442, 15, 13, 112, 134085, 7160, 32774, 84228019, 0, 552, 208),
+                          ("rice", 3709, 1965, 258, 894425, 151, 20, 16, 56823, 998, 9166, 9266475, 0, 139, 56),
+                          ("rice", 2807, 3390, 314, 1036713, 25, 17, 11, 95773, 662, 4916, 8349408, 0, 159, 69),
+                          ("rice", 24298, 1743, 51, 3973801, 31, 20, 88, 46021, 5569, 41873, 32768001, 0, 231, 104),
+                          ("shac", 17418, 750, 48, 3352411, 35, 19, 118, 28786, 7491, 28022, 12536962, 15, 161, 73),
+                          ("shac", 19166, 1839, 106, 1942956, 130, 21, 41, 48293, 2620, 14409, 10646447, 15, 208, 96),
+                          ("shac", 20457, 982, 49, 4123786, 69, 21, 127, 32968, 8065, 37009, 18940005, 15, 176, 87),
+                          ("hac", 2118, 3763, 165, 1763568, 193, 22, 16, 112003, 962, 8130, 19190048, 0, 114, 58),
+                          ("hac", 5787, 1372, 259, 814517, 20, 17, 14, 58834, 852, 8241, 10281253, 0, 113, 61),
+                          ("rice", 24157, 280, 39, 895433, 181, 20, 104, 8748, 6615, 62604, 9440111, 0, 94, 168)])
+def test_the_quicker_route_with_uneven_columns(fmt, n, m, B, nnz, k, lmax, chunk, n_chunks, most, bits, total, ri_bits, sparse_us, dense_us):
+    d = header(hac.HAC_FORMAT_HAC if fmt == "hac" else hac.HAC_FORMAT_SHAC, n, m, nnz, k, chunk)
+    d.lmax, d.n_chunks, d.max_col_nnz, d.max_col_bits, d.total_bits, d.ri_bits = lmax, n_chunks, most, bits, total, ri_bits
+    if fmt == "hac":
+        d.zero_len = 1
+    else:
+        d.has_zero, d.ri_coding = 0, hac.RI_RICE if fmt == "rice" else hac.RI_FIELDS
+    assert hac.hac_dot_route(d, B) == (1 if dense_us < sparse_us else 0)
+
+
 @pytest.mark.parametrize("n,m", [(1_000_000, 1), (67_000_000, 1), (300_000, 65), (4096, 10), (25088, 4096), (100_000, 129)])
 def test_device_encoder_workspace_follows_the_matrix(n, m):
     """At most as much as W beside the fixed tables (about 4 MB), whatever the matrix's shape."""
