@@ -134,14 +134,20 @@ def test_dense_route_matches_the_oracle(hac, name, W):
 def test_dense_route_decode_without_its_lds_copies(hac):
     # the decode kernel keeps a block's stream words, ri fields and the column index in LDS when
     # they fit; these layers do not fit: 256 chunks of a very sparse, tall HAC layer span more
-    # stream words than the staging area, 256 chunks of 100 non-zeros carry more ri bits than
-    # theirs, and a layer with more than 8191 columns has too long an index
+    # stream words than the staging area ever has (20480), 256 chunks of 500 non-zeros carry more ri bits than
+    # there is ever room for (28672 words), 256 chunks of 700 with Rice-coded gaps more words again, and a layer with more
+    # than 8191 columns has too long an index
     tall = workloads.make_layer(30000, 24, 0.02, 0.999, 8, "uniform", 71)
-    fat = workloads.make_layer(2000, 300, 0.02, 0.5, 16, "uniform", 72)
+    fat = workloads.make_layer(8000, 300, 0.02, 0.5, 16, "uniform", 72)
     wide = workloads.make_layer(24, 9000, 0.02, 0.7, 8, "uniform", 73)
     cases = [("tall", tall, hac.hac_encode(tall), hac.hac_dot), ("tall/rice", tall, hac.shac_encode(tall, ri_coding=1), hac.shac_dot),
-             ("fat ri", fat, hac.shac_encode(fat, chunk_nnz=100), hac.shac_dot),
+             ("fat ri", fat, hac.shac_encode(fat, chunk_nnz=500), hac.shac_dot),
+             ("fat rice", fat, hac.shac_encode(fat, ri_coding=1, chunk_nnz=700), hac.shac_dot),
              ("wide", wide, hac.hac_encode(wide), hac.hac_dot), ("wide", wide, hac.shac_encode(wide), hac.shac_dot)]
+    descs = {what: blob.desc for what, _, blob, _ in cases}
+    assert descs["tall"].n_chunks <= 256 and descs["tall"].n_words > 20480                    # one block
+    assert 256 * 500 * descs["fat ri"].ri_bits / 32 > 28672 and descs["fat ri"].n_chunks > 256
+    assert 0.9 * 256 * 700 * descs["fat rice"].total_bits / descs["fat rice"].nnz / 32 > 20480
     for what, W, blob, f in cases:
         db = blob.to_device(dev())
         for B in (1, 33):

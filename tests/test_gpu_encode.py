@@ -197,22 +197,51 @@ def test_device_blob_over_columns(hac, n, m):
                           hac.shac_encode(W, ri_coding=hac.RI_RICE).data)
 
 
-def test_device_encodes_side_by_side(hac):
-    """More calls at once than there is pinned memory for, each on a stream of its own."""
-    import concurrent.futures as cf
-    Ws = [alphabet_matrix(5 + i, lambda j: 3 + j, 200 + i, 40) for i in range(24)]
-    Wd = [torch.from_numpy(W).to(dev()) for W in Ws]
-    torch.cuda.synchronize()
+# a segment of a column is 32 rows up to 8.4 million entries and twice as many from each doubling on, 512 from 67 million, where W is also read past
+# the caches: shapes just above each line, with a last segment, a last word and a last tile of columns that are not full
+@pytest.mark.parametrize("n,m,rows", [(3007, 2803, 64), (4111, 4099, 128), (5801, 5797, 256), (9001, 7459, 512), (1100203, 61, 512)])
+def test_device_blob_over_rows_per_segment(hac, n, m, rows):
+    assert rows == min(512, 32 << max(0, (n * m - 1) // 262144 // 32).bit_length())
+    g = torch.Generator(device=dev())
+    g.manual_seed(n)
+    kinds = {"few": (0.04, 20), "values outside LDS": (0.04, 1500)}
+    if rows == 64:
+        kinds["few zeros"] = (0.97, 9)
+    for kind, (density, k) in kinds.items():
+        keep = torch.rand((n, m), generator=g, device=dev()) < density
+        Wd = torch.where(keep, torch.randint(1, k + 1, (n, m), generator=g, device=dev()).float() * 0.01 - 0.003, torch.zeros((), device=dev()))
+        Wd[n // 4:n // 2, m // 3] = 0.0                                    # segments of a column without a non-zero
+        W = Wd.cpu().numpy()
+        for what in ("hac", "shac", "rice"):
+            print(f"[case] encode_dev {n} x {m} {kind} {what}", flush=True)
+            ri = hac.RI_RICE if what == "rice" else hac.RI_FIELDS
+            got = hac.hac_encode_dev(Wd, hac.HAC_FORMAT_HAC if what == "hac" else hac.HAC_FORMAT_SHAC, ri_coding=ri).tensor.cpu().numpy()
+            assert np.array_equal(got, (hac.hac_encode(W) if what == "hac" else hac.shac_encode(W, ri_coding=ri)).data)
 
-    def one(i):
-        stream = torch.cuda.Stream()
-        with torch.cuda.stream(stream):
-            for _ in range(5):
-                got = hac.hac_encode_dev(Wd[i], hac.HAC_FORMAT_HAC).tensor.cpu().numpy()
-        return got
-    with cf.ThreadPoolExecutor(24) as pool:
-        for W, got in zip(Ws, pool.map(one, range(24))):
-            assert np.array_equal(got, hac.hac_encode(W).data)
+
+def test_device_encodes_side_by_side(hac):
+    """More calls at once than there is pinned memory for, each on a stream of its own: all wait for one event, so that all
+    have asked for that memory before the first gets on.  Alphabets whose code is built on the device, on the host from a list in pinned memory, and on the
+    host from a list that is copied."""
+    import concurrent.futures as cf
+    counts = [(700 if i % 3 == 1 else 4200 if i % 3 == 2 else 5 + i) for i in range(24)]
+    Ws = [alphabet_matrix(k, lambda j: 3 + j % 5, 200 + i, 160) for i, k in enumerate(counts)]
+    Wd = [torch.from_numpy(W).to(dev()) for W in Ws]
+    hac.hac_encode_dev(Wd[0], hac.HAC_FORMAT_HAC)                            # (the pinned memory itself is allocated by the first call)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        torch.cuda._sleep(50_000_000)
+        gate = torch.cuda.Event()
+        gate.record()
+
+        def one(i):
+            stream = torch.cuda.Stream()
+            stream.wait_event(gate)
+            with torch.cuda.stream(stream):
+                return hac.hac_encode_dev(Wd[i], hac.HAC_FORMAT_HAC).tensor.cpu().numpy()
+        with cf.ThreadPoolExecutor(24) as pool:
+            for W, got in zip(Ws, pool.map(one, range(24))):
+                assert np.array_equal(got, hac.hac_encode(W).data)
 
 
 def gap_matrix(kind):

@@ -69,7 +69,7 @@ def test_noalloc_takes_products_that_want_more_on_the_quicker_route(n, m, prune,
 
 
 # times of both routes, us (sparse, dense), as measured while the sparse route passed over its lists 32 columns at a time with one
-# wavefront per column of W: the data that the rule was fitted to, not what the sparse route takes now (the last shape: 13 to 14)
+# wavefront per column of W: the data that the rule of that time was fitted to, not what the routes take now (the last shape, sparse: 13 to 14)
 @pytest.mark.parametrize("n,m,prune,B,sparse_us,dense_us",
                          [(15097, 501, 0.57, 246, 457, 106), (17139, 478, 0.57, 244, 430, 139), (25088, 1000, 0.90, 512, 397, 183),
                           (4608, 512, 0.60, 784, 156, 75), (25088, 4096, 0.90, 300, 812, 423), (2000, 2000, 0.80, 2048, 287, 124),
