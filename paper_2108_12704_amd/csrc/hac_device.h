@@ -64,8 +64,9 @@ __device__ __forceinline__ void load_entry(const DevBlob& d, uint32_t g, uint32_
 // word sources: the blob's stream / ri words in global memory, or a copy staged
 // in LDS that starts at word `wbase`
 // ---------------------------------------------------------------------------
-template <bool LDS>
+template <bool LDS, bool INLINE = true>           // INLINE: see decode_symbol
 struct WordSrc {
+    static constexpr bool kInline = INLINE;
     const uint32_t* w;
     uint32_t wbase;
     __device__ __forceinline__ uint32_t word(uint32_t i) const {
@@ -126,33 +127,47 @@ __device__ __forceinline__ bool longer_codes(const DevBlob& d) { return d.lmax >
 // Code longer than the first-level table: {(symbol << 6) | length, value bits}.  Its length is the number of bounds it has passed,
 // four of them read at once (all lanes the same words), then two reads.  Some lane of a wavefront is here at almost every step of a HAC
 // stream: one length after the other, two reads each, made that lane's search the longest part of the step.
-__device__ __forceinline__ uint2 decode_long(const DevBlob& d, const Tables& t, uint32_t top)
+__device__ __forceinline__ uint2 decode_long(const Tables& t, const uint32_t* symsort, const float* codebook, uint32_t lut_bits, uint32_t lmax,
+                                             uint32_t k_sym, uint32_t top)
 {
-    if (!longer_codes(d)) return make_uint2(d.lmax ? d.lmax : 1u, 0u);       // no such code: a damaged stream; still makes progress
+    if (lmax <= lut_bits || !k_sym) return make_uint2(lmax ? lmax : 1u, 0u);    // no such code: a damaged stream; still makes progress
     lds_cu32* bound = (lds_cu32*)t.bound;
     const uint32_t half = top >> 1;
-    uint32_t l = d.lut_bits + 1;
-    for (uint32_t u = d.lut_bits + 1; u < d.lmax; u += 4) {                     // (from lmax on no bound is passed)
+    uint32_t l = lut_bits + 1;
+    for (uint32_t u = lut_bits + 1; u < lmax; u += 4) {                         // (from lmax on no bound is passed)
         const uint32_t b0 = bound[u], b1 = bound[u + 1], b2 = bound[u + 2], b3 = bound[u + 3];
         l += (half >= b0 ? 1u : 0u) + (half >= b1 ? 1u : 0u) + (half >= b2 ? 1u : 0u) + (half >= b3 ? 1u : 0u);
     }
     uint32_t at = bound[kBounds + l] + (top >> (32 - l));
-    at = at < d.k_sym ? at : d.k_sym - 1u;                                      // (of a damaged stream)
+    at = at < k_sym ? at : k_sym - 1u;                                          // (of a damaged stream)
     if (t.small) {
         const u32x2 e = ((lds_cu2*)t.long2)[at];
         return make_uint2(e.x << 6 | l, e.y);
     }
-    const uint32_t sy = d.symsort[at];
-    return make_uint2(sy << 6 | l, __float_as_uint(d.codebook[sy]));
+    const uint32_t sy = symsort[at];
+    return make_uint2(sy << 6 | l, __float_as_uint(codebook[sy]));
+}
+
+__device__ __noinline__ uint2 call_decode_long(const uint32_t* bound, const uint2* long2, const uint32_t* symsort, const float* codebook, uint32_t lut_bits,
+                                               uint32_t lmax, uint32_t k_sym, uint32_t top)
+{
+    const Tables t = { nullptr, bound, long2, k_sym <= kCodebookLdsMax };
+    return decode_long(t, symsort, codebook, lut_bits, lmax, k_sym, top);
 }
 
 struct Decoded { uint32_t sym, len; float val; };
 
+// INLINE: everywhere but where a loop waits for a word of the blob and stores several values per codeword (hac_decode_dev): the call is quicker there, with
+// and without long codewords (7272 x 22, 25 % non-zero, sHAC 38.9 -> 33.6 us; 18037 x 12, 36 %, Rice-coded gaps 136 -> 127).
+template <bool INLINE>
 __device__ __forceinline__ Decoded decode_symbol(const DevBlob& d, const Tables& t, uint32_t top)
 {
     const u32x2 raw = ((lds_cu2*)t.lut2)[top >> (32 - d.lut_bits)];
     uint2 e = make_uint2(raw.x, raw.y);
-    if ((e.x & 63u) == 0) e = decode_long(d, t, top);
+    if ((e.x & 63u) == 0) {
+        if (INLINE) e = decode_long(t, d.symsort, d.codebook, d.lut_bits, d.lmax, d.k_sym, top);
+        else e = call_decode_long(t.bound, t.long2, d.symsort, d.codebook, d.lut_bits, d.lmax, d.k_sym, top);
+    }
     Decoded r;
     r.len = e.x & 63u; r.sym = e.x >> 6; r.val = __uint_as_float(e.y);
     return r;
@@ -284,7 +299,7 @@ __device__ __forceinline__ void hac_advance(const DevBlob& d, const Tables& tb, 
                 top = z + d.lmax <= 32 ? top << z : src.peek32(st.bp);
             }
         }
-        const Decoded q = decode_symbol(d, tb, top);
+        const Decoded q = decode_symbol<Src::kInline>(d, tb, top);
         st.bp += q.len;
         if (d.has_zero && q.sym == 0) {
             st.row++;
@@ -342,7 +357,7 @@ __device__ __forceinline__ void hac_advance_zrun(const DevBlob& d, const Tables&
         const uint32_t x0 = z < 32u ? hi : mid, x1 = z < 32u ? mid : lo;
         const uint32_t zz = z & 31u;
         const uint32_t top = (x0 << zz) | ((x1 >> 1) >> (zz ^ 31u));
-        const Decoded sy = decode_symbol(d, tb, top);
+        const Decoded sy = decode_symbol<true>(d, tb, top);
         st.row += z;
         rm1 += (int32_t)(z + sy.len);
         emit(st.wpos, st.row, sy.sym, sy.val);
@@ -357,7 +372,7 @@ __device__ __forceinline__ void shac_advance(const DevBlob& d, const Tables& tb,
                                              ChunkState& st, uint32_t limit, Emit emit)
 {
     while (st.wpos < limit) {
-        const Decoded q = decode_symbol(d, tb, src.peek32(st.bp));
+        const Decoded q = decode_symbol<Src::kInline>(d, tb, src.peek32(st.bp));
         st.bp += q.len;
         emit(st.wpos, 0u, q.sym, q.val);
         st.wpos++;
@@ -377,7 +392,7 @@ __device__ __forceinline__ void shac_advance(const DevBlob& d, const Tables& tb,
     uint32_t w0 = sw[q - 2], w1 = sw[q - 1], w2 = sw[q];
     ALIGN_DECODE_LOOP();
     while (st.wpos < limit) {
-        const Decoded sy = decode_symbol(d, tb, __builtin_amdgcn_alignbit(w0, w1, (uint32_t)s));
+        const Decoded sy = decode_symbol<true>(d, tb, __builtin_amdgcn_alignbit(w0, w1, (uint32_t)s));
         s -= (int32_t)sy.len;
         const bool on = s < 0;                                             // into the next word
         w0 = on ? w1 : w0; w1 = on ? w2 : w1;
@@ -418,7 +433,7 @@ __device__ __forceinline__ void gap_advance(const DevBlob& d, const Tables& tb, 
         } else {
             gapv = mid; top = lo; used = 64;
         }
-        const Decoded sy = decode_symbol(d, tb, top);
+        const Decoded sy = decode_symbol<true>(d, tb, top);
         const uint32_t row = st.row + gapv;
         rm1 += (int32_t)(used + sy.len);
         st.row = row + 1;
@@ -447,7 +462,7 @@ __device__ __forceinline__ void gap_advance_slow(const DevBlob& d, const Tables&
             gapv = src.peek32(st.bp);
             st.bp += 32;
         }
-        const Decoded q = decode_symbol(d, tb, src.peek32(st.bp));
+        const Decoded q = decode_symbol<Src::kInline>(d, tb, src.peek32(st.bp));
         st.bp += q.len;
         const uint32_t row = st.row + gapv;
         st.row = row + 1;

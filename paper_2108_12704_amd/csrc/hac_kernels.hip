@@ -80,7 +80,7 @@ decode_kernel(DevBlob d, float* vals, int32_t* sym, int32_t* row_out, int32_t* c
     const uint32_t chunk = hac_internal::chunk_of_column(d.chunk, cend - d.colpos[col]);
     st.wpos = d.colpos[col] + (g - d.colchunk[col]) * chunk;
     st.wend = st.wpos + chunk < cend ? st.wpos + chunk : cend;
-    WordSrc<false> src = { d.stream, 0 };
+    WordSrc<false, false> src = { d.stream, 0 };
     if (SHAC && d.rice) {
         gap_advance_slow(d, tb, src, st, st.wend, [&](uint32_t p, uint32_t row, uint32_t s, float v) {
             if (sym) sym[p] = (int32_t)s;
