@@ -565,7 +565,7 @@ int shac_decode_dev(const hac_desc_t *desc, const void *d_blob,
 /* The kernels launched by the calling thread's most recent successful hac_dot / shac_dot /
  * im_dot / hac_dot_noalloc call, in launch order, separated by "; ", spelled as a profiler prints
  * them without their namespace (e.g. "transpose_panel32_kernel<128u>; dot_batch_kernel<false, 4, true,
- * false>").  For attributing profiler rows to calls; never NULL. */
+ * false, 1>"), but for dot_split_kernel's last template argument, the kind of its sums.  For attributing profiler rows to calls; never NULL. */
 const char *hac_last_kernels(void);
 
 /* Text for a status code; never NULL. */

@@ -183,8 +183,8 @@ __device__ __forceinline__ uint32_t table_words_dev(const DevBlob& d)
 //
 // The copy is split in three so that every trip to memory carries as many loads as possible and a
 // kernel can put its own loads beside them: request_tables issues everything that depends on
-// nothing (first-level entries, canonical table, codebook, symbol order), request_table_values the
-// shared values of the first-level entries (they depend on the entries), store_tables writes LDS.
+// nothing (first-level entries and, where codewords are longer than those, canonical table and symbol
+// order), request_table_values the shared values of the entries and of the symbols in that order, store_tables writes LDS.
 // A loop of load / store pairs would pay one trip per turn and per table instead.  Loads of the
 // first kTabTurns turns of every loop are issued from clamped, valid indices on every thread;
 // what a small block or a long table leaves over is copied the plain way.

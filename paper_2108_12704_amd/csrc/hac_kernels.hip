@@ -241,7 +241,7 @@ decode_to_index_kernel(DevBlob d, IdxT* idx, uint64_t pitch, uint32_t shac, uint
 // ---------------------------------------------------------------------------
 // X (B x n, row-major) -> XT, feature-major in panels of `wp` batch columns:
 // XT[(b / wp) * n * wp + r * wp + b % wp] = X[b][r] (see panel_width).  What it holds past the batch is not read, or goes into sums
-// that are not stored; four columns of padding are not written (9973 x 1511, 7 %, 37 rows 21.7 -> 20.9 us for the whole product).
+// that are not stored.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 transpose_pad_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64_t ldx,
@@ -271,7 +271,8 @@ transpose_pad_kernel(const float* __restrict__ X, uint32_t B, uint32_t n, uint64
 // Same re-layout for panels of exactly 32 batch columns: a block turns 32 batch rows x F features into one contiguous piece of a
 // panel (F = 128: 16 KB).  With X 16-byte aligned (vec = 1) the reads are 128-bit (4 F bytes per batch row) and so are the
 // writes.  A small X is a matter of latency, and of CUs that have nothing to do: F = 32 where 128 would leave fewer than kTurnBlocks blocks
-// (4096 features, 64 rows 13.5 -> 13.2 us for the whole product; 25088, 32 rows 23.0 -> 22.7; but 256 rows 109.5 and 110.7).
+// (4096 features, 64 rows 13.5 -> 13.2 us for the whole product; 25088, 32 rows 23.0 -> 22.7; but 256 rows 109.5 and 110.7).  Four columns of padding
+// are not written (9973 x 1511, 7 %, 37 rows 21.7 -> 20.9 us for the whole product).
 constexpr uint32_t kTurnBlocks = 512;
 template <uint32_t F>
 __global__ void __launch_bounds__(256)
